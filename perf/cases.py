@@ -1,0 +1,182 @@
+"""The workloads by which this library's speed is followed.
+
+A case is one evaluation of a coordinate network: a model that a program keeps (weights quantized once, activation
+scales measured once on the coordinates where they are static) is given coordinates on the device and returns the
+signal's values.  All passes go through ``Model.forward`` (and ``Model.calibrate``) with the default flags, so the
+library chooses the kernels.  Sizes are those of ``synth.WORKLOADS``, of the tests, or generic image and volume sizes.
+
+A case's values:
+  act     "sine" (SIREN), "wavelet" (real-valued wavelet layers), "complex" (complex-valued wavelet layers; width = complex width)
+  mode    "in" / "both" (which sides of the weights are rotated), "w8a32" / "w32a32" (floating-point activations)
+  scales  "static", "dynamic" (measured on line in every call), "calibrate" (measured by Model.calibrate, then a static forward)
+  fan_in, width, hidden, fan_out   the network: `hidden` layers of `width` features and the output layer
+  bits    of weights and activations
+  rows, cols   cols > 0: a pixel grid of rows x cols on [-1, 1]^2; cols = 0: `rows` random points of the cube [-1, 1]^fan_in
+"""
+import numpy as np
+import torch
+
+import paper_2508_13478_amd as dhq
+from paper_2508_13478_amd import synth
+
+OMEGA0 = 30.0
+WAVELET_S0 = 10.0
+
+
+def _case(name, act, mode, scales, fan_in, width, hidden, fan_out, bits, rows, cols):
+    c = {"act": act, "mode": mode, "scales": scales, "fan_in": fan_in, "width": width, "hidden": hidden, "fan_out": fan_out,
+         "bits": bits, "rows": rows, "cols": cols}
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # a small image on a small network: the latency of one call (workload C1)
+        _case("small image, 64 wide", "sine", "in", "static", 2, 64, 3, 3, 8, 64, 64),
+        # a batch of point queries against an image network: far fewer rows than the chip holds at once
+        _case("1000 points, 256 wide", "sine", "in", "static", 2, 256, 5, 3, 8, 1000, 0),
+        # an ordinary image (workload C2)
+        _case("image, 256 wide", "sine", "in", "static", 2, 256, 4, 3, 8, 256, 256),
+        # a photograph whose sides are no multiples of anything, on the wavelet architecture
+        _case("photograph, wavelet 256", "wavelet", "in", "static", 2, 256, 5, 3, 8, 321, 481),
+        # the largest image on the widest network (workload C5)
+        _case("large image, 512 wide", "sine", "in", "static", 2, 512, 6, 3, 8, 2048, 2048),
+        # the wavelet architecture with complex features as published: a width that is no power of two
+        _case("image, complex wavelet 181", "complex", "in", "static", 2, 181, 3, 3, 8, 256, 256),
+        # both sides of the weights rotated
+        _case("image, both sides 256", "sine", "both", "static", 2, 256, 5, 3, 8, 512, 512),
+        _case("image, both sides 512", "sine", "both", "static", 2, 512, 6, 3, 8, 512, 512),
+        # activation scales measured on line, in every call
+        _case("image, on-line scales 256", "sine", "in", "dynamic", 2, 256, 5, 3, 8, 512, 512),
+        # a volume with one channel on an odd width, sampled at random points: its scales measured, then evaluated
+        _case("volume, calibrated 200", "sine", "in", "calibrate", 3, 200, 4, 1, 8, 150001, 0),
+        # the full-precision network the quantized one is compared with
+        _case("image, W32A32 256", "sine", "w32a32", "static", 2, 256, 5, 3, 8, 512, 512),
+        # weights quantized only, on the widest network
+        _case("image, W8A32 512", "sine", "w8a32", "static", 2, 512, 6, 3, 8, 512, 512),
+    ]
+
+
+def draw(rng):
+    """A case of the same ranges: the families above with their options, sizes log-uniform from a few hundred rows up to where
+    a pass costs what the largest listed one of its kind costs."""
+    def log_uniform(lo, hi):
+        return int(round(lo * (hi / lo) ** rng.random()))
+
+    kind = rng.choice(["fused", "fused", "fused", "odd", "both", "dynamic", "calibrate", "complex", "float", "float"])
+    act, mode, scales = "sine", "in", "static"
+    fan_in = rng.choice([2, 2, 2, 1, 3, 4])
+    width = rng.choice([32, 64, 128, 256, 256, 512])
+    hidden = rng.randint(2, 6)
+    fan_out = rng.choice([3, 3, 1, 2, 4, 5])
+    bits = rng.choice([8, 8, 8, 6, 4])
+    if kind == "fused":
+        act = rng.choice(["sine", "sine", "wavelet"])
+    elif kind == "odd":
+        act = rng.choice(["sine", "sine", "wavelet"])
+        width = log_uniform(20, 512)
+        fan_in = rng.choice([2, 3, 5, 12, 40])
+    elif kind == "both":
+        mode = "both"
+        act = rng.choice(["sine", "sine", "wavelet"])
+    elif kind == "dynamic":
+        scales = "dynamic"
+        mode = rng.choice(["in", "in", "both"])
+        width = rng.choice([width, width, log_uniform(20, 512)])
+    elif kind == "calibrate":
+        scales = "calibrate"
+        width = rng.choice([width, log_uniform(20, 512)])
+    elif kind == "complex":
+        act, bits, hidden = "complex", 8, rng.randint(2, 4)
+        width = rng.choice([16, 32, 64, 128, 256, rng.randint(20, 250)])
+    else:
+        mode = rng.choice(["w8a32", "w32a32"])
+        act = rng.choice(["sine", "sine", "wavelet"])
+        width = rng.choice([width, width, log_uniform(20, 512)])
+        bits = 8
+    real = 2 * width if act == "complex" else width
+    ops_per_row = 2 * (fan_in * real + (hidden - 1) * real * real + real * fan_out)
+    most_ops = 8e12 if kind == "fused" else 5e11
+    most = int(min(2_000_000, most_ops / ops_per_row))
+    n = log_uniform(min(300, most), most)
+    if fan_in == 2 and rng.random() < 0.6:
+        side = max(2, int(n ** 0.5))
+        cols = max(2, min(int(side * rng.choice([1.0, 1.0, 1.333, 1.5])), n))
+        return _case("", act, mode, scales, fan_in, width, hidden, fan_out, bits, max(1, n // cols), cols)
+    return _case("", act, mode, scales, fan_in, width, hidden, fan_out, bits, n, 0)
+
+
+def _dims(case):
+    return [case["fan_in"]] + [case["width"]] * case["hidden"] + [case["fan_out"]]
+
+
+def _rows(case):
+    return case["rows"] * (case["cols"] or 1)
+
+
+def _coords(case, seed):
+    if case["cols"]:
+        # the pixel centres of an image, at a sub-pixel phase of its own (resampling, a moved view)
+        shift = np.random.default_rng(seed).uniform(-0.5, 0.5, 2)
+        y = (torch.arange(case["rows"], dtype=torch.float64, device="cuda") + 0.5 + shift[0]) * (2.0 / case["rows"]) - 1.0
+        x = (torch.arange(case["cols"], dtype=torch.float64, device="cuda") + 0.5 + shift[1]) * (2.0 / case["cols"]) - 1.0
+        yy, xx = torch.meshgrid(y, x, indexing="ij")
+        return torch.stack([xx.reshape(-1), yy.reshape(-1)], dim=1).clamp(-1.0, 1.0).float().contiguous()
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.rand((case["rows"], case["fan_in"]), generator=g, device="cuda") * 2.0 - 1.0
+
+
+def _model(case, seed):
+    dims, bits = _dims(case), case["bits"]
+    if case["act"] == "complex":
+        W, b = synth.wire_init(dims, OMEGA0, seed)
+        return dhq.Model.complex_wavelet(dims, OMEGA0, W, b, WAVELET_S0, bits, bits)
+    W, b = synth.siren_init(dims, OMEGA0, seed)
+    mode = {"in": dhq.DHQ_ROTATE_IN, "both": dhq.DHQ_ROTATE_BOTH, "w8a32": dhq.DHQ_W8A32, "w32a32": dhq.DHQ_W32A32}[case["mode"]]
+    return dhq.Model(dims, OMEGA0, W, b, bits, bits, mode=mode, wavelet_s0=WAVELET_S0 if case["act"] == "wavelet" else None)
+
+
+def prepare(case, seed):
+    """The model and the coordinates; static activation scales come from a calibration on every eighth coordinate."""
+    model, x = _model(case, seed), _coords(case, seed)
+    if case["scales"] == "static" and case["mode"] in ("in", "both"):
+        model.calibrate(x[::8].contiguous() if x.shape[0] >= 8 else x)
+    flags = dhq.DHQ_AUTO | (dhq.DHQ_DYNAMIC if case["scales"] == "dynamic" else 0)
+    if case["scales"] == "dynamic":
+        dhq.dhq_reserve_dynamic(model.handle, x.shape[0])
+    return {"model": model, "x": x, "flags": flags, "calibrate": case["scales"] == "calibrate"}
+
+
+def run(state):
+    """One evaluation of the signal: coordinates in, values out (and the scales, where the pass measures them)."""
+    model = state["model"]
+    if state["calibrate"]:
+        model.calibrate(state["x"])
+        return model.forward(state["x"], flags=state["flags"]), model.scales()[1]
+    return model.forward(state["x"], flags=state["flags"])
+
+
+def work(case):
+    """Coordinates read and values written once, every weight read once (one byte, or four in the full-precision network);
+    two operations per multiply-add of the un-padded layers."""
+    dims, n = _dims(case), _rows(case)
+    if case["act"] == "complex":
+        dims = [dims[0]] + [2 * d for d in dims[1:-1]] + [dims[-1]]
+    macs = sum(a * b for a, b in zip(dims[:-1], dims[1:]))
+    return {"bytes": 4 * n * (dims[0] + dims[-1]) + macs * (4 if case["mode"] in ("w8a32", "w32a32") else 1), "flops": 2 * macs * n}
+
+
+def tolerance(case):
+    """Floating-point networks: up to 1.5e-6 (largest 6.3e-6) was seen against fp64, from the 32-bit sums and sines.
+    Quantized networks: an activation within rounding of the border between two codes may fall on either side, and the sine
+    layers after it amplify that one code.  Seen between the two implementations the library has (whole-network kernels and
+    layer by layer: they order the transform's sums differently) and for scales moved by three units in the last place:
+    rel 2.4e-3 with max 0.10 at 8 bits, max 0.66 at 4 and 6 bits (a code weighs more); 1.6e-2 with max 0.8 for the complex
+    wavelets, whose modulus is not bounded by one."""
+    if case["mode"] in ("w8a32", "w32a32"):
+        return {"rel": 6e-6, "max": 3e-5}
+    if case["act"] == "complex":
+        return {"rel": 0.03, "max": 0.99}
+    return {"rel": 1e-2, "max": 0.5 if case["bits"] == 8 else 0.9}
