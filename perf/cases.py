@@ -34,28 +34,28 @@ def _case(name, act, mode, scales, fan_in, width, hidden, fan_out, bits, rows, c
 def listed():
     return [
         # a small image on a small network: the latency of one call (workload C1)
-        _case("small image, 64 wide", "sine", "in", "static", 2, 64, 3, 3, 8, 64, 64),
+        _case("small image 64 wide", "sine", "in", "static", 2, 64, 3, 3, 8, 64, 64),
         # a batch of point queries against an image network: far fewer rows than the chip holds at once
-        _case("1000 points, 256 wide", "sine", "in", "static", 2, 256, 5, 3, 8, 1000, 0),
+        _case("1000 points 256 wide", "sine", "in", "static", 2, 256, 5, 3, 8, 1000, 0),
         # an ordinary image (workload C2)
-        _case("image, 256 wide", "sine", "in", "static", 2, 256, 4, 3, 8, 256, 256),
+        _case("image 256 wide", "sine", "in", "static", 2, 256, 4, 3, 8, 256, 256),
         # a photograph whose sides are no multiples of anything, on the wavelet architecture
-        _case("photograph, wavelet 256", "wavelet", "in", "static", 2, 256, 5, 3, 8, 321, 481),
+        _case("photograph wavelet 256", "wavelet", "in", "static", 2, 256, 5, 3, 8, 321, 481),
         # the largest image on the widest network (workload C5)
-        _case("large image, 512 wide", "sine", "in", "static", 2, 512, 6, 3, 8, 2048, 2048),
+        _case("large image 512 wide", "sine", "in", "static", 2, 512, 6, 3, 8, 2048, 2048),
         # the wavelet architecture with complex features as published: a width that is no power of two
-        _case("image, complex wavelet 181", "complex", "in", "static", 2, 181, 3, 3, 8, 256, 256),
+        _case("image complex wavelet 181", "complex", "in", "static", 2, 181, 3, 3, 8, 256, 256),
         # both sides of the weights rotated
-        _case("image, both sides 256", "sine", "both", "static", 2, 256, 5, 3, 8, 512, 512),
-        _case("image, both sides 512", "sine", "both", "static", 2, 512, 6, 3, 8, 512, 512),
+        _case("image both sides 256", "sine", "both", "static", 2, 256, 5, 3, 8, 512, 512),
+        _case("image both sides 512", "sine", "both", "static", 2, 512, 6, 3, 8, 512, 512),
         # activation scales measured on line, in every call
-        _case("image, on-line scales 256", "sine", "in", "dynamic", 2, 256, 5, 3, 8, 512, 512),
+        _case("image on-line scales 256", "sine", "in", "dynamic", 2, 256, 5, 3, 8, 512, 512),
         # a volume with one channel on an odd width, sampled at random points: its scales measured, then evaluated
-        _case("volume, calibrated 200", "sine", "in", "calibrate", 3, 200, 4, 1, 8, 150001, 0),
+        _case("volume calibrated 200", "sine", "in", "calibrate", 3, 200, 4, 1, 8, 150001, 0),
         # the full-precision network the quantized one is compared with
-        _case("image, W32A32 256", "sine", "w32a32", "static", 2, 256, 5, 3, 8, 512, 512),
+        _case("image W32A32 256", "sine", "w32a32", "static", 2, 256, 5, 3, 8, 512, 512),
         # weights quantized only, on the widest network
-        _case("image, W8A32 512", "sine", "w8a32", "static", 2, 512, 6, 3, 8, 512, 512),
+        _case("image W8A32 512", "sine", "w8a32", "static", 2, 512, 6, 3, 8, 512, 512),
     ]
 
 
