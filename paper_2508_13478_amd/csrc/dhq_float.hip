@@ -27,11 +27,12 @@
 // MFMA read, MFMA result -> vector ALU read) are covered by explicit s_nop.
 //
 // Every other shape (and DHQ_LAYERWISE on the shapes above) runs layer by layer through
-// float_layer_kernel: one fp32 MFMA GEMM with the bias + sine epilogue per layer, activations
-// in device memory between the layers, 65 536 rows at a time.
+// float_layer_kernel: one GEMM on bf16 pieces (fp32 accuracy) with the bias + sine epilogue per layer, activations
+// in device memory between the layers, a chunk of rows at a time.
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <utility>
 #include <vector>
@@ -44,6 +45,11 @@
 #define FLT_TILE (FLT_WAVES * 32)
 #define FLT_AGPR_X 128   // first accumulation register of the activations
 #define FLT_AHEAD 8      // weight groups (of four k steps) in flight
+// Bytes of each of the two activation buffers of the layer-by-layer path: both together stay within the 256 MiB
+// memory-side cache, which is worth more than fewer launches (width 512, 262 144 rows: 3.47 ms in chunks of 32 768 rows = 96 MiB
+// per buffer, 3.68 ms in chunks of 65 536), while narrower networks take as many rows as fit (width 60: 0.24 ms in chunks of
+// 65 536 rows, 0.40 ms in chunks of 32 768).
+#define FLT_ACT_BYTES ((int64_t)96 << 20)
 
 typedef float dhq_v16f __attribute__((ext_vector_type(16)));
 
@@ -65,13 +71,12 @@ struct float_args {
     float_layer_desc layer[DHQ_MAX_LAYERS];
 };
 
-// One layer of the layer-by-layer path: weights as B fragments [M tile][k group J][quarter q][lane]
-// float4, lane (c, kk) holding W[32 T + c][32 J + 16 kk + 4 q + e], e = 0..3 (zero beyond M and K);
-// bias (times omega0 / 2 pi in the sine layers).
+// One layer of the layer-by-layer path: weights as fragments of their three bf16 pieces (see float_layer_kernel), biases
+// [feature tile][lane half][16] (times omega0 / 2 pi where an activation follows).
 struct float_lw_layer {
-    float *wfrag_dev = nullptr;
-    float *bias_dev = nullptr;
-    int K = 0, M = 0, NG = 0, Mt = 0;
+    const unsigned char *wfrag_dev = nullptr;  // inside the plan's lw_blob_dev, like the biases
+    const float *bias_dev = nullptr;
+    int K = 0, M = 0, nkb = 0, Mt = 0;
 };
 
 struct dhq_float_plan {
@@ -84,7 +89,10 @@ struct dhq_float_plan {
     float rev = 0.f;
     dhq_act actf = {DHQ_ACT_KIND_SINE, 0.f};  // what follows every layer but the last
     float_lw_layer lw[DHQ_MAX_LAYERS];
-    float *act[2] = {nullptr, nullptr};  // DHQ_CHUNK x widest layer, fp32
+    unsigned char *lw_blob_dev = nullptr;
+    unsigned char *act[2] = {nullptr, nullptr};  // chunk_rows rows of fragments of the widest layer
+    int64_t chunk_rows = 0;
+    int device = 0;
 };
 
 // ----------------------------------------------------------------------------- device code
@@ -278,111 +286,315 @@ __global__ __launch_bounds__(FLT_THREADS) void dhq_float_kernel(const float_args
 }
 
 // ---------------------------------------------------------------- layer by layer, any shape
-// out = epilogue(in W^T + b) for one layer: in n x K, out n x M, both row-major fp32.  Coordinates
-// are the MFMA row dimension (A operand), features the columns (B operand: the packed weights),
-// so the 32 lanes of a wave half store 128 contiguous bytes of one output row.  A wave takes 32
-// rows and up to FLW_TILES column tiles; k runs in groups of 32: lane (r, kk) reads the sixteen
-// inputs 32 J + 16 kk + i of its row (64 contiguous bytes, so that a row's cache line is fetched
-// once) and feeds them to sixteen MFMAs per tile, MFMA i taking k = 32 J + i and 32 J + 16 + i.
-#define FLW_WAVES 4
-#define FLW_TILES 4
+// One GEMM kernel per layer.  The fp32 MFMA delivers 64 multiply-adds per clock and SIMD, the bf16 one 1024, and three
+// bf16 pieces hold an fp32 value without loss: hi = bf16(a), mid = bf16(a - hi), lo = a - hi - mid (rounded to nearest,
+// 8 significant bits each, both differences exact).  So every product a w is taken as the six bf16 products whose
+// weight is at least 2^-17 of it,
+//     hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi),
+// each exact in the MFMA and summed in fp32.  Left out are mid lo, lo mid and lo lo: at most 2^-24 of |a w| together,
+// half an ulp of the product, with a random sign.  A layer then costs 6 / 16 of the fp32 MFMA time.
+//
+// Layout.  Features are the MFMA M dimension (weights = A operand), coordinates its N dimension, so that a lane's
+// accumulators are half of one coordinate's features and become, split into pieces, that lane's B operands of the next
+// layer without leaving the lane: k block kb = 2 T + b of the next layer takes accumulators 8 b .. 8 b + 7 of tile T, i.e.
+// slot j of lane half h is feature 32 T + 8 (2 b + j / 4) + 4 h + j % 4; the weights are packed in that k order.
+// Activations cross device memory as fragments, [tile of 32 coordinates][k block][piece][lane] x 16 B, weights as
+// [feature tile][k block][piece][lane] x 16 B: every access of a wave is 1 KiB contiguous and goes straight into LDS.
+//
+// A workgroup of WF x WC waves computes WF TF feature tiles x WC TC coordinate tiles, a wave TF x TC of them.
+// Bound by the matrix unit: a 65 536 x 512 x 512 layer takes 173 us = 1.19 PFLOP/s of bf16 products, which is what a large
+// bf16 library product reaches on this card with random operands (1.22-1.35; 1.69 with zeros: the clock follows the
+// operands).  The fp32 MFMA form of this kernel took 370 us.  Error against fp64 at width 512, six layers: 3.4e-8 rms
+// (1.7e-7 largest) against 3.9e-8 (1.9e-7) for the fp32 MFMA, which rounds after every two products instead of every sixteen.
+typedef __bf16 flt_v8b __attribute__((ext_vector_type(8)));
+typedef __bf16 flt_v2b __attribute__((ext_vector_type(2)));
 
-// NTT: column tiles per wave (NTT, or all of a layer with fewer: its few tiles then cost no more than their own MFMAs).
-template <int ACT, int NTT>
-__global__ __launch_bounds__(64 * FLW_WAVES) void float_layer_kernel(const float *__restrict__ in, int64_t n, int K, int NG,
-                                                                     int vec, const float4 *__restrict__ wfrag, int M, int Mt,
-                                                                     const float *__restrict__ bias, float rev, float c2,
-                                                                     float *__restrict__ out)
+__device__ __forceinline__ unsigned flt_pack_bf16(float a, float b)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & 31, h = lane >> 5;
-    // wave-uniform, so that the row part of every store address is scalar arithmetic
-    const int64_t row0 = ((int64_t)blockIdx.x * FLW_WAVES + __builtin_amdgcn_readfirstlane(wave)) * 32;
-    if (row0 >= n) return;  // no barrier below
-    const int T0 = blockIdx.y * NTT;
-    const int nt = (Mt - T0 < NTT) ? Mt - T0 : NTT;
-    const int64_t arow = (row0 + c < n) ? row0 + c : n - 1;  // rows past the end repeat the last one and are not stored
-    const float *ap = in + arow * K;
-    dhq_v16f acc[NTT];
+    const flt_v2b p = {(__bf16)a, (__bf16)b};  // one packed conversion, rounded to nearest even
+    return __builtin_bit_cast(unsigned, p);
+}
+// The three bf16 pieces of two values, value 0 in the low halves.
+__device__ __forceinline__ void flt_split3(float a0, float a1, unsigned &hi, unsigned &mid, unsigned &lo)
+{
+    hi = flt_pack_bf16(a0, a1);
+    const float r0 = a0 - __uint_as_float(hi << 16), r1 = a1 - __uint_as_float(hi & 0xffff0000u);
+    mid = flt_pack_bf16(r0, r1);
+    lo = flt_pack_bf16(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
+}
+// Eight values to a lane's 16 bytes of each of the three fragments at dst, dst + 1 KiB, dst + 2 KiB.
+__device__ __forceinline__ void flt_store_pieces(const float (&y)[8], unsigned char *__restrict__ dst)
+{
+    uint4 hi, mid, lo;
+    flt_split3(y[0], y[1], hi.x, mid.x, lo.x);
+    flt_split3(y[2], y[3], hi.y, mid.y, lo.y);
+    flt_split3(y[4], y[5], hi.z, mid.z, lo.z);
+    flt_split3(y[6], y[7], hi.w, mid.w, lo.w);
+    *reinterpret_cast<uint4 *>(dst) = hi;
+    *reinterpret_cast<uint4 *>(dst + 1024) = mid;
+    *reinterpret_cast<uint4 *>(dst + 2048) = lo;
+}
+
+// The six products of one k block, small ones first; w, x: {hi, mid, lo}.
+__device__ __forceinline__ dhq_v16f flt_mfma6(const dhq_v4i (&w)[3], const dhq_v4i (&x)[3], dhq_v16f acc)
+{
+    constexpr int pw[6] = {0, 2, 1, 0, 1, 0}, px[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-    for (int t = 0; t < NTT; ++t)
+    for (int i = 0; i < 6; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w[pw[i]]), __builtin_bit_cast(flt_v8b, x[px[i]]), acc, 0, 0, 0);
+    return acc;
+}
+
+// The network's input: n x K row-major fp32 to fragments in natural k order (slot j of lane half h of block kb is
+// k = 16 kb + 8 h + j; zero beyond K and n).  One wave per tile and k block.
+__global__ __launch_bounds__(256) void float_pack_kernel(const float *__restrict__ in, int64_t n, int K, int nkb, int64_t n_frag,
+                                                         unsigned char *__restrict__ out)
+{
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (w >= n_frag) return;
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int64_t ct = w / nkb, row = ct * 32 + c;
+    const int k0 = 16 * (int)(w - ct * nkb) + 8 * h;
+    float y[8];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-    // this lane's sixteen inputs of k group J (zero beyond K): 64 contiguous bytes of its row
-    auto load_a = [&](int J, float4 (&a)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int k0 = 32 * J + 16 * h + 4 * q;
-            if (vec && k0 + 3 < K) {
-                a[q] = *reinterpret_cast<const float4 *>(ap + k0);
-            } else {
-                a[q].x = (k0 < K) ? ap[k0] : 0.f;
-                a[q].y = (k0 + 1 < K) ? ap[k0 + 1] : 0.f;
-                a[q].z = (k0 + 2 < K) ? ap[k0 + 2] : 0.f;
-                a[q].w = (k0 + 3 < K) ? ap[k0 + 3] : 0.f;
-            }
-        }
-    };
-    // tiles past the layer's last one re-read the last one's weights; their results are dropped
-    const float4 *wp[NTT];
-#pragma unroll
-    for (int t = 0; t < NTT; ++t) wp[t] = wfrag + (size_t)(T0 + (t < nt ? t : nt - 1)) * NG * 4 * 64 + lane;
-    float4 a[4], w[NTT];
-    load_a(0, a);
-#pragma unroll
-    for (int t = 0; t < NTT; ++t) w[t] = wp[t][0];
-    for (int J = 0; J < NG; ++J) {
-        // the next operands are fetched while the current MFMAs run (inputs one group of 32 k ahead, weights
-        // one quarter group ahead); consecutive MFMAs go to different accumulators
-        const int Jn = (J + 1 < NG) ? J + 1 : J;
-        float4 an[4];
-        load_a(Jn, an);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int nxt = (q < 3) ? 4 * J + q + 1 : 4 * Jn;
-            float4 wn[NTT];
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) wn[t] = wp[t][(size_t)nxt * 64];
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].x, w[t].x, acc[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].y, w[t].y, acc[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].z, w[t].z, acc[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].w, w[t].w, acc[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < NTT; ++t) w[t] = wn[t];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) a[q] = an[q];
+    for (int j = 0; j < 8; ++j) y[j] = (row < n && k0 + j < K) ? in[row * K + k0 + j] : 0.f;
+    flt_store_pieces(y, out + (size_t)w * 3072 + lane * 16);
+}
+
+struct float_layer_args {
+    const unsigned char *in;   // activations, [n_ct][nkb][3] KiB
+    const unsigned char *w;    // weights, [n_ft][nkb][3] KiB
+    const float *bias;         // [n_ft][lane half][16], times omega0 / 2 pi where a sine follows
+    unsigned char *out;        // activations, [n_ct][2 n_ft][3] KiB
+    int n_ct, n_ft, nkb;       // nkb: even
+    int nF, nC;                // workgroups over the features and over the coordinates
+    float rev, c2;
+};
+
+// 1 KiB from device memory straight into LDS (as fused_issue_copy does): src and dst wave-uniform, voff = lane * 16.
+__device__ __forceinline__ void flt_copy_kib(unsigned voff, const unsigned char *src, unsigned dst)
+{
+    const unsigned long long a = (unsigned long long)src;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    const unsigned long long sa = ((unsigned long long)hi << 32) | lo;
+    const unsigned m0v = __builtin_amdgcn_readfirstlane(dst);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sa), "s"(m0v) : "memory", "m0");
+}
+
+// Waits for every load of this wave.  The builtin, not inline assembly: the compiler then knows that the activations it
+// loaded one stage ago have arrived and does not wait for the loads that were issued since.
+__device__ __forceinline__ void flt_wait_loads()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unrestricted
+    asm volatile("" ::: "memory");
+}
+
+// KS: k blocks per stage.  The weights of a stage go through LDS, shared by the WC waves of a row of tiles, in three
+// buffers: while stage s computes, stage s + 2 is copied in, and the barrier in front of stage s says that s + 1 is in place,
+// so that its first fragments are fetched before stage s ends.  The activations of a tile are used by WF waves only and
+// go straight into registers, one stage ahead.  A stage's requests are spread over its MFMAs: all at its start, the
+// 64 KiB a CU asks for there keep its memory pipeline busy for 1 kclk, in which no wave gets to its MFMAs.
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
+struct float_layer_tile {
+    static constexpr int NW = WF * WC, FT = WF * TF, CT = WC * TC;
+    static constexpr int BLOCKS = 3 * FT * KS;  // KiB of weights per stage: [feature tile][k block][piece]
+    static constexpr int PER_WAVE = (BLOCKS + NW - 1) / NW;
+    static constexpr int NX = 3 * TC * KS, REQUESTS = NX + PER_WAVE;  // per stage and wave
+    static constexpr int NI = KS * TF, GROUPS = 6 * NI;               // steps of a stage, groups of TC MFMAs
+    const float_layer_args &A;
+    const unsigned char *lds;
+    unsigned lds0, voff;
+    int lane, wave, wf, wc, f0, c0, n_stages;
+    const unsigned char *src[PER_WAVE];
+    const unsigned char *xsrc[TC];
+    dhq_v4i x[2][TC][KS][3], w[2][3];
+    dhq_v16f acc[TF][TC];
+    __device__ __forceinline__ float_layer_tile(const float_layer_args &A_) : A(A_) {}
+
+    // 1 KiB of the weights of stage s, this wave's i-th, into buffer buf; nothing past the last k block
+    template <int I>
+    __device__ __forceinline__ void copy_weights(int s, int buf)
+    {
+        const int q = wave + I * NW;
+        if ((BLOCKS % NW != 0 && q >= BLOCKS) || s * KS + (KS > 1 ? (q / 3) % KS : 0) >= A.nkb) return;
+        flt_copy_kib(voff, src[I] + (size_t)s * (3072 * KS), lds0 + (buf * BLOCKS + q) * 1024);
     }
-    // accumulator v of a lane: row row0 + 8 (v / 4) + 4 h + v % 4, feature 32 (T0 + t) + c; a store address is a
-    // scalar base (row, tile) plus the lane's constant offset; whole 32-row blocks skip the row checks
-    const int nrows = (n - row0 < 32) ? (int)(n - row0) : 32;
-    const bool full = (nrows == 32);
-    const unsigned loff = (unsigned)(4 * h * M + c);
-    auto epi = [&](float a, float bf) {
-        return ACT != DHQ_ACT_KIND_NONE ? dhq_activate_rev_any(__builtin_fmaf(a, rev, bf), dhq_act{ACT, c2}) : a + bf;
-    };
+    // the I-th fragment of the activations of stage s (past the last k block: the last one again, not used)
+    template <int XB, int I>
+    __device__ __forceinline__ void load_x(int s)
+    {
+        constexpr int k = I / (3 * TC), c = (I / 3) % TC, p = I % 3;
+        const int kb = s * KS + k < A.nkb ? s * KS + k : A.nkb - 1;
+        x[XB][c][k][p] = *reinterpret_cast<const dhq_v4i *>(xsrc[c] + (size_t)(kb * 3 + p) * 1024 + voff);
+    }
+    template <int XB, int... I>
+    __device__ __forceinline__ void load_x_all(int s, std::integer_sequence<int, I...>) { (load_x<XB, I>(s), ...); }
+    template <int... I>
+    __device__ __forceinline__ void copy_weights_all(int s, int buf, std::integer_sequence<int, I...>) { (copy_weights<I>(s, buf), ...); }
+    template <int WB>
+    __device__ __forceinline__ void load_w(int buf, int k, int f)
+    {
+        const dhq_v4i *b = reinterpret_cast<const dhq_v4i *>(lds + buf * BLOCKS * 1024) + lane;
 #pragma unroll
-    for (int t = 0; t < NTT; ++t) {
-        if (t < nt) {
-            const int f = 32 * (T0 + t) + c;
-            if (f < M) {
-                const float bf = bias[f];
-                float *tile_out = out + (size_t)row0 * M + (size_t)(T0 + t) * 32;  // wave-uniform
-                if (full) {
+        for (int p = 0; p < 3; ++p) w[WB][p] = b[(((wf * TF + f) * KS + k) * 3 + p) * 64];
+    }
+    // Request R of stage s, issued in front of MFMA group G: the activations first.
+    template <int S, int G, int R>
+    __device__ __forceinline__ void request(int s, int b2)
+    {
+        if constexpr (R < REQUESTS) {
+            if constexpr (R * (3 * GROUPS / 4) / REQUESTS == G) {
+                if constexpr (R < NX) load_x<S ^ 1, R>(s + 1);
+                else copy_weights<R - NX>(s + 2, b2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            request<S, G, R + 1>(s, b2);
+        }
+    }
+    // Group G of stage s: product G % 6 (small ones first) of step G / 6 for this wave's TC coordinate tiles.
+    template <int S, int G>
+    __device__ __forceinline__ void group(int s, int b0, int b1, int b2)
+    {
+        constexpr int I = G / 6, i = G % 6, k = I / TF, f = I % TF, wb = (S * NI + I) & 1;
+        constexpr int pw[6] = {0, 2, 1, 0, 1, 0}, px[6] = {2, 0, 1, 1, 0, 0};
+        if constexpr (i == 0) {  // the next step's weight fragments
+            if constexpr (I + 1 < NI) load_w<wb ^ 1>(b0, (I + 1) / TF, (I + 1) % TF);
+            else load_w<wb ^ 1>(b1, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        request<S, G, 0>(s, b2);
+        if (KS == 1 || s * KS + k < A.nkb) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        (tile_out + (size_t)(8 * (v >> 2) + (v & 3)) * M)[loff] = epi(acc[t][v], bf);
-                } else {
+            for (int c = 0; c < TC; ++c)
+                acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w[wb][pw[i]]),
+                                                                    __builtin_bit_cast(flt_v8b, x[S][c][k][px[i]]), acc[f][c], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (G + 1 < GROUPS) group<S, G + 1>(s, b0, b1, b2);
+    }
+    // Stage s (its weights in buffer b0, the next one's in b1, the one after that goes to b2); S: parity of s.
+    template <int S>
+    __device__ __forceinline__ void stage(int s, int b0, int b1, int b2)
+    {
+        flt_wait_loads();
+        __syncthreads();
+        group<S, 0>(s, b0, b1, b2);
+    }
+};
+
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
+__global__ __launch_bounds__(64 * WF * WC) void float_layer_kernel(const float_layer_args A)
+{
+    using tile_t = float_layer_tile<ACT, WF, WC, TF, TC, KS>;
+    extern __shared__ __align__(16) unsigned char lds[];
+    tile_t R(A);
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    R.lane = lane;
+    R.voff = lane * 16;
+    R.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    R.wf = R.wave % WF;
+    R.wc = R.wave / WF;
+    // consecutive workgroups go to the eight XCDs in turn: the workgroups that read the same coordinates get the same
+    // XCD, so that all but the first find them in its L2
+    const int xcd = blockIdx.x & 7, rest = blockIdx.x >> 3;
+    const int fb = rest % A.nF, cb = (rest / A.nF) * 8 + xcd;
+    if (cb >= A.nC) return;  // the whole workgroup: no barrier has been reached
+    R.f0 = fb * tile_t::FT;
+    R.c0 = cb * tile_t::CT;
+    R.lds = lds;
+    R.lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    R.n_stages = (A.nkb + KS - 1) / KS;
+    // this wave's share of a stage's weights: 1 KiB blocks wave, wave + NW, ...; tiles past the last one are read again
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (8 * (v >> 2) + (v & 3) + 4 * h < nrows) (tile_out + (size_t)(8 * (v >> 2) + (v & 3)) * M)[loff] = epi(acc[t][v], bf);
-                }
+    for (int i = 0; i < tile_t::PER_WAVE; ++i) {
+        const int q = R.wave + i * tile_t::NW, t = q / (3 * KS), r = q % (3 * KS);
+        const int f = R.f0 + t < A.n_ft ? R.f0 + t : A.n_ft - 1;
+        R.src[i] = A.w + ((size_t)f * A.nkb * 3 + r) * 1024;
+    }
+#pragma unroll
+    for (int c = 0; c < TC; ++c) {
+        const int ct = R.c0 + R.wc * TC + c < A.n_ct ? R.c0 + R.wc * TC + c : A.n_ct - 1;
+        R.xsrc[c] = A.in + (size_t)ct * A.nkb * 3072;
+    }
+#pragma unroll
+    for (int f = 0; f < TF; ++f)
+#pragma unroll
+        for (int c = 0; c < TC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) R.acc[f][c][v] = 0.f;
+    R.copy_weights_all(0, 0, std::make_integer_sequence<int, tile_t::PER_WAVE>{});
+    R.copy_weights_all(1, 1, std::make_integer_sequence<int, tile_t::PER_WAVE>{});
+    R.template load_x_all<0>(0, std::make_integer_sequence<int, tile_t::NX>{});
+    flt_wait_loads();
+    __syncthreads();
+    R.template load_w<0>(0, 0, 0);
+    int b0 = 0, b1 = 1, b2 = 2;
+    for (int s = 0; s < R.n_stages; s += 2) {
+        R.template stage<0>(s, b0, b1, b2);
+        R.template stage<1>(s + 1, b1, b2, b0);  // (an odd count: the last one computes nothing)
+        const int t = b0;  // two stages on: b0, b1, b2 -> b2, b0, b1
+        b0 = b2; b2 = b1; b1 = t;
+    }
+#pragma unroll
+    for (int f = 0; f < TF; ++f) {
+        const int T = R.f0 + R.wf * TF + f;
+        if (T >= A.n_ft) break;
+        float bias[16];
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) *reinterpret_cast<float4 *>(&bias[v]) = *reinterpret_cast<const float4 *>(A.bias + (T * 2 + h) * 16 + v);
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+            const int ct = R.c0 + R.wc * TC + c;
+            if (ct >= A.n_ct) break;
+            unsigned char *dst = A.out + ((size_t)ct * A.n_ft + T) * 6144 + lane * 16;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                float y[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    y[j] = dhq_activate_rev_any(__builtin_fmaf(R.acc[f][c][8 * b + j], A.rev, bias[8 * b + j]), dhq_act{ACT, A.c2});
+                flt_store_pieces(y, dst + b * 3072);
             }
         }
+    }
+}
+
+// The output layer: one tile of 32 features x 32 coordinates per wave, fragments straight from device memory (each is
+// used once), no activation; bound by reading the activations.
+__global__ __launch_bounds__(256) void float_out_kernel(const unsigned char *__restrict__ in, const unsigned char *__restrict__ wfrag,
+                                                        const float *__restrict__ bias, int64_t n, int n_ct, int nkb, int M,
+                                                        float *__restrict__ out)
+{
+    const int ct = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), T = blockIdx.y;
+    if (ct >= n_ct) return;
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const dhq_v4i *xp = reinterpret_cast<const dhq_v4i *>(in + (size_t)ct * nkb * 3072) + lane;
+    const dhq_v4i *wp = reinterpret_cast<const dhq_v4i *>(wfrag + (size_t)T * nkb * 3072) + lane;
+    dhq_v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int kb0 = 0; kb0 < nkb; kb0 += 4) {
+        dhq_v4i x[4][3], w[4][3];  // four k blocks in flight; blocks past the last one are read again and not used
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int kb = kb0 + i < nkb ? kb0 + i : nkb - 1;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                x[i][p] = xp[(kb * 3 + p) * 64];
+                w[i][p] = wp[(kb * 3 + p) * 64];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (kb0 + i < nkb) acc = flt_mfma6(w[i], x[i], acc);
+    }
+    const int64_t row = (int64_t)ct * 32 + c;
+    if (row >= n) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int f = 32 * T + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (f < M) out[row * M + f] = acc[v] + bias[(T * 2 + h) * 16 + v];
     }
 }
 
@@ -425,6 +637,7 @@ int dhq_float_create(const int *dims, int L, float omega0, dhq_act act, const st
         return DHQ_EHIP;
     }
     P->n_cu = prop.multiProcessorCount;
+    P->device = device;
     int rc = float_create_layerwise(P, dims, L, rev, W, b);
     if (rc == DHQ_OK && dhq_float_shape_ok(dims, L)) rc = float_create_fused(P, dims, L, rev, W, b);
     if (rc != DHQ_OK) {
@@ -498,37 +711,89 @@ static int float_create_fused(dhq_float_plan *P, const int *dims, int L, double 
     return DHQ_OK;
 }
 
+// The three bf16 pieces of an fp32 value (nearest even; a value whose first piece would round beyond the largest bf16 is
+// truncated instead).
+static uint16_t host_bf16(float v)
+{
+    uint32_t u;
+    memcpy(&u, &v, 4);
+    uint32_t r = u + 0x7fffu + ((u >> 16) & 1u);
+    if (((r >> 23) & 0xffu) == 0xffu) r = u;
+    return (uint16_t)(r >> 16);
+}
+static float host_from_bf16(uint16_t b)
+{
+    const uint32_t u = (uint32_t)b << 16;
+    float v;
+    memcpy(&v, &u, 4);
+    return v;
+}
+// A row of n values as three rows of pieces.
+static void host_split3(const float *a, int n, uint16_t *hi, uint16_t *mid, uint16_t *lo)
+{
+    for (int i = 0; i < n; ++i) {
+        float r = a[i];
+        hi[i] = host_bf16(r);
+        r -= host_from_bf16(hi[i]);
+        mid[i] = host_bf16(r);
+        lo[i] = host_bf16(r - host_from_bf16(mid[i]));
+    }
+}
+
 // Fragments, biases and the two activation buffers of the layer-by-layer path.
 static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, double rev, const std::vector<std::vector<float>> &W,
                                   const std::vector<std::vector<float>> &b)
 {
-    int max_dim = 1;
-    for (int l = 0; l <= L; ++l) max_dim = dims[l] > max_dim ? dims[l] : max_dim;
+    int max_nkb = 1;
+    size_t w_off[DHQ_MAX_LAYERS], b_off[DHQ_MAX_LAYERS], bytes = 0;
     for (int l = 0; l < L; ++l) {
         float_lw_layer &Ly = P->lw[l];
         Ly.K = dims[l];
         Ly.M = dims[l + 1];
-        Ly.NG = (Ly.K + 31) / 32;
+        Ly.nkb = (l == 0) ? (Ly.K + 31) / 32 * 2 : 2 * P->lw[l - 1].Mt;  // even
         Ly.Mt = (Ly.M + 31) / 32;
-        std::vector<float> frag((size_t)Ly.Mt * Ly.NG * 4 * 64 * 4, 0.0f);
-        for (int T = 0; T < Ly.Mt; ++T)
-            for (int J = 0; J < Ly.NG; ++J)
-                for (int q = 0; q < 4; ++q)
-                    for (int ln = 0; ln < 64; ++ln)
-                        for (int e = 0; e < 4; ++e) {
-                            const int row = 32 * T + (ln & 31), k = 32 * J + 16 * (ln >> 5) + 4 * q + e;
-                            if (row < Ly.M && k < Ly.K)
-                                frag[((((size_t)T * Ly.NG + J) * 4 + q) * 64 + ln) * 4 + e] = W[l][(size_t)row * Ly.K + k];
-                        }
-        std::vector<float> bias(Ly.M);
-        for (int f = 0; f < Ly.M; ++f) bias[f] = (l != L - 1) ? (float)((double)b[l][f] * rev) : b[l][f];
-        if (hipMalloc((void **)&Ly.wfrag_dev, sizeof(float) * frag.size()) != hipSuccess) return DHQ_ENOMEM;
-        if (hipMalloc((void **)&Ly.bias_dev, sizeof(float) * bias.size()) != hipSuccess) return DHQ_ENOMEM;
-        if (hipMemcpy(Ly.wfrag_dev, frag.data(), sizeof(float) * frag.size(), hipMemcpyHostToDevice) != hipSuccess) return DHQ_EHIP;
-        if (hipMemcpy(Ly.bias_dev, bias.data(), sizeof(float) * bias.size(), hipMemcpyHostToDevice) != hipSuccess) return DHQ_EHIP;
+        if (Ly.nkb > max_nkb) max_nkb = Ly.nkb;
+        w_off[l] = bytes;
+        b_off[l] = bytes + (size_t)Ly.Mt * Ly.nkb * 3072;
+        bytes = (b_off[l] + (size_t)Ly.Mt * 128 + 1023) / 1024 * 1024;
     }
-    for (int i = 0; i < 2; ++i)
-        if (hipMalloc((void **)&P->act[i], sizeof(float) * (size_t)DHQ_CHUNK * max_dim) != hipSuccess) return DHQ_ENOMEM;
+    std::vector<unsigned char> blob(bytes, 0);
+    for (int l = 0; l < L; ++l) {
+        const float_lw_layer &Ly = P->lw[l];
+        uint16_t *frag = reinterpret_cast<uint16_t *>(blob.data() + w_off[l]);
+        std::vector<uint16_t> pieces((size_t)3 * Ly.nkb * 16, 0);  // of one row, zero beyond K
+        for (int f = 0; f < Ly.M; ++f) {
+            uint16_t *row[3] = {pieces.data(), pieces.data() + Ly.nkb * 16, pieces.data() + 2 * Ly.nkb * 16};
+            host_split3(W[l].data() + (size_t)f * Ly.K, Ly.K, row[0], row[1], row[2]);
+            for (int kb = 0; kb < Ly.nkb; ++kb)
+                for (int h = 0; h < 2; ++h) {
+                    // slots 0..3 and 4..7 of a lane are four consecutive k each
+                    const int k0 = (l == 0) ? 16 * kb + 8 * h : flt_feature(8 * kb, h), k4 = (l == 0) ? k0 + 4 : flt_feature(8 * kb + 4, h);
+                    uint16_t *dst = frag + ((size_t)((f >> 5) * Ly.nkb + kb) * 3 * 64 + 32 * h + (f & 31)) * 8;
+                    for (int p = 0; p < 3; ++p) {
+                        memcpy(dst + (size_t)p * 512, row[p] + k0, 8);
+                        memcpy(dst + (size_t)p * 512 + 4, row[p] + k4, 8);
+                    }
+                }
+        }
+        float *bias = reinterpret_cast<float *>(blob.data() + b_off[l]);
+        for (int T = 0; T < Ly.Mt; ++T)
+            for (int h = 0; h < 2; ++h)
+                for (int v = 0; v < 16; ++v) {
+                    const int f = flt_feature(16 * T + v, h);
+                    if (f < Ly.M) bias[(size_t)(T * 2 + h) * 16 + v] = (l != L - 1) ? (float)((double)b[l][f] * rev) : b[l][f];
+                }
+    }
+    if (hipMalloc((void **)&P->lw_blob_dev, bytes) != hipSuccess) return DHQ_ENOMEM;
+    if (hipMemcpy(P->lw_blob_dev, blob.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return DHQ_EHIP;
+    for (int l = 0; l < L; ++l) {
+        P->lw[l].wfrag_dev = P->lw_blob_dev + w_off[l];
+        P->lw[l].bias_dev = reinterpret_cast<const float *>(P->lw_blob_dev + b_off[l]);
+    }
+    P->chunk_rows = (FLT_ACT_BYTES / ((int64_t)max_nkb * 3072) * 32) / 256 * 256;
+    const size_t act_bytes = (size_t)(P->chunk_rows / 32) * max_nkb * 3072;
+    if (hipMalloc((void **)&P->act[0], 2 * act_bytes) != hipSuccess) return DHQ_ENOMEM;
+    P->act[1] = P->act[0] + act_bytes;
     return DHQ_OK;
 }
 
@@ -536,56 +801,83 @@ void dhq_float_destroy(dhq_float_plan *P)
 {
     if (!P) return;
     if (P->blob_dev) (void)hipFree(P->blob_dev);
-    for (int l = 0; l < DHQ_MAX_LAYERS; ++l) {
-        if (P->lw[l].wfrag_dev) (void)hipFree(P->lw[l].wfrag_dev);
-        if (P->lw[l].bias_dev) (void)hipFree(P->lw[l].bias_dev);
-    }
-    for (int i = 0; i < 2; ++i)
-        if (P->act[i]) (void)hipFree(P->act[i]);
+    if (P->lw_blob_dev) (void)hipFree(P->lw_blob_dev);
+    if (P->act[0]) (void)hipFree(P->act[0]);
     delete P;
 }
 
 bool dhq_float_has_fused(const dhq_float_plan *P) { return P && P->nf != 0; }
 
-template <int ACT>
-static void float_layer_launch_act(int ntt, float c2, dim3 grid, hipStream_t st, const float *in, int64_t n, int K, int NG, int vec,
-                                   const float4 *wf, int M, int Mt, const float *bias, float rev, float *out)
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
+static hipError_t float_layer_launch_t(float_layer_args a, int device, hipStream_t st)
 {
-    switch (ntt) {
-        case 1: float_layer_kernel<ACT, 1><<<grid, 64 * FLW_WAVES, 0, st>>>(in, n, K, NG, vec, wf, M, Mt, bias, rev, c2, out); break;
-        case 2: float_layer_kernel<ACT, 2><<<grid, 64 * FLW_WAVES, 0, st>>>(in, n, K, NG, vec, wf, M, Mt, bias, rev, c2, out); break;
-        case 3: float_layer_kernel<ACT, 3><<<grid, 64 * FLW_WAVES, 0, st>>>(in, n, K, NG, vec, wf, M, Mt, bias, rev, c2, out); break;
-        default: float_layer_kernel<ACT, FLW_TILES><<<grid, 64 * FLW_WAVES, 0, st>>>(in, n, K, NG, vec, wf, M, Mt, bias, rev, c2, out); break;
-    }
+    using tile_t = float_layer_tile<ACT, WF, WC, TF, TC, KS>;
+    auto kern = float_layer_kernel<ACT, WF, WC, TF, TC, KS>;
+    const size_t lds = (size_t)3 * tile_t::BLOCKS * 1024;
+    const hipError_t e = dhq_lds_limit_once(kern, lds, device);
+    if (e != hipSuccess) return e;
+    a.nF = (a.n_ft + tile_t::FT - 1) / tile_t::FT;
+    a.nC = (a.n_ct + tile_t::CT - 1) / tile_t::CT;
+    kern<<<(unsigned)((a.nC + 7) / 8 * 8 * a.nF), 64 * WF * WC, lds, st>>>(a);
+    return hipGetLastError();
 }
-static void float_layer_launch(int ntt, dhq_act act, dim3 grid, hipStream_t st, const float *in, int64_t n, int K, int NG, int vec,
-                               const float4 *wf, int M, int Mt, const float *bias, float rev, float *out)
+
+// The tile shape (features x coordinates of a workgroup) with the least time for its fullest CU: workgroups per CU, rounded
+// up, times what one costs in MFMA tiles.  The cost of a tile is 1 where a workgroup computes 128 x 256 (the fewest LDS and
+// L2 bytes per MFMA), 1.2 at 64 x 256 and 128 x 128, 2 at 128 x 32.  Measured, whole forwards in us, for the four in that order:
+//   width 512 x 65 536 rows  559  605  603  891        width 300 x 33 000 rows  167  155  184  244
+//   width 512 x 9 000 rows   139  139  139  160        width 100 x 100 000 rows 118  135  136  160
+//   width 512 x 4 000 rows   137   96   98   84        width 48 x 100 000 rows   76   71   91  110
+template <int ACT>
+static hipError_t float_layer_launch(const float_layer_args &a, int n_cu, int device, hipStream_t st)
 {
-    if (act.kind == DHQ_ACT_KIND_SINE) float_layer_launch_act<DHQ_ACT_KIND_SINE>(ntt, 0.f, grid, st, in, n, K, NG, vec, wf, M, Mt, bias, rev, out);
-    else if (act.kind == DHQ_ACT_KIND_WAVELET) float_layer_launch_act<DHQ_ACT_KIND_WAVELET>(ntt, act.c2, grid, st, in, n, K, NG, vec, wf, M, Mt, bias, rev, out);
-    else float_layer_launch_act<DHQ_ACT_KIND_NONE>(ntt, 0.f, grid, st, in, n, K, NG, vec, wf, M, Mt, bias, rev, out);
+    const int64_t f4 = (a.n_ft + 3) / 4, f2 = (a.n_ft + 1) / 2, c8 = (a.n_ct + 7) / 8, c4 = (a.n_ct + 3) / 4;
+    auto cost = [&](int64_t workgroups, int64_t each) { return (workgroups + n_cu - 1) / n_cu * each; };
+    const int64_t c128x256 = cost(f4 * c8, 32), c64x256 = cost(f2 * c8, 19), c128x128 = cost(f4 * c4, 19), c128x32 = cost(f4 * a.n_ct, 8);
+    const int64_t least = std::min(std::min(c128x256, c64x256), std::min(c128x128, c128x32));
+    if (c128x32 == least) return float_layer_launch_t<ACT, 4, 1, 1, 1, 2>(a, device, st);
+    if (c128x128 == least) return float_layer_launch_t<ACT, 2, 2, 2, 2, 2>(a, device, st);
+    if (c64x256 == least) return float_layer_launch_t<ACT, 1, 4, 2, 2, 2>(a, device, st);
+    return float_layer_launch_t<ACT, 1, 4, 4, 2, 1>(a, device, st);
 }
 
 hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
     const int L = P->n_layers;
-    for (int64_t start = 0; start < n; start += DHQ_CHUNK) {
-        const int64_t rows = (n - start < DHQ_CHUNK) ? n - start : DHQ_CHUNK;
-        const float *cur = coords + start * P->lw[0].K;
+    if (n <= 0) return hipSuccess;
+    // as few chunks as the buffers allow, of equal size
+    const int64_t chunks = (n + P->chunk_rows - 1) / P->chunk_rows, per = (n + chunks - 1) / chunks, step = (per + 255) / 256 * 256;
+    for (int64_t start = 0; start < n; start += step) {
+        const int64_t rows = (n - start < step) ? n - start : step;
+        const int n_ct = (int)((rows + 31) / 32);
+        const int64_t n_frag = (int64_t)n_ct * P->lw[0].nkb;
+        float_pack_kernel<<<(unsigned)((n_frag + 3) / 4), 256, 0, st>>>(coords + start * P->lw[0].K, rows, P->lw[0].K, P->lw[0].nkb, n_frag,
+                                                                        P->act[0]);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         for (int l = 0; l < L; ++l) {
             const float_lw_layer &Ly = P->lw[l];
-            float *dst = (l == L - 1) ? out + start * Ly.M : P->act[l & 1];
-            const int ntt = Ly.Mt < FLW_TILES ? Ly.Mt : FLW_TILES;  // column tiles per wave
-            const dim3 grid((unsigned)((rows + 32 * FLW_WAVES - 1) / (32 * FLW_WAVES)), (unsigned)((Ly.Mt + ntt - 1) / ntt));
-            // one 16-byte load per lane needs rows that start on 16-byte boundaries
-            const int vec = (Ly.K % 4 == 0 && ((uintptr_t)cur & 15) == 0) ? 1 : 0;
-            const float4 *wf = reinterpret_cast<const float4 *>(Ly.wfrag_dev);
-            const dhq_act act = (l == L - 1) ? dhq_act{DHQ_ACT_KIND_NONE, 0.f} : P->actf;
-            float_layer_launch(ntt, act, grid, st, cur, rows, Ly.K, Ly.NG, vec, wf, Ly.M, Ly.Mt, Ly.bias_dev, P->rev, dst);
-            const hipError_t e = hipGetLastError();
+            if (l == L - 1) {
+                const dim3 grid((unsigned)((n_ct + 3) / 4), (unsigned)Ly.Mt);
+                float_out_kernel<<<grid, 256, 0, st>>>(P->act[l & 1], Ly.wfrag_dev, Ly.bias_dev, rows, n_ct, Ly.nkb, Ly.M, out + start * Ly.M);
+                e = hipGetLastError();
+            } else {
+                float_layer_args a;
+                memset(&a, 0, sizeof(a));
+                a.in = P->act[l & 1];
+                a.out = P->act[(l + 1) & 1];
+                a.w = Ly.wfrag_dev;
+                a.bias = Ly.bias_dev;
+                a.n_ct = n_ct;
+                a.n_ft = Ly.Mt;
+                a.nkb = Ly.nkb;
+                a.rev = P->rev;
+                a.c2 = P->actf.c2;
+                e = P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_layer_launch<DHQ_ACT_KIND_WAVELET>(a, P->n_cu, P->device, st)
+                                                         : float_layer_launch<DHQ_ACT_KIND_SINE>(a, P->n_cu, P->device, st);
+            }
             if (e != hipSuccess) return e;
-            cur = dst;
         }
     }
     return hipSuccess;

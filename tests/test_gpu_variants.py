@@ -871,3 +871,32 @@ def test_forward_replays_from_a_captured_graph(variant):
         assert np.array_equal(out.cpu().numpy(), eager.cpu().numpy()), f"replay {rep}"
         assert bool(torch.isfinite(scratch).all())
     m.close()
+
+
+@pytest.mark.parametrize("width,n", [(33, 100001), (100, 20011), (200, 75009), (512, 33003), (512, 4001), (65, 31)])
+def test_float_layer_tile_shapes_and_chunks(width, n):
+    """The layer-by-layer fp32 path on sizes that reach each of its tile shapes (64 x 256, 128 x 128, 128 x 256, 128 x 32),
+    with partial tiles of features and coordinates and more than one chunk: within the tolerance of the oracle at
+    the first and last rows and at random ones, and the same bits in a call of a few hundred rows (another tile shape: every
+    shape adds a sum's terms in the same order)."""
+    torch = _torch()
+    dims = [2, width, width, width, 3]
+    _say(f"float tiles width {width} n={n}")
+    W, b = synth.siren_init(dims, 30.0, 4000 + width)
+    rng = np.random.default_rng(width + n)
+    x = rng.uniform(-1, 1, size=(n, 2)).astype(np.float32)
+    idx = np.unique(np.concatenate([np.arange(min(n, 130)), np.arange(max(0, n - 130), n), rng.integers(0, n, 300)]))
+    m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32)
+    out = m.forward(_dev(x), flags=dhq.DHQ_LAYERWISE)
+    sub = m.forward(_dev(x[idx]), flags=dhq.DHQ_LAYERWISE)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out).all())
+    got = out.cpu().numpy()[idx]
+    assert np.array_equal(sub.cpu().numpy(), got)
+    exp, _ = o.mlp_float(dims, 30.0, W, b, x[idx])
+    err = np.abs(got.astype(np.float64) - exp).max()
+    _say(f"  max-abs err {err:.2e}")
+    # per layer a sine argument of at most 8 revolutions is off by 2^-24 of its size per rounding of the sum's last terms
+    # (3e-6 rad); the output layer's weights (at most sqrt(6 / 512) / 30) average it down: the bound of the other tests
+    assert err <= FLOAT_TOL_WIDE
+    m.close()
