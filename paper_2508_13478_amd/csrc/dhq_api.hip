@@ -100,17 +100,20 @@ static void fwht_f64(double *v, int n)
             }
 }
 
-// The same transform down a column of a row-major matrix (stride = row length), on doubles
-// or on 64-bit integers.
+// The same transform down every column of a row-major n x cols matrix, a pair of rows at a time, on doubles or on 64-bit
+// integers.
 template <typename T>
-static void fwht_strided(T *v, int n, size_t stride)
+static void fwht_columns(T *v, int n, int cols)
 {
     for (int h = 1; h < n; h <<= 1)
         for (int i = 0; i < n; i += 2 * h)
             for (int j = i; j < i + h; ++j) {
-                const T a = v[(size_t)j * stride], b = v[(size_t)(j + h) * stride];
-                v[(size_t)j * stride] = a + b;
-                v[(size_t)(j + h) * stride] = a - b;
+                T *p = v + (size_t)j * cols, *q = v + (size_t)(j + h) * cols;
+                for (int k = 0; k < cols; ++k) {
+                    const T a = p[k], b = q[k];
+                    p[k] = a + b;
+                    q[k] = a - b;
+                }
             }
 }
 
@@ -199,8 +202,7 @@ static int quantize_layer_host(dhq_model *m, int l, const float *W, const float 
         }
         fwht_f64(row, Kp);
     }
-    if (m->rot_out)
-        for (int k = 0; k < Kp; ++k) fwht_strided(rot.data() + k, Mg, (size_t)Kp);
+    if (m->rot_out) fwht_columns(rot.data(), Mg, Kp);
     const double inv = m->rot_out ? 1.0 / sqrt((double)Mg * (double)Kp) : 1.0 / sqrt((double)Kp);
     double amax = 0.0;
     for (size_t i = 0; i < rot.size(); ++i) {
@@ -209,30 +211,44 @@ static int quantize_layer_host(dhq_model *m, int l, const float *W, const float 
         if (a > amax) amax = a;
     }
     Ly.s_w = amax == 0.0 ? 1.0f : (float)(amax / qmax_w);
-    // the quantizer: clamp(rne(w^ / s_w)); nearbyint rounds half to even
+    // the quantizer: clamp(rne(w^ / s_w)).  |w^ / s_w| is at most qmax and a little, so adding and subtracting 1.5 2^52
+    // rounds half to even; the loop then vectorizes, where a call of nearbyint per weight took as long as the transform.
     Ly.wq_host.resize((size_t)Mg * Kp);
-    const double sd = (double)Ly.s_w;
+    const double sd = (double)Ly.s_w, round_magic = 6755399441055744.0;
     for (size_t i = 0; i < rot.size(); ++i) {
-        double q = nearbyint(rot[i] / sd);
-        if (q > qmax_w) q = qmax_w;
-        if (q < -qmax_w) q = -qmax_w;
-        Ly.wq_host[i] = (int8_t)q;
+        double q = (rot[i] / sd + round_magic) - round_magic;
+        q = q > qmax_w ? qmax_w : q;
+        q = q < -qmax_w ? -qmax_w : q;
+        Ly.wq_host[i] = (int8_t)(int)q;
     }
     // U = the integer matrix whose product with the codes is what the epilogue scales: Wq itself, or
     // in the two-sided variant H_Mp Wq (the un-rotation z = acc' H_Mp runs in int32 and
     // z[j] = sum_k q[k] U[j][k]).
-    std::vector<int64_t> U(Ly.wq_host.begin(), Ly.wq_host.end());
-    if (m->rot_out)
-        for (int k = 0; k < Kp; ++k) fwht_strided(U.data() + k, Mg, (size_t)Kp);
+    std::vector<int64_t> U;
+    if (m->rot_out) {
+        U.assign(Ly.wq_host.begin(), Ly.wq_host.end());
+        fwht_columns(U.data(), Mg, Kp);
+    }
     Ly.sum_abs_max = 0;
     Ly.norm2_max = 0.0;
     for (int j = 0; j < Mg; ++j) {
         int64_t sum = 0;
         double sq = 0.0;
-        for (int k = 0; k < Kp; ++k) {
-            const int64_t u = U[(size_t)j * Kp + k];
-            sum += u < 0 ? -u : u;
-            sq += (double)u * (double)u;
+        if (m->rot_out) {
+            for (int k = 0; k < Kp; ++k) {
+                const int64_t u = U[(size_t)j * Kp + k];
+                sum += u < 0 ? -u : u;
+                sq += (double)u * (double)u;
+            }
+        } else {
+            int s1 = 0, s2 = 0;  // at most 512 terms of 127 and of 127^2
+            const int8_t *u = Ly.wq_host.data() + (size_t)j * Kp;
+            for (int k = 0; k < Kp; ++k) {
+                s1 += u[k] < 0 ? -u[k] : u[k];
+                s2 += u[k] * u[k];
+            }
+            sum = s1;
+            sq = s2;
         }
         // |z[j]| <= qmax_a sum_k |U[j][k]|: refuse weights for which that bound leaves int32
         if (m->rot_out && sum * (int64_t)m->qmax_a > (int64_t)INT32_MAX) return DHQ_EUNSUPPORTED;
