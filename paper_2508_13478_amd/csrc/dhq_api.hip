@@ -143,6 +143,8 @@ extern "C" void dhq_free(dhq_model *m)
     if (m->dyn_absmax) (void)hipFree(m->dyn_absmax);
     if (m->dyn_params) (void)hipFree(m->dyn_params);
     dhq_fused_destroy(m->fused);
+    dhq_fused_destroy(m->pad_fused);
+    dhq_pair_destroy(m->pad_pair);
     dhq_wide_destroy(m->wide);
     dhq_pair_destroy(m->pair);
     dhq_float_destroy(m->flt);
@@ -431,9 +433,11 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
         if (rc == DHQ_OK && hipMemset(m->dyn_params, 0, sizeof(float) * 3 * DHQ_MAX_LAYERS) != hipSuccess) rc = DHQ_EHIP;
     }
     if (rc == DHQ_OK) rc = scratch_on_device(m->device, &m->scratch);
-    if (rc == DHQ_OK && !m->rot_out) rc = dhq_fused_create(m, &m->fused);
+    if (rc == DHQ_OK && !m->rot_out) rc = dhq_fused_create(m, false, &m->fused);
     if (rc == DHQ_OK && !m->rot_out && !cplx) rc = dhq_wide_create(m, &m->wide);
-    if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, &m->pair);  // (also the complex wavelet, which the one-wave kernel does not have)
+    if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, false, &m->pair);  // (also the complex wavelet, which the one-wave kernel does not have)
+    if (rc == DHQ_OK && !m->rot_out) rc = dhq_fused_create(m, true, &m->pad_fused);
+    if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, true, &m->pad_pair);
     if (rc == DHQ_OK && m->rot_out) rc = dhq_fused2_create(m, &m->fused2);
     if (rc != DHQ_OK) {
         dhq_free(m);
@@ -525,6 +529,8 @@ static int update_fused_scales(dhq_model *m)
 {
     m->fused_sine_ok = sine_range_ok_static(m);
     int rc = dhq_fused_update_scales(m, m->fused);
+    if (rc == DHQ_OK) rc = dhq_fused_update_scales(m, m->pad_fused);
+    if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pad_pair);
     if (rc == DHQ_OK) rc = dhq_wide_update_scales(m, m->wide);
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pair);
     if (rc == DHQ_OK) rc = dhq_fused2_update_scales(m, m->fused2);
@@ -697,6 +703,13 @@ struct dyn_ws {
 struct dyn_sizes {
     size_t act, codes, acc;
 };
+// (What dhq_noalloc_max_rows promises follows from these; the buffer `act0` also holds the codes of the per-layer fused
+// kernels, which for a padded network's few rows may be the larger of the two: dyn_act0_bytes.)
+static size_t dyn_act0_bytes(const dhq_model *m, int64_t n, size_t act)
+{
+    const size_t need = m->pad_fused ? dhq_fused_dynamic_bytes(m->pad_fused, n) : 0;
+    return need > act ? need : act;
+}
 static dyn_sizes dyn_buffer_sizes(const dhq_model *m, int64_t n)
 {
     // the per-layer fused kernels store whole workgroup tiles
@@ -722,7 +735,7 @@ static int ensure_dyn_workspace(dhq_model *m, int64_t n)
     m->dyn_acc = nullptr;
     m->dyn_rows = 0;
     const dyn_sizes z = dyn_buffer_sizes(m, n);
-    if (hipMalloc((void **)&m->dyn_act0, z.act) != hipSuccess) return DHQ_ENOMEM;
+    if (hipMalloc((void **)&m->dyn_act0, dyn_act0_bytes(m, n, z.act)) != hipSuccess) return DHQ_ENOMEM;
     if (hipMalloc((void **)&m->dyn_act1, z.act) != hipSuccess) return DHQ_ENOMEM;
     if (hipMalloc((void **)&m->dyn_codes, z.codes) != hipSuccess) return DHQ_ENOMEM;
     if (z.acc && hipMalloc((void **)&m->dyn_acc, z.acc) != hipSuccess) return DHQ_ENOMEM;
@@ -753,7 +766,7 @@ static int forward_dynamic(const dhq_model *m, const dyn_ws &ws, const float *co
     if (per_layer_fused) {
         const hipError_t e =
             m->fused2 ? dhq_fused2_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st)
-            : m->fused ? dhq_fused_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st)
+            : (m->fused || m->pad_fused) ? dhq_fused_dynamic_launch(m, m->fused ? m->fused : m->pad_fused, coords_dev, n, out_dev, ws.act0, ws.partial, ws.params, st)
                        : dhq_pair_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
@@ -785,7 +798,7 @@ static int check_dynamic_call(const dhq_model *m, int64_t n, uint32_t path, bool
     const bool dyn_fused_ok = (m->fused || m->fused2 || m->pair) && m->dyn_sine_ok;  // per-layer fused kernels of the dynamic mode
     if (m->flt) return DHQ_EUNSUPPORTED;
     if (path == DHQ_FUSED && !dyn_fused_ok) return DHQ_EUNSUPPORTED;
-    *per_layer_fused = path != DHQ_LAYERWISE && dyn_fused_ok;
+    *per_layer_fused = (path != DHQ_LAYERWISE && dyn_fused_ok) || (path == DHQ_AUTO && m->pad_fused && m->dyn_sine_ok);
     return DHQ_OK;
 }
 
@@ -830,9 +843,17 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if (path == DHQ_FUSED && !fused_ok) return DHQ_EUNSUPPORTED;
     if (path != DHQ_LAYERWISE && fused_ok) {
         const hipError_t e = m->fused2 ? dhq_fused2_launch(m->fused2, coords_dev, n, out_dev, st)
-                             : m->fused ? dhq_fused_launch(m, coords_dev, n, out_dev, st)
+                             : m->fused ? dhq_fused_launch(m, m->fused, coords_dev, n, out_dev, st)
                              : dhq_use_pair(m) ? dhq_pair_launch(m->pair, coords_dev, n, out_dev, st)
                                                : dhq_wide_launch(m->wide, coords_dev, n, out_dev, st);
+        return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
+    }
+    // Hidden widths that round up to a whole-network kernel's: the padded features cost less than the layer-by-layer path's
+    // passes over memory at every size (complex width 181 = 362 real features, 3 layers, 65 536 rows: 322 us layer by layer,
+    // 67 us padded; 4 x 200 features, 150 001 rows: 289 us less of 370).
+    if (path == DHQ_AUTO && m->fused_sine_ok && (m->pad_fused || m->pad_pair)) {
+        const hipError_t e = m->pad_fused ? dhq_fused_launch(m, m->pad_fused, coords_dev, n, out_dev, st)
+                                          : dhq_pair_launch(m->pad_pair, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
     const int K0 = m->dims[0], Mo = m->dims[m->n_layers];
@@ -878,6 +899,11 @@ extern "C" int dhq_forward_noalloc(const dhq_model *m, const float *coords_dev, 
     ws.partial = reinterpret_cast<float *>(base);
     base += DHQ_NOALLOC_PARTIAL_BYTES;
     ws.act0 = reinterpret_cast<float *>(base);
+    if (per_layer_fused && m->pad_fused) {
+        // the one buffer these kernels use; it fits wherever the layer-by-layer path's buffers do, except that it is rounded
+        // up to whole workgroup tiles
+        if (dhq_fused_dynamic_bytes(m->pad_fused, n) > DHQ_NOALLOC_SCRATCH_BYTES) per_layer_fused = false;
+    }
     base += round256(z.act);
     ws.act1 = reinterpret_cast<float *>(base);
     base += round256(z.act);

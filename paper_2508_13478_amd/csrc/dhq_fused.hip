@@ -64,6 +64,8 @@ struct fused_args {
 
 struct dhq_fused_plan {
     int nf = 0;                      // hidden width
+    int act_kind = DHQ_ACT_KIND_SINE;
+    bool padded = false;             // the network's own hidden widths are smaller, padded to nf
     unsigned char *blob_dev = nullptr;
     size_t blob_bytes = 0;
     fused_args args;
@@ -137,7 +139,8 @@ struct hm_sched {
 // One layer's GEMM with the dequantize + bias + sine epilogue, the split into binary16 pieces and
 // the H_32 products, software-pipelined by hand according to hm_sched.  On return xt[T][v]
 // holds, for this lane's coordinate, row 8 (v / 4) + 4 h + v % 4 of H_32 * (activations of tile T).
-// ACTK: the activation (sine, or the wavelet with envelope constant c2).
+// ACTK: the activation (sine, or the wavelet with envelope constant c2), plus DHQ_SPLIT_RN where the pieces round to
+// nearest.
 template <int NT, int KB, int NCD, int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ wA, const float4 *__restrict__ wB,
                                                    const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
@@ -210,13 +213,13 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
                 // accumulators v, v + 1 (v even) are neighbouring features 2m, 2m + 1: the pair the complex wavelet takes
                 const float t0 = __builtin_fmaf((float)acc[Td % 3][v], c1, bias0), t1 = __builtin_fmaf((float)acc[Td % 3][v + 1], c1, bias1);
                 float a0, a1;
-                if constexpr (ACTK == DHQ_ACT_KIND_WAVELET_COMPLEX) {
+                if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
                     dhq_activate_pair_rev<false>(t0, t1, c2, a0, a1);
                 } else {
-                    a0 = dhq_activate_rev(t0, dhq_act{ACTK, c2});
-                    a1 = dhq_activate_rev(t1, dhq_act{ACTK, c2});
+                    a0 = dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), c2});
+                    a1 = dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), c2});
                 }
-                hm_split_pair(a0, a1, hp[Td & 1][v >> 1], lp[Td & 1][v >> 1]);
+                hm_split_pair<ACTK>(a0, a1, hp[Td & 1][v >> 1], lp[Td & 1][v >> 1]);
             }
         }
         if (T >= 0 || Td >= 0 || S.hm_n[g] > 0) __builtin_amdgcn_sched_barrier(0);
@@ -350,44 +353,51 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     }
 }
 
-// ---- one layer per launch: the dynamic quantization module (Sec. 3.3) ------------------------
+// ---- one launch per layer: the dynamic quantization module (Sec. 3.3) ------------------------
 // With scales measured on line, a layer's quantizer needs max |x^| over the whole batch before
 // it can emit a single code, so the network cannot stay in registers from end to end.  These
-// kernels cut the fused kernel at exactly that point: a launch folds the maxima the previous
-// launch's workgroups left into this layer's constants (every workgroup for itself: a few hundred
-// floats and three fp64 operations cost less than a launch in between), quantizes its input
-// with them, runs the layer (GEMM, epilogue, transform of the output) and writes the
-// transformed output x^ (fp32) plus each workgroup's max |x^|.  Per hidden
-// layer the activations cross device memory once in each direction, in the lanes' register order
-// ([wave tile][float4 q][lane]: every 16-byte access of a wave is 1 KiB contiguous).
-//   MODE 0  input layer: coordinates in, x^ out        MODE 1  hidden layer: x^ in, x^ out
-//   MODE 2  output layer: x^ in, signal values out
+// kernels cut the fused kernel at exactly that point.  The launch of layer l
+//   - folds the maxima the previous launch's workgroups left into this layer's constants (every workgroup for
+//     itself: a few hundred floats and three fp64 operations cost less than a launch in between);
+//   - runs the layer below again (GEMM, epilogue, transform), from that layer's input codes, which the previous
+//     launch stored, or from the coordinates: its output x^ is this layer's input;
+//   - quantizes x^, stores the codes for the next launch, runs this layer and keeps only each workgroup's
+//     max |x^| of the result.
+// So every hidden layer is computed twice and what crosses device memory between two launches is one byte per
+// feature in each direction instead of a float (which is what the codes are there for: the float could only be
+// quantized after the launch that made it).  Five hidden layers of 256 on 262 144 rows: 565 us
+// with the floats (5.2 TB/s), 354 us with the codes, bound by vector instruction issue as the whole-network kernel is.  The codes cross memory in the
+// lanes' register order ([wave tile][k block][lane] x 16 B: every access of a wave is 1 KiB contiguous), and a wave
+// overwrites the codes it has read itself, so one buffer serves all layers.
+//   MODE 0  input layer (no layer below)   MODE 1  hidden layer   MODE 2  output layer: signal values out
 struct fusedl_args {
-    const float *coords;       // MODE 0
-    const float4 *xin;         // MODE 1, 2
-    float4 *xout;              // MODE 0, 1
+    const float *coords;
+    dhq_v4i *codes;            // MODE 1, 2: in (unless the layer below is the input layer); MODE 1: out
     float *out;                // MODE 2
     const unsigned char *blk;  // this layer's block of the packed weights (fragments, then biases)
+    const unsigned char *blk_below;  // MODE 1, 2: the block of the layer below
     const float *partial_in;   // max |x^| of this layer's input, one float per workgroup of the launch before
     int partial_count;
     int kp;                    // length of this layer's rotated input
     double c1_over_sa;         // epilogue multiplier divided by the activation scale
     float *dyn;                // this layer's {1 / (s_a sqrt(Kp)), epilogue multiplier, s_a}: written by workgroup 0
+    const float *dyn_below;    // MODE 1, 2: those of the layer below, written by the launch before
     float *partial;            // MODE 0, 1: max |x^| of the output per workgroup (not the buffer partial_in points to)
     int64_t n;
-    int chunks;                // block size in KiB
+    int chunks, chunks_below;  // block sizes in KiB
     int k0, k0p, m_out, qmax;
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
 };
 
-// ACTK: the activation after the layer (MODE 0, 1).
-template <int NF, int MODE, int ACTK>
+// BELOW0: the layer below is the input layer.  ACTK: the activation of the hidden layers.
+template <int NF, int MODE, bool BELOW0, int ACTK>
 __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fusedl_args A)
 {
-    constexpr int NT = NF / 32, NKB = NF / 32, NR = NF / 2;
+    constexpr int NT = NF / 32, NKB = NF / 32;
     constexpr int KB = (MODE == 0) ? 1 : NKB;      // k blocks of this layer's GEMM
+    constexpr int KBB = BELOW0 ? 1 : NKB;          // k blocks of the layer below
     constexpr int MT = (MODE == 2) ? 1 : NT;       // M tiles of this layer's GEMM
-    extern __shared__ __align__(16) unsigned char lds[];
+    extern __shared__ __align__(16) unsigned char lds[];  // this layer's block, then that of the layer below
     __shared__ float red_in[FUSED_WAVES], red[FUSED_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
@@ -396,6 +406,13 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
     dhq_v4i hA[2];
     fused_h32_operand(c, h, hA);
     fused_issue_copy(A.blk, lds, A.chunks, wave, lane, FUSED_WAVES);
+    const unsigned char *lds_below = lds + (MT * KB + 1) * 1024;
+    float inv_below = 0.f, c1_below = 0.f;
+    if constexpr (MODE != 0) {
+        fused_issue_copy(A.blk_below, lds + (MT * KB + 1) * 1024, A.chunks_below, wave, lane, FUSED_WAVES);
+        inv_below = A.dyn_below[0];
+        c1_below = A.dyn_below[1];
+    }
     // this layer's constants from the maxima of its input
     float inv, c1, s_a;
     {
@@ -415,43 +432,47 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
     }
     const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
     float mx = 0.f;
-    bool landed = false;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // the weights are in LDS
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const int64_t ci = tile * FUSED_TILE + wave * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;  // lanes past the end repeat the last coordinate: no effect on the maximum
-        const size_t slot = ((size_t)tile * FUSED_WAVES + wave) * (NR / 4) * 64 + lane;
+        dhq_v4i *const codes = A.codes + ((size_t)tile * FUSED_WAVES + wave) * NKB * 64 + lane;
         dhq_v4i cd[NKB];
+        dhq_v16f xt[NT];
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
-        if constexpr (MODE == 0) {
-            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, inv, A.qmax);
+        if constexpr (MODE == 0 || BELOW0) {
+            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, MODE == 0 ? inv : inv_below, A.qmax);
         } else {
 #pragma unroll
-            for (int q = 0; q < NR / 4; ++q) {
-                const float4 x = A.xin[slot + (size_t)q * 64];
-                cd[q / 4][q % 4] = (int)fused_quant4(x.x, x.y, x.z, x.w, inv, qlo, qhi);
-            }
+            for (int kb = 0; kb < NKB; ++kb) cd[kb] = codes[kb * 64];
         }
-        if (!landed) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();  // the weights are in LDS
-            landed = true;
+        if constexpr (MODE != 0) {
+            fused_gemm_sine_hm<NT, KBB, NKB, ACTK>(reinterpret_cast<const dhq_v4i *>(lds_below),
+                                                   reinterpret_cast<const float4 *>(lds_below + NT * KBB * 1024), cd, c1_below, xt, hA,
+                                                   lane, h, A.c2);
+            __syncthreads();  // keeps the two waves of a SIMD in the same phase, as in the whole-network kernel
+            fused_tile_stages<NT>(xt);
+            fused_quantize<NT>(xt, cd, inv, qlo, qhi);
+            if constexpr (MODE == 1) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) codes[kb * 64] = cd[kb];
+            }
         }
         if constexpr (MODE == 2) {
             fused_output_layer<NKB>(wA, reinterpret_cast<const float *>(lds + MT * KB * 1024), cd, c1, A.out, ci, valid, A.m_out,
                                     lane, h);
         } else {
-            dhq_v16f xt[NT];
             fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
                                                   A.c2);
+            __syncthreads();
             fused_tile_stages<NT>(xt);
 #pragma unroll
-            for (int q = 0; q < NR / 4; ++q) {
-                const float4 x = make_float4(xt[q >> 2][4 * (q & 3)], xt[q >> 2][4 * (q & 3) + 1], xt[q >> 2][4 * (q & 3) + 2],
-                                             xt[q >> 2][4 * (q & 3) + 3]);
-                mx = fmaxf(fmaxf(mx, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
-                A.xout[slot + (size_t)q * 64] = x;
+            for (int T = 0; T < NT; ++T) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(xt[T][v]));
             }
         }
     }
@@ -551,30 +572,33 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 }
 
 // ------------------------------------------------------------------------------- host code
-static bool fused_shape_ok(const dhq_model *m, int *nf_out)
+// `padded`: hidden widths that are no multiple of 32 or differ, but round up to the same power of two.
+static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
 {
     const int L = m->n_layers;
     if (L < 2) return false;
     if (m->dims[0] > 4 || m->dims[L] > 32) return false;
-    const int nf = m->dims[1];
+    const int nf = dhq_padded_width(m->dims, L);
     if (nf != 32 && nf != 64 && nf != 128 && nf != 256) return false;
-    for (int l = 1; l < L; ++l)
-        if (m->dims[l] != nf) return false;
+    if (dhq_all_hidden_are(m->dims, L, nf) == padded) return false;
+    if (padded && !dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2)) return false;
     *nf_out = nf;
     return true;
 }
 
-int dhq_fused_create(const dhq_model *m, dhq_fused_plan **plan_out)
+int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
 {
     *plan_out = nullptr;
     int nf = 0;
-    if (!fused_shape_ok(m, &nf)) return DHQ_OK;
+    if (!fused_shape_ok(m, padded, &nf)) return DHQ_OK;
     const int L = m->n_layers;
     const int NT = nf / 32, NKB = nf / 32;
 
     dhq_fused_plan *P = new (std::nothrow) dhq_fused_plan();
     if (!P) return DHQ_ENOMEM;
     P->nf = nf;
+    P->act_kind = m->act_kind;
+    P->padded = padded;
     memset(&P->args, 0, sizeof(P->args));
 
     // block sizes: fragments [Mt][Kb] KiB + one KiB of biases
@@ -611,6 +635,8 @@ int dhq_fused_create(const dhq_model *m, dhq_fused_plan **plan_out)
             float *bias = reinterpret_cast<float *>(blob.data() + off + (size_t)Mt * Kb * 1024);
             const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
             for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = src[f];
+            if (l < L - 1)
+                for (int f = Ly.M; f < nf; ++f) bias[bias_slot(f)] = dhq_pad_bias(m->act_kind, f);
         }
         P->args.layer[l].blob_off = (uint32_t)off;
         P->args.layer[l].chunks = (uint32_t)(bytes / 1024);
@@ -675,14 +701,18 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, const fused_args &a,
 template <int NF>
 static hipError_t fused_launch_t(const dhq_fused_plan *P, const fused_args &a, int act_kind, unsigned grid, hipStream_t st)
 {
+    if (P->padded) {
+        if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(P, a, grid, st);
+        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(P, a, grid, st)
+                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(P, a, grid, st);
+    }
     if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(P, a, grid, st);
     return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET>(P, a, grid, st)
                                             : fused_launch_act<NF, DHQ_ACT_KIND_SINE>(P, a, grid, st);
 }
 
-hipError_t dhq_fused_launch(const dhq_model *m, const float *coords, int64_t n, float *out, hipStream_t st)
+hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
-    const dhq_fused_plan *P = m->fused;
     if (!P) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
     fused_args a = P->args;
@@ -701,41 +731,47 @@ hipError_t dhq_fused_launch(const dhq_model *m, const float *coords, int64_t n, 
     }
 }
 
-// The dynamic mode on the per-layer kernels above.  ws0 / ws1: two buffers of rows(n) x width
-// floats (rows(n) = n rounded up to a whole workgroup tile); partial: room for 2 x
-// DHQ_ABSMAX_PARTIALS floats (two sets of per-workgroup maxima, used alternately: a layer's
-// slower workgroups still read one set while its faster ones already write the other);
+// The dynamic mode on the per-layer kernels above.  ws: dhq_fused_dynamic_bytes bytes for the codes of one layer's input
+// (rows rounded up to whole workgroup tiles); partial: room for 2 x DHQ_ABSMAX_PARTIALS floats (two sets of per-workgroup
+// maxima, used alternately: a layer's slower workgroups still read one set while its faster ones already write the other);
 // dyn: three floats per layer.
 size_t dhq_fused_dynamic_rows(int64_t n) { return (size_t)((n + FUSED_TILE - 1) / FUSED_TILE) * FUSED_TILE; }
+size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *P, int64_t n) { return dhq_fused_dynamic_rows(n) * (size_t)P->nf; }
 
-template <int NF, int MODE, int ACTK>
+template <int NF, int MODE, bool BELOW0, int ACTK>
 static hipError_t fusedl_launch_t(const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
-    auto kern = dhq_fused_layer_kernel<NF, MODE, ACTK>;
-    const size_t lds = (size_t)a.chunks * 1024;
+    auto kern = dhq_fused_layer_kernel<NF, MODE, BELOW0, ACTK>;
+    const size_t lds = (size_t)(a.chunks + a.chunks_below) * 1024;
     hipError_t e = dhq_lds_limit_once(kern, lds, device);
     if (e != hipSuccess) return e;
     kern<<<grid, FUSED_THREADS, lds, st>>>(a);
     return hipGetLastError();
 }
-template <int NF>
-static hipError_t fusedl_launch_mode(int mode, int act_kind, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
+template <int NF, int ACTK>
+static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
-    const bool wav = (act_kind == DHQ_ACT_KIND_WAVELET);
-    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX && mode < 2)
-        return mode == 0 ? fusedl_launch_t<NF, 0, DHQ_ACT_KIND_WAVELET_COMPLEX>(a, grid, device, st)
-                         : fusedl_launch_t<NF, 1, DHQ_ACT_KIND_WAVELET_COMPLEX>(a, grid, device, st);
-    switch (mode) {
-        case 0: return wav ? fusedl_launch_t<NF, 0, DHQ_ACT_KIND_WAVELET>(a, grid, device, st) : fusedl_launch_t<NF, 0, DHQ_ACT_KIND_SINE>(a, grid, device, st);
-        case 1: return wav ? fusedl_launch_t<NF, 1, DHQ_ACT_KIND_WAVELET>(a, grid, device, st) : fusedl_launch_t<NF, 1, DHQ_ACT_KIND_SINE>(a, grid, device, st);
-        default: return fusedl_launch_t<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);  // the output layer has no activation
+    if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
+    if (layer < n_layers - 1)
+        return layer == 1 ? fusedl_launch_t<NF, 1, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 1, false, ACTK>(a, grid, device, st);
+    return layer == 1 ? fusedl_launch_t<NF, 2, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 2, false, ACTK>(a, grid, device, st);
+}
+template <int NF>
+static hipError_t fusedl_launch_nf(const dhq_fused_plan *P, int layer, int L, const fusedl_args &a, unsigned grid, hipStream_t st)
+{
+    if (P->padded) {  // (the complex wavelet has no range bound for on-line scales beyond one hidden layer, which the caller checks)
+        if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
+        if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
+        return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
     }
+    if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET>(layer, L, a, grid, P->device, st);
+    if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(layer, L, a, grid, P->device, st);
+    return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE>(layer, L, a, grid, P->device, st);
 }
 
-hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const float *coords, int64_t n, float *out, float *ws0, float *ws1,
-                                    float *partial, float *dyn, hipStream_t st)
+hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, float *out,
+                                    void *ws, float *partial, float *dyn, hipStream_t st)
 {
-    const dhq_fused_plan *P = m->fused;
     if (!P) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
     const int L = m->n_layers;
@@ -746,16 +782,19 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const float *coords, int
     int count = 0;
     hipError_t e = dhq_launch_wht_absmax_partials(coords, n, m->layer[0].K, m->layer[0].Kp, pbuf[0], &count, st);
     if (e != hipSuccess) return e;
-    float *bufs[2] = {ws0, ws1};
     for (int l = 0; l < L; ++l) {
         fusedl_args a;
         memset(&a, 0, sizeof(a));
         a.coords = coords;
-        a.xin = reinterpret_cast<const float4 *>(bufs[(l + 1) & 1]);
-        a.xout = reinterpret_cast<float4 *>(bufs[l & 1]);
+        a.codes = reinterpret_cast<dhq_v4i *>(ws);
         a.out = out;
         a.blk = P->blob_dev + P->args.layer[l].blob_off;
         a.chunks = (int)P->args.layer[l].chunks;
+        if (l > 0) {
+            a.blk_below = P->blob_dev + P->args.layer[l - 1].blob_off;
+            a.chunks_below = (int)P->args.layer[l - 1].chunks;
+            a.dyn_below = dyn + 3 * (l - 1);
+        }
         a.partial_in = pbuf[l & 1];
         a.partial_count = count;
         a.kp = m->layer[l].Kp;
@@ -765,12 +804,11 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const float *coords, int
         a.n = n;
         a.k0 = P->args.k0; a.k0p = P->args.k0p; a.m_out = P->args.m_out; a.qmax = P->args.qmax;
         a.c2 = dhq_hidden_act(m).c2;
-        const int mode = (l == 0) ? 0 : (l == L - 1 ? 2 : 1);
         switch (P->nf) {
-            case 32: e = fusedl_launch_mode<32>(mode, m->act_kind, a, grid, P->device, st); break;
-            case 64: e = fusedl_launch_mode<64>(mode, m->act_kind, a, grid, P->device, st); break;
-            case 128: e = fusedl_launch_mode<128>(mode, m->act_kind, a, grid, P->device, st); break;
-            case 256: e = fusedl_launch_mode<256>(mode, m->act_kind, a, grid, P->device, st); break;
+            case 32: e = fusedl_launch_nf<32>(P, l, L, a, grid, st); break;
+            case 64: e = fusedl_launch_nf<64>(P, l, L, a, grid, st); break;
+            case 128: e = fusedl_launch_nf<128>(P, l, L, a, grid, st); break;
+            case 256: e = fusedl_launch_nf<256>(P, l, L, a, grid, st); break;
             default: e = hipErrorInvalidValue;
         }
         if (e != hipSuccess) return e;

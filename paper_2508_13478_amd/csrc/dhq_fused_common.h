@@ -53,6 +53,8 @@ __device__ __forceinline__ void fused_issue_copy(const unsigned char *src, unsig
 
 // ---- pieces for running a 32-point Hadamard factor on the matrix unit ------------------------
 typedef _Float16 dhq_v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 dhq_v2h __attribute__((ext_vector_type(2)));
+typedef float dhq_v2f __attribute__((ext_vector_type(2)));
 typedef float dhq_v16f __attribute__((ext_vector_type(16)));
 
 // Two floats to packed binary16, rounded toward zero; element 0 in the low half.  (The
@@ -71,12 +73,64 @@ __device__ __forceinline__ void hm_remainders(float a0, float a1, unsigned hi, f
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(a0), "v"(hi));
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(a1), "v"(hi));
 }
+// The rounding of the two packings, chosen by an instance's activation kind: with DHQ_SPLIT_RN both pieces round to
+// nearest, so that hi + lo is within 2^-23 |a| and the transform is no worse than fp32 butterflies (rms 0.75e-6 against
+// 0.9e-6 at width 256, truncation 1.3e-6).  The zero-padded networks run these instances, because the layer-by-layer
+// kernels that were their only path use fp32 butterflies; the conversion issues at half rate (3 % of a forward).
+#define DHQ_SPLIT_RN 16
+#define DHQ_KIND(ACTK) ((ACTK) & 15)
+template <int ACTK>
+__device__ __forceinline__ unsigned hm_pack_piece(float a, float b)
+{
+    if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) {
+        // (not inline assembly: the compiler has to see the write to keep an MFMA that reads it two wait states away)
+        const dhq_v2f v = {a, b};
+        return __builtin_bit_cast(unsigned, __builtin_convertvector(v, dhq_v2h));
+    } else {
+        return hm_pack_half2(a, b);
+    }
+}
+template <int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void hm_split_pair(float a0, float a1, unsigned &hi, unsigned &lo)
 {
-    hi = hm_pack_half2(a0, a1);
+    hi = hm_pack_piece<ACTK>(a0, a1);
     float r0, r1;
     hm_remainders(a0, a1, hi, r0, r1);
-    lo = hm_pack_half2(r0, r1);
+    lo = hm_pack_piece<ACTK>(r0, r1);
+}
+
+// A network whose hidden widths all round up to the same power of two n runs on the n-wide kernels: the rotation
+// zero-pads a layer's input to n anyway, so the padded features only have to come out of the activation as exact zeros.
+// Their weights are zero; their biases (in revolutions) are 0 for the sine, and for the wavelets an argument at which the
+// envelope underflows to zero: 255 revolutions for the real one where (255 c2)^2 >= 169 (exp2 of less than -150 is 0 in
+// fp32), in the imaginary part for the complex one, whose envelope decays with it whatever c2 is.
+#define DHQ_PAD_REV 255.0f
+static inline bool dhq_pad_act_ok(int act_kind, float c2)
+{
+    return act_kind != DHQ_ACT_KIND_WAVELET || fabsf(c2) * DHQ_PAD_REV >= 13.0f;
+}
+static inline float dhq_pad_bias(int act_kind, int f)
+{
+    if (act_kind == DHQ_ACT_KIND_WAVELET) return DHQ_PAD_REV;
+    return (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX && (f & 1)) ? DHQ_PAD_REV : 0.0f;
+}
+// The common rounded-up hidden width, or 0 where the hidden layers differ in it.
+static inline int dhq_padded_width(const int *dims, int n_layers)
+{
+    int nf = 0;
+    for (int l = 1; l < n_layers; ++l) {
+        int p = 1;
+        while (p < dims[l]) p <<= 1;
+        if (nf != 0 && p != nf) return 0;
+        nf = p;
+    }
+    return nf;
+}
+static inline bool dhq_all_hidden_are(const int *dims, int n_layers, int nf)
+{
+    for (int l = 1; l < n_layers; ++l)
+        if (dims[l] != nf) return false;
+    return true;
 }
 
 // One dword of the A operand of an H_32 product: entries +-1 (binary16) of row `row` of the

@@ -73,6 +73,7 @@ struct pair_args {
 
 struct dhq_pair_plan {
     int act_kind = DHQ_ACT_KIND_SINE;
+    bool padded = false;       // the network's own hidden widths are smaller, padded to 512
     unsigned char *blob_dev = nullptr;
     size_t blob_bytes = 0;
     pair_args args;
@@ -255,21 +256,21 @@ __device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
         __builtin_amdgcn_sched_barrier(0);
         if constexpr ((e2 & 1) == 0) {
             constexpr int pl = (e2 - 4) / 2, ph = (e2 - 2) / 2;  // pairs whose low / high pieces are packed now
-            if constexpr (e2 >= 4 && pl < NE / 2) C.lp[(pl / 8) & 1][pl % 8] = hm_pack_half2(C.er[0], C.er[1]);
-            if constexpr (e2 >= 2 && ph < NE / 2) C.hp[(ph / 8) & 1][ph % 8] = hm_pack_half2(C.ar[(e2 - 2) & 3], C.ar[(e2 - 1) & 3]);
+            if constexpr (e2 >= 4 && pl < NE / 2) C.lp[(pl / 8) & 1][pl % 8] = hm_pack_piece<ACTK>(C.er[0], C.er[1]);
+            if constexpr (e2 >= 2 && ph < NE / 2) C.hp[(ph / 8) & 1][ph % 8] = hm_pack_piece<ACTK>(C.ar[(e2 - 2) & 3], C.ar[(e2 - 1) & 3]);
         } else {
             constexpr int pm = (e2 - 3) / 2;  // pair whose remainders are taken now
             if constexpr (e2 >= 3 && pm < NE / 2)
                 hm_remainders(C.ar[(e2 - 3) & 3], C.ar[(e2 - 2) & 3], C.hp[(pm / 8) & 1][pm % 8], C.er[0], C.er[1]);
         }
         if constexpr (e2 >= 0 && e2 < NE) {
-            if constexpr (ACTK == DHQ_ACT_KIND_WAVELET_COMPLEX) {
+            if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
                 // accumulators e2 - 1, e2 (e2 odd) are the features 2m, 2m + 1 = (Re, Im) of one complex feature; both
                 // results are consumed from the step after this one on (the packing of the high pieces)
                 if constexpr ((e2 & 1) == 0) C.et = C.ey;
                 else dhq_activate_pair_rev<false>(C.et, C.ey, C.c2, C.ar[(e2 - 1) & 3], C.ar[e2 & 3]);
             } else {
-                C.ar[e2 & 3] = dhq_activate_rev(C.ey, dhq_act{ACTK, C.c2});
+                C.ar[e2 & 3] = dhq_activate_rev(C.ey, dhq_act{DHQ_KIND(ACTK), C.c2});
             }
         }
         if constexpr (e1 >= 0 && e1 < NE) C.ey = __builtin_fmaf(C.ex, C.c1, pair_comp(C.bq[(e1 / 4) % 3], e1 % 4));
@@ -351,15 +352,15 @@ __device__ __forceinline__ void pair_step0(pair_ctx<ACTK> &C, int h)
         for (int v = 0; v < 16; ++v) x[v] = (float)C.acc[0][v];
 #pragma unroll
         for (int v = 0; v < 16; ++v) x[v] = __builtin_fmaf(x[v], C.c1, pair_comp(C.bq0[v >> 2], v & 3));
-        if constexpr (ACTK == DHQ_ACT_KIND_WAVELET_COMPLEX) {
+        if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
 #pragma unroll
             for (int d = 0; d < 8; ++d) dhq_activate_pair_rev<false>(x[2 * d], x[2 * d + 1], C.c2, x[2 * d], x[2 * d + 1]);
         } else {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) x[v] = dhq_activate_rev(x[v], dhq_act{ACTK, C.c2});
+            for (int v = 0; v < 16; ++v) x[v] = dhq_activate_rev(x[v], dhq_act{DHQ_KIND(ACTK), C.c2});
         }
 #pragma unroll
-        for (int d = 0; d < 8; ++d) hm_split_pair(x[2 * d], x[2 * d + 1], C.hp[G & 1][d], C.lp[G & 1][d]);
+        for (int d = 0; d < 8; ++d) hm_split_pair<ACTK>(x[2 * d], x[2 * d + 1], C.hp[G & 1][d], C.lp[G & 1][d]);
     }
     if constexpr (G + 1 < PAIR_NT) {
 #pragma unroll
@@ -868,14 +869,14 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel_debug(cons
 }
 
 // ------------------------------------------------------------------------------- host code
-bool dhq_pair_shape_ok(const dhq_model *m)
+// `padded`: hidden widths of 257 .. 511, or of both kinds.
+static bool pair_shape_ok(const dhq_model *m, bool padded)
 {
     const int L = m->n_layers;
     if (L < 2) return false;
     if (m->dims[0] > 4 || m->dims[L] > 32) return false;
-    for (int l = 1; l < L; ++l)
-        if (m->dims[l] != 512) return false;
-    return true;
+    if (dhq_padded_width(m->dims, L) != 512 || dhq_all_hidden_are(m->dims, L, 512) == padded) return false;
+    return !padded || dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2);
 }
 
 // k position jj of lane half u in k block kb of a hidden layer's A fragment holds rotated input
@@ -900,10 +901,10 @@ static void pair_pack_tile(const dhq_layer &Ly, int T, int Kb, bool first, int8_
         }
 }
 
-int dhq_pair_create(const dhq_model *m, dhq_pair_plan **plan_out)
+int dhq_pair_create(const dhq_model *m, bool padded, dhq_pair_plan **plan_out)
 {
     *plan_out = nullptr;
-    if (!dhq_pair_shape_ok(m)) return DHQ_OK;
+    if (!pair_shape_ok(m, padded)) return DHQ_OK;
     const int L = m->n_layers;
     dhq_pair_plan *P = new (std::nothrow) dhq_pair_plan();
     if (!P) return DHQ_ENOMEM;
@@ -927,6 +928,8 @@ int dhq_pair_create(const dhq_model *m, dhq_pair_plan **plan_out)
         float *bias = reinterpret_cast<float *>(blob.data() + bias_off) + (size_t)l * 512;
         const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
         for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = src[f];
+        if (l < L - 1)
+            for (int f = Ly.M; f < 512; ++f) bias[bias_slot(f)] = dhq_pad_bias(m->act_kind, f);
     }
     P->blob_bytes = blob.size();
     if (hipMalloc((void **)&P->blob_dev, P->blob_bytes) != hipSuccess) {
@@ -948,6 +951,7 @@ int dhq_pair_create(const dhq_model *m, dhq_pair_plan **plan_out)
     P->args.bias_off = (uint32_t)bias_off;
     P->args.c2 = dhq_hidden_act(m).c2;
     P->act_kind = m->act_kind;
+    P->padded = padded;
     P->lds_bytes = (size_t)PAIR_BIAS + 3 * 2048;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, m->device) != hipSuccess) {
@@ -991,6 +995,10 @@ hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t 
     const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
     auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET>
                 : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET_COMPLEX> : dhq_fused_pair_kernel<DHQ_ACT_KIND_SINE>;
+    if (P->padded)
+        kern = (P->act_kind == DHQ_ACT_KIND_WAVELET)           ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>
+               : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>
+                                                               : dhq_fused_pair_kernel<DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>;
     hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
     kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);

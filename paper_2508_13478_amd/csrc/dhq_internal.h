@@ -77,6 +77,10 @@ struct dhq_model {
     dhq_fused_plan *fused = nullptr;  // hidden width 32..256; null if the shape has no such kernel
     dhq_wide_plan *wide = nullptr;    // hidden width 512, one wave per SIMD
     dhq_pair_plan *pair = nullptr;    // hidden width 512, two waves per SIMD that split the features
+    // the same kernels for hidden widths that round up to one of theirs (DHQ_AUTO only: DHQ_FUSED and the test hooks keep to
+    // the exact widths)
+    dhq_fused_plan *pad_fused = nullptr;
+    dhq_pair_plan *pad_pair = nullptr;
     int wide_kernel = 0;              // which of the two runs: 0 the default, 1 one wave, 2 two waves (dhq_select_wide_kernel)
     dhq_float_plan *flt = nullptr;    // floating-point activations (DHQ_W8A32 / DHQ_W32A32)
     dhq_fused2_plan *fused2 = nullptr;  // two-sided variant, hidden width 32..256, fan-out <= 4
@@ -180,18 +184,18 @@ hipError_t dhq_launch_epilogue_pairs(const int32_t *acc, int64_t n, int M, float
 // ---- fused path (defined in dhq_fused.hip) -------------------------------------------------
 // Builds the packed weights for the whole-network kernel if the shape is supported.
 // Returns DHQ_OK with *plan == nullptr when it is not.
-int dhq_fused_create(const dhq_model *m, dhq_fused_plan **plan);
+int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan);
 void dhq_fused_destroy(dhq_fused_plan *plan);
 // Refreshes the per-layer constants after the activation scales changed.
 int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *plan);
-hipError_t dhq_fused_launch(const dhq_model *m, const float *coords, int64_t n, float *out,
+hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, float *out,
                             hipStream_t st);
-// Dynamic mode, one launch per layer with the transformed activations passing through ws0 / ws1
-// (dhq_fused_dynamic_rows(n) x hidden width floats each); partial: 2 x DHQ_ABSMAX_PARTIALS floats of
-// scratch; dyn: three floats per layer.
+// Dynamic mode, one launch per layer with the codes passing through ws (dhq_fused_dynamic_bytes(plan, n) bytes);
+// partial: 2 x DHQ_ABSMAX_PARTIALS floats of scratch; dyn: three floats per layer.
 size_t dhq_fused_dynamic_rows(int64_t n);
-hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const float *coords, int64_t n, float *out, float *ws0, float *ws1,
-                                    float *partial, float *dyn, hipStream_t st);
+size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *plan, int64_t n);
+hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, float *out,
+                                    void *ws, float *partial, float *dyn, hipStream_t st);
 
 
 // Hidden width 512 (defined in dhq_fused_wide.hip); same contract as the functions above.
@@ -202,7 +206,7 @@ hipError_t dhq_wide_launch(const dhq_wide_plan *plan, const float *coords, int64
 
 
 // Hidden width 512 on two waves per SIMD (defined in dhq_fused_pair.hip); same contract.
-int dhq_pair_create(const dhq_model *m, dhq_pair_plan **plan);
+int dhq_pair_create(const dhq_model *m, bool padded, dhq_pair_plan **plan);
 void dhq_pair_destroy(dhq_pair_plan *plan);
 int dhq_pair_update_scales(const dhq_model *m, dhq_pair_plan *plan);
 hipError_t dhq_pair_launch(const dhq_pair_plan *plan, const float *coords, int64_t n, float *out, hipStream_t st);

@@ -1,0 +1,79 @@
+"""Hidden widths that are no width of a whole-network kernel but round up to one: DHQ_AUTO runs them zero-padded."""
+import numpy as np
+import pytest
+
+import paper_2508_13478_amd as dhq
+from oracle import dhq_oracle as o
+from paper_2508_13478_amd import synth
+
+pytestmark = pytest.mark.gpu
+OUT_TOL = 2e-3          # a coordinate without a code difference is within 1e-6 of the oracle; one with may move this far
+
+
+def _dev(x):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")
+
+
+def _host(t):
+    import torch
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+# smallest and largest of each padded range, unequal widths with the same rounded-up one, every fan-in
+SHAPES = [[3, 20, 20, 3], [1, 17, 1], [2, 33, 63, 48, 32], [4, 65, 128, 100, 5], [2, 200, 200, 200, 1], [3, 129, 255, 3],
+          [2, 257, 257, 3], [1, 511, 300, 2], [4, 512, 363, 512, 32]]
+
+
+@pytest.mark.parametrize("dims", SHAPES, ids=["x".join(map(str, d)) for d in SHAPES])
+@pytest.mark.parametrize("s0", [None, 2.0], ids=["sine", "wavelet"])
+def test_padded_widths(dims, s0):
+    W, b = synth.siren_init(dims, 30.0, 5 + dims[1])
+    rng = np.random.default_rng(dims[1])
+    m = dhq.Model(dims, 30.0, W, b, wavelet_s0=s0)
+    assert not m.has_fused()                               # DHQ_FUSED keeps to the exact widths
+    for n in (1, 127, 257, 9000 + 7):
+        print(f"[padded] {dims} s0={s0} n={n}", flush=True)
+        x = rng.uniform(-1, 1, size=(n, dims[0])).astype(np.float32)
+        net = o.quantize_net(dims, 30.0, 8, 8, W, b, gabor_s0=s0) if s0 is not None else o.quantize_net(dims, 30.0, 8, 8, W, b)
+        exp = o.forward(net, x, calibrate=True)
+        m.set_act_scales(net.s_a)
+        auto, lw = _host(m.forward(_dev(x))), _host(m.forward(_dev(x), flags=dhq.DHQ_LAYERWISE))
+        with pytest.raises(dhq.DhqError) as e:
+            m.forward(_dev(x), flags=dhq.DHQ_FUSED)
+        assert e.value.status == dhq.DHQ_EUNSUPPORTED
+        err, err_lw = (np.abs(v.astype(np.float64) - exp).max(axis=1) for v in (auto, lw))
+        print(f"  beyond {OUT_TOL}: {(err > OUT_TOL).sum()} (layer by layer {(err_lw > OUT_TOL).sum()}), max {err.max():.2e}, "
+              f"median {np.median(err):.1e} ({np.median(err_lw):.1e}), rms {np.sqrt((err**2).mean()):.2e} "
+              f"({np.sqrt((err_lw**2).mean()):.2e})", flush=True)
+        assert (err > OUT_TOL).mean() <= max(3e-3, 1.0 / n) and err.max() <= 2e-2 and np.median(err) <= 1e-5
+        # on-line scales: as the oracle's; up to 256 features one kernel per layer of the same arithmetic, so a static
+        # forward with the measured scales gives the same bits
+        dyn = _host(m.forward(_dev(x), flags=dhq.DHQ_DYNAMIC))
+        s_dyn = m.dynamic_scales()
+        rel = np.abs(s_dyn / net.s_a - 1)
+        # Layers 0 and 1 see inputs without a quantizer's decision upstream that could differ on the maximum's coordinate
+        # (or only layer 0's few codes); after that the coordinate that holds a layer's maximum may carry a code that fp32
+        # and fp64 round differently.  One such code moves an input of the next layers by one step, 1 / 127 of the largest:
+        # at most 1e-2 of the maximum.
+        assert rel[:2].max() <= 1e-5 and rel.max() <= 1e-2
+        if max(dims[1:-1]) <= 256:
+            m.set_act_scales(s_dyn)
+            assert np.array_equal(dyn, _host(m.forward(_dev(x))))
+            out = _dev(np.zeros((n, dims[-1]), np.float32))
+            if n <= dhq.dhq_noalloc_max_rows(m.handle):
+                dhq.dhq_forward_noalloc(m.handle, _dev(x), out)
+                assert np.array_equal(dyn, _host(out))
+    m.close()
+
+
+def test_padded_cosine_keeps_the_layer_by_layer_path():
+    """A wavelet without an envelope (s0 = 0) is 1 at 0: no padded feature can come out as zero."""
+    dims = [2, 40, 40, 3]
+    W, b = synth.siren_init(dims, 30.0, 3)
+    m = dhq.Model(dims, 30.0, W, b, wavelet_s0=0.0)
+    x = _dev(np.random.default_rng(0).uniform(-1, 1, size=(999, 2)).astype(np.float32))
+    m.calibrate(x)
+    assert np.array_equal(_host(m.forward(x)), _host(m.forward(x, flags=dhq.DHQ_LAYERWISE)))
+    m.close()
