@@ -293,7 +293,7 @@ def main() -> int:
         res.pop("int8_tops"); res.pop("pct_int8_mfma_peak"); res.pop("alu")
         res["roofline"] = {"bound": "mfma", "achieved": tf, "peak": 157.3, "unit": "TFLOP/s", "frac": tf / 157.3,
                            "traffic": None,
-                           "kernel": (f"dhq_float_kernel<{wl.dims[1]}>" if fused else "float_layer_kernel, all launches of one forward"),
+                           "kernel": (f"dhq_float_kernel<{wl.dims[1]}>" if fused and wl.dims[1] <= 128 else "float_layer_kernel, all launches of one forward"),
                            "algorithmic_hbm_bytes_per_launch": 4 * (wl.dims[0] + wl.dims[-1]) * n,
                            "algorithmic_ops_per_launch": ops}
     if not fused and not floating:

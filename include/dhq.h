@@ -122,9 +122,9 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  * the fp32 MFMA, where W is the original weight matrix (DHQ_W32A32) or
  * W~ = (s_w Wq) H_Kp / sqrt(Kp), the de-quantized weights taken back to the original basis
  * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits: with fan-in <= 4,
- * equal hidden widths of 32 / 64 / 128 / 256 and fan-out <= 32 one fused kernel runs the whole
- * network (DHQ_AUTO, DHQ_FUSED), every other shape (and DHQ_LAYERWISE) runs one fp32 GEMM kernel
- * per layer.  Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
+ * equal hidden widths of 32 / 64 / 128 / 256 and fan-out <= 32 DHQ_FUSED is accepted: one fused kernel
+ * runs the whole network up to width 128 (DHQ_AUTO, DHQ_FUSED); width 256, where that is slower at
+ * every size, and every other shape (and DHQ_LAYERWISE) run one GEMM kernel of fp32 accuracy per layer.  Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
  * DHQ_DYNAMIC and the test hooks return DHQ_EUNSUPPORTED; dhq_forward needs none.
  */
 int dhq_quantize_weights_mode(const dhq_net_desc *desc, uint32_t mode, const float *const *W_host,

@@ -13,20 +13,19 @@
 // the activations are consumed exactly where the previous layer's epilogue left them, and
 // the weights are packed offline in that order.  Nothing is ever shuffled.
 //
-// The weights of a 256-wide layer are 256 KiB in fp32, more than LDS holds, and every MFMA
-// needs only 256 B of them per wave: they are read straight from device memory (they stay
+// Every MFMA needs only 256 B of weights per wave: they are read straight from device memory (they stay
 // in L2), one 16-byte load per lane and four MFMAs, eight groups (4096 matrix-unit clocks)
 // ahead of use.  The kernel is bound by the matrix unit (64 clocks per instruction); the
 // vector ALU only does one multiply-add and one sine per accumulator.
 //
-// Registers: one wave per SIMD.  The current activations (B operands, 128 per lane at width
-// 256) live in accumulation registers a128..a255, addressed by number from inline assembly
+// Registers: one wave per SIMD.  The current activations (B operands, 64 per lane at width
+// 128) live in accumulation registers a128..a255, addressed by number from inline assembly
 // (the MFMA included: the builtin cannot take B from an accumulation register without a
 // copy); the build checks on the compiler's assembly output that compiler-generated code never
 // touches them.  Wait states the compiler can no longer see (accumulation-register write ->
 // MFMA read, MFMA result -> vector ALU read) are covered by explicit s_nop.
 //
-// Every other shape (and DHQ_LAYERWISE on the shapes above) runs layer by layer through
+// Hidden widths of 32, 64 and 128.  Every other shape (and DHQ_LAYERWISE on the shapes above) runs layer by layer through
 // float_layer_kernel: one GEMM on bf16 pieces (fp32 accuracy) with the bias + sine epilogue per layer, activations
 // in device memory between the layers, a chunk of rows at a time.
 #include <math.h>
@@ -653,6 +652,8 @@ static int float_create_fused(dhq_float_plan *P, const int *dims, int L, double 
                               const std::vector<std::vector<float>> &b)
 {
     const int nf = dims[1], NT = nf / 32, NR = nf / 2, CHN = NT >= 2 ? 2 : 1;
+    P->nf = nf;
+    if (nf == 256) return DHQ_OK;  // runs layer by layer (dhq_float_launch)
     std::vector<float> blob;
     auto bias_block = [&](int l, int tiles, bool sine) {
         // [tile][h][16]: register v of lane half h holds feature 32 T + 8 (v / 4) + 4 h + v % 4
@@ -707,7 +708,6 @@ static int float_create_fused(dhq_float_plan *P, const int *dims, int L, double 
     P->args.m_out = dims[L];
     P->args.rev = (float)rev;
     P->args.c2 = P->actf.c2;
-    P->nf = nf;
     return DHQ_OK;
 }
 
@@ -887,6 +887,16 @@ hipError_t dhq_float_launch(const dhq_float_plan *P, const float *coords, int64_
 {
     if (!P || P->nf == 0) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
+    // Width 256 has no kernel of its own: one that kept the activations in registers and multiplied on the fp32 matrix
+    // instructions was slower than the layer-by-layer kernels at every size.  Measured, that kernel / layer by layer, five
+    // hidden layers, us:
+    //   rows       1 000     4 096    16 384    65 536      262 144
+    //   width 256  142 / 43  142 / 52  151 / 94  304 / 249  1129 / 968
+    //   width 128   43 / 31   44 / 34   46 / 54   96 / 125   364 / 429
+    //   width 64    16 / 26   16 / 27   17 / 36   33 / 71    119 / 189
+    // (At width 128 the line would lie at 8 192 rows; a network's values would then depend in their last bits on how many
+    // rows a call brings, so it stays on one path.)
+    if (P->nf == 256) return dhq_float_launch_layerwise(P, coords, n, out, st);
     float_args a = P->args;
     a.coords = coords;
     a.out = out;
@@ -906,10 +916,6 @@ hipError_t dhq_float_launch(const dhq_float_plan *P, const float *coords, int64_
         case 128:
             if (wav) dhq_float_kernel<128, DHQ_ACT_KIND_WAVELET><<<grid, FLT_THREADS, 0, st>>>(a);
             else dhq_float_kernel<128, DHQ_ACT_KIND_SINE><<<grid, FLT_THREADS, 0, st>>>(a);
-            break;
-        case 256:
-            if (wav) dhq_float_kernel<256, DHQ_ACT_KIND_WAVELET><<<grid, FLT_THREADS, 0, st>>>(a);
-            else dhq_float_kernel<256, DHQ_ACT_KIND_SINE><<<grid, FLT_THREADS, 0, st>>>(a);
             break;
         default: return hipErrorInvalidValue;
     }
