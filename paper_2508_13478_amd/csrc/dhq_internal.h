@@ -64,7 +64,6 @@ struct dhq_model {
     float *act0 = nullptr, *act1 = nullptr;  // DHQ_CHUNK x max dim, fp32
     int8_t *codes = nullptr;                 // DHQ_CHUNK x max Kp
     int32_t *acc_ws = nullptr;               // two-sided variant: DHQ_CHUNK x max Mg rotated accumulators
-    unsigned *absmax_dev = nullptr;          // one word for calibration
     int max_dim = 0, max_kp = 0, max_mg = 0;
     // dynamic mode (scales measured on line): whole-batch buffers, grown on demand, and per
     // layer one absmax word and three floats {quantizer multiplier, epilogue multiplier, s_a}
@@ -73,7 +72,7 @@ struct dhq_model {
     int32_t *dyn_acc = nullptr;
     int64_t dyn_rows = 0;
     unsigned *dyn_absmax = nullptr;  // DHQ_MAX_LAYERS absmax words, then 2 x DHQ_ABSMAX_PARTIALS floats of scratch
-    float *dyn_params = nullptr;     // DHQ_MAX_LAYERS x 3
+    float *dyn_params = nullptr;     // DHQ_MAX_LAYERS x 3 of the last dynamic forward, as many of the last calibration
     dhq_fused_plan *fused = nullptr;  // hidden width 32..256; null if the shape has no such kernel
     dhq_wide_plan *wide = nullptr;    // hidden width 512, one wave per SIMD
     dhq_pair_plan *pair = nullptr;    // hidden width 512, two waves per SIMD that split the features

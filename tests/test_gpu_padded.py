@@ -77,3 +77,20 @@ def test_padded_cosine_keeps_the_layer_by_layer_path():
     m.calibrate(x)
     assert np.array_equal(_host(m.forward(x)), _host(m.forward(x, flags=dhq.DHQ_LAYERWISE)))
     m.close()
+
+
+@pytest.mark.parametrize("dims,mode,n", [([2, 200, 200, 1], dhq.DHQ_ROTATE_IN, 5000), ([3, 200, 200, 1], dhq.DHQ_ROTATE_IN, 70001),
+                                         ([2, 64, 64, 3], dhq.DHQ_ROTATE_BOTH, 140001), ([2, 33, 33, 3], dhq.DHQ_ROTATE_IN, 150000)],
+                         ids=["one_chunk", "chunks", "two_sided", "beyond_the_codes_room"])
+def test_calibrated_scales_are_the_dynamic_ones(dims, mode, n):
+    """Calibration on one chunk, on several with the codes kept between the layers, and on more rows than the codes have
+    room for (33 features: 64 code bytes against 132 of floats, 135 168 rows): the on-line scales of the layer-by-layer
+    path, bit for bit."""
+    W, b = synth.siren_init(dims, 30.0, 17)
+    m = dhq.Model(dims, 30.0, W, b, mode=mode)
+    x = _dev(np.random.default_rng(n).uniform(-1, 1, size=(n, dims[0])).astype(np.float32))
+    m.calibrate(x)
+    s_cal = m.scales()[1]
+    m.forward(x, flags=dhq.DHQ_LAYERWISE | dhq.DHQ_DYNAMIC)
+    assert np.array_equal(s_cal, m.dynamic_scales())
+    m.close()
