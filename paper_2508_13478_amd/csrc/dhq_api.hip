@@ -144,6 +144,7 @@ extern "C" void dhq_free(dhq_model *m)
     dhq_fused_destroy(m->fused);
     dhq_fused_destroy(m->pad_fused);
     dhq_pair_destroy(m->pad_pair);
+    dhq_pair_destroy(m->pair2);
     dhq_wide_destroy(m->wide);
     dhq_pair_destroy(m->pair);
     dhq_float_destroy(m->flt);
@@ -225,7 +226,7 @@ static int quantize_layer_host(dhq_model *m, int l, const float *W, const float 
     // U = the integer matrix whose product with the codes is what the epilogue scales: Wq itself, or
     // in the two-sided variant H_Mp Wq (the un-rotation z = acc' H_Mp runs in int32 and
     // z[j] = sum_k q[k] U[j][k]).
-    std::vector<int64_t> U;
+    std::vector<int32_t> &U = Ly.u_host;  // at most 512 codes of 127 each
     if (m->rot_out) {
         U.assign(Ly.wq_host.begin(), Ly.wq_host.end());
         fwht_columns(U.data(), Mg, Kp);
@@ -436,6 +437,8 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
     if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, false, &m->pair);  // (also the complex wavelet, which the one-wave kernel does not have)
     if (rc == DHQ_OK && !m->rot_out) rc = dhq_fused_create(m, true, &m->pad_fused);
     if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, true, &m->pad_pair);
+    if (rc == DHQ_OK) rc = dhq_pair2_create(m, &m->pair2);
+    for (int l = 0; l < L; ++l) std::vector<int32_t>().swap(m->layer[l].u_host);
     if (rc == DHQ_OK && m->rot_out) rc = dhq_fused2_create(m, &m->fused2);
     if (rc != DHQ_OK) {
         dhq_free(m);
@@ -529,6 +532,7 @@ static int update_fused_scales(dhq_model *m)
     int rc = dhq_fused_update_scales(m, m->fused);
     if (rc == DHQ_OK) rc = dhq_fused_update_scales(m, m->pad_fused);
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pad_pair);
+    if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pair2);
     if (rc == DHQ_OK) rc = dhq_wide_update_scales(m, m->wide);
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pair);
     if (rc == DHQ_OK) rc = dhq_fused2_update_scales(m, m->fused2);
@@ -897,6 +901,8 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
                                           : dhq_pair_launch(m->pad_pair, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
+    // Two-sided at width 512: the whole-network kernel with the layer-by-layer path's bits (and its range of arguments).
+    if (path == DHQ_AUTO && m->pair2) return dhq_pair2_launch(m->pair2, coords_dev, n, out_dev, st) == hipSuccess ? DHQ_OK : DHQ_EHIP;
     const int K0 = m->dims[0], Mo = m->dims[m->n_layers];
     for (int64_t off = 0; off < n; off += DHQ_CHUNK) {
         const int64_t rows = (n - off) < DHQ_CHUNK ? (n - off) : DHQ_CHUNK;

@@ -54,6 +54,8 @@
 #define PAIR_PF 2              // LDS prefetch distance of the A fragments, in MFMAs
 #define PAIR_EARLY 4           // tiles whose outgoing rows leave during the GEMM phase
 
+#define PAIR2_MAX_U 32639      // largest entry that two int8 digits hold: 256 * 127 + 127
+
 struct pair_args {
     const float *coords;
     float *out;
@@ -620,6 +622,348 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
+// ---- two-sided rotation (Eq. 4 with both factors) at this width -------------------------------
+// The layer's output comes out of the GEMM in the rotated basis and is multiplied by H_512 once more, exactly, in
+// int32.  That product is linear in the weights: z = (q W'^T) H = q (H W')^T, so the kernel multiplies by U = H W'
+// instead and has no un-rotation at all.  An entry of U takes up to 17 bits (a sum of 512 codes); it travels as two int8
+// digits, u = 256 u1 + u0, where every |u| <= 32639 (the sum of 512 bell-shaped codes stays below about a tenth of that;
+// weights with larger entries keep the layer-by-layer path): acc = q u1, acc <<= 8, acc += q u0 in the same
+// accumulators, wrapping, the same int32 as before.  That is twice the MFMAs and weight bytes of the one-sided layer
+// against nine integer butterfly stages and an exchange between the waves.
+//
+// The forward transform gives the bits of the layer-by-layer kernels: fp32 butterflies in their order of stages, feature
+// bits 0, 1, 6, 7, 8, 2, 3, 4, 5.  Only the order of the stages decides the bits, not where a value lives, so the nine bits
+// of the output feature are dealt to the hardware in that order (the rows of U are permuted offline):
+//   accumulator v bits 0..3 <- feature bits 0, 1, 6, 7   the stages inside a tile, one butterfly per GEMM step
+//   tile T bits 0..2        <- 8, 2, 3                   register stages after the GEMM
+//   lane half               <- 4                         a lane swap, which trades places with v bit 0
+//   role                    <- 5                         the exchange between the two waves of a pair, as above
+// Role 1 has v bit 3 the other way round (feature bit 7 = v bit 3 xor role), so that both roles keep registers 0..7 and send
+// 8..15; the stage over that bit is a multiply-add by +-1, which rounds like the addition.
+//
+// Six hidden layers of 512, 262 144 rows: 2 402 us layer by layer (per layer a GEMM and an un-rotation kernel, 5 KiB of
+// traffic per row), 800 us here; 117 -> 85 us on 1 000 rows.
+static inline int pair2_feature(int role, int T, int v, int h)
+{
+    return (v & 3) | ((T >> 1) & 1) << 2 | ((T >> 2) & 1) << 3 | h << 4 | role << 5 | ((v >> 2) & 1) << 6 | ((v >> 3) ^ role) << 7 | (T & 1) << 8;
+}
+// Rotated feature of byte jj of lane half u in k block kb of the codes a layer leaves: dwords 2 role, 2 role + 1 are the kept
+// registers of tile kb % 8, whose bit 0 and the lane half have traded places; kb / 8 is the role bit after the exchange.
+static inline int pair2_code_feature(int kb, int u, int jj)
+{
+    const int T = kb & 7, role = jj >> 3, i = jj & 7;
+    return u | ((i >> 1) & 1) << 1 | ((T >> 1) & 1) << 2 | ((T >> 2) & 1) << 3 | (i & 1) << 4 | (kb >> 3) << 5 | (i >> 2) << 6 | role << 7 | (T & 1) << 8;
+}
+
+template <int ACTK>
+struct pair2_ctx {
+    pair_stream &S;
+    dhq_v4i (&cd)[PAIR_KB];
+    dhq_v16f (&y)[PAIR_NT];  // activations, then the transform inside the tiles
+    const unsigned char *bufs[2];
+    const float4 *bias;
+    int cc, layer;
+    float c1, c2, sgn;       // sgn: +1 for role 0, -1 for role 1
+    dhq_v4i fr[PAIR_PF + 1];
+    float4 bq[2];
+    dhq_v16i acc[2];
+    float ey;
+    __device__ __forceinline__ pair2_ctx(pair_stream &S_, dhq_v4i (&cd_)[PAIR_KB], dhq_v16f (&y_)[PAIR_NT]) : S(S_), cd(cd_), y(y_) {}
+};
+
+// Butterfly B (stage B / 8) inside a tile.
+template <int B>
+__device__ __forceinline__ void pair2_butterfly(dhq_v16f &x, float sgn)
+{
+// the wavelet ends in a product, which must not melt into the first stage's additions
+#pragma clang fp contract(off)
+    constexpr int st = B / 8, j = B % 8;
+    constexpr int v0 = ((j >> st) << (st + 1)) | (j & ((1 << st) - 1)), v1 = v0 | (1 << st);
+    const float a = x[v0], b = x[v1];
+    if constexpr (st < 3) {
+        x[v0] = a + b;
+        x[v1] = a - b;
+    } else {
+        x[v0] = __builtin_fmaf(a, sgn, b);   // role 0: a + b; role 1 holds them the other way round: b - a
+        x[v1] = __builtin_fmaf(b, -sgn, a);  // role 0: a - b; role 1: a + b
+    }
+}
+
+// One step of a hidden layer: the MFMA of step G (tile G / 32, digit plane (G / 16) % 2, high one first, k block G % 16), half
+// of the epilogue of one value of the tile before, one butterfly of the tile before that.
+template <int G, int ACTK>
+__device__ __forceinline__ void pair2_step(pair2_ctx<ACTK> &C)
+{
+    constexpr int NM = PAIR_NT * 2 * PAIR_KB, PF = PAIR_PF;
+    if constexpr (G >= 0 && G + PF < NM) {
+        constexpr int pf = G + PF;
+        if constexpr (pf % PAIR_KB == 0) pair_enter_chunk(C.S, C.cc + pf / PAIR_KB);
+        C.fr[pf % (PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[(pf / PAIR_KB) & 1])[(pf % PAIR_KB) * 64 + C.S.lane];
+    }
+    if constexpr (G + PF >= 0 && G + PF < NM) {
+        constexpr int rel = (G + PF) % PAIR_KB;
+        if constexpr (rel == 1) pair_copy_slot<0>(C.S);
+        if constexpr (rel == 3) pair_copy_slot<1>(C.S);
+        if constexpr (rel == 5) pair_copy_slot<2>(C.S);
+        if constexpr (rel == 7) pair_copy_slot<3>(C.S);
+    }
+    if constexpr (G == 9) pair_copy_bias(C.S, C.layer + 1);
+    if constexpr (G >= 0 && G < NM) {
+        constexpr int t = G / 32, r = G % 32;
+        if constexpr (r == 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) C.acc[t & 1][v] = 0;
+        }
+        if constexpr (r == 16) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) C.acc[t & 1][v] = (int)((unsigned)C.acc[t & 1][v] << 8);
+        }
+        C.acc[t & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(C.fr[G % (PF + 1)], C.cd[G % PAIR_KB], C.acc[t & 1], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int E = G - 32, F = G - 64;
+    if constexpr (F >= 0 && F < NM) pair2_butterfly<F % 32>(C.y[F / 32], C.sgn);
+    if constexpr (E >= 0 && E < NM) {
+        constexpr int td = E / 32, v = (E % 32) / 2;
+        if constexpr ((E & 1) == 0) C.ey = __builtin_fmaf((float)C.acc[td & 1][v], C.c1, pair_comp(C.bq[(E / 8) & 1], v & 3));
+        else C.y[td][v] = dhq_activate_rev_any(C.ey, dhq_act{ACTK, C.c2});
+    }
+    if constexpr (E + 8 >= 0 && (E + 8) % 8 == 0 && E + 8 < NM) {
+        constexpr int ge = (E + 8) / 8;  // biases of values 4 (ge % 4) .. + 3 of tile ge / 4; the slot's last value is done
+        C.bq[ge & 1] = C.bias[ge * 2];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int ACTK, int... Gs>
+__device__ __forceinline__ void pair2_steps(pair2_ctx<ACTK> &C, std::integer_sequence<int, Gs...>)
+{
+    (pair2_step<Gs - PAIR_PF>(C), ...);
+}
+
+template <int ACTK>
+__device__ __forceinline__ void pair2_hidden(pair_stream &S, int &cc, int layer, float c1, dhq_v4i (&cd)[PAIR_KB],
+                                             dhq_v16f (&y)[PAIR_NT], int h)
+{
+    pair2_ctx<ACTK> C(S, cd, y);
+    C.cc = cc;
+    C.c1 = c1;
+    C.c2 = S.A->c2;
+    C.sgn = S.role ? -1.f : 1.f;
+    C.ey = 0.f;
+    C.layer = layer;
+    C.bias = reinterpret_cast<const float4 *>(S.lds + PAIR_BIAS + pair_bias_slot(layer) * 2048) + S.role * 64 + h;
+    pair_enter_chunk(S, cc);
+    {
+        const dhq_v4i *src = reinterpret_cast<const dhq_v4i *>(S.lds + 2 * PAIR_BUF + S.grp * 16384) + S.lane;
+#pragma unroll
+        for (int T = 0; T < PAIR_KB; ++T) cd[T] = src[T * 64];
+    }
+    C.bufs[0] = S.lds + (cc & 1) * PAIR_BUF + S.role * 16384;
+    C.bufs[1] = S.lds + ((cc + 1) & 1) * PAIR_BUF + S.role * 16384;
+#pragma unroll
+    for (int m = 0; m < PAIR_PF; ++m) C.fr[m % (PAIR_PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[0])[m * 64 + S.lane];
+    pair2_steps<ACTK>(C, std::make_integer_sequence<int, PAIR_PF + PAIR_NT * 32 + 64>{});
+    cc += 2 * PAIR_NT;
+}
+
+// The input layer (fan-in <= 4): one chunk, per role [tile][digit plane] fragments.
+template <int T, int ACTK>
+__device__ __forceinline__ void pair2_input_tile(pair2_ctx<ACTK> &C)
+{
+    const dhq_v4i *fr = reinterpret_cast<const dhq_v4i *>(C.bufs[0]) + T * 128 + C.S.lane;
+    const dhq_v4i f1 = fr[0], f0 = fr[64];
+    float4 bq[4];
+#pragma unroll
+    for (int gg = 0; gg < 4; ++gg) bq[gg] = C.bias[(T * 4 + gg) * 2];
+    if constexpr (T == 0) pair_copy_slot<0>(C.S);
+    if constexpr (T == 1) pair_copy_slot<1>(C.S);
+    if constexpr (T == 2) pair_copy_slot<2>(C.S);
+    if constexpr (T == 3) pair_copy_slot<3>(C.S);
+    if constexpr (T == 4) pair_copy_bias(C.S, 1);
+    dhq_v16i acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0;
+    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, C.cd[0], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, C.cd[0], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        C.y[T][v] = dhq_activate_rev_any(__builtin_fmaf((float)acc[v], C.c1, pair_comp(bq[v >> 2], v & 3)), dhq_act{ACTK, C.c2});
+}
+template <int ACTK, int... Ts>
+__device__ __forceinline__ void pair2_input_tiles(pair2_ctx<ACTK> &C, std::integer_sequence<int, Ts...>)
+{
+    (pair2_input_tile<Ts>(C), ...);
+}
+template <int T, int ACTK, int... Bs>
+__device__ __forceinline__ void pair2_tile_butterflies(pair2_ctx<ACTK> &C, std::integer_sequence<int, Bs...>)
+{
+    (pair2_butterfly<Bs>(C.y[T], C.sgn), ...);
+}
+template <int ACTK, int... Ts>
+__device__ __forceinline__ void pair2_input_butterflies(pair2_ctx<ACTK> &C, std::integer_sequence<int, Ts...>)
+{
+    (pair2_tile_butterflies<Ts>(C, std::make_integer_sequence<int, 32>{}), ...);
+}
+
+template <int ACTK>
+__device__ __forceinline__ void pair2_input_layer(pair_stream &S, int &cc, float c1, dhq_v4i (&cd)[PAIR_KB], dhq_v16f (&y)[PAIR_NT], int h)
+{
+    pair2_ctx<ACTK> C(S, cd, y);
+    C.cc = cc;
+    C.c1 = c1;
+    C.c2 = S.A->c2;
+    C.sgn = S.role ? -1.f : 1.f;
+    C.layer = 0;
+    C.bias = reinterpret_cast<const float4 *>(S.lds + PAIR_BIAS + pair_bias_slot(0) * 2048) + S.role * 64 + h;
+    pair_enter_chunk(S, cc);
+    C.bufs[0] = C.bufs[1] = S.lds + (cc & 1) * PAIR_BUF + S.role * 16384;
+    pair2_input_tiles<ACTK>(C, std::make_integer_sequence<int, PAIR_NT>{});
+    pair2_input_butterflies<ACTK>(C, std::make_integer_sequence<int, PAIR_NT>{});
+    cc += 1;
+}
+
+// Tiles T0 .. T0 + 3: outgoing registers to the exchange area, then the partner's.
+template <int T0>
+__device__ __forceinline__ void pair2_exchange(pair_stream &S, const dhq_v16f (&y)[PAIR_NT], float (&zl)[PAIR_NT][8], float (&zh)[PAIR_NT][8])
+{
+#pragma unroll
+    for (int T = T0; T < T0 + 4; ++T) {
+        float4 *d = pair_x_slot(S, S.wave, T);
+        d[0] = make_float4(y[T][8], y[T][9], y[T][10], y[T][11]);
+        d[64] = make_float4(y[T][12], y[T][13], y[T][14], y[T][15]);
+    }
+    pair_barrier();
+    pair_recv<T0>(S, y, zl, zh);
+    pair_recv<T0 + 1>(S, y, zl, zh);
+    pair_recv<T0 + 2>(S, y, zl, zh);
+    pair_recv<T0 + 3>(S, y, zl, zh);
+    pair_barrier();  // everyone has read them: the slots are free again
+}
+
+// The stages over tile bits and lane half, the exchange, the quantizer; the codes go to the exchange area, which may be read
+// after the next barrier.  (On entry nobody reads the exchange area any more: every wave took its codes before the barriers
+// of this layer's later chunks, or before the input layer's chunk.)
+__device__ __forceinline__ void pair2_transform_quant(pair_stream &S, dhq_v16f (&y)[PAIR_NT], float inv, int qlo, int qhi)
+{
+#pragma unroll
+    for (int s = 1; s < PAIR_NT; s <<= 1) {
+#pragma unroll
+        for (int T = 0; T < PAIR_NT; ++T) {
+            if ((T & s) == 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float a = y[T][v], b = y[T | s][v];
+                    y[T][v] = a + b;
+                    y[T | s][v] = a - b;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int T = 0; T < PAIR_NT; ++T) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+            // the upper lanes of v for the lower lanes of v + 1: both halves of a pair then sit in one lane
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(y[T][v]), __float_as_uint(y[T][v + 1]), false, false);
+            const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+            y[T][v] = a + b;
+            y[T][v + 1] = a - b;
+        }
+    }
+    float zl[PAIR_NT][8], zh[PAIR_NT][8];
+    pair2_exchange<0>(S, y, zl, zh);
+    pair2_exchange<4>(S, y, zl, zh);
+    const float inv_hi = S.role ? -inv : inv;  // role 1's difference is minus the true one
+    unsigned char *dst = S.lds + 2 * PAIR_BUF + S.grp * 16384 + S.lane * 16 + S.role * 8;
+#pragma unroll
+    for (int T = 0; T < PAIR_NT; ++T) {
+        const unsigned a0 = fused_quant4(zl[T][0], zl[T][1], zl[T][2], zl[T][3], inv, qlo, qhi);
+        const unsigned a1 = fused_quant4(zl[T][4], zl[T][5], zl[T][6], zl[T][7], inv, qlo, qhi);
+        const unsigned b0 = fused_quant4(zh[T][0], zh[T][1], zh[T][2], zh[T][3], inv_hi, qlo, qhi);
+        const unsigned b1 = fused_quant4(zh[T][4], zh[T][5], zh[T][6], zh[T][7], inv_hi, qlo, qhi);
+        *reinterpret_cast<uint2 *>(dst + T * 1024) = make_uint2(a0, a1);
+        *reinterpret_cast<uint2 *>(dst + (T + 8) * 1024) = make_uint2(b0, b1);
+    }
+}
+
+template <int ACTK>
+__global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair2_kernel(const pair_args A)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int h = lane >> 5;
+    const int L = A.n_layers;
+    const int64_t n_tiles = (A.n + PAIR_TILE - 1) / PAIR_TILE;
+    if ((int64_t)blockIdx.x >= n_tiles) return;
+    const int my_tiles = (int)((n_tiles - 1 - blockIdx.x) / gridDim.x) + 1;
+    const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
+
+    pair_stream S;
+    pair_stream_init(S, &A, lds, wave, lane);
+    int cc = 0;
+    pair_copy_now(S, 0, 0);
+    pair_copy_bias(S, 0);
+
+    for (int it = 0; it < my_tiles; ++it) {
+        const int64_t tile = (int64_t)blockIdx.x + (int64_t)it * gridDim.x;
+        dhq_v4i cd[PAIR_KB];
+#pragma unroll
+        for (int kb = 0; kb < PAIR_KB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
+        {
+            unsigned tid = threadIdx.x;  // (worked out afresh in every pass, see dhq_fused_pair_kernel)
+            asm volatile("" : "+v"(tid));
+            const int64_t ci = tile * PAIR_TILE + S.grp * 32 + (tid & 31);
+            const int64_t cl = ci < A.n ? ci : A.n - 1;  // lanes past the end repeat the last coordinate and store nothing
+            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
+        }
+        dhq_v16f y[PAIR_NT];
+        pair2_input_layer<ACTK>(S, cc, A.c1[0], cd, y, h);
+        pair2_transform_quant(S, y, A.inv_in[1], qlo, qhi);
+        for (int l = 1; l < L - 1; ++l) {
+            pair2_hidden<ACTK>(S, cc, l, A.c1[l], cd, y, h);
+            pair2_transform_quant(S, y, A.inv_in[l + 1], qlo, qhi);
+        }
+        // output layer: one zero-padded tile in two digit planes
+        {
+            pair_enter_chunk(S, cc);
+            const unsigned char *buf = lds + (cc & 1) * PAIR_BUF;
+            pair_copy_slot<0>(S); pair_copy_slot<1>(S); pair_copy_slot<2>(S); pair_copy_slot<3>(S);
+            pair_copy_bias(S, 0);
+            if (S.role == 0) {
+                unsigned tid = threadIdx.x;
+                asm volatile("" : "+v"(tid));
+                const int lane = tid & 63, h = (tid >> 5) & 1;
+                const int64_t ci = tile * PAIR_TILE + S.grp * 32 + (tid & 31);
+                const bool valid = ci < A.n;
+                const dhq_v4i *src = reinterpret_cast<const dhq_v4i *>(lds + 2 * PAIR_BUF + S.grp * 16384) + lane;
+                const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(buf);
+                dhq_v16i acc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = 0;
+#pragma unroll
+                for (int kb = 0; kb < PAIR_KB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wA[kb * 64 + lane], src[kb * 64], acc, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+#pragma unroll
+                for (int kb = 0; kb < PAIR_KB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wA[1024 + kb * 64 + lane], src[kb * 64], acc, 0, 0, 0);
+                const float *wB = reinterpret_cast<const float *>(lds + PAIR_BIAS + pair_bias_slot(L - 1) * 2048);
+                const float c1 = A.c1[L - 1];
+                if (valid) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+                        if (row < A.m_out) A.out[ci * A.m_out + row] = __builtin_fmaf((float)acc[v], c1, wB[((v >> 2) * 2 + h) * 4 + (v & 3)]);
+                    }
+                }
+            }
+            cc += 1;
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
 // ---- one layer per launch: the dynamic quantization module (Sec. 3.3) at this width -----------
 // With scales measured on line a layer's quantizer needs max |x^| over the whole batch before it
 // can emit a code, so the whole-network kernel is cut at exactly that point, as
@@ -1000,6 +1344,110 @@ hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t 
                : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>
                                                                : dhq_fused_pair_kernel<DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>;
     hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
+    if (e != hipSuccess) return e;
+    kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
+    return hipGetLastError();
+}
+
+// ---- the two-sided kernel ----
+// Fragment of one tile and digit plane: byte jj of lane (i, u) of k block kb is the digit of U[row(i)][feature(kb, u, jj)].
+template <typename Row, typename Col>
+static void pair2_pack(const std::vector<int32_t> &U, int Kp, int n_rows, int Kb, int plane, Row row_of, Col col_of, int8_t *frag)
+{
+    for (int kb = 0; kb < Kb; ++kb)
+        for (int ln = 0; ln < 64; ++ln) {
+            const int row = row_of(ln & 31);
+            if (row >= n_rows) continue;  // stays zero
+            for (int jj = 0; jj < 16; ++jj) {
+                const int k = col_of(kb, ln >> 5, jj);
+                if (k < 0) continue;
+                const int32_t u = U[(size_t)row * Kp + k], u0 = ((u + 128) & 255) - 128;
+                frag[((size_t)kb * 64 + ln) * 16 + jj] = (int8_t)(plane ? (u - u0) / 256 : u0);
+            }
+        }
+}
+
+int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
+{
+    *plan_out = nullptr;
+    const int L = m->n_layers;
+    if (!m->rot_out || L < 2 || m->dims[0] > 4 || m->dims[L] > 32 || !dhq_all_hidden_are(m->dims, L, 512)) return DHQ_OK;
+    if (m->act_kind != DHQ_ACT_KIND_SINE && m->act_kind != DHQ_ACT_KIND_WAVELET) return DHQ_OK;
+    for (int l = 0; l < L; ++l)
+        for (int32_t u : m->layer[l].u_host)
+            if (u > PAIR2_MAX_U || u < -PAIR2_MAX_U) return DHQ_OK;
+    dhq_pair_plan *P = new (std::nothrow) dhq_pair_plan();
+    if (!P) return DHQ_ENOMEM;
+    memset(&P->args, 0, sizeof(P->args));
+    const int n_chunks = 2 + 16 * (L - 2);
+    const size_t bias_off = (size_t)(n_chunks + 1) * PAIR_BUF;
+    std::vector<unsigned char> blob(bias_off + (size_t)L * 512 * sizeof(float), 0);
+    int8_t *frags = reinterpret_cast<int8_t *>(blob.data());
+    for (int l = 0; l < L; ++l) {
+        const dhq_layer &Ly = m->layer[l];
+        const bool first = (l == 0), last = (l == L - 1);
+        const int Kp = Ly.Kp;
+        auto col = [&](int kb, int u, int jj) { return first ? (u == 0 && jj < Kp ? jj : -1) : pair2_code_feature(kb, u, jj); };
+        float *bias = reinterpret_cast<float *>(blob.data() + bias_off) + (size_t)l * 512;
+        if (last) {
+            auto row = [](int i) { return i; };
+            for (int p = 0; p < 2; ++p)
+                pair2_pack(Ly.u_host, Kp, Ly.M, PAIR_KB, 1 - p, row, col, frags + (size_t)(n_chunks - 1) * PAIR_BUF + (size_t)p * 16384);
+            for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = Ly.bias_host[f];
+            continue;
+        }
+        for (int role = 0; role < 2; ++role)
+            for (int T = 0; T < PAIR_NT; ++T) {
+                // row 8 g + 4 h + e of an MFMA tile is accumulator 4 g + e of lane half h
+                auto row = [&](int i) { return pair2_feature(role, T, 4 * (i >> 3) + (i & 3), (i >> 2) & 1); };
+                for (int p = 0; p < 2; ++p) {
+                    int8_t *dst = first ? frags + (size_t)role * 16384 + (size_t)(2 * T + p) * 1024
+                                        : frags + (size_t)(1 + 16 * (l - 1) + 2 * T + p) * PAIR_BUF + (size_t)role * 16384;
+                    pair2_pack(Ly.u_host, Kp, 512, first ? 1 : PAIR_KB, 1 - p, row, col, dst);
+                }
+                for (int i = 0; i < 32; ++i) bias[bias_slot(32 * (8 * role + T) + i)] = Ly.bias_rev_host[row(i)];
+            }
+    }
+    P->blob_bytes = blob.size();
+    if (hipMalloc((void **)&P->blob_dev, P->blob_bytes) != hipSuccess) {
+        delete P;
+        return DHQ_ENOMEM;
+    }
+    hipDeviceProp_t prop;
+    if (hipMemcpy(P->blob_dev, blob.data(), P->blob_bytes, hipMemcpyHostToDevice) != hipSuccess ||
+        hipGetDeviceProperties(&prop, m->device) != hipSuccess) {
+        dhq_pair_destroy(P);
+        return DHQ_EHIP;
+    }
+    P->args.blob = P->blob_dev;
+    P->args.n_layers = L;
+    P->args.k0 = m->dims[0];
+    P->args.k0p = m->layer[0].Kp;
+    P->args.m_out = m->dims[L];
+    P->args.qmax = m->qmax_a;
+    P->args.n_chunks = n_chunks;
+    P->args.bias_off = (uint32_t)bias_off;
+    P->args.c2 = dhq_hidden_act(m).c2;
+    P->act_kind = m->act_kind;
+    P->lds_bytes = (size_t)PAIR_BIAS + 3 * 2048;
+    P->n_cu = prop.multiProcessorCount;
+    P->device = m->device;
+    *plan_out = P;
+    return DHQ_OK;
+}
+
+hipError_t dhq_pair2_launch(const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
+{
+    if (!P) return hipErrorInvalidValue;
+    if (n <= 0) return hipSuccess;
+    pair_args a = P->args;
+    a.coords = coords;
+    a.out = out;
+    a.n = n;
+    const int64_t tiles = (n + PAIR_TILE - 1) / PAIR_TILE;
+    const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
+    auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET) ? dhq_fused_pair2_kernel<DHQ_ACT_KIND_WAVELET> : dhq_fused_pair2_kernel<DHQ_ACT_KIND_SINE>;
+    const hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
     kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
     return hipGetLastError();

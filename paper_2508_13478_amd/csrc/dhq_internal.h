@@ -33,6 +33,7 @@ struct dhq_layer {
     std::vector<int8_t> wq_host;  // copy of the codes for dhq_get_weight_codes
     std::vector<float> bias_host;      // M
     std::vector<float> bias_rev_host;  // M
+    std::vector<int32_t> u_host;       // two-sided: H_Mp Wq (Mg x Kp), until the plans are made
     // for the range check of the sine's argument: over the outputs j < M of the integer matrix U the
     // epilogue's input is a product with (Wq, or H_Mp Wq when two-sided)
     int64_t sum_abs_max = 0;        // max_j sum_k |U[j][k]|
@@ -80,6 +81,8 @@ struct dhq_model {
     // the exact widths)
     dhq_fused_plan *pad_fused = nullptr;
     dhq_pair_plan *pad_pair = nullptr;
+    // two-sided variant, hidden width 512 (DHQ_AUTO only: the same bits as layer by layer)
+    dhq_pair_plan *pair2 = nullptr;
     int wide_kernel = 0;              // which of the two runs: 0 the default, 1 one wave, 2 two waves (dhq_select_wide_kernel)
     dhq_float_plan *flt = nullptr;    // floating-point activations (DHQ_W8A32 / DHQ_W32A32)
     dhq_fused2_plan *fused2 = nullptr;  // two-sided variant, hidden width 32..256, fan-out <= 4
@@ -214,6 +217,10 @@ hipError_t dhq_pair_launch(const dhq_pair_plan *plan, const float *coords, int64
 size_t dhq_pair_dynamic_rows(int64_t n);
 hipError_t dhq_pair_dynamic_launch(const dhq_model *m, const float *coords, int64_t n, float *out, float *ws0, float *ws1,
                                    float *partial, float *dyn, hipStream_t st);
+// Two-sided variant at width 512, static scales: the whole network, same bits as the layer-by-layer path.  Null plan where the
+// shape or the size of the un-rotated weights' entries does not fit.
+int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan);
+hipError_t dhq_pair2_launch(const dhq_pair_plan *plan, const float *coords, int64_t n, float *out, hipStream_t st);
 // Which width-512 kernel a model runs at the moment.
 #define DHQ_WIDE_DEFAULT_TWO_WAVES 1
 static inline bool dhq_use_pair(const dhq_model *m)
