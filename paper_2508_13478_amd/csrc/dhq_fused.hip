@@ -293,7 +293,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int L = A.n_layers;
-    const int64_t n_tiles = (A.n + FUSED_TILE - 1) / FUSED_TILE;
+    // 32-row tiles are dealt to wave 0 of every workgroup, then to wave 1 and so on, so that a last pass with too few of
+    // them for all waves leaves the higher waves of every workgroup without one (they only help to copy the weights in)
+    // rather than some workgroups: waves w and w + 4 share a SIMD, and one that has it alone needs about two thirds of the time.
+    const int64_t n_tiles = (A.n + 31) / 32, stride = (int64_t)gridDim.x * FUSED_WAVES;
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
 
     dhq_v4i hA[2];
@@ -303,8 +306,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     if ((int64_t)blockIdx.x < n_tiles)
         fused_issue_copy(A.blob + A.layer[0].blob_off, lds, (int)A.layer[0].chunks, wave, lane, FUSED_WAVES);
 
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t ci = tile * FUSED_TILE + wave * 32 + c;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += stride) {
+        const int64_t wave_tile = tile + (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x;
+        const bool active = wave_tile < n_tiles;
+        const int64_t ci = wave_tile * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;
 
@@ -324,7 +329,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             }
             const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds + p * BLK);
             const float c1 = A.layer[l].c1;
-            if (l == 0)
+            if (!active) {
+            } else if (l == 0)
                 fused_gemm_sine_hm<NT, 1, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + p * BLK + NT * 1024), cd, c1, xt,
                                                      hA, lane, h, A.c2);
             else
@@ -334,8 +340,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             // do vector work, but a wave in its vector phase starves the MFMA chain of the
             // other; keep the phases aligned across the workgroup.
             __syncthreads();
-            fused_tile_stages<NT>(xt);
-            fused_quantize<NT>(xt, cd, A.layer[l + 1].inv_in, qlo, qhi);
+            if (active) {
+                fused_tile_stages<NT>(xt);
+                fused_quantize<NT>(xt, cd, A.layer[l + 1].inv_in, qlo, qhi);
+            }
             p ^= 1;
         }
 
@@ -343,12 +351,166 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
         {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (tile + gridDim.x < n_tiles)
+            if (tile + stride < n_tiles)
                 fused_issue_copy(A.blob + A.layer[0].blob_off, lds + (p ^ 1) * BLK, (int)A.layer[0].chunks, wave, lane, FUSED_WAVES);
-            fused_output_layer<NKB>(reinterpret_cast<const dhq_v4i *>(lds + p * BLK),
-                                    reinterpret_cast<const float *>(lds + p * BLK + NKB * 1024), cd, A.layer[L - 1].c1, A.out, ci,
-                                    valid, A.m_out, lane, h);
+            if (active)
+                fused_output_layer<NKB>(reinterpret_cast<const dhq_v4i *>(lds + p * BLK),
+                                        reinterpret_cast<const float *>(lds + p * BLK + NKB * 1024), cd, A.layer[L - 1].c1, A.out, ci,
+                                        valid, A.m_out, lane, h);
             p ^= 1;
+        }
+    }
+}
+
+// ---- few rows: the features of 32 coordinates split over the waves of a workgroup --------------
+// In the kernel above a wave carries 32 coordinates alone, and a pass takes the time of two waves per SIMD going through
+// every feature (5.5 us per 256-wide layer) however few rows there are.  Here a workgroup of NT waves carries 32 coordinates
+// and each wave one M tile: its GEMM, epilogue and H_32 products.  For the stages over the tile index the work is
+// re-split by rows through LDS (wave w takes rows 16 w / NT .. of every tile), and the codes are joined in LDS, from where
+// every wave reads the whole B operand, as the two waves of a pair do at width 512.  The weights are not staged: a fragment is
+// read by one wave only, straight from device memory, while the layer before is in its epilogue.  Same operations in the
+// same order per value, hence the same bits as the kernel above; what a layer takes is latency: a forward of
+// five 256-wide layers on 1 000 rows 31.7 -> 11.1 us.
+template <int NF, int ACTK>
+__global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_args A)
+{
+    constexpr int NT = NF / 32, NKB = NF / 32, RPW = 16 / NT;
+    __shared__ float4 xs[NT * 4 * 64];    // [tile][row group g][lane]: rows 4 g .. 4 g + 3 of the lane's coordinate
+    __shared__ dhq_v4i codes[NKB * 64];   // [k block][lane]: the next layer's B operand
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 31, h = lane >> 5;
+    const int L = A.n_layers;
+    const int n_tiles = (int)((A.n + 31) / 32);  // fewer than a full pass of the kernel above has
+    const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
+    dhq_v4i hA[2];
+    fused_h32_operand(c, h, hA);
+    for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t ci = (int64_t)tile * 32 + c;
+        const bool valid = ci < A.n;
+        const int64_t cl = valid ? ci : A.n - 1;
+        dhq_v4i fr[NKB];
+        float4 bias[4];
+        {
+            const unsigned char *blk = A.blob + A.layer[0].blob_off;
+            fr[0] = reinterpret_cast<const dhq_v4i *>(blk)[wave * 64 + lane];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * 1024)[(wave * 4 + g) * 2 + h];
+        }
+        dhq_v16i acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0;
+        {
+            dhq_v4i cd = dhq_v4i{0, 0, 0, 0};
+            cd[0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[0], cd, acc, 0, 0, 0);
+        }
+        for (int l = 0; l < L - 1; ++l) {
+            const float c1 = A.layer[l].c1;
+            float4 b[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) b[g] = bias[g];
+            // the next layer's fragments and biases, in time for its GEMM (the output layer: one tile, wave 0's)
+            {
+                const unsigned char *blk = A.blob + A.layer[l + 1].blob_off;
+                const bool last = (l + 1 == L - 1);
+                if (!last || wave == 0) {
+#pragma unroll
+                    for (int kb = 0; kb < NKB; ++kb) fr[kb] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * NKB + kb) * 64 + lane];
+                    const float4 *wB = reinterpret_cast<const float4 *>(blk + (last ? 1 : NT) * NKB * 1024);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) bias[g] = wB[(wave * 4 + g) * 2 + h];
+                }
+            }
+            unsigned hp[8], lp[8];
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) {
+                const float4 bb = b[v >> 2];
+                const float bias0 = (v & 2) ? bb.z : bb.x, bias1 = (v & 2) ? bb.w : bb.y;
+                const float t0 = __builtin_fmaf((float)acc[v], c1, bias0), t1 = __builtin_fmaf((float)acc[v + 1], c1, bias1);
+                float a0, a1;
+                if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
+                    dhq_activate_pair_rev<false>(t0, t1, A.c2, a0, a1);
+                } else {
+                    a0 = dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), A.c2});
+                    a1 = dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), A.c2});
+                }
+                hm_split_pair<ACTK>(a0, a1, hp[v >> 1], lp[v >> 1]);
+            }
+            dhq_v16f x;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) x[v] = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                dhq_v4i p;  // small pieces first
+#pragma unroll
+                for (int d = 0; d < 4; ++d) p[d] = (int)((k & 1) ? hp[4 * (k >> 1) + d] : lp[4 * (k >> 1) + d]);
+                x = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(dhq_v8h, hA[k >> 1]), __builtin_bit_cast(dhq_v8h, p), x, 0, 0, 0);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) xs[(wave * 4 + g) * 64 + lane] = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
+            __syncthreads();
+            float z[NT][RPW];
+#pragma unroll
+            for (int T = 0; T < NT; ++T) {
+                if constexpr (RPW == 2) {
+                    const float2 p = reinterpret_cast<const float2 *>(xs)[((T * 4 + (wave >> 1)) * 64 + lane) * 2 + (wave & 1)];
+                    z[T][0] = p.x; z[T][1] = p.y;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < RPW; i += 4) {
+                        const float4 p = xs[(T * 4 + wave * (RPW / 4) + i / 4) * 64 + lane];
+                        z[T][i] = p.x; z[T][i + 1] = p.y; z[T][i + 2] = p.z; z[T][i + 3] = p.w;
+                    }
+                }
+            }
+#pragma unroll
+            for (int s = 1; s < NT; s <<= 1) {
+#pragma unroll
+                for (int T = 0; T < NT; ++T) {
+                    if ((T & s) == 0) {
+#pragma unroll
+                        for (int i = 0; i < RPW; ++i) {
+                            const float p = z[T][i], q = z[T | s][i];
+                            z[T][i] = p + q;
+                            z[T | s][i] = p - q;
+                        }
+                    }
+                }
+            }
+            const float inv = A.layer[l + 1].inv_in;
+#pragma unroll
+            for (int T = 0; T < NT; ++T) {
+                if constexpr (RPW == 2) {
+                    if ((T & 1) == 0) {
+                        const unsigned w = fused_quant4(z[T][0], z[T][1], z[T + 1][0], z[T + 1][1], inv, qlo, qhi);
+                        unsigned short *d = reinterpret_cast<unsigned short *>(codes) + lane * 8 + wave;
+                        d[T * 512] = (unsigned short)w;
+                        d[(T + 1) * 512] = (unsigned short)(w >> 16);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < RPW; i += 4)
+                        reinterpret_cast<unsigned *>(codes)[(T * 64 + lane) * 4 + wave * (RPW / 4) + i / 4] =
+                            fused_quant4(z[T][i], z[T][i + 1], z[T][i + 2], z[T][i + 3], inv, qlo, qhi);
+                }
+            }
+            __syncthreads();
+            if (l + 1 < L - 1 || wave == 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = 0;
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[kb], codes[kb * 64 + lane], acc, 0, 0, 0);
+            }
+        }
+        if (wave == 0 && valid) {
+            const float c1 = A.layer[L - 1].c1;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+                const float4 bb = bias[v >> 2];
+                const float bv = (v & 3) == 0 ? bb.x : (v & 3) == 1 ? bb.y : (v & 3) == 2 ? bb.z : bb.w;
+                if (row < A.m_out) A.out[ci * A.m_out + row] = __builtin_fmaf((float)acc[v], c1, bv);
+            }
         }
     }
 }
@@ -689,26 +851,62 @@ int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *P)
     return DHQ_OK;
 }
 
-template <int NF, int ACTK>
-static hipError_t fused_launch_act(const dhq_fused_plan *P, const fused_args &a, unsigned grid, hipStream_t st)
+// The most 32-row tiles per CU that the split kernel takes: alone, or as the rest after full passes (a launch more).  Whole
+// forwards of five hidden layers in us, split kernel / higher waves idle / the start of both (all waves of fewer workgroups):
+//   tiles per CU     1                  2                  3                  4
+//   width 256 alone  12.2 / 24.1 / 32   18.9 / 25.4 / 33   27.5 / 26.5 / 34   34.2 / 27.7 / 34
+//   width 256 rest   52.9 / 59.7 / 67   60.6 / 60.3 / 67   67.4 / 63.6 / 67   75.3 / 66.0 / 68
+//   width 128 alone   9.2 / 12.3 / 16    9.5 / 12.8 / 17   11.7 / 13.1 / 17   14.1 / 13.5 / 17
+//   width 128 rest   26.8 / 29.2 / 33   27.7 / 29.4 / 32   29.7 / 29.3 / 32   32.3 / 29.3 / 32
+// Width 64 (six layers) alone 9.2 against 11.6 for all waves of fewer workgroups; as a rest it gains nothing over the launch.
+static int fused_split_most(int nf, bool rest)
 {
-    auto kern = dhq_fused_kernel<NF, ACTK>;
-    hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
-    if (e != hipSuccess) return e;
-    kern<<<grid, FUSED_THREADS, P->lds_bytes, st>>>(a);
+    return nf == 256 ? (rest ? 1 : 2) : nf == 128 ? (rest ? 2 : 3) : (rest ? 0 : 4);
+}
+// A call's rows go to full passes of dhq_fused_kernel (FUSED_WAVES wave tiles of 32 rows per CU); what is left of a last
+// pass runs on dhq_fused_split_kernel where that is faster than the pass.
+template <int NF, int ACTK>
+static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args a, hipStream_t st)
+{
+    const int64_t tiles = (a.n + 31) / 32, pass = (int64_t)P->n_cu * FUSED_WAVES, rest = tiles % pass;
+    int64_t head = a.n;  // rows for the full passes
+    if constexpr (NF >= 64) {
+        if (rest != 0 && rest <= (int64_t)fused_split_most(NF, tiles > pass) * P->n_cu) head = (tiles - rest) * 32;
+    }
+    const int64_t n = a.n;
+    if (head > 0) {
+        a.n = head;
+        const int64_t head_tiles = (head + 31) / 32;
+        // up to four waves of each workgroup have a SIMD each; more than that and fewer workgroups with all their waves
+        // are as fast and use less power (width 256, 49 152 rows: 37.8 us against 39.2)
+        const int64_t want = head_tiles <= 4 * (int64_t)P->n_cu ? head_tiles : (head_tiles + FUSED_WAVES - 1) / FUSED_WAVES;
+        const unsigned grid = (unsigned)(want < P->n_cu ? want : P->n_cu);
+        auto kern = dhq_fused_kernel<NF, ACTK>;
+        hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
+        if (e != hipSuccess) return e;
+        kern<<<grid, FUSED_THREADS, P->lds_bytes, st>>>(a);
+        e = hipGetLastError();
+        if (e != hipSuccess || head == n) return e;
+    }
+    if constexpr (NF >= 64) {
+        a.coords += head * a.k0;
+        a.out += head * a.m_out;
+        a.n = n - head;
+        dhq_fused_split_kernel<NF, ACTK><<<(unsigned)rest, NF * 2, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 template <int NF>
-static hipError_t fused_launch_t(const dhq_fused_plan *P, const fused_args &a, int act_kind, unsigned grid, hipStream_t st)
+static hipError_t fused_launch_t(const dhq_fused_plan *P, const fused_args &a, int act_kind, hipStream_t st)
 {
     if (P->padded) {
-        if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(P, a, grid, st);
-        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(P, a, grid, st)
-                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(P, a, grid, st);
+        if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(P, a, st);
+        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(P, a, st)
+                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(P, a, st);
     }
-    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(P, a, grid, st);
-    return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET>(P, a, grid, st)
-                                            : fused_launch_act<NF, DHQ_ACT_KIND_SINE>(P, a, grid, st);
+    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(P, a, st);
+    return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET>(P, a, st)
+                                            : fused_launch_act<NF, DHQ_ACT_KIND_SINE>(P, a, st);
 }
 
 hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
@@ -720,13 +918,11 @@ hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const f
     a.out = out;
     a.n = n;
     a.c2 = dhq_hidden_act(m).c2;
-    const int64_t tiles = (n + FUSED_TILE - 1) / FUSED_TILE;
-    const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
     switch (P->nf) {
-        case 32: return fused_launch_t<32>(P, a, m->act_kind, grid, st);
-        case 64: return fused_launch_t<64>(P, a, m->act_kind, grid, st);
-        case 128: return fused_launch_t<128>(P, a, m->act_kind, grid, st);
-        case 256: return fused_launch_t<256>(P, a, m->act_kind, grid, st);
+        case 32: return fused_launch_t<32>(P, a, m->act_kind, st);
+        case 64: return fused_launch_t<64>(P, a, m->act_kind, st);
+        case 128: return fused_launch_t<128>(P, a, m->act_kind, st);
+        case 256: return fused_launch_t<256>(P, a, m->act_kind, st);
         default: return hipErrorInvalidValue;
     }
 }
