@@ -528,7 +528,7 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
 // So every hidden layer is computed twice and what crosses device memory between two launches is one byte per
 // feature in each direction instead of a float (which is what the codes are there for: the float could only be
 // quantized after the launch that made it).  Five hidden layers of 256 on 262 144 rows: 565 us
-// with the floats (5.2 TB/s), 354 us with the codes, bound by vector instruction issue as the whole-network kernel is.  The codes cross memory in the
+// with the floats (5.2 TB/s), 305 us with the codes, bound by vector instruction issue as the whole-network kernel is.  The codes cross memory in the
 // lanes' register order ([wave tile][k block][lane] x 16 B: every access of a wave is 1 KiB contiguous), and a wave
 // overwrites the codes it has read itself, so one buffer serves all layers.
 //   MODE 0  input layer (no layer below)   MODE 1  hidden layer   MODE 2  output layer: signal values out
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
         }
     }
     const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
-    float mx = 0.f;
+    float mx[4] = {0.f, 0.f, 0.f, 0.f};  // four chains of three-operand maxima
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // the weights are in LDS
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -634,14 +634,15 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
 #pragma unroll
             for (int T = 0; T < NT; ++T) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(xt[T][v]));
+                for (int v = 0; v < 16; v += 2) mx[(v >> 1) & 3] = fmaxf(fmaxf(fabsf(xt[T][v]), fabsf(xt[T][v + 1])), mx[(v >> 1) & 3]);
             }
         }
     }
     if constexpr (MODE != 2) {
+        float mw = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
 #pragma unroll
-        for (int m = 1; m < 64; m *= 2) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-        if (lane == 0) red[wave] = mx;
+        for (int m = 1; m < 64; m *= 2) mw = fmaxf(mw, __shfl_xor(mw, m, 64));
+        if (lane == 0) red[wave] = mw;
         __syncthreads();
         if (threadIdx.x == 0) {
             float r = red[0];
