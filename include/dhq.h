@@ -55,7 +55,8 @@ typedef enum {
 } dhq_status;
 
 /* dhq_forward flags: which implementation runs.  0 picks the fused kernel when the
- * network shape has one and the layer-by-layer path otherwise. */
+ * network shape has one or its hidden widths all round up to such a shape's (zero-padded), a kernel with
+ * the layer-by-layer path's bits for two-sided networks of width 512, and the layer-by-layer path otherwise. */
 #define DHQ_AUTO 0u
 #define DHQ_LAYERWISE 1u /* two to four kernels per layer, activations round-trip device memory */
 #define DHQ_FUSED 2u     /* one kernel for the whole network; DHQ_EUNSUPPORTED if the shape has none */
