@@ -164,6 +164,9 @@ int dhq_quantize_weights_wavelet(const dhq_net_desc *desc, uint32_t mode, float 
  * The model that comes back has the real dims (fan-in, 2 x width, ..., fan-out): every other
  * call (scales, calibration, forward, the test hooks, dhq_get_weight_codes) sees that real
  * network.  Whole-network kernel: hidden widths 16 / 32 / 64 / 128 / 256 complex (32 .. 512 real).
+ * Those kernels hold activations of up to 65 504, while the modulus is bounded by exp(omega0^2 / 4 s0^2) only: unless
+ * that (or, with static scales, what a hidden layer's argument can reach) stays below, DHQ_AUTO runs the network layer by
+ * layer; DHQ_FUSED still accepts it, and saturates larger moduli.
  */
 int dhq_quantize_weights_complex(const dhq_net_desc *desc, float s0, const float *const *W_re,
                                  const float *const *W_im, const float *const *b_re,

@@ -13,6 +13,7 @@
 #include <new>
 #include <vector>
 
+#include "dhq_fused_common.h"
 #include "dhq_internal.h"
 
 #define DHQ_VERSION_NUM 200
@@ -360,6 +361,19 @@ static bool sine_range_ok_dynamic(const dhq_model *m)
         if (!(sine_arg_bound(m, l, sqrt((double)m->layer[l].K) / (double)m->qmax_a) <= DHQ_SINE_MAX_REV)) return false;
     return true;
 }
+// Whether DHQ_AUTO may run the whole-network kernels' binary16 pieces: always for activations bounded by 1; for the complex
+// wavelet where s0, or (static scales) the bound on a hidden layer's argument, keeps the modulus within them.
+static bool pieces_ok_static(const dhq_model *m)
+{
+    if (m->act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX) return true;
+    for (int l = 0; l < m->n_layers - 1; ++l)
+        if (!(dhq_complex_log2_modulus(dhq_hidden_act(m).c2, sine_arg_bound(m, l, (double)m->layer[l].s_a)) <= DHQ_PIECE_LOG2)) return false;
+    return true;
+}
+static bool pieces_ok_dynamic(const dhq_model *m)
+{
+    return m->act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX || dhq_complex_log2_modulus(dhq_hidden_act(m).c2, INFINITY) <= DHQ_PIECE_LOG2;
+}
 
 // The offline step behind every dhq_quantize_weights* entry point; act_kind follows every layer but the last.
 static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, float wavelet_s0, const float *const *W_host,
@@ -401,6 +415,7 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
     // everything that can be refused is refused before the device is touched
     for (int l = 0; l < L && rc == DHQ_OK; ++l) rc = quantize_layer_host(m, l, W_host[l], b_host[l]);
     if (rc == DHQ_OK) m->dyn_sine_ok = sine_range_ok_dynamic(m);
+    if (rc == DHQ_OK) m->dyn_pieces_ok = pieces_ok_dynamic(m);
     if (rc == DHQ_OK && hipGetDevice(&m->device) != hipSuccess) rc = DHQ_EHIP;
     if (rc == DHQ_OK && precision != DHQ_W8A8) {
         // floating-point activations: the network runs on the original weights (W32A32) or on the
@@ -552,6 +567,7 @@ extern "C" int dhq_quantize_weights_complex(const dhq_net_desc *desc, float s0, 
 static int update_fused_scales(dhq_model *m)
 {
     m->fused_sine_ok = sine_range_ok_static(m);
+    m->pieces_ok = pieces_ok_static(m);
     int rc = dhq_fused_update_scales(m, m->fused);
     if (rc == DHQ_OK) rc = dhq_fused_update_scales(m, m->pad_fused);
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pad_pair);
@@ -866,7 +882,8 @@ static int check_dynamic_call(const dhq_model *m, int64_t n, uint32_t path, bool
     const bool dyn_fused_ok = (m->fused || m->fused2 || m->pair) && m->dyn_sine_ok;  // per-layer fused kernels of the dynamic mode
     if (m->flt) return DHQ_EUNSUPPORTED;
     if (path == DHQ_FUSED && !dyn_fused_ok) return DHQ_EUNSUPPORTED;
-    *per_layer_fused = (path != DHQ_LAYERWISE && dyn_fused_ok) || (path == DHQ_AUTO && m->pad_fused && m->dyn_sine_ok);
+    *per_layer_fused = (path == DHQ_FUSED && dyn_fused_ok) ||
+                       (path == DHQ_AUTO && (dyn_fused_ok || (m->pad_fused && m->dyn_sine_ok)) && m->dyn_pieces_ok);
     return DHQ_OK;
 }
 
@@ -909,7 +926,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if (!coords_dev || !out_dev) return DHQ_EINVAL;
     if (!m->have_scales) return DHQ_ENOSCALE;
     if (path == DHQ_FUSED && !fused_ok) return DHQ_EUNSUPPORTED;
-    if (path != DHQ_LAYERWISE && fused_ok) {
+    if ((path == DHQ_FUSED && fused_ok) || (path == DHQ_AUTO && fused_ok && m->pieces_ok)) {
         const hipError_t e = m->fused2 ? dhq_fused2_launch(m->fused2, coords_dev, n, out_dev, st)
                              : m->fused ? dhq_fused_launch(m, m->fused, coords_dev, n, out_dev, st)
                              : dhq_use_pair(m) ? dhq_pair_launch(m->pair, coords_dev, n, out_dev, st)

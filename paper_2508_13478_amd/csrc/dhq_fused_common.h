@@ -2,6 +2,8 @@
 #ifndef DHQ_FUSED_COMMON_H
 #define DHQ_FUSED_COMMON_H
 
+#include <math.h>
+
 #include "dhq_device.h"
 
 // Feature index held by register s of lane half u after an in-register butterfly network whose
@@ -105,8 +107,20 @@ __device__ __forceinline__ void hm_split_pair(float a0, float a1, unsigned &hi, 
 // envelope underflows to zero: 255 revolutions for the real one where (255 c2)^2 >= 169 (exp2 of less than -150 is 0 in
 // fp32), in the imaginary part for the complex one, whose envelope decays with it whatever c2 is.
 #define DHQ_PAD_REV 255.0f
+// The binary16 pieces of an activation hold up to 65 504.  The sine and the real wavelet are bounded by 1, the modulus of
+// the complex wavelet, exp(-omega0 Im y - |s0 y|^2), only by exp(omega0^2 / 4 s0^2): beyond DHQ_PIECE_LOG2 a network runs on the
+// layer-by-layer kernels, whose transform is fp32 (rounded to nearest a piece becomes infinite and its sums NaN, truncated it
+// saturates; either ends as a finite, wrong code).  With t = omega0 Im y / 2 pi in revolutions, |t| <= t_max, the
+// modulus is 2^-(k t + (c2 t)^2), k = 2 pi log2(e), largest at t = -k / 2 c2^2.
+#define DHQ_PIECE_LOG2 15.99
+static inline double dhq_complex_log2_modulus(float c2, double t_max)
+{
+    const double k = 9.0647202836543876, q = (double)c2 * (double)c2;
+    return 2.0 * q * t_max >= k ? k * k / (4.0 * q) : k * t_max - q * t_max * t_max;
+}
 static inline bool dhq_pad_act_ok(int act_kind, float c2)
 {
+    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return dhq_complex_log2_modulus(c2, INFINITY) <= DHQ_PIECE_LOG2;
     return act_kind != DHQ_ACT_KIND_WAVELET || fabsf(c2) * DHQ_PAD_REV >= 13.0f;
 }
 static inline float dhq_pad_bias(int act_kind, int f)

@@ -59,6 +59,7 @@ struct dhq_model {
     bool rot_out = false;  // two-sided variant: weights also rotated over the output features
     bool fused_sine_ok = true;  // with the current static scales (or fp32 weights) no sine argument can leave the hardware's range
     bool dyn_sine_ok = true;  // scales measured on line cannot push a sine argument out of the hardware's range
+    bool pieces_ok = true, dyn_pieces_ok = true;  // no activation can leave the range of the whole-network kernels' binary16 pieces
     uint32_t precision = 0;  // DHQ_W8A8 / DHQ_W8A32 / DHQ_W32A32
     dhq_layer layer[DHQ_MAX_LAYERS];
     // workspace of the layer-by-layer path: two activation buffers, one code buffer
