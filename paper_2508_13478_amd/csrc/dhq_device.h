@@ -69,12 +69,13 @@ __device__ __forceinline__ float dhq_activate_rev(float t, dhq_act act)
 //   exp(j omega0 y - |s0 y|^2) = exp(-omega0 Im y - s0^2 |y|^2) (cos(omega0 Re y) + j sin(omega0 Re y)),
 // the envelope as a base-2 exponential: (c2 t)^2 = (s0 y)^2 log2 e as for the real wavelet, and
 // omega0 Im y log2 e = 2 pi log2(e) ti.  ANY: take the fractional part of tr first (any finite argument).
+// scale: a power of two that both parts are multiplied by.
 template <bool ANY>
-__device__ __forceinline__ void dhq_activate_pair_rev(float tr, float ti, float c2, float &ar, float &ai)
+__device__ __forceinline__ void dhq_activate_pair_rev(float tr, float ti, float c2, float &ar, float &ai, float scale = 1.f)
 {
     const float gr = tr * c2, gi = ti * c2;
     const float e = __builtin_fmaf(gr, gr, __builtin_fmaf(gi, gi, ti * 9.0647202836543876f));
-    const float mag = __builtin_amdgcn_exp2f(-e);
+    const float mag = __builtin_amdgcn_exp2f(-e) * scale;
     const float f = ANY ? __builtin_amdgcn_fractf(tr) : tr;
     ar = __builtin_amdgcn_cosf(f) * mag;
     ai = __builtin_amdgcn_sinf(f) * mag;

@@ -46,7 +46,7 @@ struct fused_layer_desc {
     uint32_t blob_off;   // byte offset of the layer's block in the packed weight blob
     uint32_t chunks;     // block size in KiB (1 KiB = what one wave copies per instruction)
     float c1;            // sine layers: s_a s_w omega0 / (2 pi); output layer: s_a s_w
-    float inv_in;        // 1 / (s_a sqrt(Kp)) of this layer's input quantizer
+    float inv_in;        // 1 / (s_a sqrt(Kp)) of this layer's input quantizer (divided by `scale` behind split activations)
 };
 
 struct fused_args {
@@ -59,6 +59,7 @@ struct fused_args {
     int m_out;     // fan-out of the output layer (<= 32)
     int qmax;
     float c2;      // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
+    float scale;   // padded networks: what the activations are multiplied by before they are split
     fused_layer_desc layer[DHQ_MAX_LAYERS];
 };
 
@@ -139,17 +140,18 @@ struct hm_sched {
 // One layer's GEMM with the dequantize + bias + sine epilogue, the split into binary16 pieces and
 // the H_32 products, software-pipelined by hand according to hm_sched.  On return xt[T][v]
 // holds, for this lane's coordinate, row 8 (v / 4) + 4 h + v % 4 of H_32 * (activations of tile T).
-// ACTK: the activation (sine, or the wavelet with envelope constant c2), plus DHQ_SPLIT_RN where the pieces round to
-// nearest.
+// ACTK: the activation (sine, or the wavelet with envelope constant c2), plus DHQ_SPLIT_RN where the activations are scaled
+// before they are split and hi rounds to nearest (xt then comes out times `scale`).
 template <int NT, int KB, int NCD, int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ wA, const float4 *__restrict__ wB,
                                                    const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
-                                                   const dhq_v4i (&hA)[2], int lane, int h, float c2 = 0.f)
+                                                   const dhq_v4i (&hA)[2], int lane, int h, float c2 = 0.f, float scale = 1.f)
 {
     constexpr hm_sched<NT, KB> S{};
     // the multiplier in a vector register: a multiply-add whose operands are all vector registers issues in about
     // 3 clocks per wave, one with a scalar operand in about 4.5 (measured with a register-only loop)
     asm volatile("" : "+v"(c1));
+    if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) asm volatile("" : "+v"(scale));
     constexpr int LAST = S.last;
     constexpr int NM = NT * KB;
     constexpr int EPS = 16 / KB;  // accumulators drained per step (KB <= 8: an even number)
@@ -214,10 +216,10 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
                 const float t0 = __builtin_fmaf((float)acc[Td % 3][v], c1, bias0), t1 = __builtin_fmaf((float)acc[Td % 3][v + 1], c1, bias1);
                 float a0, a1;
                 if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
-                    dhq_activate_pair_rev<false>(t0, t1, c2, a0, a1);
+                    dhq_activate_pair_rev<false>(t0, t1, c2, a0, a1, hm_scaled<ACTK>(1.f, scale));
                 } else {
-                    a0 = dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), c2});
-                    a1 = dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), c2});
+                    a0 = hm_scaled<ACTK>(dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), c2}), scale);
+                    a1 = hm_scaled<ACTK>(dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), c2}), scale);
                 }
                 hm_split_pair<ACTK>(a0, a1, hp[Td & 1][v >> 1], lp[Td & 1][v >> 1]);
             }
@@ -333,10 +335,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             if (!active) {
             } else if (l == 0)
                 fused_gemm_sine_hm<NT, 1, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + p * BLK + NT * 1024), cd, c1, xt,
-                                                     hA, lane, h, A.c2);
+                                                     hA, lane, h, A.c2, A.scale);
             else
                 fused_gemm_sine_hm<NT, NKB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + p * BLK + NT * NKB * 1024), cd,
-                                                       c1, xt, hA, lane, h, A.c2);
+                                                       c1, xt, hA, lane, h, A.c2, A.scale);
             // The two waves of a SIMD overlap well while both feed the matrix unit or both
             // do vector work, but a wave in its vector phase starves the MFMA chain of the
             // other; keep the phases aligned across the workgroup.
@@ -430,10 +432,10 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
                 const float t0 = __builtin_fmaf((float)acc[v], c1, bias0), t1 = __builtin_fmaf((float)acc[v + 1], c1, bias1);
                 float a0, a1;
                 if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
-                    dhq_activate_pair_rev<false>(t0, t1, A.c2, a0, a1);
+                    dhq_activate_pair_rev<false>(t0, t1, A.c2, a0, a1, hm_scaled<ACTK>(1.f, A.scale));
                 } else {
-                    a0 = dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), A.c2});
-                    a1 = dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), A.c2});
+                    a0 = hm_scaled<ACTK>(dhq_activate_rev(t0, dhq_act{DHQ_KIND(ACTK), A.c2}), A.scale);
+                    a1 = hm_scaled<ACTK>(dhq_activate_rev(t1, dhq_act{DHQ_KIND(ACTK), A.c2}), A.scale);
                 }
                 hm_split_pair<ACTK>(a0, a1, hp[v >> 1], lp[v >> 1]);
             }
@@ -550,6 +552,7 @@ struct fusedl_args {
     int chunks, chunks_below;  // block sizes in KiB
     int k0, k0p, m_out, qmax;
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
+    float scale, unscale;      // padded networks: what the activations are multiplied by before they are split, and 1 over it
 };
 
 // BELOW0: the layer below is the input layer.  ACTK: the activation of the hidden layers.
@@ -615,10 +618,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
         if constexpr (MODE != 0) {
             fused_gemm_sine_hm<NT, KBB, NKB, ACTK>(reinterpret_cast<const dhq_v4i *>(lds_below),
                                                    reinterpret_cast<const float4 *>(lds_below + NT * KBB * 1024), cd, c1_below, xt, hA,
-                                                   lane, h, A.c2);
+                                                   lane, h, A.c2, A.scale);
             __syncthreads();  // keeps the two waves of a SIMD in the same phase, as in the whole-network kernel
             fused_tile_stages<NT>(xt);
-            fused_quantize<NT>(xt, cd, inv, qlo, qhi);
+            fused_quantize<NT>(xt, cd, hm_scaled<ACTK>(inv, A.unscale), qlo, qhi);
             if constexpr (MODE == 1) {
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb) codes[kb * 64] = cd[kb];
@@ -629,7 +632,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
                                     lane, h);
         } else {
             fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
-                                                  A.c2);
+                                                  A.c2, A.scale);
             __syncthreads();
             fused_tile_stages<NT>(xt);
 #pragma unroll
@@ -649,7 +652,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
             float r = red[0];
 #pragma unroll
             for (int w = 1; w < FUSED_WAVES; ++w) r = fmaxf(r, red[w]);
-            A.partial[blockIdx.x] = r;
+            A.partial[blockIdx.x] = hm_scaled<ACTK>(r, A.unscale);
         }
     }
 }
@@ -764,6 +767,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     P->act_kind = m->act_kind;
     P->padded = padded;
     memset(&P->args, 0, sizeof(P->args));
+    P->args.scale = padded ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, dhq_hidden_act(m).c2)) : 1.f;
 
     // block sizes: fragments [Mt][Kb] KiB + one KiB of biases
     std::vector<unsigned char> blob;
@@ -849,6 +853,7 @@ int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *P)
         const dhq_layer &Ly = m->layer[l];
         P->args.layer[l].c1 = dhq_c1(m, l);
         P->args.layer[l].inv_in = (float)(1.0 / ((double)Ly.s_a * sqrt((double)Ly.Kp)));
+        if (l > 0) P->args.layer[l].inv_in /= P->args.scale;  // a power of two
     }
     return DHQ_OK;
 }
@@ -1002,6 +1007,8 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
         a.n = n;
         a.k0 = P->args.k0; a.k0p = P->args.k0p; a.m_out = P->args.m_out; a.qmax = P->args.qmax;
         a.c2 = dhq_hidden_act(m).c2;
+        a.scale = P->args.scale;
+        a.unscale = 1.f / P->args.scale;
         switch (P->nf) {
             case 32: e = fusedl_launch_nf<32>(P, l, L, a, grid, st); break;
             case 64: e = fusedl_launch_nf<64>(P, l, L, a, grid, st); break;

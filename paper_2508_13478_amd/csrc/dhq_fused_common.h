@@ -75,30 +75,42 @@ __device__ __forceinline__ void hm_remainders(float a0, float a1, unsigned hi, f
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(a0), "v"(hi));
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(a1), "v"(hi));
 }
-// The rounding of the two packings, chosen by an instance's activation kind: with DHQ_SPLIT_RN both pieces round to
-// nearest, so that hi + lo is within 2^-23 |a| and the transform is no worse than fp32 butterflies (rms 0.75e-6 against
-// 0.9e-6 at width 256, truncation 1.3e-6).  The zero-padded networks run these instances, because the layer-by-layer
-// kernels that were their only path use fp32 butterflies; the conversion issues at half rate (3 % of a forward).
+// The zero-padded networks (instances with DHQ_SPLIT_RN in the activation kind) split more finely, because the layer-by-layer
+// kernels that were their only path transform in fp32: activations are multiplied by a power of two first (`scale`, taken
+// out again in the quantizer's multiplier), hi rounds to nearest, and hi + lo is within 2^-23 |a| wherever lo is no
+// subnormal: down to |a| = 2^-16 for activations bounded by 1 (scale 2^15), 2^-39 absolute below.  (lo as well rounded to
+// nearest is no closer: a - hi is at most 2^12 units of a's last place, of which lo drops at most one either way.  Without the
+// scale the bound holds down to |a| = 1/4 only, 2^-25 below it, and in a wavelet network of activations around 1e-4
+// every third row had a code of another value; now as many as with fp32 butterflies, 0.2 %.)  The packed conversion of hi
+// issues at half rate, 3 % of a forward; the multiplication is another 5 % of a sine network's (3 x 257, 65 536 rows: 60.0 ->
+// 62.6 us), 3 % of a wavelet's, 2 % of a complex one's (one for both parts).  Two mixed-precision multiply-adds that round
+// to binary16 in place of the subtractions and lo's conversion are slower: they issue at half rate too.
 #define DHQ_SPLIT_RN 16
 #define DHQ_KIND(ACTK) ((ACTK) & 15)
 template <int ACTK>
-__device__ __forceinline__ unsigned hm_pack_piece(float a, float b)
+__device__ __forceinline__ float hm_scaled(float a, float scale)
+{
+    return (ACTK & DHQ_SPLIT_RN) != 0 ? a * scale : a;
+}
+// hi of two (scaled) activations.
+template <int ACTK>
+__device__ __forceinline__ unsigned hm_pack_hi(float a0, float a1)
 {
     if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) {
         // (not inline assembly: the compiler has to see the write to keep an MFMA that reads it two wait states away)
-        const dhq_v2f v = {a, b};
+        const dhq_v2f v = {a0, a1};
         return __builtin_bit_cast(unsigned, __builtin_convertvector(v, dhq_v2h));
     } else {
-        return hm_pack_half2(a, b);
+        return hm_pack_half2(a0, a1);
     }
 }
 template <int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void hm_split_pair(float a0, float a1, unsigned &hi, unsigned &lo)
 {
-    hi = hm_pack_piece<ACTK>(a0, a1);
+    hi = hm_pack_hi<ACTK>(a0, a1);
     float r0, r1;
     hm_remainders(a0, a1, hi, r0, r1);
-    lo = hm_pack_piece<ACTK>(r0, r1);
+    lo = hm_pack_half2(r0, r1);
 }
 
 // A network whose hidden widths all round up to the same power of two n runs on the n-wide kernels: the rotation
@@ -118,10 +130,19 @@ static inline double dhq_complex_log2_modulus(float c2, double t_max)
     const double k = 9.0647202836543876, q = (double)c2 * (double)c2;
     return 2.0 * q * t_max >= k ? k * k / (4.0 * q) : k * t_max - q * t_max * t_max;
 }
+// The power of two a padded network's activations are split at (hm_split_pair): the largest that keeps them within a
+// piece.  A complex network has to leave eight bits of it (moduli of up to 254), or it stays layer by layer.
+#define DHQ_PIECE_SPARE 8
+static inline int dhq_piece_scale_log2(int act_kind, float c2)
+{
+    if (act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX) return 15;
+    const double spare = DHQ_PIECE_LOG2 - dhq_complex_log2_modulus(c2, INFINITY);
+    return spare >= 15.0 ? 15 : spare >= 0.0 ? (int)spare : -1;  // (NaN: -1)
+}
 static inline bool dhq_pad_act_ok(int act_kind, float c2)
 {
-    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return dhq_complex_log2_modulus(c2, INFINITY) <= DHQ_PIECE_LOG2;
-    return act_kind != DHQ_ACT_KIND_WAVELET || fabsf(c2) * DHQ_PAD_REV >= 13.0f;
+    if (act_kind == DHQ_ACT_KIND_WAVELET && !(fabsf(c2) * DHQ_PAD_REV >= 13.0f)) return false;
+    return dhq_piece_scale_log2(act_kind, c2) >= DHQ_PIECE_SPARE;
 }
 static inline float dhq_pad_bias(int act_kind, int f)
 {

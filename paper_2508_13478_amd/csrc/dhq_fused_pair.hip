@@ -69,8 +69,9 @@ struct pair_args {
     int chunk_base;            // first of them: 0 (the whole network), or a single layer's first chunk
     uint32_t bias_off;         // byte offset of the bias table in the blob: [layer][512] floats, bias_slot order per tile
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
+    float scale;               // padded networks: what the activations are multiplied by before they are split
     float c1[DHQ_MAX_LAYERS];
-    float inv_in[DHQ_MAX_LAYERS];
+    float inv_in[DHQ_MAX_LAYERS];  // (behind split activations divided by `scale`)
 };
 
 struct dhq_pair_plan {
@@ -160,6 +161,7 @@ struct pair_ctx {
     const float4 *bias;           // this layer's biases in LDS, this wave's first tile, lane half folded in
     int cc, layer;
     float c1, c2;
+    float scale;                  // padded networks: what the activations are multiplied by before they are split
     dhq_v4i fr[PAIR_PF + 1];
     float4 bq[3];
     float4 bq0[4];
@@ -258,8 +260,8 @@ __device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
         __builtin_amdgcn_sched_barrier(0);
         if constexpr ((e2 & 1) == 0) {
             constexpr int pl = (e2 - 4) / 2, ph = (e2 - 2) / 2;  // pairs whose low / high pieces are packed now
-            if constexpr (e2 >= 4 && pl < NE / 2) C.lp[(pl / 8) & 1][pl % 8] = hm_pack_piece<ACTK>(C.er[0], C.er[1]);
-            if constexpr (e2 >= 2 && ph < NE / 2) C.hp[(ph / 8) & 1][ph % 8] = hm_pack_piece<ACTK>(C.ar[(e2 - 2) & 3], C.ar[(e2 - 1) & 3]);
+            if constexpr (e2 >= 4 && pl < NE / 2) C.lp[(pl / 8) & 1][pl % 8] = hm_pack_half2(C.er[0], C.er[1]);
+            if constexpr (e2 >= 2 && ph < NE / 2) C.hp[(ph / 8) & 1][ph % 8] = hm_pack_hi<ACTK>(C.ar[(e2 - 2) & 3], C.ar[(e2 - 1) & 3]);
         } else {
             constexpr int pm = (e2 - 3) / 2;  // pair whose remainders are taken now
             if constexpr (e2 >= 3 && pm < NE / 2)
@@ -270,9 +272,9 @@ __device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
                 // accumulators e2 - 1, e2 (e2 odd) are the features 2m, 2m + 1 = (Re, Im) of one complex feature; both
                 // results are consumed from the step after this one on (the packing of the high pieces)
                 if constexpr ((e2 & 1) == 0) C.et = C.ey;
-                else dhq_activate_pair_rev<false>(C.et, C.ey, C.c2, C.ar[(e2 - 1) & 3], C.ar[e2 & 3]);
+                else dhq_activate_pair_rev<false>(C.et, C.ey, C.c2, C.ar[(e2 - 1) & 3], C.ar[e2 & 3], hm_scaled<ACTK>(1.f, C.scale));
             } else {
-                C.ar[e2 & 3] = dhq_activate_rev(C.ey, dhq_act{DHQ_KIND(ACTK), C.c2});
+                C.ar[e2 & 3] = hm_scaled<ACTK>(dhq_activate_rev(C.ey, dhq_act{DHQ_KIND(ACTK), C.c2}), C.scale);
             }
         }
         if constexpr (e1 >= 0 && e1 < NE) C.ey = __builtin_fmaf(C.ex, C.c1, pair_comp(C.bq[(e1 / 4) % 3], e1 % 4));
@@ -306,6 +308,8 @@ __device__ __forceinline__ void pair_hidden(pair_stream &S, int &cc, int layer, 
     C.cc = cc;
     C.c1 = c1;
     C.c2 = S.A->c2;
+    C.scale = S.A->scale;
+    if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) asm volatile("" : "+v"(C.scale));
     C.ex = C.ey = C.et = 0.f;
     C.layer = layer;
     C.bias = reinterpret_cast<const float4 *>(S.lds + PAIR_BIAS + pair_bias_slot(layer) * 2048) + S.role * 64 + h;
@@ -356,10 +360,11 @@ __device__ __forceinline__ void pair_step0(pair_ctx<ACTK> &C, int h)
         for (int v = 0; v < 16; ++v) x[v] = __builtin_fmaf(x[v], C.c1, pair_comp(C.bq0[v >> 2], v & 3));
         if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
 #pragma unroll
-            for (int d = 0; d < 8; ++d) dhq_activate_pair_rev<false>(x[2 * d], x[2 * d + 1], C.c2, x[2 * d], x[2 * d + 1]);
+            for (int d = 0; d < 8; ++d)
+                dhq_activate_pair_rev<false>(x[2 * d], x[2 * d + 1], C.c2, x[2 * d], x[2 * d + 1], hm_scaled<ACTK>(1.f, C.scale));
         } else {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) x[v] = dhq_activate_rev(x[v], dhq_act{DHQ_KIND(ACTK), C.c2});
+            for (int v = 0; v < 16; ++v) x[v] = hm_scaled<ACTK>(dhq_activate_rev(x[v], dhq_act{DHQ_KIND(ACTK), C.c2}), C.scale);
         }
 #pragma unroll
         for (int d = 0; d < 8; ++d) hm_split_pair<ACTK>(x[2 * d], x[2 * d + 1], C.hp[G & 1][d], C.lp[G & 1][d]);
@@ -384,6 +389,8 @@ __device__ __forceinline__ void pair_input_layer(pair_stream &S, int &cc, float 
     C.cc = cc;
     C.c1 = c1;
     C.c2 = S.A->c2;
+    C.scale = S.A->scale;
+    if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) asm volatile("" : "+v"(C.scale));
     C.layer = 0;
     C.bias = reinterpret_cast<const float4 *>(S.lds + PAIR_BIAS + pair_bias_slot(0) * 2048) + S.role * 64 + h;
     pair_enter_chunk(S, cc);
@@ -1294,6 +1301,7 @@ int dhq_pair_create(const dhq_model *m, bool padded, dhq_pair_plan **plan_out)
     P->args.n_chunks = n_chunks;
     P->args.bias_off = (uint32_t)bias_off;
     P->args.c2 = dhq_hidden_act(m).c2;
+    P->args.scale = padded ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, P->args.c2)) : 1.f;
     P->act_kind = m->act_kind;
     P->padded = padded;
     P->lds_bytes = (size_t)PAIR_BIAS + 3 * 2048;
@@ -1323,6 +1331,7 @@ int dhq_pair_update_scales(const dhq_model *m, dhq_pair_plan *P)
         const dhq_layer &Ly = m->layer[l];
         P->args.c1[l] = dhq_c1(m, l);
         P->args.inv_in[l] = (float)(1.0 / ((double)Ly.s_a * sqrt((double)Ly.Kp)));
+        if (l > 0) P->args.inv_in[l] /= P->args.scale;  // a power of two
     }
     return DHQ_OK;
 }
@@ -1428,6 +1437,7 @@ int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
     P->args.n_chunks = n_chunks;
     P->args.bias_off = (uint32_t)bias_off;
     P->args.c2 = dhq_hidden_act(m).c2;
+    P->args.scale = 1.f;
     P->act_kind = m->act_kind;
     P->lds_bytes = (size_t)PAIR_BIAS + 3 * 2048;
     P->n_cu = prop.multiProcessorCount;

@@ -68,6 +68,58 @@ def test_padded_widths(dims, s0):
     m.close()
 
 
+@pytest.mark.parametrize("width", [20, 200, 300])
+def test_small_activations_keep_fp32_accuracy(width):
+    """A wavelet layer whose envelope leaves only activations of 1e-6 .. 1e-3: what the transform loses in them has to stay relative to
+    them, as it does in the layer-by-layer path's fp32 butterflies."""
+    s0, dims = 10.0, [2, width, 3]
+    rng = np.random.default_rng(width)
+    W = [rng.uniform(-0.02, 0.02, (width, 2)).astype(np.float32), rng.uniform(-0.3, 0.3, (3, width)).astype(np.float32)]
+    b = [rng.uniform(0.28, 0.32, width).astype(np.float32), np.zeros(3, np.float32)]
+    x = rng.uniform(-1, 1, size=(20000, 2)).astype(np.float32)
+    net = o.quantize_net(dims, 30.0, 8, 8, W, b, gabor_s0=s0)
+    exp, dump = o.forward(net, x, calibrate=True, dump=True)
+    assert 1e-5 < np.abs(dump.act[0]).max() < 2e-3
+    m = dhq.Model(dims, 30.0, W, b, wavelet_s0=s0)
+    m.set_act_scales(net.s_a)
+    # a row is off where one of its Kp codes has fallen the other way, by half a code of the smaller weights at least; x^ in
+    # codes (up to 127) is off by some 2^-23 * 127 = 1.5e-5 (the wavelet's own rounding and the sums'), so a row has such a
+    # code with a probability of about 2 * 1.5e-5 * Kp, at most 1.6e-2; pieces with an absolute error of 2^-25 give a third and more
+    code = float(net.s_a[1]) * float(net.s_w[1])
+    off = {}
+    for name, flags in (("auto", dhq.DHQ_AUTO), ("layer by layer", dhq.DHQ_LAYERWISE)):
+        err = np.abs(_host(m.forward(_dev(x), flags=flags)).astype(np.float64) - exp).max(axis=1)
+        off[name] = (err > 0.5 * code).mean()
+    print(f"[padded] small activations, width {width}: rows with another code {off}", flush=True)
+    assert max(off.values()) <= 2e-2
+    m.close()
+
+
+@pytest.mark.parametrize("dims_c", [[2, 181, 181, 3], [1, 20, 20, 1], [3, 45, 45, 45, 5], [4, 100, 100, 2]],
+                         ids=["181", "20", "45", "100"])
+def test_padded_complex_widths(dims_c):
+    """Complex widths that are no power of two, on few rows and on many, against the oracle (the bounds of the complex networks: a
+    differing code moves the output by about the network's own quantization error)."""
+    Wc, bc = synth.wire_init(dims_c, 30.0, 11 + dims_c[1])
+    dims, W, b = o.complex_net_to_real(dims_c, Wc, bc)
+    m = dhq.Model.complex_wavelet(dims_c, 30.0, Wc, bc, 10.0)
+    rng = np.random.default_rng(dims_c[1])
+    for n in (1, 33, 300, 9007):
+        print(f"[padded] complex {dims_c} n={n}", flush=True)
+        x = rng.uniform(-1, 1, size=(n, dims_c[0])).astype(np.float32)
+        net = o.quantize_net(dims, 30.0, 8, 8, W, b, gabor_s0=o.ComplexSpread(10.0))
+        exp = o.forward(net, x, calibrate=True)
+        ref, _ = o.mlp_float(dims, 30.0, W, b, x, want_f32=False, gabor_s0=o.ComplexSpread(10.0))
+        m.set_act_scales(net.s_a)
+        auto, lw = _host(m.forward(_dev(x))), _host(m.forward(_dev(x), flags=dhq.DHQ_LAYERWISE))
+        for v in (auto, lw):
+            err = np.abs(v.astype(np.float64) - exp).max(axis=1)
+            print(f"  beyond {OUT_TOL}: {(err > OUT_TOL).sum()}, max {err.max():.2e}, median {np.median(err):.1e}", flush=True)
+            assert (err > OUT_TOL).mean() <= max(3e-3, 1.0 / n)
+            assert err.max() <= max(2e-2, 10 * np.sqrt(np.mean((exp - ref) ** 2))) and np.median(err) <= 1e-5
+    m.close()
+
+
 def test_padded_cosine_keeps_the_layer_by_layer_path():
     """A wavelet without an envelope (s0 = 0) is 1 at 0: no padded feature can come out as zero."""
     dims = [2, 40, 40, 3]
