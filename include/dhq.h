@@ -66,8 +66,8 @@ typedef enum {
  * coordinates, instead of using the scales stored in the model (Sec. 3.3, "dynamic
  * quantization module ... between layers").  With DHQ_LAYERWISE: an absmax pass added to every layer, any
  * shape.  With DHQ_FUSED (and DHQ_AUTO where available): one kernel per layer that keeps the
- * layer's arithmetic in registers and passes only the transformed activations through device
- * memory; exists on every shape that has a whole-network kernel (either rotation mode),
+ * layer's arithmetic in registers and passes only the transformed activations (few rows) or the
+ * codes they are quantized to (many) through device memory; exists on every shape that has a whole-network kernel (either rotation mode),
  * DHQ_EUNSUPPORTED otherwise. */
 #define DHQ_DYNAMIC 4u
 

@@ -777,6 +777,7 @@ extern "C" int dhq_calibrate(dhq_model *m, const float *coords_dev, int64_t n, v
 // per-workgroup maxima, and the per-layer constants {quantizer multiplier, epilogue multiplier, s_a}.
 struct dyn_ws {
     float *act0, *act1;
+    size_t act_bytes;  // of each of the two
     int8_t *codes;
     int32_t *acc;
     float *partial;  // 2 x DHQ_ABSMAX_PARTIALS floats
@@ -787,9 +788,9 @@ struct dyn_ws {
 struct dyn_sizes {
     size_t act, codes, acc;
 };
-// (What dhq_noalloc_max_rows promises follows from these; the buffer `act0` also holds the codes of the per-layer fused
-// kernels, which for a padded network's few rows may be the larger of the two: dyn_act0_bytes.)
-static size_t dyn_act0_bytes(const dhq_model *m, int64_t n, size_t act)
+// (What dhq_noalloc_max_rows promises follows from these; the two activation buffers also hold what the per-layer fused
+// kernels of a padded network pass on, which is wider than its activations: dyn_act_bytes.)
+static size_t dyn_act_bytes(const dhq_model *m, int64_t n, size_t act)
 {
     const size_t need = m->pad_fused ? dhq_fused_dynamic_bytes(m->pad_fused, n) : 0;
     return need > act ? need : act;
@@ -819,8 +820,10 @@ static int ensure_dyn_workspace(dhq_model *m, int64_t n)
     m->dyn_acc = nullptr;
     m->dyn_rows = 0;
     const dyn_sizes z = dyn_buffer_sizes(m, n);
-    if (hipMalloc((void **)&m->dyn_act0, dyn_act0_bytes(m, n, z.act)) != hipSuccess) return DHQ_ENOMEM;
-    if (hipMalloc((void **)&m->dyn_act1, z.act) != hipSuccess) return DHQ_ENOMEM;
+    const size_t act = dyn_act_bytes(m, n, z.act);
+    if (hipMalloc((void **)&m->dyn_act0, act) != hipSuccess) return DHQ_ENOMEM;
+    if (hipMalloc((void **)&m->dyn_act1, act) != hipSuccess) return DHQ_ENOMEM;
+    m->dyn_act_bytes = act;
     if (hipMalloc((void **)&m->dyn_codes, z.codes) != hipSuccess) return DHQ_ENOMEM;
     if (z.acc && hipMalloc((void **)&m->dyn_acc, z.acc) != hipSuccess) return DHQ_ENOMEM;
     m->dyn_rows = n;
@@ -841,16 +844,17 @@ extern "C" int dhq_reserve_dynamic(dhq_model *m, int64_t n)
 //
 // Two realisations: layer by layer (absmax pass, quantizer, GEMM: three launches per layer, any
 // shape), or -- where the whole-network fused kernel exists -- one launch per layer that keeps
-// the layer's arithmetic in registers and passes only the transformed activations through
+// the layer's arithmetic in registers and passes only the transformed activations, or their codes, through
 // device memory (dhq_fused_dynamic_launch).  Enqueues kernels only.
 static int forward_dynamic(const dhq_model *m, const dyn_ws &ws, const float *coords_dev, int64_t n, float *out_dev,
                            bool per_layer_fused, hipStream_t st)
 {
     const int L = m->n_layers;
     if (per_layer_fused) {
+        void *const bufs[2] = {ws.act0, ws.act1};
         const hipError_t e =
             m->fused2 ? dhq_fused2_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st)
-            : (m->fused || m->pad_fused) ? dhq_fused_dynamic_launch(m, m->fused ? m->fused : m->pad_fused, coords_dev, n, out_dev, ws.act0, ws.partial, ws.params, st)
+            : (m->fused || m->pad_fused) ? dhq_fused_dynamic_launch(m, m->fused ? m->fused : m->pad_fused, coords_dev, n, out_dev, bufs, ws.act_bytes, ws.partial, ws.params, st)
                        : dhq_pair_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
@@ -915,7 +919,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
         // here when this call brings more rows than dhq_reserve_dynamic or any earlier call provided for.
         rc = ensure_dyn_workspace(const_cast<dhq_model *>(m), n);
         if (rc != DHQ_OK) return rc;
-        const dyn_ws ws = {m->dyn_act0, m->dyn_act1, m->dyn_codes, m->dyn_acc,
+        const dyn_ws ws = {m->dyn_act0, m->dyn_act1, m->dyn_act_bytes, m->dyn_codes, m->dyn_acc,
                            reinterpret_cast<float *>(m->dyn_absmax + DHQ_MAX_LAYERS), m->dyn_params};
         return forward_dynamic(m, ws, coords_dev, n, out_dev, per_layer_fused, st);
     }
@@ -986,14 +990,12 @@ extern "C" int dhq_forward_noalloc(const dhq_model *m, const float *coords_dev, 
     ws.partial = reinterpret_cast<float *>(base);
     base += DHQ_NOALLOC_PARTIAL_BYTES;
     ws.act0 = reinterpret_cast<float *>(base);
-    if (per_layer_fused && m->pad_fused) {
-        // the one buffer these kernels use; it fits wherever the layer-by-layer path's buffers do, except that it is rounded
-        // up to whole workgroup tiles
-        if (dhq_fused_dynamic_bytes(m->pad_fused, n) > DHQ_NOALLOC_SCRATCH_BYTES) per_layer_fused = false;
-    }
-    base += round256(z.act);
+    ws.act_bytes = round256(z.act);
+    // a padded network's per-layer fused kernels use these two buffers only, but wider rows: half of the scratch each
+    if (per_layer_fused && m->pad_fused) ws.act_bytes = DHQ_NOALLOC_SCRATCH_BYTES / 2;
+    base += ws.act_bytes;
     ws.act1 = reinterpret_cast<float *>(base);
-    base += round256(z.act);
+    base += ws.act_bytes;
     ws.codes = reinterpret_cast<int8_t *>(base);
     base += round256(z.codes);
     ws.acc = z.acc ? reinterpret_cast<int32_t *>(base) : nullptr;

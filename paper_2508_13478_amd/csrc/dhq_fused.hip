@@ -521,40 +521,142 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
 // ---- one launch per layer: the dynamic quantization module (Sec. 3.3) ------------------------
 // With scales measured on line, a layer's quantizer needs max |x^| over the whole batch before
 // it can emit a single code, so the network cannot stay in registers from end to end.  These
-// kernels cut the fused kernel at exactly that point.  The launch of layer l
-//   - folds the maxima the previous launch's workgroups left into this layer's constants (every workgroup for
-//     itself: a few hundred floats and three fp64 operations cost less than a launch in between);
-//   - runs the layer below again (GEMM, epilogue, transform), from that layer's input codes, which the previous
-//     launch stored, or from the coordinates: its output x^ is this layer's input;
-//   - quantizes x^, stores the codes for the next launch, runs this layer and keeps only each workgroup's
-//     max |x^| of the result.
-// So every hidden layer is computed twice and what crosses device memory between two launches is one byte per
-// feature in each direction instead of a float (which is what the codes are there for: the float could only be
-// quantized after the launch that made it).  Five hidden layers of 256 on 262 144 rows: 565 us
-// with the floats (5.2 TB/s), 305 us with the codes, bound by vector instruction issue as the whole-network kernel is.  The codes cross memory in the
-// lanes' register order ([wave tile][k block][lane] x 16 B: every access of a wave is 1 KiB contiguous), and a wave
-// overwrites the codes it has read itself, so one buffer serves all layers.
+// kernels cut the fused kernel at exactly that point: the launch of layer l folds the maxima the previous launch's
+// workgroups left into this layer's constants (every workgroup for itself: a few hundred floats and three fp64
+// operations cost less than a launch in between), quantizes its input x^ with them, runs the layer (GEMM, epilogue,
+// transform) and leaves each workgroup's max |x^| of the result.  How x^ gets from one launch to the next:
+//   - as floats (dhq_fused_layer_xhat_kernel): written by the launch that made them, four bytes a feature in each
+//     direction;
+//   - not at all (dhq_fused_layer_kernel): a launch runs the layer below again, from that layer's input codes, which the
+//     previous launch stored (they could only be quantized after the launch that made them), or from the coordinates, and
+//     stores the codes it makes of the result for the next launch.  One byte a feature in each direction, and every
+//     hidden layer computed twice.
+// The same operations on the same values, so the same bits.  The floats are bound by memory from about half a pass of the
+// chip on; the second computation costs its latency however few rows there are.  Five hidden layers of 256, floats / codes:
+// 1 000 rows 65 / 82 us, 262 144 rows 561 (5.2 TB/s) / 353 us (bound by vector instruction issue as the whole-network kernel
+// is); fused_pass_floats draws the line.  Everything crosses memory in the lanes' register order ([wave tile][k block][lane] x 16 B
+// codes, [wave tile][float4][lane]: every access of a wave is 1 KiB contiguous); a wave overwrites the codes it has read
+// itself, so one buffer of them serves all layers, while the floats take two in turn.
 //   MODE 0  input layer (no layer below)   MODE 1  hidden layer   MODE 2  output layer: signal values out
 struct fusedl_args {
     const float *coords;
     dhq_v4i *codes;            // MODE 1, 2: in (unless the layer below is the input layer); MODE 1: out
+    const float4 *xin;         // floats, MODE 1, 2: in
+    float4 *xout;              // floats, MODE 0, 1: out (not the buffer xin points to)
     float *out;                // MODE 2
     const unsigned char *blk;  // this layer's block of the packed weights (fragments, then biases)
-    const unsigned char *blk_below;  // MODE 1, 2: the block of the layer below
+    const unsigned char *blk_below;  // codes, MODE 1, 2: the block of the layer below
     const float *partial_in;   // max |x^| of this layer's input, one float per workgroup of the launch before
     int partial_count;
     int kp;                    // length of this layer's rotated input
     double c1_over_sa;         // epilogue multiplier divided by the activation scale
     float *dyn;                // this layer's {1 / (s_a sqrt(Kp)), epilogue multiplier, s_a}: written by workgroup 0
-    const float *dyn_below;    // MODE 1, 2: those of the layer below, written by the launch before
+    const float *dyn_below;    // codes, MODE 1, 2: those of the layer below, written by the launch before
     float *partial;            // MODE 0, 1: max |x^| of the output per workgroup (not the buffer partial_in points to)
     int64_t n;
     int chunks, chunks_below;  // block sizes in KiB
     int k0, k0p, m_out, qmax;
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
-    float scale, unscale;      // padded networks: what the activations are multiplied by before they are split, and 1 over it
+    float scale, unscale;      // what the activations are multiplied by before they are split (padded networks), and 1 over it
 };
 
+// This layer's constants from the maxima of its input.
+__device__ __forceinline__ void fusedl_constants(const fusedl_args &A, float (&red_in)[FUSED_WAVES], int wave, int lane, float &inv, float &c1)
+{
+    float mi = 0.f, s_a;
+    for (int i = threadIdx.x; i < A.partial_count; i += FUSED_THREADS) mi = fmaxf(mi, A.partial_in[i]);
+#pragma unroll
+    for (int m = 1; m < 64; m *= 2) mi = fmaxf(mi, __shfl_xor(mi, m, 64));
+    if (lane == 0) red_in[wave] = mi;
+    __syncthreads();
+    mi = red_in[0];
+#pragma unroll
+    for (int w = 1; w < FUSED_WAVES; ++w) mi = fmaxf(mi, red_in[w]);
+    dhq_dyn_constants(mi, A.kp, A.qmax, A.c1_over_sa, inv, c1, s_a);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        A.dyn[0] = inv; A.dyn[1] = c1; A.dyn[2] = s_a;
+    }
+}
+// Each workgroup's maximum of its lanes' mw.
+__device__ __forceinline__ void fusedl_store_max(const fusedl_args &A, float (&red)[FUSED_WAVES], int wave, int lane, float mw)
+{
+#pragma unroll
+    for (int m = 1; m < 64; m *= 2) mw = fmaxf(mw, __shfl_xor(mw, m, 64));
+    if (lane == 0) red[wave] = mw;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float r = red[0];
+#pragma unroll
+        for (int w = 1; w < FUSED_WAVES; ++w) r = fmaxf(r, red[w]);
+        A.partial[blockIdx.x] = r * A.unscale;
+    }
+}
+
+// x^ between the launches as floats.  ACTK: the activation of the hidden layers (MODE 0, 1).
+template <int NF, int MODE, int ACTK>
+__global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_xhat_kernel(const fusedl_args A)
+{
+    constexpr int NT = NF / 32, NKB = NF / 32, NR = NF / 2;
+    constexpr int KB = (MODE == 0) ? 1 : NKB;      // k blocks of this layer's GEMM
+    constexpr int MT = (MODE == 2) ? 1 : NT;       // M tiles of this layer's GEMM
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ float red_in[FUSED_WAVES], red[FUSED_WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane & 31, h = lane >> 5;
+    const int64_t n_tiles = (A.n + FUSED_TILE - 1) / FUSED_TILE;
+    const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
+    dhq_v4i hA[2];
+    fused_h32_operand(c, h, hA);
+    fused_issue_copy(A.blk, lds, A.chunks, wave, lane, FUSED_WAVES);
+    float inv, c1;
+    fusedl_constants(A, red_in, wave, lane, inv, c1);
+    const float inv_x = inv * A.unscale;
+    const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
+    float mx = 0.f;
+    bool landed = false;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t ci = tile * FUSED_TILE + wave * 32 + c;
+        const bool valid = ci < A.n;
+        const int64_t cl = valid ? ci : A.n - 1;  // lanes past the end repeat the last coordinate: no effect on the maximum
+        const size_t slot = ((size_t)tile * FUSED_WAVES + wave) * (NR / 4) * 64 + lane;
+        dhq_v4i cd[NKB];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
+        if constexpr (MODE == 0) {
+            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, inv, A.qmax);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NR / 4; ++q) {
+                const float4 x = A.xin[slot + (size_t)q * 64];
+                cd[q / 4][q % 4] = (int)fused_quant4(x.x, x.y, x.z, x.w, inv_x, qlo, qhi);
+            }
+        }
+        if (!landed) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();  // the weights are in LDS
+            landed = true;
+        }
+        if constexpr (MODE == 2) {
+            fused_output_layer<NKB>(wA, reinterpret_cast<const float *>(lds + MT * KB * 1024), cd, c1, A.out, ci, valid, A.m_out,
+                                    lane, h);
+        } else {
+            dhq_v16f xt[NT];
+            fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
+                                                  A.c2, A.scale);
+            fused_tile_stages<NT>(xt);
+#pragma unroll
+            for (int q = 0; q < NR / 4; ++q) {
+                const float4 x = make_float4(xt[q >> 2][4 * (q & 3)], xt[q >> 2][4 * (q & 3) + 1], xt[q >> 2][4 * (q & 3) + 2],
+                                             xt[q >> 2][4 * (q & 3) + 3]);
+                mx = fmaxf(fmaxf(mx, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
+                A.xout[slot + (size_t)q * 64] = x;
+            }
+        }
+    }
+    if constexpr (MODE != 2) fusedl_store_max(A, red, wave, lane, mx);
+}
+
+// Codes between the launches, the layer below computed again.
 // BELOW0: the layer below is the input layer.  ACTK: the activation of the hidden layers.
 template <int NF, int MODE, bool BELOW0, int ACTK>
 __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fusedl_args A)
@@ -579,23 +681,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
         inv_below = A.dyn_below[0];
         c1_below = A.dyn_below[1];
     }
-    // this layer's constants from the maxima of its input
-    float inv, c1, s_a;
-    {
-        float mi = 0.f;
-        for (int i = threadIdx.x; i < A.partial_count; i += FUSED_THREADS) mi = fmaxf(mi, A.partial_in[i]);
-#pragma unroll
-        for (int m = 1; m < 64; m *= 2) mi = fmaxf(mi, __shfl_xor(mi, m, 64));
-        if (lane == 0) red_in[wave] = mi;
-        __syncthreads();
-        mi = red_in[0];
-#pragma unroll
-        for (int w = 1; w < FUSED_WAVES; ++w) mi = fmaxf(mi, red_in[w]);
-        dhq_dyn_constants(mi, A.kp, A.qmax, A.c1_over_sa, inv, c1, s_a);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            A.dyn[0] = inv; A.dyn[1] = c1; A.dyn[2] = s_a;
-        }
-    }
+    float inv, c1;
+    fusedl_constants(A, red_in, wave, lane, inv, c1);
     const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
     float mx[4] = {0.f, 0.f, 0.f, 0.f};  // four chains of three-operand maxima
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -642,19 +729,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
             }
         }
     }
-    if constexpr (MODE != 2) {
-        float mw = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
-#pragma unroll
-        for (int m = 1; m < 64; m *= 2) mw = fmaxf(mw, __shfl_xor(mw, m, 64));
-        if (lane == 0) red[wave] = mw;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float r = red[0];
-#pragma unroll
-            for (int w = 1; w < FUSED_WAVES; ++w) r = fmaxf(r, red[w]);
-            A.partial[blockIdx.x] = hm_scaled<ACTK>(r, A.unscale);
-        }
-    }
+    if constexpr (MODE != 2) fusedl_store_max(A, red, wave, lane, fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
 }
 
 // ---- test hook: one layer of the whole-network kernel on caller-supplied codes ---------------
@@ -934,12 +1009,51 @@ hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const f
     }
 }
 
-// The dynamic mode on the per-layer kernels above.  ws: dhq_fused_dynamic_bytes bytes for the codes of one layer's input
-// (rows rounded up to whole workgroup tiles); partial: room for 2 x DHQ_ABSMAX_PARTIALS floats (two sets of per-workgroup
-// maxima, used alternately: a layer's slower workgroups still read one set while its faster ones already write the other);
-// dyn: three floats per layer.
+// Whether the launches of a dynamic call on n rows pass floats (see the kernels).  The codes' time goes by whole passes of the
+// chip (FUSED_TILE rows per CU), the floats' by rows, so the floats are ahead in a pass that few CUs take part in: at most these
+// 256ths of them, in the first, the second and the third pass.  Measured, floats / codes in us, four or five hidden
+// layers (one, complex), by CUs in use:
+//                     16         64         96        128        256        264        304
+//   sine 32         26 /  28    27 /  28    28 /  28    30 /  29    32 /  29    38 /  36    38 /  36
+//   sine 64         30 /  33    32 /  34    33 /  35    37 /  35    48 /  36    57 /  49    57 /  49
+//   sine 128        41 /  46    48 /  47    51 /  48    55 /  49    78 /  51    95 /  76    98 /  76
+//   sine 256        67 /  84    80 /  85    88 /  86    97 /  88   139 /  99   176 / 155   179 / 153
+//   wavelet 32      23 /  25    24 /  26    25 /  26    26 /  26    28 /  27    33 /  34    33 /  35
+//   wavelet 64      28 /  32    29 /  33    30 /  33    33 /  33    42 /  35    50 /  48    51 /  49
+//   wavelet 128     38 /  46    43 /  47    47 /  48    50 /  49    68 /  50    84 /  78    86 /  79
+//   wavelet 256     64 /  84    73 /  85    81 /  86    88 /  87   115 /  93   147 / 152   153 / 154
+//   complex 64      11 /  12    11 /  12    11 /  12    12 /  12    13 /  12    15 /  16    16 /  16
+//   complex 256     19 /  23    20 /  23    21 /  23    23 /  23    32 /  23    41 /  37    41 /  37
+// (The codes' times follow the clock the card sustains, 7 % up or down from one card to the next; the floats' do not.)
+static bool fused_pass_floats(const dhq_fused_plan *P, int64_t n)
+{
+    static const short most[4][3][3] = {
+        {{104, 0, 0}, {176, 192, 32}, {176, 160, 200}},  // width 32: sine, wavelet, complex wavelet
+        {{120, 0, 0}, {136, 0, 0}, {200, 48, 0}},        // 64
+        {{62, 0, 0}, {110, 0, 0}, {168, 0, 0}},          // 128
+        {{80, 0, 0}, {120, 112, 0}, {128, 0, 0}},        // 256
+    };
+    const int64_t tiles = (n + FUSED_TILE - 1) / FUSED_TILE, pass = (tiles - 1) / P->n_cu, in_last = tiles - pass * P->n_cu;
+    const int w = P->nf == 32 ? 0 : P->nf == 64 ? 1 : P->nf == 128 ? 2 : 3;
+    const int k = P->act_kind == DHQ_ACT_KIND_WAVELET ? 1 : P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX ? 2 : 0;
+    return n > 0 && pass < 3 && in_last * 256 <= (int64_t)most[w][k][pass] * P->n_cu;
+}
+
+// The dynamic mode on the per-layer kernels above.  ws[0], ws[1]: two buffers of ws_bytes each, at least
+// dhq_fused_dynamic_bytes (rows rounded up to whole workgroup tiles); the codes take the first one, the floats both;
+// partial: room for 2 x DHQ_ABSMAX_PARTIALS floats (two sets of per-workgroup maxima, used alternately: a layer's slower
+// workgroups still read one set while its faster ones already write the other); dyn: three floats per layer.
 size_t dhq_fused_dynamic_rows(int64_t n) { return (size_t)((n + FUSED_TILE - 1) / FUSED_TILE) * FUSED_TILE; }
-size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *P, int64_t n) { return dhq_fused_dynamic_rows(n) * (size_t)P->nf; }
+// What any call of up to n rows takes of each buffer: its codes, or the floats of the most rows up to n that pass them.
+size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *P, int64_t n)
+{
+    const int64_t last = (int64_t)3 * P->n_cu * FUSED_TILE;
+    int64_t floats = n < last ? n : last;
+    while (floats > 0 && !fused_pass_floats(P, floats)) floats -= FUSED_TILE;
+    const size_t codes = dhq_fused_dynamic_rows(n) * (size_t)P->nf;
+    const size_t xhat = floats > 0 ? dhq_fused_dynamic_rows(floats) * (size_t)P->nf * sizeof(float) : 0;
+    return codes > xhat ? codes : xhat;
+}
 
 template <int NF, int MODE, bool BELOW0, int ACTK>
 static hipError_t fusedl_launch_t(const fusedl_args &a, unsigned grid, int device, hipStream_t st)
@@ -951,9 +1065,23 @@ static hipError_t fusedl_launch_t(const fusedl_args &a, unsigned grid, int devic
     kern<<<grid, FUSED_THREADS, lds, st>>>(a);
     return hipGetLastError();
 }
+template <int NF, int MODE, int ACTK>
+static hipError_t fusedl_launch_xhat(const fusedl_args &a, unsigned grid, int device, hipStream_t st)
+{
+    auto kern = dhq_fused_layer_xhat_kernel<NF, MODE, ACTK>;
+    const size_t lds = (size_t)a.chunks * 1024;
+    hipError_t e = dhq_lds_limit_once(kern, lds, device);
+    if (e != hipSuccess) return e;
+    kern<<<grid, FUSED_THREADS, lds, st>>>(a);
+    return hipGetLastError();
+}
 template <int NF, int ACTK>
 static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
+    if (a.xout) {  // floats; the output layer has no activation
+        if (layer == 0) return fusedl_launch_xhat<NF, 0, ACTK>(a, grid, device, st);
+        return layer < n_layers - 1 ? fusedl_launch_xhat<NF, 1, ACTK>(a, grid, device, st) : fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);
+    }
     if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
     if (layer < n_layers - 1)
         return layer == 1 ? fusedl_launch_t<NF, 1, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 1, false, ACTK>(a, grid, device, st);
@@ -973,13 +1101,16 @@ static hipError_t fusedl_launch_nf(const dhq_fused_plan *P, int layer, int L, co
 }
 
 hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, float *out,
-                                    void *ws, float *partial, float *dyn, hipStream_t st)
+                                    void *const (&ws)[2], size_t ws_bytes, float *partial, float *dyn, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
     const int L = m->n_layers;
     const int64_t tiles = (n + FUSED_TILE - 1) / FUSED_TILE;
     const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
+    // (buffers sized for the layer-by-layer path, whose rows are narrower than a padded network's, may be too small for floats)
+    if (dhq_fused_dynamic_rows(n) * (size_t)P->nf > ws_bytes) return hipErrorInvalidValue;
+    const bool floats = fused_pass_floats(P, n) && dhq_fused_dynamic_rows(n) * (size_t)P->nf * sizeof(float) <= ws_bytes;
     // the input layer's scale: max over the rotated coordinates, left as per-workgroup maxima
     float *pbuf[2] = {partial, partial + DHQ_ABSMAX_PARTIALS};
     int count = 0;
@@ -989,7 +1120,11 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
         fusedl_args a;
         memset(&a, 0, sizeof(a));
         a.coords = coords;
-        a.codes = reinterpret_cast<dhq_v4i *>(ws);
+        a.codes = reinterpret_cast<dhq_v4i *>(ws[0]);
+        if (floats) {
+            a.xin = reinterpret_cast<const float4 *>(ws[(l + 1) & 1]);
+            a.xout = reinterpret_cast<float4 *>(ws[l & 1]);
+        }
         a.out = out;
         a.blk = P->blob_dev + P->args.layer[l].blob_off;
         a.chunks = (int)P->args.layer[l].chunks;

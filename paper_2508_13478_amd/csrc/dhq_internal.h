@@ -73,6 +73,7 @@ struct dhq_model {
     int8_t *dyn_codes = nullptr;
     int32_t *dyn_acc = nullptr;
     int64_t dyn_rows = 0;
+    size_t dyn_act_bytes = 0;  // of dyn_act0 and of dyn_act1
     unsigned *dyn_absmax = nullptr;  // DHQ_MAX_LAYERS absmax words, then 2 x DHQ_ABSMAX_PARTIALS floats of scratch
     float *dyn_params = nullptr;     // DHQ_MAX_LAYERS x 3 of the last dynamic forward, as many of the last calibration
     dhq_fused_plan *fused = nullptr;  // hidden width 32..256; null if the shape has no such kernel
@@ -193,12 +194,12 @@ void dhq_fused_destroy(dhq_fused_plan *plan);
 int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *plan);
 hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, float *out,
                             hipStream_t st);
-// Dynamic mode, one launch per layer with the codes passing through ws (dhq_fused_dynamic_bytes(plan, n) bytes);
-// partial: 2 x DHQ_ABSMAX_PARTIALS floats of scratch; dyn: three floats per layer.
+// Dynamic mode, one launch per layer with codes or floats passing through two buffers of ws_bytes each, at least
+// dhq_fused_dynamic_bytes(plan, n); partial: 2 x DHQ_ABSMAX_PARTIALS floats of scratch; dyn: three floats per layer.
 size_t dhq_fused_dynamic_rows(int64_t n);
 size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *plan, int64_t n);
 hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, float *out,
-                                    void *ws, float *partial, float *dyn, hipStream_t st);
+                                    void *const (&ws)[2], size_t ws_bytes, float *partial, float *dyn, hipStream_t st);
 
 
 // Hidden width 512 (defined in dhq_fused_wide.hip); same contract as the functions above.
