@@ -91,6 +91,7 @@ struct dhq_float_plan {
     unsigned char *lw_blob_dev = nullptr;
     unsigned char *act[2] = {nullptr, nullptr};  // chunk_rows rows of fragments of the widest layer
     int64_t chunk_rows = 0;
+    bool narrow = false;  // every layer input up to 64 wide: float_narrow_kernel
     int device = 0;
 };
 
@@ -597,6 +598,105 @@ __global__ __launch_bounds__(256) void float_out_kernel(const unsigned char *__r
     }
 }
 
+// ---- narrow networks: hidden widths up to 64 ----------------------------------------------------
+// A layer of such a network is a few MFMAs per 32 coordinates, so what it takes is latency and memory, and the tiles above,
+// with their stages of LDS copies and fragments of six bytes a value, were slower than one wave per tile that holds the
+// layer's whole weights in registers: 4 layers of 20 features on 65 536 rows 45 -> 19 us, 4 of 48 58 -> 37 us.  Between the
+// layers the activations travel as floats in the lanes' order, [tile of 32 coordinates][feature tile][float4 q][lane], and
+// are split into pieces by the wave that reads them: the same pieces, products and order of sums as above, so the same bits
+// (of sines; a wavelet above goes into its pieces before its last product is rounded to fp32).
+// NT: feature tiles (of the output layer: one, gridDim.y of them); NKB: k blocks.  A wave takes every gridDim.x * 4-th tile.
+struct float_narrow_args {
+    const float *in;           // FIRST: n x K coordinates, else the layer below's output
+    float *out;                // LAST: n x M, else the layer above's input
+    const unsigned char *w;    // [feature tile][k block][piece] KiB
+    const float *bias;         // [feature tile][lane half][16]
+    int64_t n;
+    int n_ct, K, M;
+    float rev, c2;
+};
+template <int ACT, int NT, int NKB, bool FIRST, bool LAST>
+__global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_args A)
+{
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int stride = (int)gridDim.x * 4, T0 = LAST ? (int)blockIdx.y : 0;
+    int ct = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (ct >= A.n_ct) return;
+    // the eight inputs of k block kb
+    auto load = [&](int tile, float (&v)[NKB][8]) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+            if constexpr (FIRST) {
+                const int64_t row = (int64_t)tile * 32 + c;
+                const int k0 = 16 * kb + 8 * h;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[kb][j] = (row < A.n && k0 + j < A.K) ? A.in[row * A.K + k0 + j] : 0.f;
+            } else {
+                const float4 *src = reinterpret_cast<const float4 *>(A.in) + ((size_t)tile * (NKB * 2) + kb * 2) * 64 + lane;
+                const float4 a = src[0], b = src[64];
+                v[kb][0] = a.x; v[kb][1] = a.y; v[kb][2] = a.z; v[kb][3] = a.w;
+                v[kb][4] = b.x; v[kb][5] = b.y; v[kb][6] = b.z; v[kb][7] = b.w;
+            }
+        }
+    };
+    float v[NKB][8];
+    load(ct, v);
+    dhq_v4i w[NT][NKB][3];
+    float bias[NT][16];
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) w[T][kb][p] = reinterpret_cast<const dhq_v4i *>(A.w)[(((T0 + T) * NKB + kb) * 3 + p) * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) *reinterpret_cast<float4 *>(&bias[T][i]) = *reinterpret_cast<const float4 *>(A.bias + ((T0 + T) * 2 + h) * 16 + i);
+    }
+    for (; ct < A.n_ct; ct += stride) {
+        dhq_v4i x[NKB][3];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                unsigned hi, mid, lo;
+                flt_split3(v[kb][2 * d], v[kb][2 * d + 1], hi, mid, lo);
+                x[kb][0][d] = (int)hi; x[kb][1][d] = (int)mid; x[kb][2][d] = (int)lo;
+            }
+        if (ct + stride < A.n_ct) load(ct + stride, v);  // arrives during the products
+        dhq_v16f acc[NT];
+#pragma unroll
+        for (int T = 0; T < NT; ++T) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[T][i] = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) acc[T] = flt_mfma6(w[T][kb], x[kb], acc[T]);
+        }
+#pragma unroll
+        for (int T = 0; T < NT; ++T) {
+            if constexpr (LAST) {
+                const int64_t row = (int64_t)ct * 32 + c;
+                if (row < A.n) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int f = 32 * (T0 + T) + 8 * (i >> 2) + 4 * h + (i & 3);
+                        if (f < A.M) A.out[row * A.M + f] = acc[T][i] + bias[T][i];
+                    }
+                }
+            } else {
+                float4 *dst = reinterpret_cast<float4 *>(A.out) + ((size_t)ct * NT + T) * 256 + lane;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        y[e] = dhq_activate_rev_any(__builtin_fmaf(acc[T][4 * q + e], A.rev, bias[T][4 * q + e]), dhq_act{ACT, A.c2});
+                    dst[q * 64] = make_float4(y[0], y[1], y[2], y[3]);
+                }
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------- host code
 // Feature held by register kk of lane half h (the D layout of the 32 x 32 MFMA).
 static int flt_feature(int kk, int h) { return 32 * (kk >> 4) + 8 * ((kk >> 2) & 3) + 4 * h + (kk & 3); }
@@ -745,6 +845,7 @@ static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, dou
                                   const std::vector<std::vector<float>> &b)
 {
     int max_nkb = 1;
+    P->narrow = true;
     size_t w_off[DHQ_MAX_LAYERS], b_off[DHQ_MAX_LAYERS], bytes = 0;
     for (int l = 0; l < L; ++l) {
         float_lw_layer &Ly = P->lw[l];
@@ -753,6 +854,7 @@ static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, dou
         Ly.nkb = (l == 0) ? (Ly.K + 31) / 32 * 2 : 2 * P->lw[l - 1].Mt;  // even
         Ly.Mt = (Ly.M + 31) / 32;
         if (Ly.nkb > max_nkb) max_nkb = Ly.nkb;
+        if (Ly.nkb > 4) P->narrow = false;
         w_off[l] = bytes;
         b_off[l] = bytes + (size_t)Ly.Mt * Ly.nkb * 3072;
         bytes = (b_off[l] + (size_t)Ly.Mt * 128 + 1023) / 1024 * 1024;
@@ -841,6 +943,30 @@ static hipError_t float_layer_launch(const float_layer_args &a, int n_cu, int de
     return float_layer_launch_t<ACT, 1, 4, 4, 2, 1>(a, device, st);
 }
 
+template <int ACT, int NT, bool FIRST, bool LAST>
+static hipError_t float_narrow_launch_t(const float_narrow_args &a, int nkb, int m_tiles, int n_cu, hipStream_t st)
+{
+    const int want = (a.n_ct + 3) / 4, most = 4 * n_cu;
+    const dim3 grid((unsigned)(want < most ? want : most), (unsigned)(LAST ? m_tiles : 1));
+    if (nkb == 2) float_narrow_kernel<ACT, NT, 2, FIRST, LAST><<<grid, 256, 0, st>>>(a);
+    else float_narrow_kernel<ACT, NT, 4, FIRST, LAST><<<grid, 256, 0, st>>>(a);
+    return hipGetLastError();
+}
+template <int ACT>
+static hipError_t float_narrow_launch(const dhq_float_plan *P, int l, const float_narrow_args &a, hipStream_t st)
+{
+    const float_lw_layer &Ly = P->lw[l];
+    const bool first = (l == 0), last = (l == P->n_layers - 1);
+    if (last)
+        return first ? float_narrow_launch_t<DHQ_ACT_KIND_NONE, 1, true, true>(a, Ly.nkb, Ly.Mt, P->n_cu, st)
+                     : float_narrow_launch_t<DHQ_ACT_KIND_NONE, 1, false, true>(a, Ly.nkb, Ly.Mt, P->n_cu, st);
+    if (Ly.Mt == 1)
+        return first ? float_narrow_launch_t<ACT, 1, true, false>(a, Ly.nkb, 1, P->n_cu, st)
+                     : float_narrow_launch_t<ACT, 1, false, false>(a, Ly.nkb, 1, P->n_cu, st);
+    return first ? float_narrow_launch_t<ACT, 2, true, false>(a, Ly.nkb, 1, P->n_cu, st)
+                 : float_narrow_launch_t<ACT, 2, false, false>(a, Ly.nkb, 1, P->n_cu, st);
+}
+
 hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
@@ -851,6 +977,27 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
     for (int64_t start = 0; start < n; start += step) {
         const int64_t rows = (n - start < step) ? n - start : step;
         const int n_ct = (int)((rows + 31) / 32);
+        if (P->narrow) {
+            for (int l = 0; l < L; ++l) {
+                const float_lw_layer &Ly = P->lw[l];
+                float_narrow_args a;
+                memset(&a, 0, sizeof(a));
+                a.in = (l == 0) ? coords + start * Ly.K : reinterpret_cast<const float *>(P->act[l & 1]);
+                a.out = (l == L - 1) ? out + start * Ly.M : reinterpret_cast<float *>(P->act[(l + 1) & 1]);
+                a.w = Ly.wfrag_dev;
+                a.bias = Ly.bias_dev;
+                a.n = rows;
+                a.n_ct = n_ct;
+                a.K = Ly.K;
+                a.M = Ly.M;
+                a.rev = P->rev;
+                a.c2 = P->actf.c2;
+                const hipError_t e = P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_narrow_launch<DHQ_ACT_KIND_WAVELET>(P, l, a, st)
+                                                                          : float_narrow_launch<DHQ_ACT_KIND_SINE>(P, l, a, st);
+                if (e != hipSuccess) return e;
+            }
+            continue;
+        }
         const int64_t n_frag = (int64_t)n_ct * P->lw[0].nkb;
         float_pack_kernel<<<(unsigned)((n_frag + 3) / 4), 256, 0, st>>>(coords + start * P->lw[0].K, rows, P->lw[0].K, P->lw[0].nkb, n_frag,
                                                                         P->act[0]);
