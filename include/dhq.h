@@ -119,13 +119,17 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  * mode = DHQ_ROTATE_IN is dhq_quantize_weights.
  *
  * mode | DHQ_W8A32 / DHQ_W32A32 (with DHQ_ROTATE_IN only) builds the comparison networks of
- * Sec. 1 / Table 2 with floating-point activations: y = W a + b, a = sin(omega0 y) in fp32 on
- * the fp32 MFMA, where W is the original weight matrix (DHQ_W32A32) or
+ * Sec. 1 / Table 2 with floating-point activations: y = W a + b, a = sin(omega0 y) with fp32
+ * accuracy, where W is the original weight matrix (DHQ_W32A32) or
  * W~ = (s_w Wq) H_Kp / sqrt(Kp), the de-quantized weights taken back to the original basis
- * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits: with fan-in <= 4,
- * equal hidden widths of 32 / 64 / 128 / 256 and fan-out <= 32 DHQ_FUSED is accepted: one fused kernel
- * runs the whole network up to width 128 (DHQ_AUTO, DHQ_FUSED); width 256, where that is slower at
- * every size, and every other shape (and DHQ_LAYERWISE) run one GEMM kernel of fp32 accuracy per layer.  Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
+ * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  With fan-in <= 4,
+ * equal hidden widths of 32 / 64 / 128 and fan-out <= 32, DHQ_AUTO and DHQ_FUSED run the whole network
+ * in one kernel on the fp32 MFMA.  Every other shape, and DHQ_LAYERWISE, runs one kernel per layer
+ * that multiplies three-piece bf16 splits (fp32 accuracy; at width 256 faster than one kernel for the
+ * network at every size, so DHQ_FUSED, which is accepted there, gives the same kernels).  These write the
+ * model's workspace between the layers: up to 192 MiB, held from creation on (64 MiB where no hidden layer is
+ * wider than 64; 65 536 rows' worth, at most 96 MiB, where DHQ_AUTO is the whole-network kernel).
+ * Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
  * DHQ_DYNAMIC and the test hooks return DHQ_EUNSUPPORTED; dhq_forward needs none.
  */
 int dhq_quantize_weights_mode(const dhq_net_desc *desc, uint32_t mode, const float *const *W_host,

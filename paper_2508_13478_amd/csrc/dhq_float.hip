@@ -49,6 +49,9 @@
 // per buffer, 3.68 ms in chunks of 65 536), while narrower networks take as many rows as fit (width 60: 0.24 ms in chunks of
 // 65 536 rows, 0.40 ms in chunks of 32 768).
 #define FLT_ACT_BYTES ((int64_t)96 << 20)
+// A third of that for the narrow networks, whose rows are short (131 072 rows of 64 features; the launches' latency no longer
+// shows), and no more than DHQ_CHUNK rows where DHQ_AUTO has the whole-network kernel and only DHQ_LAYERWISE comes here.
+#define FLT_ACT_BYTES_NARROW ((int64_t)32 << 20)
 
 typedef float dhq_v16f __attribute__((ext_vector_type(16)));
 
@@ -892,8 +895,13 @@ static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, dou
         P->lw[l].wfrag_dev = P->lw_blob_dev + w_off[l];
         P->lw[l].bias_dev = reinterpret_cast<const float *>(P->lw_blob_dev + b_off[l]);
     }
-    P->chunk_rows = (FLT_ACT_BYTES / ((int64_t)max_nkb * 3072) * 32) / 256 * 256;
-    const size_t act_bytes = (size_t)(P->chunk_rows / 32) * max_nkb * 3072;
+    // bytes of 32 rows of the widest hidden layer: fragments, or floats in the narrow networks
+    int max_mt = 1;
+    for (int l = 0; l < L - 1; ++l) max_mt = P->lw[l].Mt > max_mt ? P->lw[l].Mt : max_mt;
+    const int64_t tile_bytes = P->narrow ? (int64_t)max_mt * 4096 : (int64_t)max_nkb * 3072;
+    P->chunk_rows = ((P->narrow ? FLT_ACT_BYTES_NARROW : FLT_ACT_BYTES) / tile_bytes * 32) / 256 * 256;
+    if (dhq_float_shape_ok(dims, L) && dims[1] != 256 && P->chunk_rows > DHQ_CHUNK) P->chunk_rows = DHQ_CHUNK;
+    const size_t act_bytes = (size_t)(P->chunk_rows / 32 * tile_bytes);
     if (hipMalloc((void **)&P->act[0], 2 * act_bytes) != hipSuccess) return DHQ_ENOMEM;
     P->act[1] = P->act[0] + act_bytes;
     return DHQ_OK;

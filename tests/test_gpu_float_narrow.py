@@ -63,3 +63,21 @@ def test_narrow_against_oracle_and_the_wide_kernels(dims, s0):
         assert err <= _tol(dims) * max(1.0, np.abs(exp).max())
     m.close()
     mw.close()
+
+
+@pytest.mark.parametrize("dims,most", [([2, 32, 32, 3], 17), ([2, 64, 64, 3], 34), ([2, 128, 128, 3], 101), ([2, 20, 20, 3], 68),
+                                       ([2, 48, 48, 48, 3], 68), ([2, 300, 300, 3], 202)])
+def test_workspace_of_a_model(dims, most):
+    """Device memory that a model holds, in MB: 65 536 rows of the layer-by-layer path's two buffers where DHQ_AUTO is the
+    whole-network kernel, 64 MiB in narrow networks, 192 MiB in wide ones (and a little for weights and the allocator's rounding)."""
+    import torch
+    W, b = synth.siren_init(dims, 30.0, 1)
+    first = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32)  # the library's own image is loaded now
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    models = [dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32) for _ in range(4)]
+    used = (free - torch.cuda.mem_get_info()[0]) / 4e6
+    print(f"[float workspace] {dims}: {used:.1f} MB a model", flush=True)
+    assert used <= most + 5
+    for m in models + [first]:
+        m.close()
