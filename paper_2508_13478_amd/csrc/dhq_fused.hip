@@ -284,8 +284,16 @@ __device__ __forceinline__ void fused_output_layer(const dhq_v4i *__restrict__ w
     }
 }
 
-// FULL: every wave has a tile in every pass (the test for it costs 0.5 % of a forward).
-template <int NF, int ACTK, bool FULL>
+// ROWS: which rows a wave takes, and whether it has to look.
+//   FUSED_DEALT  32-row tiles go to wave 0 of every workgroup, then to wave 1 and so on, so that a last pass with too few of
+//     them for all waves leaves the higher waves of every workgroup without one (they only help to copy the weights in)
+//     rather than some workgroups: waves w and w + 4 share a SIMD, and one that has it alone needs about two thirds of the time.
+//   FUSED_WHOLE  the same where every wave has a tile in every pass; the test for it costs 0.5 % of a forward.
+//   FUSED_IN_A_ROW  a workgroup takes FUSED_TILE rows in a row, and waves beyond the end repeat the last one: for a last pass
+//     that more than half of the waves have a tile in, where dealing gains nothing and CUs without work leave the others a
+//     higher clock (100 003 rows, 3 layers of 64 and of 256 features: 12.0 and 38.9 us, dealt 12.2 and 39.8).
+enum { FUSED_DEALT, FUSED_WHOLE, FUSED_IN_A_ROW };
+template <int NF, int ACTK, int ROWS>
 __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_args A)
 {
     constexpr int NT = NF / 32;   // M tiles of a hidden layer
@@ -296,10 +304,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int L = A.n_layers;
-    // 32-row tiles are dealt to wave 0 of every workgroup, then to wave 1 and so on, so that a last pass with too few of
-    // them for all waves leaves the higher waves of every workgroup without one (they only help to copy the weights in)
-    // rather than some workgroups: waves w and w + 4 share a SIMD, and one that has it alone needs about two thirds of the time.
-    const int64_t n_tiles = (A.n + 31) / 32, stride = (int64_t)gridDim.x * FUSED_WAVES;
+    constexpr bool IN_A_ROW = (ROWS == FUSED_IN_A_ROW);
+    const int64_t n_tiles = IN_A_ROW ? (A.n + FUSED_TILE - 1) / FUSED_TILE : (A.n + 31) / 32;
+    const int64_t stride = IN_A_ROW ? gridDim.x : (int64_t)gridDim.x * FUSED_WAVES;
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
 
     dhq_v4i hA[2];
@@ -310,8 +317,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
         fused_issue_copy(A.blob + A.layer[0].blob_off, lds, (int)A.layer[0].chunks, wave, lane, FUSED_WAVES);
 
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += stride) {
-        const int64_t wave_tile = tile + (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x;
-        const bool active = FULL || wave_tile < n_tiles;
+        const int64_t wave_tile = IN_A_ROW ? tile * FUSED_WAVES + wave : tile + (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x;
+        const bool active = ROWS != FUSED_DEALT || wave_tile < n_tiles;
         const int64_t ci = wave_tile * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;
@@ -958,12 +965,16 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args a, hipStr
     const int64_t n = a.n;
     if (head > 0) {
         a.n = head;
-        const int64_t head_tiles = (head + 31) / 32;
         // up to four waves of each workgroup have a SIMD each; more than that and fewer workgroups with all their waves
         // are as fast and use less power (width 256, 49 152 rows: 37.8 us against 39.2)
-        const int64_t want = head_tiles <= 4 * (int64_t)P->n_cu ? head_tiles : (head_tiles + FUSED_WAVES - 1) / FUSED_WAVES;
+        const int64_t head_tiles = (head + 31) / 32, last = head_tiles % pass;
+        const bool most = last > 4 * (int64_t)P->n_cu;
+        const int64_t want = most ? (head_tiles + FUSED_WAVES - 1) / FUSED_WAVES : head_tiles;
         const unsigned grid = (unsigned)(want < P->n_cu ? want : P->n_cu);
-        auto kern = head_tiles % ((int64_t)grid * FUSED_WAVES) == 0 ? dhq_fused_kernel<NF, ACTK, true> : dhq_fused_kernel<NF, ACTK, false>;
+        auto kern = last == 0 ? dhq_fused_kernel<NF, ACTK, FUSED_WHOLE> : dhq_fused_kernel<NF, ACTK, FUSED_DEALT>;
+        if constexpr (NF >= 64) {  // (width 32 is no faster in a row: 5 layers, 100 003 rows 11.0 us either way)
+            if (most) kern = dhq_fused_kernel<NF, ACTK, FUSED_IN_A_ROW>;
+        }
         hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
         if (e != hipSuccess) return e;
         kern<<<grid, FUSED_THREADS, P->lds_bytes, st>>>(a);
