@@ -726,7 +726,7 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
         float *bufs[2] = {m->act0, m->act1};
         for (int k = 0; k < l; ++k) {
             const dhq_layer &Ly = m->layer[k];
-            const dhq_wht_fold fold = {reinterpret_cast<float *>(m->dyn_absmax + k), 1, dhq_c1_over_sa(m, k), params + 3 * k};
+            const dhq_wht_fold fold = {nullptr, 0, 0.0, params + 3 * k};
             hipError_t e = dhq_launch_wht_quant(cur, rows, Ly.K, Ly.Kp, 0.0f, m->qmax_a, m->codes, &fold, st);
             if (e == hipSuccess) e = gemm_epilogue(m, k, m->codes, rows, m->acc_ws, params + 3 * k, bufs[k & 1], st);
             if (e != hipSuccess) return e;
@@ -746,7 +746,7 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
                 return DHQ_EHIP;
         }
         if (!keep || l == L - 1) continue;
-        const dhq_wht_fold fold = {reinterpret_cast<float *>(m->dyn_absmax + l), 1, dhq_c1_over_sa(m, l), params + 3 * l};
+        const dhq_wht_fold fold = {nullptr, 0, 0.0, params + 3 * l};  // the finishing kernel of the maximum has left them there
         for (int64_t off = 0; off < n; off += DHQ_CHUNK) {
             const int64_t rows = (n - off) < DHQ_CHUNK ? (n - off) : DHQ_CHUNK;
             if (!one_chunk && input(l, off, rows, &res) != hipSuccess) return DHQ_EHIP;

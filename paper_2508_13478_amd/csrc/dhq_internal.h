@@ -107,7 +107,8 @@ static inline hipError_t dhq_lds_limit_once(Kern kern, size_t bytes, int device)
 // inv = 1 / (s_a * sqrt(Kp)) because the butterflies run un-normalised.
 // Dynamic mode (fold != nullptr): inv is ignored; the kernel folds the `count` per-workgroup maxima that
 // dhq_launch_wht_absmax_partials left in `partial` into max |x^| and derives the layer's constants from it,
-// and stores dyn_out[0..2] = {1 / (s_a sqrt(Kp)), s_a * c1_over_sa, s_a} for the kernels that follow.
+// and stores dyn_out[0..2] = {1 / (s_a sqrt(Kp)), s_a * c1_over_sa, s_a} for the kernels that follow.  With partial null and
+// count 0 the constants are in dyn_out already (the fold takes about a microsecond of a launch).
 struct dhq_wht_fold {
     const float *partial;
     int count;

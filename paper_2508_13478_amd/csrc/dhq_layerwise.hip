@@ -170,6 +170,8 @@ __global__ __launch_bounds__(256) void wht_quant_kernel(const float *__restrict_
         }
         __syncthreads();
         inv = red[4];
+    } else if (dyn_out) {
+        inv = dyn_out[0];  // folded before
     }
     constexpr int EPL = wht_shape<KP>::EPL;
     constexpr int LPR = wht_shape<KP>::LPR;
@@ -290,7 +292,7 @@ hipError_t dhq_launch_wht_quant(const float *in, int64_t n, int K, int Kp, float
                                 int8_t *codes, const dhq_wht_fold *fold, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (fold && (!fold->partial || !fold->dyn_out || fold->count < 1 || fold->count > DHQ_ABSMAX_PARTIALS)) return hipErrorInvalidValue;
+    if (fold && (!fold->dyn_out || (fold->partial ? fold->count < 1 || fold->count > DHQ_ABSMAX_PARTIALS : fold->count != 0))) return hipErrorInvalidValue;
     switch (Kp) {
         case 1: return launch_wht<1>(in, n, K, inv, qmax, codes, fold, st);
         case 2: return launch_wht<2>(in, n, K, inv, qmax, codes, fold, st);
