@@ -20,8 +20,8 @@
 #define DHQ_SINE_MAX_REV 256.0  // the hardware sine and cosine are defined up to this many revolutions
 
 // What dhq_lds_limit_once has already set: (kernel, device) -> bytes.  A fixed table searched
-// linearly (the library has a few dozen kernel instances); when it is full the attribute is
-// simply set again on every call.  Entries are only ever added, by whole-word stores, so
+// linearly (a program runs a few of the library's instances, some three hundred, on each device); when it is full the
+// attribute is simply set again on every call.  Entries are only ever added, by whole-word stores, so
 // concurrent callers at worst set an attribute twice.
 #define DHQ_LDS_TABLE 256
 static struct { const void *kern; int device; int bytes; } lds_table[DHQ_LDS_TABLE];
@@ -656,20 +656,16 @@ static hipError_t gemm_epilogue(const dhq_model *m, int l, const int8_t *codes, 
     return dhq_launch_unrotate(acc_ws, rows, Ly.Mp, Ly.M, c1, bias, dhq_layer_act(m, l), dyn, nullptr, dst, st);
 }
 
-// Runs layers [0, upto) of the layer-by-layer path on `rows` coordinates with the model's static
-// scales.  The result of layer upto-1 lands in *result (one of the workspace buffers, or
-// `final_out` for the network's last layer when it is given).
-static hipError_t run_layers(const dhq_model *m, const layer_ws &ws, const float *in, int64_t rows, int upto,
-                             float *final_out, const float **result, hipStream_t st)
+// Runs the layer-by-layer path on `rows` coordinates with the model's static scales.
+static hipError_t run_layers(const dhq_model *m, const layer_ws &ws, const float *in, int64_t rows, float *out, hipStream_t st)
 {
     const float *cur = in;
     int which = 0;
-    // Two-sided variant, whole network: a layer's un-rotation kernel goes on to rotate and quantize the next layer's
+    // Two-sided variant: a layer's un-rotation kernel goes on to rotate and quantize the next layer's
     // input in the same lanes, so between two layers only codes and rotated accumulators cross device memory.
-    // (Not for a prefix of the network, whose last activations the caller wants, nor for the complex wavelet,
-    // whose activation is a kernel of its own.)
-    const bool chain = m->rot_out && upto == m->n_layers && m->act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX;
-    for (int l = 0; l < upto; ++l) {
+    // (Not for the complex wavelet, whose activation is a kernel of its own.)
+    const bool chain = m->rot_out && m->act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX;
+    for (int l = 0; l < m->n_layers; ++l) {
         const dhq_layer &Ly = m->layer[l];
         const bool last = (l == m->n_layers - 1);
         hipError_t e = hipSuccess;
@@ -685,13 +681,12 @@ static hipError_t run_layers(const dhq_model *m, const layer_ws &ws, const float
             if (e != hipSuccess) return e;
             continue;
         }
-        float *dst = (last && final_out) ? final_out : ws.act[which];
+        float *dst = last ? out : ws.act[which];
         e = gemm_epilogue(m, l, ws.codes, rows, ws.acc, nullptr, dst, st);
         if (e != hipSuccess) return e;
         cur = dst;
         which ^= 1;
     }
-    *result = cur;
     return hipSuccess;
 }
 
@@ -950,9 +945,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     const int K0 = m->dims[0], Mo = m->dims[m->n_layers];
     for (int64_t off = 0; off < n; off += DHQ_CHUNK) {
         const int64_t rows = (n - off) < DHQ_CHUNK ? (n - off) : DHQ_CHUNK;
-        const float *res = nullptr;
-        if (run_layers(m, chunk_ws(m), coords_dev + off * K0, rows, m->n_layers, out_dev + off * Mo, &res, st) != hipSuccess)
-            return DHQ_EHIP;
+        if (run_layers(m, chunk_ws(m), coords_dev + off * K0, rows, out_dev + off * Mo, st) != hipSuccess) return DHQ_EHIP;
     }
     return DHQ_OK;
 }

@@ -1089,19 +1089,28 @@ static hipError_t fusedl_launch_xhat(const fusedl_args &a, unsigned grid, int de
 template <int NF, int ACTK>
 static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
+    // the complex wavelet has a bound on its arguments with on-line scales for one hidden layer only, which the caller checks
+    constexpr bool ONE_HIDDEN = (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX);
+    if (ONE_HIDDEN && n_layers != 2) return hipErrorInvalidValue;
+    const bool last = (layer == n_layers - 1);
     if (a.xout) {  // floats; the output layer has no activation
         if (layer == 0) return fusedl_launch_xhat<NF, 0, ACTK>(a, grid, device, st);
-        return layer < n_layers - 1 ? fusedl_launch_xhat<NF, 1, ACTK>(a, grid, device, st) : fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);
+        if (last) return fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);
+        if constexpr (!ONE_HIDDEN) return fusedl_launch_xhat<NF, 1, ACTK>(a, grid, device, st);
+    } else {
+        if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
+        if (last && layer == 1) return fusedl_launch_t<NF, 2, true, ACTK>(a, grid, device, st);
+        if constexpr (!ONE_HIDDEN) {
+            if (last) return fusedl_launch_t<NF, 2, false, ACTK>(a, grid, device, st);
+            return layer == 1 ? fusedl_launch_t<NF, 1, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 1, false, ACTK>(a, grid, device, st);
+        }
     }
-    if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
-    if (layer < n_layers - 1)
-        return layer == 1 ? fusedl_launch_t<NF, 1, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 1, false, ACTK>(a, grid, device, st);
-    return layer == 1 ? fusedl_launch_t<NF, 2, true, ACTK>(a, grid, device, st) : fusedl_launch_t<NF, 2, false, ACTK>(a, grid, device, st);
+    return hipErrorInvalidValue;
 }
 template <int NF>
 static hipError_t fusedl_launch_nf(const dhq_fused_plan *P, int layer, int L, const fusedl_args &a, unsigned grid, hipStream_t st)
 {
-    if (P->padded) {  // (the complex wavelet has no range bound for on-line scales beyond one hidden layer, which the caller checks)
+    if (P->padded) {
         if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
         if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
         return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);

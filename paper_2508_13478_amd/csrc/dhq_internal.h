@@ -120,7 +120,7 @@ hipError_t dhq_launch_wht_quant(const float *in, int64_t n, int K, int Kp, float
 
 // The same rotation, reduced to max |un-normalised x^| over all rows: *absmax_bits (float bits;
 // cleared by the caller before the first of several calls that are to accumulate) is raised to
-// that maximum.  `partial` is scratch for DHQ_ABSMAX_PARTIALS floats.  If dyn != nullptr, also
+// that maximum.  `partial` is scratch for DHQ_ABSMAX_PARTIALS floats.  Also
 // dyn[0..2] = {1 / (s_a sqrt(Kp)), s_a * c1_over_sa, s_a} with s_a = (float)(max|x^| / qmax)
 // (1 if the tensor is all zero).  Two launches.
 #define DHQ_ABSMAX_PARTIALS 2048

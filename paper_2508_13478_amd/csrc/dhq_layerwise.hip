@@ -236,8 +236,8 @@ __global__ __launch_bounds__(256) void wht_absmax_kernel(const float *__restrict
     if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// One workgroup: *absmax_bits = max(*absmax_bits, partial[0 .. count)); then, if dyn is given,
-// the constants of the dynamic mode for that maximum.
+// One workgroup: *absmax_bits = max(*absmax_bits, partial[0 .. count)); then the constants of the dynamic mode for that
+// maximum.
 __global__ __launch_bounds__(256) void absmax_finish_kernel(const float *__restrict__ partial, int count,
                                                             unsigned *__restrict__ absmax_bits, int Kp, int qmax,
                                                             double c1_over_sa, float *__restrict__ dyn)
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256) void absmax_finish_kernel(const float *__restr
         unsigned bits = __float_as_uint(mx);
         if (*absmax_bits > bits) bits = *absmax_bits;
         *absmax_bits = bits;
-        if (dyn) dyn_scale_write(bits, Kp, qmax, c1_over_sa, dyn);
+        dyn_scale_write(bits, Kp, qmax, c1_over_sa, dyn);
     }
 }
 
@@ -330,7 +330,7 @@ hipError_t dhq_launch_wht_absmax(const float *in, int64_t n, int K, int Kp, unsi
                                  int qmax, double c1_over_sa, float *dyn, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (!partial || !absmax_bits) return hipErrorInvalidValue;
+    if (!partial || !absmax_bits || !dyn) return hipErrorInvalidValue;
     return wht_absmax_dispatch(in, n, K, Kp, absmax_bits, partial, qmax, c1_over_sa, dyn, nullptr, st);
 }
 
