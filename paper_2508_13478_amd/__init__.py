@@ -94,10 +94,25 @@ def _ok(rc: int, what: str) -> None:
         raise DhqError(rc, what)
 
 
+_current_stream = None
+
+
+def _resolve_current_stream():
+    """PyTorch's current stream of the current device as a raw pointer.  Building a torch.cuda.Stream object for it takes a
+    good part of a small call, so the function that returns the pointer itself is used where this PyTorch has it."""
+    global _current_stream
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
+    if raw is None:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    else:
+        _current_stream = lambda: raw(device())
+    return _current_stream
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        return (_current_stream or _resolve_current_stream())() or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

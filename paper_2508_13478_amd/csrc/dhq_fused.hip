@@ -955,7 +955,7 @@ static int fused_split_most(int nf, bool rest)
 // A call's rows go to full passes of dhq_fused_kernel (FUSED_WAVES wave tiles of 32 rows per CU); what is left of a last
 // pass runs on dhq_fused_split_kernel where that is faster than the pass.
 template <int NF, int ACTK>
-static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args a, hipStream_t st)
+static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipStream_t st)
 {
     const int64_t tiles = (a.n + 31) / 32, pass = (int64_t)P->n_cu * FUSED_WAVES, rest = tiles % pass;
     int64_t head = a.n;  // rows for the full passes
@@ -990,7 +990,7 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args a, hipStr
     return hipGetLastError();
 }
 template <int NF>
-static hipError_t fused_launch_t(const dhq_fused_plan *P, const fused_args &a, int act_kind, hipStream_t st)
+static hipError_t fused_launch_t(const dhq_fused_plan *P, fused_args &a, int act_kind, hipStream_t st)
 {
     if (P->padded) {
         if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(P, a, st);

@@ -900,3 +900,19 @@ def test_float_layer_tile_shapes_and_chunks(width, n):
     # (3e-6 rad); the output layer's weights (at most sqrt(6 / 512) / 30) average it down: the bound of the other tests
     assert err <= FLOAT_TOL_WIDE
     m.close()
+
+
+def test_calls_go_to_the_current_stream():
+    """Without a stream argument a call is enqueued on PyTorch's current stream of the current device, the default one or another, and
+    inside a capture on the capturing one."""
+    torch = _torch()
+    import paper_2508_13478_amd as pkg
+    default = torch.cuda.current_stream().cuda_stream
+    assert pkg._stream_ptr(None) == (default or None)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert pkg._stream_ptr(None) == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+        g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        assert pkg._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+    assert pkg._stream_ptr(None) == (default or None) and pkg._stream_ptr(s) == s.cuda_stream == pkg._stream_ptr(s.cuda_stream)
