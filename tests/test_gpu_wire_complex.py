@@ -90,7 +90,7 @@ def case(dims_c, side, seed=0xC0DE, bits=8):
 
 
 # complex widths: 32, 128 and 256 have a whole-network kernel (real widths 64, 256 and 512: the last on the two-wave
-# kernel), 20 and 181 (the width the published architecture uses next to a 256-wide real network) do not
+# kernel), 20 and 181 (the width the published architecture uses next to a 256-wide real network) do not: DHQ_AUTO pads them
 SHAPES = [([2, 32, 32, 32, 3], 64), ([2, 128, 128, 128, 128, 3], 96), ([2, 20, 20, 1], 50), ([2, 181, 181, 3], 40),
           ([2, 256, 256, 256, 3], 72)]
 
@@ -161,7 +161,7 @@ def test_complex_forward(dims_c, side):
 
 def test_complex_three_inputs_wide_and_ragged():
     """Three real inputs, 181 complex features (362 real ones, padded to 512 for the rotation), two outputs,
-    a row count that is no multiple of any tile, through the layer-by-layer path."""
+    a row count that is no multiple of any tile, through the layer-by-layer path and through DHQ_AUTO's zero-padded one."""
     torch = _torch()
     dims_c = [3, 181, 181, 2]
     Wc, bc = synth.wire_init(dims_c, OMEGA0, 77)
@@ -175,11 +175,12 @@ def test_complex_three_inputs_wide_and_ragged():
     assert not m.has_fused()
     for l in range(3):
         assert np.array_equal(m.weight_codes(l), net.Wq[l])
-    out = m.forward(_dev(x))
-    torch.cuda.synchronize()
-    err = np.abs(out.cpu().numpy().astype(np.float64) - exp).max(axis=1)
-    _say(f"  complex 181: {(err > OUT_TOL).sum()} of {err.size} coords beyond {OUT_TOL}, max {err.max():.2e}, median {np.median(err):.1e}")
-    assert (err > OUT_TOL).mean() <= 3e-3 and err.max() <= 5e-2 and np.median(err) <= 1e-5
+    for flags in (dhq.DHQ_LAYERWISE, dhq.DHQ_AUTO):
+        out = m.forward(_dev(x), flags=flags)
+        torch.cuda.synchronize()
+        err = np.abs(out.cpu().numpy().astype(np.float64) - exp).max(axis=1)
+        _say(f"  complex 181: {(err > OUT_TOL).sum()} of {err.size} coords beyond {OUT_TOL}, max {err.max():.2e}, median {np.median(err):.1e}")
+        assert (err > OUT_TOL).mean() <= 3e-3 and err.max() <= 5e-2 and np.median(err) <= 1e-5
     m.close()
 
 
