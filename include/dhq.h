@@ -59,9 +59,10 @@ typedef enum {
  * the layer-by-layer path's bits for two-sided networks of width 512, and the layer-by-layer path otherwise. */
 #define DHQ_AUTO 0u
 #define DHQ_LAYERWISE 1u /* two to four kernels per layer, activations round-trip device memory */
-#define DHQ_FUSED 2u     /* one kernel for the whole network; DHQ_EUNSUPPORTED if the shape has none */
+#define DHQ_FUSED 2u     /* one kernel for the whole network (two launches for some row counts); DHQ_EUNSUPPORTED if the shape has none */
 /* Shapes with a whole-network kernel (DHQ_ROTATE_IN): at least two layers, fan-in <= 4, all hidden
- * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells. */
+ * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells.  (The one exception to "one
+ * kernel": floating-point activations at width 256, see dhq_quantize_weights_mode.) */
 /* or-ed onto the above: measure every layer's activation scale on line, on this call's own
  * coordinates, instead of using the scales stored in the model (Sec. 3.3, "dynamic
  * quantization module ... between layers").  With DHQ_LAYERWISE: an absmax pass added to every layer, any
@@ -112,8 +113,9 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  *     y    = z[:, :M] * (s_a s_w / sqrt(Mp)) + b
  * Weights for which |z| could leave int32 (bound: qmax_a * sum_k |(H_Mp W'q)[j][k]| for some
  * output j) are refused with DHQ_EUNSUPPORTED.  Such a model has a fused kernel when fan-in
- * <= 4, all hidden widths are equal and 32 / 64 / 128 / 256, and fan-out <= 32; otherwise it
- * runs on the layer-by-layer path only.  dhq_get_weight_codes returns Mp x Kp codes,
+ * <= 4, all hidden widths are equal and 32 / 64 / 128 / 256, and fan-out <= 32.  At width 512 DHQ_AUTO
+ * has one too, with the layer-by-layer path's bits (DHQ_FUSED does not: the flag and the test hooks keep to the
+ * others); every other shape runs layer by layer.  dhq_get_weight_codes returns Mp x Kp codes,
  * dhq_gemm_i8 the rotated accumulators (n x Mp) and dhq_forward_debug the un-rotated ones
  * (n x Mp).
  * mode = DHQ_ROTATE_IN is dhq_quantize_weights.
@@ -311,9 +313,9 @@ int dhq_forward_debug_fused(const dhq_model *m, const int8_t *codes_in_dev, int6
 int dhq_gemm_i8(const dhq_model *m, int32_t layer, const int8_t *codes_dev, int64_t n,
                 int32_t *acc_dev, void *stream);
 
-/* 1 if DHQ_FUSED can run this model's shape -- the whole pipeline of Sec. 3.3 (input layer, linear
- * layers with the quantization module between them, output layer) in one kernel -- else 0
- * (negative status on error). */
+/* 1 if DHQ_FUSED can run this model -- the whole pipeline of Sec. 3.3 (input layer, linear
+ * layers with the quantization module between them, output layer) in one kernel (floating-point
+ * activations at width 256: accepted, and run by the layer kernels) -- else 0 (negative status on error). */
 int dhq_has_fused(const dhq_model *m);
 
 /*

@@ -59,8 +59,9 @@ struct fused_args {
     int m_out;     // fan-out of the output layer (<= 32)
     int qmax;
     float c2;      // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
-    float scale;   // padded networks: what the activations are multiplied by before they are split
     fused_layer_desc layer[DHQ_MAX_LAYERS];
+    float scale;   // padded networks: what the activations are multiplied by before they are split (last: with the layers four
+                   // bytes on in the argument block a one-pass forward took 1 % longer, 28.6 against 28.35 us)
 };
 
 struct dhq_fused_plan {
@@ -317,9 +318,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
         fused_issue_copy(A.blob + A.layer[0].blob_off, lds, (int)A.layer[0].chunks, wave, lane, FUSED_WAVES);
 
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += stride) {
-        const int64_t wave_tile = IN_A_ROW ? tile * FUSED_WAVES + wave : tile + (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x;
+        const int64_t wave_tile = tile + (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x;  // (dealt)
         const bool active = ROWS != FUSED_DEALT || wave_tile < n_tiles;
-        const int64_t ci = wave_tile * 32 + c;
+        const int64_t ci = IN_A_ROW ? tile * FUSED_TILE + wave * 32 + c : wave_tile * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;
 
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 }
 
 // ------------------------------------------------------------------------------- host code
-// `padded`: hidden widths that are no multiple of 32 or differ, but round up to the same power of two.
+// `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
 {
     const int L = m->n_layers;
@@ -941,7 +942,7 @@ int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *P)
 }
 
 // The most 32-row tiles per CU that the split kernel takes: alone, or as the rest after full passes (a launch more).  Whole
-// forwards of five hidden layers in us, split kernel / higher waves idle / the start of both (all waves of fewer workgroups):
+// forwards of five hidden layers in us, split kernel / higher waves idle / all waves of fewer workgroups:
 //   tiles per CU     1                  2                  3                  4
 //   width 256 alone  12.2 / 24.1 / 32   18.9 / 25.4 / 33   27.5 / 26.5 / 34   34.2 / 27.7 / 34
 //   width 256 rest   52.9 / 59.7 / 67   60.6 / 60.3 / 67   67.4 / 63.6 / 67   75.3 / 66.0 / 68
@@ -965,16 +966,20 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
     const int64_t n = a.n;
     if (head > 0) {
         a.n = head;
-        // up to four waves of each workgroup have a SIMD each; more than that and fewer workgroups with all their waves
-        // are as fast and use less power (width 256, 49 152 rows: 37.8 us against 39.2)
+        // Up to four waves of each workgroup have a SIMD each; more than that and fewer workgroups with all their waves
+        // are as fast and use less power (width 256, 49 152 rows: 37.8 us against 39.2).  After many passes the test for an idle
+        // wave has cost more than the last one gains.  Dealt / in a row, us, a last pass of 20 000 rows after 5, 10 and 20
+        // full ones: 2 x 64 features 23.4 / 23.5, 41.5 / 41.3, 78.9 / 76.9; 3 x 256 115 / 119, 215 / 219, 416 / 419; of 35 000
+        // rows after 1, 5 and 29: 3 x 64 wavelets 15.8 / 15.5, 42.3 / 41.5, 205 / 200; 2 x 32 features, where in a row is never
+        // ahead, 6.6 / 6.7, 16.0 / 16.2, 73.4 / 73.7.
+        constexpr bool ROWS_MATTER = NF >= 64 || DHQ_KIND(ACTK) != DHQ_ACT_KIND_SINE;
         const int64_t head_tiles = (head + 31) / 32, last = head_tiles % pass;
-        const bool most = last > 4 * (int64_t)P->n_cu;
+        const bool most = last > 4 * (int64_t)P->n_cu, in_a_row = ROWS_MATTER && (most || head_tiles > 11 * pass);
         const int64_t want = most ? (head_tiles + FUSED_WAVES - 1) / FUSED_WAVES : head_tiles;
         const unsigned grid = (unsigned)(want < P->n_cu ? want : P->n_cu);
-        auto kern = last == 0 ? dhq_fused_kernel<NF, ACTK, FUSED_WHOLE> : dhq_fused_kernel<NF, ACTK, FUSED_DEALT>;
-        if constexpr (NF >= 64) {  // (width 32 is no faster in a row: 5 layers, 100 003 rows 11.0 us either way)
-            if (most) kern = dhq_fused_kernel<NF, ACTK, FUSED_IN_A_ROW>;
-        }
+        auto kern = last == 0  ? dhq_fused_kernel<NF, ACTK, FUSED_WHOLE>
+                    : in_a_row ? dhq_fused_kernel<NF, ACTK, FUSED_IN_A_ROW>
+                               : dhq_fused_kernel<NF, ACTK, FUSED_DEALT>;
         hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
         if (e != hipSuccess) return e;
         kern<<<grid, FUSED_THREADS, P->lds_bytes, st>>>(a);

@@ -69,9 +69,9 @@ struct pair_args {
     int chunk_base;            // first of them: 0 (the whole network), or a single layer's first chunk
     uint32_t bias_off;         // byte offset of the bias table in the blob: [layer][512] floats, bias_slot order per tile
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
-    float scale;               // padded networks: what the activations are multiplied by before they are split
     float c1[DHQ_MAX_LAYERS];
     float inv_in[DHQ_MAX_LAYERS];  // (behind split activations divided by `scale`)
+    float scale;               // padded networks: what the activations are multiplied by before they are split
 };
 
 struct dhq_pair_plan {

@@ -36,4 +36,10 @@ def test_same_bits_however_the_rows_are_dealt(width, act):
             print(f"[few rows] {act} {width} n={n}", flush=True)
             out = m.forward(x[:n]).cpu().numpy()
             assert np.array_equal(out, ref[:n])
+    # after more full passes than dealing a last one pays for: a few and most of its waves busy, and whole passes
+    for n in (32 * cu * 8 * 12 + 77, 32 * cu * 8 * 11 + 32 * cu * 6 - 5, 32 * cu * 8 * 12):
+        print(f"[few rows] {act} {width} n={n}", flush=True)
+        out = m.forward(x.repeat((n + n_all - 1) // n_all, 1)[:n].contiguous()).cpu().numpy()
+        for i in range(0, n, n_all):
+            assert np.array_equal(out[i:i + n_all], ref[:min(n_all, n - i)])
     m.close()
