@@ -916,6 +916,8 @@ def test_calls_go_to_the_current_stream():
     with torch.cuda.stream(s):
         assert pkg._stream_ptr(None) == s.cuda_stream == torch.cuda.current_stream().cuda_stream
         g = torch.cuda.CUDAGraph()
+    t = torch.zeros(4, device="cuda")
     with torch.cuda.graph(g, stream=s):
         assert pkg._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+        t += 1
     assert pkg._stream_ptr(None) == (default or None) and pkg._stream_ptr(s) == s.cuda_stream == pkg._stream_ptr(s.cuda_stream)
