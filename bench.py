@@ -285,18 +285,17 @@ def main() -> int:
             res["alu"]["counter_mfma_busy_frac"] = busy["mfma"]
             res["alu"]["counter_source"] = "stored from the rocprofv3 --pmc run summarised in profiles/dhq_fused_utilisation_pmc.md"
     if floating:
-        # fp32 activations: the same multiply-adds on the fp32 MFMA (157.3 TFLOP/s dense), or layer by layer as six products
-        # of bf16 pieces each (2 500 / 6 TFLOP/s)
+        # fp32 activations: every multiply-add as three products of binary16 pieces (2 500 / 3 TFLOP/s)
         tf = ops / (ms * 1e-3) / 1e12
-        one_kernel = fused and wl.dims[1] <= 128
-        peak = 157.3 if one_kernel else 2500.0 / 6
+        one_kernel = args.path != "layerwise"
+        peak = 2500.0 / 3
         res["metric"] = "fp32-activation SIREN forward coords/sec"
         res["dtype"] = "f32"
         res["config"]["workload"] = res["config"]["workload"].replace("W8A8, static per-layer scales from absmax calibration on the same grid", args.variant.upper())
         res.pop("int8_tops"); res.pop("pct_int8_mfma_peak"); res.pop("alu")
         res["roofline"] = {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,
                            "traffic": None,
-                           "kernel": (f"dhq_float_kernel<{wl.dims[1]}>" if one_kernel else "float_layer_kernel, all launches of one forward"),
+                           "kernel": ("float_net_kernel" if one_kernel else "float_layer_kernel, all launches of one forward"),
                            "algorithmic_hbm_bytes_per_launch": 4 * (wl.dims[0] + wl.dims[-1]) * n,
                            "algorithmic_ops_per_launch": ops}
     if not fused and not floating:
@@ -338,7 +337,7 @@ def main() -> int:
         res["layerwise_ms_per_step"] = ms_lw
     if not floating and not two_sided and not dynamic and not cplx:
         # the paper's W32A32-versus-W8A8 comparison (Table 2) on this GPU: the plain fp32 network through
-        # the library's own fp32 kernels (one fused kernel up to width 128, layer by layer beyond), and how
+        # the library's own fp32 kernel, and how
         # far the quantized output is from it
         ref_model = dhq.Model(wl.dims, wl.omega0, W, b, 8, 8, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
         ref_out = torch.empty_like(out)
@@ -348,8 +347,7 @@ def main() -> int:
         mse = float(((out.double() - ref_out.double()) ** 2).mean())
         peak = float(ref_out.max() - ref_out.min())
         res["w32a32_ms_per_step"] = ms_f
-        # (the library accepts DHQ_FUSED at width 256 as well, and runs the layer kernels)
-        res["w32a32_path"] = "fused" if ref_model.has_fused() and wl.dims[1] <= 128 else "layer by layer"
+        res["w32a32_path"] = "fused"
         res["speedup_vs_w32a32"] = ms_f / ms
         res["psnr_vs_w32a32_db"] = 10.0 * math.log10(peak * peak / mse) if mse > 0 else float("inf")
         ref_model.close()

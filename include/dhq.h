@@ -61,8 +61,7 @@ typedef enum {
 #define DHQ_LAYERWISE 1u /* two to four kernels per layer, activations round-trip device memory */
 #define DHQ_FUSED 2u     /* one kernel for the whole network (two launches for some row counts); DHQ_EUNSUPPORTED if the shape has none */
 /* Shapes with a whole-network kernel (DHQ_ROTATE_IN): at least two layers, fan-in <= 4, all hidden
- * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells.  (The one exception to "one
- * kernel": floating-point activations at width 256, see dhq_quantize_weights_mode.) */
+ * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells. */
 /* or-ed onto the above: measure every layer's activation scale on line, on this call's own
  * coordinates, instead of using the scales stored in the model (Sec. 3.3, "dynamic
  * quantization module ... between layers").  With DHQ_LAYERWISE: an absmax pass added to every layer, any
@@ -124,13 +123,13 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  * Sec. 1 / Table 2 with floating-point activations: y = W a + b, a = sin(omega0 y) with fp32
  * accuracy, where W is the original weight matrix (DHQ_W32A32) or
  * W~ = (s_w Wq) H_Kp / sqrt(Kp), the de-quantized weights taken back to the original basis
- * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  With fan-in <= 4,
- * equal hidden widths of 32 / 64 / 128 and fan-out <= 32, DHQ_AUTO and DHQ_FUSED run the whole network
- * in one kernel on the fp32 MFMA.  Every other shape, and DHQ_LAYERWISE, runs one kernel per layer
- * that multiplies three-piece bf16 splits (fp32 accuracy; at width 256 faster than one kernel for the
- * network at every size, so DHQ_FUSED, which is accepted there, gives the same kernels).  These write the
- * model's workspace between the layers: up to 192 MiB, held from creation on (64 MiB where no hidden layer is
- * wider than 64; 65 536 rows' worth, at most 96 MiB, where DHQ_AUTO is the whole-network kernel).
+ * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  DHQ_AUTO runs the whole network
+ * in one kernel that multiplies two-piece binary16 splits (fp32 accuracy), and DHQ_FUSED, which is accepted with
+ * fan-in <= 4, equal hidden widths of 32 / 64 / 128 / 256 and fan-out <= 32, is the same.  DHQ_LAYERWISE, single layers, and
+ * networks with a row of weights most of which are below 2^-17 of its largest (or one that is not finite; these take three-piece
+ * bf16 splits) run one kernel per layer, which write the model's workspace between the layers: up to 192 MiB, held
+ * from creation on (64 MiB where no hidden layer is wider than 64; 65 536 rows' worth, at most 96 MiB, in the shapes
+ * DHQ_FUSED accepts up to 128 wide).
  * Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
  * DHQ_DYNAMIC and the test hooks return DHQ_EUNSUPPORTED; dhq_forward needs none.
  */
@@ -314,8 +313,7 @@ int dhq_gemm_i8(const dhq_model *m, int32_t layer, const int8_t *codes_dev, int6
                 int32_t *acc_dev, void *stream);
 
 /* 1 if DHQ_FUSED can run this model -- the whole pipeline of Sec. 3.3 (input layer, linear
- * layers with the quantization module between them, output layer) in one kernel (floating-point
- * activations at width 256: accepted, and run by the layer kernels) -- else 0 (negative status on error). */
+ * layers with the quantization module between them, output layer) in one kernel -- else 0 (negative status on error). */
 int dhq_has_fused(const dhq_model *m);
 
 /*

@@ -895,13 +895,13 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if ((flags & ~(3u | DHQ_DYNAMIC)) != 0 || path == 3u) return DHQ_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     if (m->flt) {
-        // the whole-network fp32 kernel runs only where the sine's argument provably stays in range
+        // (the kernels reduce the sine's argument themselves; DHQ_FUSED is refused where the other whole-network kernels would be)
         const bool fused_ok = dhq_float_has_fused(m->flt) && m->fused_sine_ok;
         if (dynamic || (path == DHQ_FUSED && !fused_ok)) return DHQ_EUNSUPPORTED;
         if (n == 0) return DHQ_OK;
         if (!coords_dev || !out_dev) return DHQ_EINVAL;
-        const hipError_t e = (path != DHQ_LAYERWISE && fused_ok) ? dhq_float_launch(m->flt, coords_dev, n, out_dev, st)
-                                                                 : dhq_float_launch_layerwise(m->flt, coords_dev, n, out_dev, st);
+        const hipError_t e = path != DHQ_LAYERWISE ? dhq_float_launch(m->flt, coords_dev, n, out_dev, st)
+                                                   : dhq_float_launch_layerwise(m->flt, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
     if (dynamic) {

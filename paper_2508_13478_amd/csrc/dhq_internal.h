@@ -258,9 +258,8 @@ hipError_t dhq_fused2_debug_launch(const dhq_model *m, int layer, const int8_t *
                                    int32_t *acc, hipStream_t st);
 
 // Floating-point activations (defined in dhq_float.hip): the plain network (sine, or the wavelet `act`) on the given fp32
-// weights W[l] (dims[l+1] x dims[l]) and biases.  Every shape has the layer-by-layer path
-// (dhq_float_launch_layerwise); the shapes dhq_float_shape_ok accepts also have one kernel fused
-// over all layers (dhq_float_launch; dhq_float_has_fused tells).
+// weights W[l] (dims[l+1] x dims[l]) and biases: one kernel over all layers (dhq_float_launch) or one per layer
+// (dhq_float_launch_layerwise), any shape.  DHQ_FUSED is accepted for the shapes of dhq_float_shape_ok (dhq_float_has_fused).
 bool dhq_float_shape_ok(const int *dims, int n_layers);
 int dhq_float_create(const int *dims, int n_layers, float omega0, dhq_act act, const std::vector<std::vector<float>> &W,
                      const std::vector<std::vector<float>> &b, int device, dhq_float_plan **plan);

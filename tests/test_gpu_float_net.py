@@ -1,0 +1,51 @@
+"""fp32-activation networks: the whole-network kernel against the layer-by-layer kernels, and weights that two binary16 pieces do not hold."""
+import numpy as np
+import pytest
+
+import paper_2508_13478_amd as dhq
+from oracle import dhq_oracle as o
+from paper_2508_13478_amd import synth
+from test_gpu_variants import FLOAT_TOL_WIDE
+
+pytestmark = pytest.mark.gpu
+
+# widths on both sides of every tile shape's range, unequal ones, fan-ins beyond a k block, outputs beyond a tile, one hidden layer
+SHAPES = [[1, 1, 1], [2, 32, 32, 3], [4, 33, 33, 5], [2, 64, 64, 3], [3, 65, 128, 2], [40, 48, 17, 64, 100], [2, 129, 200, 1], [2, 256, 256, 3],
+          [17, 257, 64, 33], [2, 100, 500, 40, 3], [2, 512, 512, 3]]
+
+
+@pytest.mark.parametrize("dims", SHAPES, ids=["x".join(map(str, d)) for d in SHAPES])
+@pytest.mark.parametrize("s0", [None, 10.0], ids=["sine", "wavelet"])
+def test_same_bits_as_layer_by_layer(dims, s0):
+    """The same pieces, products and order of sums, so the same bits, whatever the tile: one row, the edges of a tile, of one round of
+    the small tiles on 256 CUs, and several rounds with a ragged end."""
+    import torch
+    W, b = synth.siren_init(dims, 30.0, 77 + sum(dims))
+    m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    for n in (1, 32, 33, 8192, 8193, 16385, 32769, 65537, 140001):
+        print(f"[float net] {dims} s0={s0} n={n}", flush=True)
+        x = torch.rand((n, dims[0]), generator=g, device="cuda") * 2 - 1
+        assert torch.equal(m.forward(x), m.forward(x, flags=dhq.DHQ_LAYERWISE))
+    m.close()
+
+
+@pytest.mark.parametrize("width", [32, 48, 256])
+def test_weights_of_very_different_sizes(width):
+    """A feature that is zero for every coordinate, with weights 2^40 times the others': the others keep fp32 accuracy."""
+    dims = [2, width, width, 3]
+    W, b = synth.siren_init(dims, 30.0, 5)
+    W[0][0], b[0][0] = 0.0, 0.0
+    for l in (1, 2):
+        W[l][:, 0] = 2.0 ** 40
+    W[1][0, :], b[1][0] = 0.0, 0.0
+    x = synth.grid_coords(40)
+    import torch
+    m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32)
+    exp, _ = o.mlp_float(dims, 30.0, W, b, x)
+    for flags in (dhq.DHQ_AUTO, dhq.DHQ_LAYERWISE):
+        out = m.forward(torch.from_numpy(x).to("cuda"), flags=flags)
+        err = np.abs(out.cpu().numpy().astype(np.float64) - exp).max()
+        print(f"[float net] width {width} flags {flags}: max-abs err {err:.2e}", flush=True)
+        assert err <= FLOAT_TOL_WIDE
+    m.close()
