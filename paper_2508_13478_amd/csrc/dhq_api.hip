@@ -692,7 +692,8 @@ static hipError_t run_layers(const dhq_model *m, const layer_ws &ws, const float
 
 static layer_ws chunk_ws(const dhq_model *m) { return layer_ws{{m->act0, m->act1}, m->codes, m->acc_ws}; }
 
-// The scales of all layers over the n rows, in chunks of the workspace.  A layer's scale needs the maximum over every row
+// The scales of all layers over the n rows.  One-sided networks up to 256 wide: dhq_fused_measure_launch.  The others in
+// chunks of the workspace, as follows.  A layer's scale needs the maximum over every row
 // before its first code can be written, so between two layers the network has to wait somewhere: as the codes of the layer
 // below, which take a quarter of a float's room.  act1 holds them for n max_kp <= its size (131 072 rows at least, since
 // Kp < 2 K); each layer's GEMM then runs twice (maximum, codes), once where one chunk takes all rows and its activations are
@@ -707,6 +708,19 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
     const bool one_chunk = n <= DHQ_CHUNK;
     float *const partial = reinterpret_cast<float *>(m->dyn_absmax + DHQ_MAX_LAYERS);
     float *const params = m->dyn_params + 3 * DHQ_MAX_LAYERS;  // like the dynamic forward's, which keep its last call's scales
+    auto finish = [&]() {
+        float host[3 * DHQ_MAX_LAYERS];
+        if (hipMemcpyAsync(host, params, sizeof(float) * 3 * L, hipMemcpyDeviceToHost, st) != hipSuccess) return DHQ_EHIP;
+        if (hipStreamSynchronize(st) != hipSuccess) return DHQ_EHIP;
+        for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];
+        return DHQ_OK;
+    };
+    if (const dhq_fused_plan *P = m->fused ? m->fused : m->pad_fused) {
+        void *const buf[2] = {m->act0, m->act1};
+        const hipError_t e = dhq_fused_measure_launch(m, P, coords_dev, n, buf, sizeof(float) * DHQ_CHUNK * m->max_dim, partial, params, st);
+        if (e == hipSuccess) return finish();
+        if (e != hipErrorInvalidValue) return DHQ_EHIP;
+    }
     if (dhq_launch_clear_words(m->dyn_absmax, L, st) != hipSuccess) return DHQ_EHIP;
     // the input of layer l for one chunk: the coordinates, or the output of the layer below from its codes
     auto codes_at = [&](int64_t off) { return reinterpret_cast<int8_t *>(m->act1) + off * m->max_kp; };
@@ -748,11 +762,7 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
             if (dhq_launch_wht_quant(res, rows, Ly.K, Ly.Kp, 0.0f, m->qmax_a, codes_at(off), &fold, st) != hipSuccess) return DHQ_EHIP;
         }
     }
-    float host[3 * DHQ_MAX_LAYERS];
-    if (hipMemcpyAsync(host, params, sizeof(float) * 3 * L, hipMemcpyDeviceToHost, st) != hipSuccess) return DHQ_EHIP;
-    if (hipStreamSynchronize(st) != hipSuccess) return DHQ_EHIP;
-    for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];
-    return DHQ_OK;
+    return finish();
 }
 
 extern "C" int dhq_calibrate(dhq_model *m, const float *coords_dev, int64_t n, void *stream)

@@ -142,7 +142,8 @@ struct hm_sched {
 // the H_32 products, software-pipelined by hand according to hm_sched.  On return xt[T][v]
 // holds, for this lane's coordinate, row 8 (v / 4) + 4 h + v % 4 of H_32 * (activations of tile T).
 // ACTK: the activation (sine, or the wavelet with envelope constant c2), plus DHQ_SPLIT_RN where the activations are scaled
-// before they are split and hi rounds to nearest (xt then comes out times `scale`).
+// before they are split and hi rounds to nearest (xt then comes out times `scale`).  With DHQ_PLAIN xt[T][v] is the activation
+// itself, any finite argument.
 template <int NT, int KB, int NCD, int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ wA, const float4 *__restrict__ wB,
                                                    const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
@@ -189,7 +190,7 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (q < S.hm_n[g]) {
+            if ((ACTK & DHQ_PLAIN) == 0 && q < S.hm_n[g]) {
                 const int Th = S.hm_tile[g][q], k = S.hm_k[g][q];
                 const int blk = k >> 1;
                 dhq_v4i b;  // small pieces first
@@ -216,6 +217,18 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
                 // accumulators v, v + 1 (v even) are neighbouring features 2m, 2m + 1: the pair the complex wavelet takes
                 const float t0 = __builtin_fmaf((float)acc[Td % 3][v], c1, bias0), t1 = __builtin_fmaf((float)acc[Td % 3][v + 1], c1, bias1);
                 float a0, a1;
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) {
+                    if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
+                        dhq_activate_pair_rev<true>(t0, t1, c2, a0, a1);
+                    } else {
+                        a0 = dhq_activate_rev_any(t0, dhq_act{DHQ_KIND(ACTK), c2});
+                        a1 = dhq_activate_rev_any(t1, dhq_act{DHQ_KIND(ACTK), c2});
+                    }
+                    asm volatile("" : "+v"(a0), "+v"(a1));  // (a wavelet's product is rounded before anything is added to it)
+                    xt[Td][v] = a0;
+                    xt[Td][v + 1] = a1;
+                    continue;
+                }
                 if constexpr (DHQ_KIND(ACTK) == DHQ_ACT_KIND_WAVELET_COMPLEX) {
                     dhq_activate_pair_rev<false>(t0, t1, c2, a0, a1, hm_scaled<ACTK>(1.f, scale));
                 } else {
@@ -247,6 +260,82 @@ __device__ __forceinline__ void fused_tile_stages(dhq_v16f (&xt)[NT])
                 }
             }
         }
+    }
+}
+
+// The whole transform in fp32, with the additions of the layer-by-layer kernels in their order (wht_butterflies: index bits
+// 0, 1, then 6, 7 where there are any, then 2, 3, 4, 5), so the same bits.  Index bits 0, 1, 3, 4 are bits of v, 2 is the lane
+// half, 5 .. the tile.  The stage over the lane half works on pairs of registers: v_permlane32_swap brings both operands
+// of one register's stage into one lane half, those of the other's into the other.  With four tiles or more the pairs are tiles
+// T, T | 2, which no later stage combines; lane half and that bit stay swapped until fused_plain_codes has four values in a
+// dword.  Below, v and v + 1 are swapped back at once.
+template <int NT>
+__device__ __forceinline__ void fused_butterflies(dhq_v16f (&x)[NT])
+{
+    auto over_v = [&](int b) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if ((v & b) == 0) {
+                    const float p = x[T][v], q = x[T][v | b];
+                    x[T][v] = p + q;
+                    x[T][v | b] = p - q;
+                }
+    };
+    auto over_tiles = [&](int b) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+            if ((T & b) == 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float p = x[T][v], q = x[T | b][v];
+                    x[T][v] = p + q;
+                    x[T | b][v] = p - q;
+                }
+            }
+    };
+    over_v(1);
+    over_v(2);
+    if constexpr (NT > 2) over_tiles(2);
+    if constexpr (NT > 4) over_tiles(4);
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+        if (NT > 2 && (T & 2) != 0) continue;
+#pragma unroll
+        for (int v = 0; v < 16; v += NT > 2 ? 1 : 2) {
+            const int T2 = NT > 2 ? (T | 2) % NT : T, v2 = NT > 2 ? v : (v + 1) % 16;
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[T][v]), __float_as_uint(x[T2][v2]), false, false);
+            const float s = __uint_as_float(r[0]) + __uint_as_float(r[1]), d = __uint_as_float(r[0]) - __uint_as_float(r[1]);
+            if constexpr (NT > 2) {
+                x[T][v] = s;
+                x[T2][v2] = d;
+            } else {
+                const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(d), false, false);
+                x[T][v] = __uint_as_float(o[0]);
+                x[T2][v2] = __uint_as_float(o[1]);
+            }
+        }
+    }
+    over_v(4);
+    over_v(8);
+    if constexpr (NT > 1) over_tiles(1);
+}
+// The codes of what fused_butterflies leaves (quantized by fused_quantize), in their places.
+template <int NT>
+__device__ __forceinline__ void fused_plain_codes(dhq_v4i (&cd)[NT])
+{
+    if constexpr (NT > 2) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+            if ((T & 2) == 0) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)cd[T][g], (unsigned)cd[T | 2][g], false, false);
+                    cd[T][g] = (int)r[0];
+                    cd[T | 2][g] = (int)r[1];
+                }
+            }
     }
 }
 
@@ -541,7 +630,7 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
 //     hidden layer computed twice.
 // The same operations on the same values, so the same bits.  The floats are bound by memory from about half a pass of the
 // chip on; the second computation costs its latency however few rows there are.  Five hidden layers of 256, floats / codes:
-// 1 000 rows 65 / 82 us, 262 144 rows 561 (5.2 TB/s) / 353 us (bound by vector instruction issue as the whole-network kernel
+// 1 000 rows 65 / 82 us, 262 144 rows 561 (5.2 TB/s) / 324 us (bound by vector instruction issue as the whole-network kernel
 // is); fused_pass_floats draws the line.  Everything crosses memory in the lanes' register order ([wave tile][k block][lane] x 16 B
 // codes, [wave tile][float4][lane]: every access of a wave is 1 KiB contiguous); a wave overwrites the codes it has read
 // itself, so one buffer of them serves all layers, while the floats take two in turn.
@@ -564,6 +653,7 @@ struct fusedl_args {
     int64_t n;
     int chunks, chunks_below;  // block sizes in KiB
     int k0, k0p, m_out, qmax;
+    int dealt;                 // codes: which rows a wave takes (FUSED_DEALT or FUSED_IN_A_ROW)
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
     float scale, unscale;      // what the activations are multiplied by before they are split (padded networks), and 1 over it
 };
@@ -677,7 +767,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
     __shared__ float red_in[FUSED_WAVES], red[FUSED_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
-    const int64_t n_tiles = (A.n + FUSED_TILE - 1) / FUSED_TILE;
+    const int64_t n_tiles = A.dealt ? (A.n + 31) / 32 : (A.n + FUSED_TILE - 1) / FUSED_TILE;
+    const int64_t stride = A.dealt ? (int64_t)gridDim.x * FUSED_WAVES : gridDim.x;
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
     dhq_v4i hA[2];
     fused_h32_operand(c, h, hA);
@@ -690,53 +782,72 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
         c1_below = A.dyn_below[1];
     }
     float inv, c1;
-    fusedl_constants(A, red_in, wave, lane, inv, c1);
+    if ((ACTK & DHQ_PLAIN) != 0 && A.partial_count == 0) {  // an earlier launch has left them
+        inv = A.dyn[0];
+        c1 = A.dyn[1];
+    } else {
+        fusedl_constants(A, red_in, wave, lane, inv, c1);
+    }
     const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
     float mx[4] = {0.f, 0.f, 0.f, 0.f};  // four chains of three-operand maxima
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // the weights are in LDS
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t ci = tile * FUSED_TILE + wave * 32 + c;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += stride) {
+        const int64_t wave_tile = A.dealt ? tile + (int64_t)uwave * gridDim.x : tile * FUSED_WAVES + uwave;
+        const bool active = wave_tile * 32 < A.n;
+        const int64_t ci = wave_tile * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;  // lanes past the end repeat the last coordinate: no effect on the maximum
-        dhq_v4i *const codes = A.codes + ((size_t)tile * FUSED_WAVES + wave) * NKB * 64 + lane;
+        dhq_v4i *const codes = A.codes + (size_t)wave_tile * NKB * 64 + lane;
         dhq_v4i cd[NKB];
         dhq_v16f xt[NT];
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
-        if constexpr (MODE == 0 || BELOW0) {
+        if (!active) {
+        } else if constexpr (MODE == 0 || BELOW0) {
             cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, MODE == 0 ? inv : inv_below, A.qmax);
         } else {
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) cd[kb] = codes[kb * 64];
         }
         if constexpr (MODE != 0) {
-            fused_gemm_sine_hm<NT, KBB, NKB, ACTK>(reinterpret_cast<const dhq_v4i *>(lds_below),
+            if (active)
+                fused_gemm_sine_hm<NT, KBB, NKB, ACTK>(reinterpret_cast<const dhq_v4i *>(lds_below),
                                                    reinterpret_cast<const float4 *>(lds_below + NT * KBB * 1024), cd, c1_below, xt, hA,
                                                    lane, h, A.c2, A.scale);
             __syncthreads();  // keeps the two waves of a SIMD in the same phase, as in the whole-network kernel
-            fused_tile_stages<NT>(xt);
-            fused_quantize<NT>(xt, cd, hm_scaled<ACTK>(inv, A.unscale), qlo, qhi);
-            if constexpr (MODE == 1) {
+            if (active) {
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT>(xt);
+                else fused_tile_stages<NT>(xt);
+                fused_quantize<NT>(xt, cd, hm_scaled<ACTK>(inv, A.unscale), qlo, qhi);
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_plain_codes<NT>(cd);
+                if constexpr (MODE == 1) {
 #pragma unroll
-                for (int kb = 0; kb < NKB; ++kb) codes[kb * 64] = cd[kb];
+                    for (int kb = 0; kb < NKB; ++kb) codes[kb * 64] = cd[kb];
+                }
             }
         }
+        if ((ACTK & DHQ_PLAIN) != 0 && !A.partial) continue;  // only the codes are wanted
         if constexpr (MODE == 2) {
-            fused_output_layer<NKB>(wA, reinterpret_cast<const float *>(lds + MT * KB * 1024), cd, c1, A.out, ci, valid, A.m_out,
+            if (active) fused_output_layer<NKB>(wA, reinterpret_cast<const float *>(lds + MT * KB * 1024), cd, c1, A.out, ci, valid, A.m_out,
                                     lane, h);
         } else {
-            fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
-                                                  A.c2, A.scale);
+            if (active)
+                fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
+                                                      A.c2, A.scale);
             __syncthreads();
-            fused_tile_stages<NT>(xt);
+            if (active) {
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT>(xt);
+                else fused_tile_stages<NT>(xt);
 #pragma unroll
-            for (int T = 0; T < NT; ++T) {
+                for (int T = 0; T < NT; ++T) {
 #pragma unroll
-                for (int v = 0; v < 16; v += 2) mx[(v >> 1) & 3] = fmaxf(fmaxf(fabsf(xt[T][v]), fabsf(xt[T][v + 1])), mx[(v >> 1) & 3]);
+                    for (int v = 0; v < 16; v += 2) mx[(v >> 1) & 3] = fmaxf(fmaxf(fabsf(xt[T][v]), fabsf(xt[T][v + 1])), mx[(v >> 1) & 3]);
+                }
             }
         }
     }
+    if ((ACTK & DHQ_PLAIN) != 0 && !A.partial) return;
     if constexpr (MODE != 2) fusedl_store_max(A, red, wave, lane, fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
 }
 
@@ -1071,6 +1182,14 @@ size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *P, int64_t n)
     return codes > xhat ? codes : xhat;
 }
 
+// Whether the launches that pass codes deal 32-row tiles over all workgroups: a last pass that at most half of the waves have a
+// tile in, as in the whole-network kernel.
+static bool fused_deal(const dhq_fused_plan *P, int64_t n)
+{
+    const int64_t waves = (int64_t)P->n_cu * FUSED_WAVES, tiles = (n + 31) / 32, last = tiles % waves;
+    return tiles > waves && last > 0 && 2 * last <= waves;
+}
+
 template <int NF, int MODE, bool BELOW0, int ACTK>
 static hipError_t fusedl_launch_t(const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
@@ -1165,6 +1284,7 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
         a.dyn = dyn + 3 * l;
         a.partial = pbuf[(l + 1) & 1];
         a.n = n;
+        a.dealt = fused_deal(P, n);
         a.k0 = P->args.k0; a.k0p = P->args.k0p; a.m_out = P->args.m_out; a.qmax = P->args.qmax;
         a.c2 = dhq_hidden_act(m).c2;
         a.scale = P->args.scale;
@@ -1180,6 +1300,84 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
         count = (int)grid;
     }
     return hipSuccess;
+}
+
+// ---- calibration ------------------------------------------------------------------------------
+// The scales of all layers, with the layer-by-layer kernels' bits: dhq_fused_layer_kernel with the transform in fp32
+// (DHQ_PLAIN), one launch per hidden layer: it computes the layer below once more from its codes, stores the codes that this makes,
+// computes the layer and leaves the maximum of its transform.  Bound by vector issue like the whole-network kernel (eight
+// add/sub stages in place of the products with H_32).  Four layers of 200 on 150 001 rows, forward included: 782 us with a
+// GEMM, a transform and a maximum over memory each, twice a layer; this way 285 us.
+// Codes of up to buf_rows rows in each of two buffers: calls with more run in groups, and those beyond two groups make
+// their codes again from the coordinates for every layer (hipErrorInvalidValue beyond eight groups: too many maxima).
+template <int NF, int ACTK>
+static hipError_t fused_measure_layer(int layer, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
+{
+    if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK | DHQ_PLAIN>(a, grid, device, st);
+    return layer == 1 ? fusedl_launch_t<NF, 1, true, ACTK | DHQ_PLAIN>(a, grid, device, st)
+                      : fusedl_launch_t<NF, 1, false, ACTK | DHQ_PLAIN>(a, grid, device, st);
+}
+template <int NF>
+static hipError_t fused_measure_nf(int act_kind, int layer, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
+{
+    if (act_kind == DHQ_ACT_KIND_WAVELET) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET>(layer, a, grid, device, st);
+    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(layer, a, grid, device, st);
+    return fused_measure_layer<NF, DHQ_ACT_KIND_SINE>(layer, a, grid, device, st);
+}
+hipError_t dhq_fused_measure_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, void *const (&buf)[2],
+                                    size_t buf_bytes, float *partial, float *dyn, hipStream_t st)
+{
+    const int L = m->n_layers;
+    const int64_t pass = (int64_t)P->n_cu * FUSED_TILE, room = (int64_t)(buf_bytes / (size_t)P->nf) / FUSED_TILE * FUSED_TILE;
+    const int64_t step = room >= pass ? room / pass * pass : room, groups = step > 0 ? (n + step - 1) / step : 9;
+    if (n <= 0 || groups > DHQ_ABSMAX_PARTIALS / P->n_cu || groups > 8) return hipErrorInvalidValue;
+    float *pbuf[2] = {partial, partial + DHQ_ABSMAX_PARTIALS};
+    int count = 0;
+    hipError_t e = dhq_launch_wht_absmax_partials(coords, n, m->layer[0].K, m->layer[0].Kp, pbuf[0], &count, st);
+    for (int l = 0; l < L - 1 && e == hipSuccess; ++l) {
+        int left = 0;  // maxima of this layer's launches
+        for (int64_t g = 0; g < groups && e == hipSuccess; ++g) {
+            const int64_t rows = n - g * step < step ? n - g * step : step, tiles = (rows + FUSED_TILE - 1) / FUSED_TILE;
+            const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
+            for (int k = groups > 2 && l > 1 ? 1 : l; k <= l && e == hipSuccess; ++k) {
+                fusedl_args a;
+                memset(&a, 0, sizeof(a));
+                a.coords = coords + g * step * m->dims[0];
+                a.codes = reinterpret_cast<dhq_v4i *>(buf[g & 1]);
+                a.blk = P->blob_dev + P->args.layer[k].blob_off;
+                a.chunks = (int)P->args.layer[k].chunks;
+                if (k > 0) {
+                    a.blk_below = P->blob_dev + P->args.layer[k - 1].blob_off;
+                    a.chunks_below = (int)P->args.layer[k - 1].chunks;
+                    a.dyn_below = dyn + 3 * (k - 1);
+                }
+                if (k == l) {
+                    a.partial_in = pbuf[l & 1];
+                    a.partial_count = count;
+                    a.partial = pbuf[(l + 1) & 1] + left;
+                }
+                a.kp = m->layer[k].Kp;
+                a.c1_over_sa = dhq_c1_over_sa(m, k);
+                a.dyn = dyn + 3 * k;
+                a.n = rows;
+                a.dealt = fused_deal(P, rows);
+                a.k0 = P->args.k0; a.k0p = P->args.k0p; a.m_out = P->args.m_out; a.qmax = P->args.qmax;
+                a.c2 = dhq_hidden_act(m).c2;
+                a.scale = a.unscale = 1.f;
+                switch (P->nf) {
+                    case 32: e = fused_measure_nf<32>(P->act_kind, k, a, grid, P->device, st); break;
+                    case 64: e = fused_measure_nf<64>(P->act_kind, k, a, grid, P->device, st); break;
+                    case 128: e = fused_measure_nf<128>(P->act_kind, k, a, grid, P->device, st); break;
+                    case 256: e = fused_measure_nf<256>(P->act_kind, k, a, grid, P->device, st); break;
+                    default: e = hipErrorInvalidValue;
+                }
+            }
+            left += (int)grid;
+        }
+        count = left;
+    }
+    if (e != hipSuccess) return e;
+    return dhq_launch_absmax_finish(pbuf[(L - 1) & 1], count, m->layer[L - 1].Kp, m->qmax_a, dhq_c1_over_sa(m, L - 1), dyn + 3 * (L - 1), st);
 }
 
 // Test hook behind dhq_forward_debug_fused: layer `layer` (one that ends in an activation) of the

@@ -86,6 +86,8 @@ __device__ __forceinline__ void hm_remainders(float a0, float a1, unsigned hi, f
 // 62.6 us), 3 % of a wavelet's, 2 % of a complex one's (one for both parts).  Two mixed-precision multiply-adds that round
 // to binary16 in place of the subtractions and lo's conversion are slower: they issue at half rate too.
 #define DHQ_SPLIT_RN 16
+// Instances that leave the activations as they are, for the transform of the layer-by-layer kernels (fused_butterflies).
+#define DHQ_PLAIN 32
 #define DHQ_KIND(ACTK) ((ACTK) & 15)
 template <int ACTK>
 __device__ __forceinline__ float hm_scaled(float a, float scale)

@@ -149,6 +149,9 @@ hipError_t dhq_launch_unrotate_quant(const int32_t *acc, int64_t n, int Mp, int 
 hipError_t dhq_launch_wht_absmax_partials(const float *in, int64_t n, int K, int Kp, float *partial, int *count,
                                           hipStream_t st);
 
+// The layer's constants from such maxima, in dyn[0..2].
+hipError_t dhq_launch_absmax_finish(const float *partial, int count, int Kp, int qmax, double c1_over_sa, float *dyn, hipStream_t st);
+
 hipError_t dhq_launch_clear_words(unsigned *p, int n, hipStream_t st);
 
 // Epilogue multiplier divided by the activation scale: s_w, times omega0 / (2 pi) in the sine
@@ -201,6 +204,10 @@ size_t dhq_fused_dynamic_rows(int64_t n);
 size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *plan, int64_t n);
 hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, float *out,
                                     void *const (&ws)[2], size_t ws_bytes, float *partial, float *dyn, hipStream_t st);
+// The scales of all layers over n rows (dhq_calibrate), with the layer-by-layer path's bits; buf: two buffers of buf_bytes for
+// codes.  hipErrorInvalidValue: more rows than it handles.
+hipError_t dhq_fused_measure_launch(const dhq_model *m, const dhq_fused_plan *plan, const float *coords, int64_t n, void *const (&buf)[2],
+                                    size_t buf_bytes, float *partial, float *dyn, hipStream_t st);
 
 
 // Hidden width 512 (defined in dhq_fused_wide.hip); same contract as the functions above.

@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) void wht_absmax_kernel(const float *__restrict
     if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// One workgroup: *absmax_bits = max(*absmax_bits, partial[0 .. count)); then the constants of the dynamic mode for that
+// One workgroup: *absmax_bits (if given) = max(*absmax_bits, partial[0 .. count)); then the constants of the dynamic mode for that
 // maximum.
 __global__ __launch_bounds__(256) void absmax_finish_kernel(const float *__restrict__ partial, int count,
                                                             unsigned *__restrict__ absmax_bits, int Kp, int qmax,
@@ -252,8 +252,10 @@ __global__ __launch_bounds__(256) void absmax_finish_kernel(const float *__restr
     if (threadIdx.x == 0) {
         mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
         unsigned bits = __float_as_uint(mx);
-        if (*absmax_bits > bits) bits = *absmax_bits;
-        *absmax_bits = bits;
+        if (absmax_bits) {
+            if (*absmax_bits > bits) bits = *absmax_bits;
+            *absmax_bits = bits;
+        }
         dyn_scale_write(bits, Kp, qmax, c1_over_sa, dyn);
     }
 }
@@ -339,6 +341,12 @@ hipError_t dhq_launch_wht_absmax_partials(const float *in, int64_t n, int K, int
 {
     if (n <= 0 || !partial || !count) return hipErrorInvalidValue;
     return wht_absmax_dispatch(in, n, K, Kp, nullptr, partial, 0, 0.0, nullptr, count, st);
+}
+
+hipError_t dhq_launch_absmax_finish(const float *partial, int count, int Kp, int qmax, double c1_over_sa, float *dyn, hipStream_t st)
+{
+    absmax_finish_kernel<<<1, 256, 0, st>>>(partial, count, nullptr, Kp, qmax, c1_over_sa, dyn);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------- int8 GEMM, MFMA

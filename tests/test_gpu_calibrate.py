@@ -1,0 +1,52 @@
+"""Calibration on the per-layer kernels of the fused networks: the layer-by-layer path's scales, bit for bit."""
+import numpy as np
+import pytest
+
+import paper_2508_13478_amd as dhq
+from paper_2508_13478_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _scales(m, x):
+    m.calibrate(x)
+    got = m.scales()[1].copy()
+    m.forward(x, flags=dhq.DHQ_LAYERWISE | dhq.DHQ_DYNAMIC)
+    return got, m.dynamic_scales()
+
+
+@pytest.mark.parametrize("dims", [[2, 32, 3], [1, 32, 32, 32, 1], [3, 64, 64, 2], [2, 128, 128, 128, 3], [4, 256, 256, 256, 5], [2, 20, 20, 3],
+                                  [3, 90, 120, 1], [2, 200, 200, 200, 3]], ids=lambda d: "x".join(map(str, d)))
+@pytest.mark.parametrize("act,bits", [("sine", 8), ("sine", 4), ("wavelet", 8), ("complex", 8)])
+def test_scales_of_every_activation_and_width(dims, act, bits):
+    """Every tile count of the transform (its stage over the lane halves differs below four tiles), rows at the edges of a wave's and
+    a workgroup's tile, and several passes."""
+    import torch
+    if act == "complex":
+        dims = [dims[0]] + [max(1, d // 2) for d in dims[1:-1]] + [dims[-1]]
+        W, b = synth.wire_init(dims, 30.0, 3)
+        m = dhq.Model.complex_wavelet(dims, 30.0, W, b, 10.0, bits, bits)
+    else:
+        W, b = synth.siren_init(dims, 30.0, 3)
+        m = dhq.Model(dims, 30.0, W, b, bits, bits, wavelet_s0=10.0 if act == "wavelet" else None)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    for n in (1, 33, 257, 70001):
+        print(f"[calibrate] {dims} {act} {bits} bits n={n}", flush=True)
+        x = torch.rand((n, dims[0]), generator=g, device="cuda") * 2 - 1
+        got, exp = _scales(m, x)
+        assert np.array_equal(got, exp)
+    m.close()
+
+
+@pytest.mark.parametrize("n", [131072, 131073, 262145, 400001, 1048577], ids=["one_buffer", "two", "three_groups", "four_groups", "too_many_groups"])
+def test_rows_beyond_the_buffers_room(n):
+    """33 features take 64 bytes of codes; a buffer has 33 floats for each of 65 536 rows, two passes' worth of them."""
+    import torch
+    dims = [2, 33, 33, 33, 3]
+    W, b = synth.siren_init(dims, 30.0, 6)
+    m = dhq.Model(dims, 30.0, W, b)
+    x = torch.rand((n, 2), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda") * 2 - 1
+    print(f"[calibrate] {dims} n={n}", flush=True)
+    got, exp = _scales(m, x)
+    assert np.array_equal(got, exp)
+    m.close()
