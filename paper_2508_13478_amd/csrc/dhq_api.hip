@@ -166,6 +166,7 @@ extern "C" void dhq_free(dhq_model *m)
     if (m->dyn_acc) (void)hipFree(m->dyn_acc);
     if (m->dyn_absmax) (void)hipFree(m->dyn_absmax);
     if (m->dyn_params) (void)hipFree(m->dyn_params);
+    if (m->cal_host) (void)hipHostFree(m->cal_host);
     dhq_fused_destroy(m->fused);
     dhq_fused_destroy(m->pad_fused);
     dhq_pair_destroy(m->pad_pair);
@@ -466,6 +467,10 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
             rc = DHQ_ENOMEM;
         if (rc == DHQ_OK && hipMalloc((void **)&m->dyn_absmax, sizeof(unsigned) * (DHQ_MAX_LAYERS + 2 * DHQ_ABSMAX_PARTIALS)) != hipSuccess) rc = DHQ_ENOMEM;
         if (rc == DHQ_OK && hipMalloc((void **)&m->dyn_params, sizeof(float) * 6 * DHQ_MAX_LAYERS) != hipSuccess) rc = DHQ_ENOMEM;
+        if (rc == DHQ_OK && hipHostMalloc((void **)&m->cal_host, sizeof(float) * 3 * DHQ_MAX_LAYERS) != hipSuccess) {
+            m->cal_host = nullptr;  // calibration copies into pageable memory then
+            (void)hipGetLastError();
+        }
         // dhq_get_dynamic_scales before any dynamic forward reports zeros
         if (rc == DHQ_OK && hipMemset(m->dyn_params, 0, sizeof(float) * 6 * DHQ_MAX_LAYERS) != hipSuccess) rc = DHQ_EHIP;
     }
@@ -709,7 +714,8 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
     float *const partial = reinterpret_cast<float *>(m->dyn_absmax + DHQ_MAX_LAYERS);
     float *const params = m->dyn_params + 3 * DHQ_MAX_LAYERS;  // like the dynamic forward's, which keep its last call's scales
     auto finish = [&]() {
-        float host[3 * DHQ_MAX_LAYERS];
+        // into pinned memory: a copy into pageable memory is staged, 24 us more of a calibration
+        float pageable[3 * DHQ_MAX_LAYERS], *const host = m->cal_host ? m->cal_host : pageable;
         if (hipMemcpyAsync(host, params, sizeof(float) * 3 * L, hipMemcpyDeviceToHost, st) != hipSuccess) return DHQ_EHIP;
         if (hipStreamSynchronize(st) != hipSuccess) return DHQ_EHIP;
         for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];

@@ -1307,9 +1307,9 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
 // (DHQ_PLAIN), one launch per hidden layer: it computes the layer below once more from its codes, stores the codes that this makes,
 // computes the layer and leaves the maximum of its transform.  Bound by vector issue like the whole-network kernel (eight
 // add/sub stages in place of the products with H_32).  Four layers of 200 on 150 001 rows, forward included: 782 us with a
-// GEMM, a transform and a maximum over memory each, twice a layer; this way 285 us.
-// Codes of up to buf_rows rows in each of two buffers: calls with more run in groups, and those beyond two groups make
-// their codes again from the coordinates for every layer (hipErrorInvalidValue beyond eight groups: too many maxima).
+// GEMM, a transform and a maximum over memory each, twice a layer; this way 285 us (24 of the
+// difference by a copy of the scales into pinned memory).  buf_bytes of codes in each of two buffers: calls with more rows
+// run in groups, and those beyond two groups make their codes again from the coordinates for every layer (hipErrorInvalidValue beyond eight groups: too many maxima).
 template <int NF, int ACTK>
 static hipError_t fused_measure_layer(int layer, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
 {
