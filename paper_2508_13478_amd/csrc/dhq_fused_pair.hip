@@ -77,6 +77,7 @@ struct pair_args {
 struct dhq_pair_plan {
     int act_kind = DHQ_ACT_KIND_SINE;
     bool padded = false;       // the network's own hidden widths are smaller, padded to 512
+    int rt = PAIR_NT;          // tiles of each role that are not all padding
     unsigned char *blob_dev = nullptr;
     size_t blob_bytes = 0;
     pair_args args;
@@ -151,7 +152,9 @@ __device__ __forceinline__ float4 *pair_x_slot(const pair_stream &S, int w, int 
     return reinterpret_cast<float4 *>(S.lds + 2 * PAIR_BUF + w * 8192 + (t & 3) * 2048) + S.lane;
 }
 
-template <int ACTK>
+// RT: the wave's tiles that are not all padding (exact networks: all eight).  The chunks, products and additions of the others
+// are left out: their activations are zero.
+template <int ACTK, int RT>
 struct pair_ctx {
     pair_stream &S;
     dhq_v4i (&cd)[PAIR_KB];       // codes of the layer input: the B operands
@@ -179,8 +182,8 @@ struct pair_ctx {
 __device__ __forceinline__ float pair_comp(const float4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
 // H_32 product K (0: low pieces of block 0, 1: high pieces of block 0, 2, 3: block 1) of tile T.
-template <int T, int K, int ACTK>
-__device__ __forceinline__ void pair_h32(pair_ctx<ACTK> &C)
+template <int T, int K, int ACTK, int RT>
+__device__ __forceinline__ void pair_h32(pair_ctx<ACTK, RT> &C)
 {
     constexpr int blk = K >> 1;
     dhq_v4i b;
@@ -197,8 +200,8 @@ __device__ __forceinline__ void pair_h32(pair_ctx<ACTK> &C)
 }
 
 // The outgoing half of tile T (registers 8..15) to this wave's exchange slot.
-template <int T, int ACTK>
-__device__ __forceinline__ void pair_send(pair_ctx<ACTK> &C)
+template <int T, int ACTK, int RT>
+__device__ __forceinline__ void pair_send(pair_ctx<ACTK, RT> &C)
 {
     float4 *dst = pair_x_slot(C.S, C.S.wave, T);
     dst[0] = make_float4(C.y[T][8], C.y[T][9], C.y[T][10], C.y[T][11]);
@@ -207,8 +210,8 @@ __device__ __forceinline__ void pair_send(pair_ctx<ACTK> &C)
 
 // The weight copy that runs while a hidden layer's chunk is consumed, by steps since the chunk was
 // entered.
-template <int REL, int ACTK>
-__device__ __forceinline__ void pair_copy_rel(pair_ctx<ACTK> &C)
+template <int REL, int ACTK, int RT>
+__device__ __forceinline__ void pair_copy_rel(pair_ctx<ACTK, RT> &C)
 {
     if constexpr (REL == 1) pair_copy_slot<0>(C.S);
     if constexpr (REL == 3) pair_copy_slot<1>(C.S);
@@ -225,10 +228,10 @@ __device__ __forceinline__ void pair_copy_rel(pair_ctx<ACTK> &C)
 //            pieces takes three more steps, and the four H_32 products of a tile issue one per
 //            step once their pieces exist (two after the tile's 8th value, two after its 16th);
 //            the outgoing halves of the first tiles leave for the exchange area once complete.
-template <int G, int ACTK>
-__device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
+template <int G, int ACTK, int RT>
+__device__ __forceinline__ void pair_step(pair_ctx<ACTK, RT> &C)
 {
-    constexpr int NM = PAIR_NT * PAIR_KB, NE = PAIR_NT * 16, PF = PAIR_PF;
+    constexpr int NM = RT * PAIR_KB, NE = RT * 16, PF = PAIR_PF;
     if constexpr (G >= 0 && G < NM) {
         constexpr int pf = G + PF;
         if constexpr (pf < NM) {
@@ -249,7 +252,7 @@ __device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
     if constexpr (G >= 0) {
         constexpr int e0 = G - PAIR_KB, e1 = e0 - 1, e2 = e0 - 2;
         constexpr int hq = e2 - 11;  // 16 t + {0, 1, 8, 9} -> product 0, 1, 2, 3 of tile t
-        if constexpr (hq >= 0 && hq / 16 < PAIR_NT) {
+        if constexpr (hq >= 0 && hq / 16 < RT) {
             constexpr int Th = hq / 16, r = hq % 16;
             if constexpr (r == 0) pair_h32<Th, 0>(C);
             if constexpr (r == 1) pair_h32<Th, 1>(C);
@@ -289,22 +292,22 @@ __device__ __forceinline__ void pair_step(pair_ctx<ACTK> &C)
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int ACTK, int... Gs>
-__device__ __forceinline__ void pair_steps(pair_ctx<ACTK> &C, std::integer_sequence<int, Gs...>)
+template <int ACTK, int RT, int... Gs>
+__device__ __forceinline__ void pair_steps(pair_ctx<ACTK, RT> &C, std::integer_sequence<int, Gs...>)
 {
     (pair_step<Gs - PAIR_PF>(C), ...);  // steps -PF (the copy's first steps) .. NSTEPS - 1
 }
 
 // A hidden layer: reads the input codes the transform left in the exchange area, then the GEMM
 // pipeline over this wave's eight tiles.  cc is the running chunk count and is advanced.
-template <int ACTK>
+template <int ACTK, int RT = PAIR_NT>
 __device__ __forceinline__ void pair_hidden(pair_stream &S, int &cc, int layer, float c1, dhq_v4i (&cd)[PAIR_KB],
                                             dhq_v16f (&y)[PAIR_NT], const dhq_v4i (&hA)[2], int h)
 {
     // last step with work: the send after the fourth H_32 product of the last tile would be
-    // e2 - 11 = 16 * 7 + 12, the product itself 16 * 7 + 9
-    constexpr int NSTEPS = 16 * (PAIR_NT - 1) + 9 + 11 + 2 + PAIR_KB + 1;
-    pair_ctx<ACTK> C(S, cd, y, hA);
+    // e2 - 11 = 16 (RT - 1) + 12, the product itself 16 (RT - 1) + 9
+    constexpr int NSTEPS = 16 * (RT - 1) + 9 + 11 + 2 + PAIR_KB + 1;
+    pair_ctx<ACTK, RT> C(S, cd, y, hA);
     C.cc = cc;
     C.c1 = c1;
     C.c2 = S.A->c2;
@@ -323,28 +326,28 @@ __device__ __forceinline__ void pair_hidden(pair_stream &S, int &cc, int layer, 
     C.bufs[1] = S.lds + ((cc + 1) & 1) * PAIR_BUF + S.role * 16384;
 #pragma unroll
     for (int m = 0; m < PAIR_PF; ++m) C.fr[m % (PAIR_PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[0])[m * 64 + S.lane];
-    pair_steps<ACTK>(C, std::make_integer_sequence<int, NSTEPS + PAIR_PF>{});
-    cc += PAIR_NT;
+    pair_steps<ACTK, RT>(C, std::make_integer_sequence<int, NSTEPS + PAIR_PF>{});
+    cc += RT;
 }
 
 // The input layer (fan-in <= 4: one k block, one chunk with all sixteen tiles): step G issues the
 // MFMA of tile G and the four H_32 products of tile G - 1, then drains tile G.
-template <int G, int ACTK>
-__device__ __forceinline__ void pair_step0(pair_ctx<ACTK> &C, int h)
+template <int G, int ACTK, int RT>
+__device__ __forceinline__ void pair_step0(pair_ctx<ACTK, RT> &C, int h)
 {
     constexpr int PF = PAIR_PF;
-    if constexpr (G + PF < PAIR_NT) C.fr[(G + PF) % (PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[0])[(G + PF) * 64 + C.S.lane];
+    if constexpr (G + PF < RT) C.fr[(G + PF) % (PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[0])[(G + PF) * 64 + C.S.lane];
     if constexpr (G == 0) pair_copy_slot<0>(C.S);
     if constexpr (G == 1) pair_copy_slot<1>(C.S);
     if constexpr (G == 2) pair_copy_slot<2>(C.S);
     if constexpr (G == 3) pair_copy_slot<3>(C.S);
     if constexpr (G == 4) pair_copy_bias(C.S, 1);
-    if constexpr (G < PAIR_NT) {
+    if constexpr (G < RT) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) C.acc[0][v] = 0;
         C.acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(C.fr[G % (PF + 1)], C.cd[0], C.acc[0], 0, 0, 0);
     }
-    if constexpr (G >= 1 && G <= PAIR_NT) {
+    if constexpr (G >= 1 && G <= RT) {
         pair_h32<G - 1, 0>(C);
         pair_h32<G - 1, 1>(C);
         pair_h32<G - 1, 2>(C);
@@ -352,7 +355,7 @@ __device__ __forceinline__ void pair_step0(pair_ctx<ACTK> &C, int h)
     }
     if constexpr (G >= 2 && G - 2 < PAIR_EARLY) pair_send<G - 2>(C);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (G < PAIR_NT) {
+    if constexpr (G < RT) {
         float x[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) x[v] = (float)C.acc[0][v];
@@ -369,23 +372,23 @@ __device__ __forceinline__ void pair_step0(pair_ctx<ACTK> &C, int h)
 #pragma unroll
         for (int d = 0; d < 8; ++d) hm_split_pair<ACTK>(x[2 * d], x[2 * d + 1], C.hp[G & 1][d], C.lp[G & 1][d]);
     }
-    if constexpr (G + 1 < PAIR_NT) {
+    if constexpr (G + 1 < RT) {
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) C.bq0[gg] = C.bias[((G + 1) * 4 + gg) * 2];
     }
     __builtin_amdgcn_sched_barrier(0);
 }
-template <int ACTK, int... Gs>
-__device__ __forceinline__ void pair_steps0(pair_ctx<ACTK> &C, int h, std::integer_sequence<int, Gs...>)
+template <int ACTK, int RT, int... Gs>
+__device__ __forceinline__ void pair_steps0(pair_ctx<ACTK, RT> &C, int h, std::integer_sequence<int, Gs...>)
 {
     (pair_step0<Gs>(C, h), ...);
 }
 
-template <int ACTK>
+template <int ACTK, int RT = PAIR_NT>
 __device__ __forceinline__ void pair_input_layer(pair_stream &S, int &cc, float c1, dhq_v4i (&cd)[PAIR_KB], dhq_v16f (&y)[PAIR_NT],
                                                  const dhq_v4i (&hA)[2], int h)
 {
-    pair_ctx<ACTK> C(S, cd, y, hA);
+    pair_ctx<ACTK, RT> C(S, cd, y, hA);
     C.cc = cc;
     C.c1 = c1;
     C.c2 = S.A->c2;
@@ -400,17 +403,18 @@ __device__ __forceinline__ void pair_input_layer(pair_stream &S, int &cc, float 
     for (int m = 0; m < PAIR_PF; ++m) C.fr[m % (PAIR_PF + 1)] = reinterpret_cast<const dhq_v4i *>(C.bufs[0])[m * 64 + S.lane];
 #pragma unroll
     for (int gg = 0; gg < 4; ++gg) C.bq0[gg] = C.bias[gg * 2];
-    pair_steps0<ACTK>(C, h, std::make_integer_sequence<int, PAIR_NT + 1>{});
+    pair_steps0<ACTK, RT>(C, h, std::make_integer_sequence<int, RT + 1>{});
     cc += 1;
 }
 
 // What the partner parked for tile T, combined with the kept half of this wave's tile T:
 // zl = own + partner (tile T of the stage over tile-index bit 3), zh = own - partner (tile T + 8;
 // minus that for role 1, which owns T + 8).
-template <int T>
+template <int T, int RT = PAIR_NT>
 __device__ __forceinline__ void pair_recv(const pair_stream &S, const dhq_v16f (&y)[PAIR_NT], float (&zl)[PAIR_NT][8],
                                           float (&zh)[PAIR_NT][8])
 {
+    if constexpr (T >= RT) return;  // zeros, which pair_transform leaves out
     const float4 *src = pair_x_slot(S, S.wave ^ 4, T);
     const float4 p0 = src[0], p1 = src[64];
     const float p[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
@@ -419,6 +423,16 @@ __device__ __forceinline__ void pair_recv(const pair_stream &S, const dhq_v16f (
         zl[T][i] = y[T][i] + p[i];
         zh[T][i] = y[T][i] - p[i];
     }
+}
+
+// The outgoing half of a tile that did not leave during the GEMM phase.
+template <int T, int RT>
+__device__ __forceinline__ void pair_send_late(const pair_stream &S, const dhq_v16f (&y)[PAIR_NT])
+{
+    if constexpr (T >= RT) return;
+    float4 *d = pair_x_slot(S, S.wave, T);
+    d[0] = make_float4(y[T][8], y[T][9], y[T][10], y[T][11]);
+    d[64] = make_float4(y[T][12], y[T][13], y[T][14], y[T][15]);
 }
 
 __device__ __forceinline__ void pair_barrier()
@@ -430,38 +444,41 @@ __device__ __forceinline__ void pair_barrier()
 // The rest of the transform: on return zl[T][i] / zh[T][i] hold the un-normalised x^ of rotated features
 // 32 T + 8 (i / 4 + 2 role) + 4 h + i % 4 and 256 + the same (zh of role 1 with its sign flipped), and
 // the exchange area is free.
-template <bool AFTER_INPUT_LAYER>
+template <bool AFTER_INPUT_LAYER, int RT = PAIR_NT>
 __device__ __forceinline__ void pair_transform(pair_stream &S, dhq_v16f (&y)[PAIR_NT], float (&zl)[PAIR_NT][8], float (&zh)[PAIR_NT][8])
 {
-    // the halves sent during the GEMM phase are in place: a hidden layer's last sends precede its last chunk
-    // barriers, the input layer has none
-    if constexpr (AFTER_INPUT_LAYER) pair_barrier();
-    pair_recv<0>(S, y, zl, zh);
-    pair_recv<1>(S, y, zl, zh);
-    pair_recv<2>(S, y, zl, zh);
-    pair_recv<3>(S, y, zl, zh);
+    // the halves sent during the GEMM phase are in place: a hidden layer's last sends (step 16 * 3 + 12 + 29) precede its last
+    // chunk's barrier (step 16 (RT - 1) - PAIR_PF) from seven tiles on, the input layer has none
+    if constexpr (AFTER_INPUT_LAYER || 16 * (RT - 1) - PAIR_PF <= 16 * (PAIR_EARLY - 1) + 12 + 29) pair_barrier();
+    pair_recv<0, RT>(S, y, zl, zh);
+    pair_recv<1, RT>(S, y, zl, zh);
+    pair_recv<2, RT>(S, y, zl, zh);
+    pair_recv<3, RT>(S, y, zl, zh);
     pair_barrier();  // everyone has read them: the slots are free again
-    {
-        float4 *d4 = pair_x_slot(S, S.wave, 4), *d5 = pair_x_slot(S, S.wave, 5), *d6 = pair_x_slot(S, S.wave, 6), *d7 = pair_x_slot(S, S.wave, 7);
-        d4[0] = make_float4(y[4][8], y[4][9], y[4][10], y[4][11]); d4[64] = make_float4(y[4][12], y[4][13], y[4][14], y[4][15]);
-        d5[0] = make_float4(y[5][8], y[5][9], y[5][10], y[5][11]); d5[64] = make_float4(y[5][12], y[5][13], y[5][14], y[5][15]);
-        d6[0] = make_float4(y[6][8], y[6][9], y[6][10], y[6][11]); d6[64] = make_float4(y[6][12], y[6][13], y[6][14], y[6][15]);
-        d7[0] = make_float4(y[7][8], y[7][9], y[7][10], y[7][11]); d7[64] = make_float4(y[7][12], y[7][13], y[7][14], y[7][15]);
-    }
+    pair_send_late<4, RT>(S, y);
+    pair_send_late<5, RT>(S, y);
+    pair_send_late<6, RT>(S, y);
+    pair_send_late<7, RT>(S, y);
     pair_barrier();
-    pair_recv<4>(S, y, zl, zh);
-    pair_recv<5>(S, y, zl, zh);
-    pair_recv<6>(S, y, zl, zh);
-    pair_recv<7>(S, y, zl, zh);
+    pair_recv<4, RT>(S, y, zl, zh);
+    pair_recv<5, RT>(S, y, zl, zh);
+    pair_recv<6, RT>(S, y, zl, zh);
+    pair_recv<7, RT>(S, y, zl, zh);
     pair_barrier();  // the exchange area is free for the codes
-    // stages over tile-index bits 0..2, within each half
+    // stages over tile-index bits 0..2, within each half; before stage s tile t is still zero if all tiles that differ from it
+    // in lower bits only are padding
 #pragma unroll
     for (int s = 1; s < PAIR_NT; s <<= 1) {
 #pragma unroll
         for (int t = 0; t < PAIR_NT; ++t) {
-            if ((t & s) == 0) {
+            if ((t & s) == 0 && (t & -s) < RT) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
+                    if (((t | s) & -s) >= RT) {
+                        zl[t | s][i] = zl[t][i];
+                        zh[t | s][i] = zh[t][i];
+                        continue;
+                    }
                     const float a = zl[t][i], b = zl[t | s][i];
                     zl[t][i] = a + b;
                     zl[t | s][i] = a - b;
@@ -477,12 +494,12 @@ __device__ __forceinline__ void pair_transform(pair_stream &S, dhq_v16f (&y)[PAI
 // The rest of the transform and the next layer's quantizer.  On return the exchange area holds,
 // per coordinate group, the next layer's whole B operand ([k block][lane] x 16 B); it may be read
 // after the next barrier.  xrow (test hook): where this lane's coordinate keeps its row of x^.
-template <bool DUMP, bool AFTER_INPUT_LAYER = true>
+template <bool DUMP, bool AFTER_INPUT_LAYER = true, int RT = PAIR_NT>
 __device__ __forceinline__ void pair_transform_quant(pair_stream &S, dhq_v16f (&y)[PAIR_NT], float inv, int qlo, int qhi, int h,
                                                      float *xrow = nullptr, int *crow = nullptr)
 {
     float zl[PAIR_NT][8], zh[PAIR_NT][8];
-    pair_transform<AFTER_INPUT_LAYER>(S, y, zl, zh);
+    pair_transform<AFTER_INPUT_LAYER, RT>(S, y, zl, zh);
     const float inv_hi = S.role ? -inv : inv;
     if constexpr (DUMP) {
         // rotated feature of zl[T][i]: 32 T + 8 (i / 4 + 2 role) + 4 h + i % 4; zh: tile T + 8, sign as above
@@ -544,7 +561,7 @@ __device__ __forceinline__ void pair_copy_now(const pair_stream &S, int j, int b
     }
 }
 
-template <int ACTK>
+template <int ACTK, int RT>
 __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair_args A)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -583,11 +600,11 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair
         }
 
         dhq_v16f y[PAIR_NT];
-        pair_input_layer<ACTK>(S, cc, A.c1[0], cd, y, hA, h);
-        pair_transform_quant<false, true>(S, y, A.inv_in[1], qlo, qhi, h);
+        pair_input_layer<ACTK, RT>(S, cc, A.c1[0], cd, y, hA, h);
+        pair_transform_quant<false, true, RT>(S, y, A.inv_in[1], qlo, qhi, h);
         for (int l = 1; l < L - 1; ++l) {
-            pair_hidden<ACTK>(S, cc, l, A.c1[l], cd, y, hA, h);
-            pair_transform_quant<false, false>(S, y, A.inv_in[l + 1], qlo, qhi, h);
+            pair_hidden<ACTK, RT>(S, cc, l, A.c1[l], cd, y, hA, h);
+            pair_transform_quant<false, false, RT>(S, y, A.inv_in[l + 1], qlo, qhi, h);
         }
 
         // output layer: one zero-padded M tile, no activation; role 0 computes it while all waves
@@ -1230,9 +1247,16 @@ static bool pair_shape_ok(const dhq_model *m, bool padded)
     return !padded || dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2);
 }
 
+// Which M tile wave role r computes as its t-th.  Exact networks: role 0 tiles 0..7, role 1 tiles 8..15, as described above.
+// In the padded ones the last tiles are padding, and role r has tiles 2 t + r, so that both have as much of it (RT = 5..8 tiles
+// each that are not; the exchange is then the stage over tile-index bit 0).  Complex width 181, twelve real tiles of sixteen,
+// 3 layers, 65 536 rows: 70.5 -> 57.5 us; 4 x 300 features 81.5 -> 60.1, 4 x 400 (wavelet) 96.7 -> 88.2.
+static int pair_place(bool padded, int T) { return padded ? (T & 1) * 8 + (T >> 1) : T; }  // 8 r + t
+static int pair_tile(bool padded, int place) { return padded ? 2 * (place & 7) + (place >> 3) : place; }
+
 // k position jj of lane half u in k block kb of a hidden layer's A fragment holds rotated input
-// feature hm_index(16 kb + jj, u): the order in which the transform leaves the codes.
-static void pair_pack_tile(const dhq_layer &Ly, int T, int Kb, bool first, int8_t *frag)
+// feature hm_index(16 kb' + jj, u), kb' = pair_tile(kb): the order in which the transform leaves the codes.
+static void pair_pack_tile(const dhq_layer &Ly, bool padded, int T, int Kb, bool first, int8_t *frag)
 {
     const int8_t *wq = Ly.wq_host.data();
     for (int kb = 0; kb < Kb; ++kb)
@@ -1244,7 +1268,7 @@ static void pair_pack_tile(const dhq_layer &Ly, int T, int Kb, bool first, int8_
                     if (first) {
                         if (u == 0 && jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + jj];
                     } else {
-                        val = wq[(size_t)row * Ly.Kp + hm_index(16 * kb + jj, u)];
+                        val = wq[(size_t)row * Ly.Kp + hm_index(16 * pair_tile(padded, kb) + jj, u)];
                     }
                 }
                 frag[((size_t)kb * 64 + ln) * 16 + jj] = val;
@@ -1260,27 +1284,36 @@ int dhq_pair_create(const dhq_model *m, bool padded, dhq_pair_plan **plan_out)
     dhq_pair_plan *P = new (std::nothrow) dhq_pair_plan();
     if (!P) return DHQ_ENOMEM;
     memset(&P->args, 0, sizeof(P->args));
-    const int n_chunks = 2 + 8 * (L - 2);
+    P->rt = PAIR_NT;
+    if (padded) {
+        int widest = 0;
+        for (int l = 1; l < L; ++l) widest = m->dims[l] > widest ? m->dims[l] : widest;
+        P->rt = (widest + 63) / 64;
+    }
+    const int n_chunks = 2 + P->rt * (L - 2);
     // chunks, one more chunk of padding (the in-kernel copy always moves 32 KiB), then the bias table
     const size_t bias_off = (size_t)(n_chunks + 1) * PAIR_BUF;
     std::vector<unsigned char> blob(bias_off + (size_t)L * 512 * sizeof(float), 0);
+    auto slot = [&](int l, int f) { return bias_slot(l == L - 1 ? f : 32 * pair_place(padded, f >> 5) + (f & 31)); };
     for (int l = 0; l < L; ++l) {
         const dhq_layer &Ly = m->layer[l];
         if (l == 0) {
-            for (int T = 0; T < 16; ++T) pair_pack_tile(Ly, T, 1, true, reinterpret_cast<int8_t *>(blob.data()) + (size_t)T * 1024);
-        } else if (l == L - 1) {
-            pair_pack_tile(Ly, 0, PAIR_KB, false, reinterpret_cast<int8_t *>(blob.data()) + (size_t)(n_chunks - 1) * PAIR_BUF);
-        } else {
             for (int T = 0; T < 16; ++T)
-                pair_pack_tile(Ly, T, PAIR_KB, false,
-                               reinterpret_cast<int8_t *>(blob.data()) + (size_t)(1 + 8 * (l - 1) + (T & 7)) * PAIR_BUF + (size_t)(T >> 3) * 16384);
+                pair_pack_tile(Ly, padded, T, 1, true, reinterpret_cast<int8_t *>(blob.data()) + (size_t)pair_place(padded, T) * 1024);
+        } else if (l == L - 1) {
+            pair_pack_tile(Ly, padded, 0, PAIR_KB, false, reinterpret_cast<int8_t *>(blob.data()) + (size_t)(n_chunks - 1) * PAIR_BUF);
+        } else {
+            for (int r = 0; r < 2; ++r)
+                for (int t = 0; t < P->rt; ++t)
+                    pair_pack_tile(Ly, padded, pair_tile(padded, 8 * r + t), PAIR_KB, false,
+                                   reinterpret_cast<int8_t *>(blob.data()) + (size_t)(1 + P->rt * (l - 1) + t) * PAIR_BUF + (size_t)r * 16384);
         }
         // biases: bias_slot order within a tile, in revolutions for the layers that end in an activation
         float *bias = reinterpret_cast<float *>(blob.data() + bias_off) + (size_t)l * 512;
         const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
-        for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = src[f];
+        for (int f = 0; f < Ly.M; ++f) bias[slot(l, f)] = src[f];
         if (l < L - 1)
-            for (int f = Ly.M; f < 512; ++f) bias[bias_slot(f)] = dhq_pad_bias(m->act_kind, f);
+            for (int f = Ly.M; f < 512; ++f) bias[slot(l, f)] = dhq_pad_bias(m->act_kind, f);
     }
     P->blob_bytes = blob.size();
     if (hipMalloc((void **)&P->blob_dev, P->blob_bytes) != hipSuccess) {
@@ -1336,6 +1369,18 @@ int dhq_pair_update_scales(const dhq_model *m, dhq_pair_plan *P)
     return DHQ_OK;
 }
 
+template <int ACTK>
+static void (*pair_kernel_of(const dhq_pair_plan *P))(const pair_args)
+{
+    if (!P->padded) return dhq_fused_pair_kernel<ACTK, PAIR_NT>;
+    switch (P->rt) {
+        case 5: return dhq_fused_pair_kernel<ACTK | DHQ_SPLIT_RN, 5>;
+        case 6: return dhq_fused_pair_kernel<ACTK | DHQ_SPLIT_RN, 6>;
+        case 7: return dhq_fused_pair_kernel<ACTK | DHQ_SPLIT_RN, 7>;
+        default: return dhq_fused_pair_kernel<ACTK | DHQ_SPLIT_RN, 8>;
+    }
+}
+
 hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
@@ -1346,12 +1391,9 @@ hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t 
     a.n = n;
     const int64_t tiles = (n + PAIR_TILE - 1) / PAIR_TILE;
     const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
-    auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET>
-                : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET_COMPLEX> : dhq_fused_pair_kernel<DHQ_ACT_KIND_SINE>;
-    if (P->padded)
-        kern = (P->act_kind == DHQ_ACT_KIND_WAVELET)           ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>
-               : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? dhq_fused_pair_kernel<DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>
-                                                               : dhq_fused_pair_kernel<DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>;
+    auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET)           ? pair_kernel_of<DHQ_ACT_KIND_WAVELET>(P)
+                : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? pair_kernel_of<DHQ_ACT_KIND_WAVELET_COMPLEX>(P)
+                                                                : pair_kernel_of<DHQ_ACT_KIND_SINE>(P);
     hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
     kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
