@@ -120,22 +120,31 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not stale():
         return LIB
     import tempfile
-    cmd = [_hipcc()] + CODEGEN_FLAGS + ["-fPIC", "-shared", "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
+    flags = CODEGEN_FLAGS + ["-fPIC"]
     if os.path.exists(LIB):
         os.remove(LIB)  # a failed build must not leave an older library behind to be loaded in its place
-    if verbose:
-        print(" ".join(cmd), flush=True)
     with tempfile.TemporaryDirectory() as td:
-        # the same sources once more to assembly, in parallel with the real build, for the register check
+        # one compiler per source side by side (dhq_fused.hip alone takes two minutes); the sources whose registers are checked
+        # once more to assembly
+        objs = [os.path.join(td, s + ".o") for s in SOURCES]
+        cmds = [[_hipcc()] + flags + ["-c", "-o", o, os.path.join(CSRC, s)] for s, o in zip(SOURCES, objs)]
+        if verbose:
+            print("\n".join(" ".join(c) for c in cmds), flush=True)
+        procs = [subprocess.Popen(c, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for c in cmds]
         checks = []
         for src, name, first in FIXED_AGPR_KERNELS:
             asm_path = os.path.join(td, src + ".s")
             checks.append((subprocess.Popen(asm_cmd(src, asm_path), stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                                             text=True), asm_path, name, first))
-        r = subprocess.run(cmd, capture_output=True, text=True)
+        outs = [p.communicate()[0] for p in procs]
+        failed = any(p.returncode != 0 for p in procs)
+        if not failed:
+            r = subprocess.run([_hipcc()] + flags + ["-shared", "-o", LIB] + objs, capture_output=True, text=True)
+            outs.append(r.stdout + r.stderr)
+            failed = r.returncode != 0
         for proc, asm_path, name, first in checks:
             out_text, _ = proc.communicate()
-            if r.returncode != 0:
+            if failed:
                 continue
             try:
                 if proc.returncode != 0:
@@ -146,8 +155,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
                 if os.path.exists(LIB):
                     os.remove(LIB)
                 raise
-    msgs = [ln for ln in (r.stdout + r.stderr).splitlines() if "not a recognized feature" not in ln]
-    if r.returncode != 0:
+    msgs = [ln for out in outs for ln in out.splitlines() if "not a recognized feature" not in ln]
+    if failed:
         raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
     if verbose and msgs:
         print("\n".join(msgs))
