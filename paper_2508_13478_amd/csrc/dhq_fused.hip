@@ -68,6 +68,7 @@ struct dhq_fused_plan {
     int nf = 0;                      // hidden width
     int act_kind = DHQ_ACT_KIND_SINE;
     bool padded = false;             // the network's own hidden widths are smaller, padded to nf
+    int skip = 0;                    // tiles of 32 features that are all padding
     unsigned char *blob_dev = nullptr;
     size_t blob_bytes = 0;
     fused_args args;
@@ -94,7 +95,7 @@ struct dhq_fused_plan {
 template <int NT, int KB>
 struct hm_sched {
     static constexpr bool STAGGER = (NT >= 2 && KB >= 2);
-    static constexpr int STEPS = (STAGGER ? (NT / 2) * 2 * KB + KB + 1 : NT * KB) + KB + 6;
+    static constexpr int STEPS = (STAGGER ? ((NT + 1) / 2) * 2 * KB + KB + 1 : NT * KB) + KB + 6;
     static constexpr int NM = NT * KB;
     int tile[STEPS], kb[STEPS], seq[STEPS];   // GEMM MFMA issued at this step (tile -1: none)
     int drain[STEPS], drain_pos[STEPS];       // tile drained at this step and which slice of it
@@ -149,13 +150,14 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
                                                    const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
                                                    const dhq_v4i (&hA)[2], int lane, int h, float c2 = 0.f, float scale = 1.f)
 {
-    constexpr hm_sched<NT, KB> S{};
+    constexpr int RT = NT - DHQ_SKIP(ACTK);  // tiles that are not all padding
+    constexpr hm_sched<RT, KB> S{};
     // the multiplier in a vector register: a multiply-add whose operands are all vector registers issues in about
     // 3 clocks per wave, one with a scalar operand in about 4.5 (measured with a register-only loop)
     asm volatile("" : "+v"(c1));
     if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) asm volatile("" : "+v"(scale));
     constexpr int LAST = S.last;
-    constexpr int NM = NT * KB;
+    constexpr int NM = RT * KB;
     constexpr int EPS = 16 / KB;  // accumulators drained per step (KB <= 8: an even number)
     constexpr int PF = (NM >= 4) ? 4 : (NM >= 2 ? 2 : 1);  // LDS prefetch distance in MFMAs
     dhq_v4i fr[PF + 1];
@@ -243,15 +245,20 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
     }
 }
 
-// The stages of the transform over the tile index: plain register add/sub.
-template <int NT>
+// The stages of the transform over the tile index: plain register add/sub.  The last SKIP tiles are zero (and not written yet);
+// before stage s a tile still is if all tiles that differ from it in lower bits only are.
+template <int NT, int SKIP = 0>
 __device__ __forceinline__ void fused_tile_stages(dhq_v16f (&xt)[NT])
 {
 #pragma unroll
     for (int s = 1; s < NT; s <<= 1) {
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
-            if ((T & s) == 0) {
+            if ((T & s) == 0 && (T & -s) < NT - SKIP) {
+                if (((T | s) & -s) >= NT - SKIP) {
+                    xt[T | s] = xt[T];
+                    continue;
+                }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const float a = xt[T][v], b = xt[T | s][v];
@@ -269,12 +276,15 @@ __device__ __forceinline__ void fused_tile_stages(dhq_v16f (&xt)[NT])
 // of one register's stage into one lane half, those of the other's into the other.  With four tiles or more the pairs are tiles
 // T, T | 2, which no later stage combines; lane half and that bit stay swapped until fused_plain_codes has four values in a
 // dword.  Below, v and v + 1 are swapped back at once.
-template <int NT>
+// The last SKIP tiles are zero, as in fused_tile_stages (`done`: the tile-index bits whose stages are behind).
+template <int NT, int SKIP = 0>
 __device__ __forceinline__ void fused_butterflies(dhq_v16f (&x)[NT])
 {
-    auto over_v = [&](int b) {
+    auto zero = [](int T, int done) { return (T & ~done) >= NT - SKIP; };
+    auto over_v = [&](int b, int done) {
 #pragma unroll
-        for (int T = 0; T < NT; ++T)
+        for (int T = 0; T < NT; ++T) {
+            if (zero(T, done)) continue;
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if ((v & b) == 0) {
@@ -282,11 +292,16 @@ __device__ __forceinline__ void fused_butterflies(dhq_v16f (&x)[NT])
                     x[T][v] = p + q;
                     x[T][v | b] = p - q;
                 }
+        }
     };
-    auto over_tiles = [&](int b) {
+    auto over_tiles = [&](int b, int done) {
 #pragma unroll
         for (int T = 0; T < NT; ++T)
-            if ((T & b) == 0) {
+            if ((T & b) == 0 && !zero(T, done)) {
+                if (zero(T | b, done)) {
+                    x[T | b] = x[T];
+                    continue;
+                }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const float p = x[T][v], q = x[T | b][v];
@@ -295,13 +310,14 @@ __device__ __forceinline__ void fused_butterflies(dhq_v16f (&x)[NT])
                 }
             }
     };
-    over_v(1);
-    over_v(2);
-    if constexpr (NT > 2) over_tiles(2);
-    if constexpr (NT > 4) over_tiles(4);
+    constexpr int high = NT > 4 ? 6 : NT > 2 ? 2 : 0;  // the tile-index bits that come before the lane half
+    over_v(1, 0);
+    over_v(2, 0);
+    if constexpr (NT > 2) over_tiles(2, 0);
+    if constexpr (NT > 4) over_tiles(4, 2);
 #pragma unroll
     for (int T = 0; T < NT; ++T) {
-        if (NT > 2 && (T & 2) != 0) continue;
+        if ((NT > 2 && (T & 2) != 0) || zero(T, high)) continue;
 #pragma unroll
         for (int v = 0; v < 16; v += NT > 2 ? 1 : 2) {
             const int T2 = NT > 2 ? (T | 2) % NT : T, v2 = NT > 2 ? v : (v + 1) % 16;
@@ -317,9 +333,9 @@ __device__ __forceinline__ void fused_butterflies(dhq_v16f (&x)[NT])
             }
         }
     }
-    over_v(4);
-    over_v(8);
-    if constexpr (NT > 1) over_tiles(1);
+    over_v(4, high);
+    over_v(8, high);
+    if constexpr (NT > 1) over_tiles(1, high);
 }
 // The codes of what fused_butterflies leaves (quantized by fused_quantize), in their places.
 template <int NT>
@@ -441,7 +457,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             // other; keep the phases aligned across the workgroup.
             __syncthreads();
             if (active) {
-                fused_tile_stages<NT>(xt);
+                fused_tile_stages<NT, DHQ_SKIP(ACTK)>(xt);
                 fused_quantize<NT>(xt, cd, A.layer[l + 1].inv_in, qlo, qhi);
             }
             p ^= 1;
@@ -817,8 +833,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
                                                    lane, h, A.c2, A.scale);
             __syncthreads();  // keeps the two waves of a SIMD in the same phase, as in the whole-network kernel
             if (active) {
-                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT>(xt);
-                else fused_tile_stages<NT>(xt);
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT, DHQ_SKIP(ACTK)>(xt);
+                else fused_tile_stages<NT, DHQ_SKIP(ACTK)>(xt);
                 fused_quantize<NT>(xt, cd, hm_scaled<ACTK>(inv, A.unscale), qlo, qhi);
                 if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_plain_codes<NT>(cd);
                 if constexpr (MODE == 1) {
@@ -837,8 +853,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
                                                       A.c2, A.scale);
             __syncthreads();
             if (active) {
-                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT>(xt);
-                else fused_tile_stages<NT>(xt);
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT, DHQ_SKIP(ACTK)>(xt);
+                else fused_tile_stages<NT, DHQ_SKIP(ACTK)>(xt);
 #pragma unroll
                 for (int T = 0; T < NT; ++T) {
 #pragma unroll
@@ -960,6 +976,9 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     P->nf = nf;
     P->act_kind = m->act_kind;
     P->padded = padded;
+    int widest = 0;
+    for (int l = 1; l < L; ++l) widest = m->dims[l] > widest ? m->dims[l] : widest;
+    P->skip = NT - (widest + 31) / 32;
     memset(&P->args, 0, sizeof(P->args));
     P->args.scale = padded ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, dhq_hidden_act(m).c2)) : 1.f;
 
@@ -1101,18 +1120,35 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
         a.coords += head * a.k0;
         a.out += head * a.m_out;
         a.n = n - head;
-        dhq_fused_split_kernel<NF, ACTK><<<(unsigned)rest, NF * 2, 0, st>>>(a);
+        dhq_fused_split_kernel<NF, ACTK & 0xff><<<(unsigned)rest, NF * 2, 0, st>>>(a);
     }
     return hipGetLastError();
+}
+// The instance of a padded network: of the tiles that are all padding up to two are left out at width 256, one at 128 (the others
+// have none).  Whole forwards of four hidden layers in us, all tiles / without those:
+// 200 features, 65 536 rows 29.8 / 27.6; 140 (wavelet) 35.8 / 29.2; 180, on-line scales 84.1 / 71.4; 90, 131 072 rows 27.0 / 23.1;
+// 200, 150 001 rows with calibration 271 / 255.
+template <int NF, typename F>
+static hipError_t fused_with_skip(int skip, F f)
+{
+    if constexpr (NF >= 256) {
+        if (skip >= 2) return f(std::integral_constant<int, DHQ_SKIPPING(2)>{});
+    }
+    if constexpr (NF >= 128) {
+        if (skip >= 1) return f(std::integral_constant<int, DHQ_SKIPPING(1)>{});
+    }
+    return f(std::integral_constant<int, 0>{});
 }
 template <int NF>
 static hipError_t fused_launch_t(const dhq_fused_plan *P, fused_args &a, int act_kind, hipStream_t st)
 {
-    if (P->padded) {
-        if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(P, a, st);
-        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(P, a, st)
-                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(P, a, st);
-    }
+    if (P->padded)
+        return fused_with_skip<NF>(P->skip, [&](auto skip) {
+            constexpr int S = DHQ_SPLIT_RN | decltype(skip)::value;
+            if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(P, a, st);
+            return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | S>(P, a, st)
+                                                    : fused_launch_act<NF, DHQ_ACT_KIND_SINE | S>(P, a, st);
+        });
     if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(P, a, st);
     return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET>(P, a, st)
                                             : fused_launch_act<NF, DHQ_ACT_KIND_SINE>(P, a, st);
@@ -1218,9 +1254,9 @@ static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args
     if (ONE_HIDDEN && n_layers != 2) return hipErrorInvalidValue;
     const bool last = (layer == n_layers - 1);
     if (a.xout) {  // floats; the output layer has no activation
-        if (layer == 0) return fusedl_launch_xhat<NF, 0, ACTK>(a, grid, device, st);
+        if (layer == 0) return fusedl_launch_xhat<NF, 0, ACTK & 0xff>(a, grid, device, st);
         if (last) return fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);
-        if constexpr (!ONE_HIDDEN) return fusedl_launch_xhat<NF, 1, ACTK>(a, grid, device, st);
+        if constexpr (!ONE_HIDDEN) return fusedl_launch_xhat<NF, 1, ACTK & 0xff>(a, grid, device, st);
     } else {
         if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
         if (last && layer == 1) return fusedl_launch_t<NF, 2, true, ACTK>(a, grid, device, st);
@@ -1234,11 +1270,13 @@ static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args
 template <int NF>
 static hipError_t fusedl_launch_nf(const dhq_fused_plan *P, int layer, int L, const fusedl_args &a, unsigned grid, hipStream_t st)
 {
-    if (P->padded) {
-        if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
-        if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
-        return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | DHQ_SPLIT_RN>(layer, L, a, grid, P->device, st);
-    }
+    if (P->padded)
+        return fused_with_skip<NF>(P->skip, [&](auto skip) {
+            constexpr int S = DHQ_SPLIT_RN | decltype(skip)::value;
+            if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET | S>(layer, L, a, grid, P->device, st);
+            if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(layer, L, a, grid, P->device, st);
+            return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | S>(layer, L, a, grid, P->device, st);
+        });
     if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET>(layer, L, a, grid, P->device, st);
     if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(layer, L, a, grid, P->device, st);
     return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE>(layer, L, a, grid, P->device, st);
@@ -1307,8 +1345,8 @@ hipError_t dhq_fused_dynamic_launch(const dhq_model *m, const dhq_fused_plan *P,
 // (DHQ_PLAIN), one launch per hidden layer: it computes the layer below once more from its codes, stores the codes that this makes,
 // computes the layer and leaves the maximum of its transform.  Bound by vector issue like the whole-network kernel (eight
 // add/sub stages in place of the products with H_32).  Four layers of 200 on 150 001 rows, forward included: 782 us with a
-// GEMM, a transform and a maximum over memory each, twice a layer; this way 285 us (24 of the
-// difference by a copy of the scales into pinned memory).  buf_bytes of codes in each of two buffers: calls with more rows
+// GEMM, a transform and a maximum over memory each, twice a layer; this way 255 us (24 of the
+// difference by a copy of the scales into pinned memory, 16 by leaving out the padding's tile).  buf_bytes of codes in each of two buffers: calls with more rows
 // run in groups, and those beyond two groups make their codes again from the coordinates for every layer (hipErrorInvalidValue beyond eight groups: too many maxima).
 template <int NF, int ACTK>
 static hipError_t fused_measure_layer(int layer, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
@@ -1318,11 +1356,14 @@ static hipError_t fused_measure_layer(int layer, const fusedl_args &a, unsigned 
                       : fusedl_launch_t<NF, 1, false, ACTK | DHQ_PLAIN>(a, grid, device, st);
 }
 template <int NF>
-static hipError_t fused_measure_nf(int act_kind, int layer, const fusedl_args &a, unsigned grid, int device, hipStream_t st)
+static hipError_t fused_measure_nf(const dhq_fused_plan *P, int layer, const fusedl_args &a, unsigned grid, hipStream_t st)
 {
-    if (act_kind == DHQ_ACT_KIND_WAVELET) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET>(layer, a, grid, device, st);
-    if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(layer, a, grid, device, st);
-    return fused_measure_layer<NF, DHQ_ACT_KIND_SINE>(layer, a, grid, device, st);
+    return fused_with_skip<NF>(P->skip, [&](auto skip) {
+        constexpr int S = decltype(skip)::value;
+        if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET | S>(layer, a, grid, P->device, st);
+        if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_measure_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(layer, a, grid, P->device, st);
+        return fused_measure_layer<NF, DHQ_ACT_KIND_SINE | S>(layer, a, grid, P->device, st);
+    });
 }
 hipError_t dhq_fused_measure_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, void *const (&buf)[2],
                                     size_t buf_bytes, float *partial, float *dyn, hipStream_t st)
@@ -1365,10 +1406,10 @@ hipError_t dhq_fused_measure_launch(const dhq_model *m, const dhq_fused_plan *P,
                 a.c2 = dhq_hidden_act(m).c2;
                 a.scale = a.unscale = 1.f;
                 switch (P->nf) {
-                    case 32: e = fused_measure_nf<32>(P->act_kind, k, a, grid, P->device, st); break;
-                    case 64: e = fused_measure_nf<64>(P->act_kind, k, a, grid, P->device, st); break;
-                    case 128: e = fused_measure_nf<128>(P->act_kind, k, a, grid, P->device, st); break;
-                    case 256: e = fused_measure_nf<256>(P->act_kind, k, a, grid, P->device, st); break;
+                    case 32: e = fused_measure_nf<32>(P, k, a, grid, st); break;
+                    case 64: e = fused_measure_nf<64>(P, k, a, grid, st); break;
+                    case 128: e = fused_measure_nf<128>(P, k, a, grid, st); break;
+                    case 256: e = fused_measure_nf<256>(P, k, a, grid, st); break;
                     default: e = hipErrorInvalidValue;
                 }
             }

@@ -16,7 +16,7 @@ def _scales(m, x):
 
 
 @pytest.mark.parametrize("dims", [[2, 32, 3], [1, 32, 32, 32, 1], [3, 64, 64, 2], [2, 128, 128, 128, 3], [4, 256, 256, 256, 5], [2, 20, 20, 3],
-                                  [3, 90, 120, 1], [2, 200, 200, 200, 3]], ids=lambda d: "x".join(map(str, d)))
+                                  [3, 90, 120, 1], [2, 150, 150, 3], [1, 180, 180, 180, 2], [2, 200, 200, 200, 3]], ids=lambda d: "x".join(map(str, d)))
 @pytest.mark.parametrize("act,bits", [("sine", 8), ("sine", 4), ("wavelet", 8), ("complex", 8)])
 def test_scales_of_every_activation_and_width(dims, act, bits):
     """Every tile count of the transform (its stage over the lane halves differs below four tiles), rows at the edges of a wave's and
