@@ -252,7 +252,7 @@ def main() -> int:
                                  else None),
                      "traffic_unit": "HBM bytes per launch, stored from the rocprofv3 --pmc runs summarised in "
                                      "profiles/dhq_fused_hbm_traffic_pmc.md (null when the kernel sources have changed since)",
-                     "kernel": ((f"dhq_fused2_kernel<{wl.dims[1]}>" if two_sided else
+                     "kernel": ((f"dhq_fused_kernel<{wl.dims[1]}, two digits>" if two_sided else
                                  (f"dhq_fused_wide_kernel<512, {2 if s0 is not None else 1}>" if args.wide_kernel == 1 else
                                   f"dhq_fused_pair_kernel<{2 if s0 is not None else 1}>") if wl.dims[1] == 512 else
                                  f"dhq_fused_kernel<{wl.dims[1]}, {2 if s0 is not None else 1}>")
@@ -325,7 +325,7 @@ def main() -> int:
         gbs = per_coord * n / (ms * 1e-3) / 1e9
         res["roofline"] = {"bound": "hbm", "achieved": gbs, "peak": 8000.0, "unit": "GB/s", "frac": gbs / 8000.0,
                            "traffic": None,
-                           "kernel": (("dhq_fused2_layer_kernel" if two_sided else
+                           "kernel": (("dhq_fused_layer_xhat_kernel" if two_sided else
                                        "dhq_fused_pair_layer_kernel" if wl.dims[1] == 512 else "dhq_fused_layer_kernel") +
                                       ", all launches of one forward" if dyn_fused
                                       else "layer-by-layer path, all kernels of one forward"),

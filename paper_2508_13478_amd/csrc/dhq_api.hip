@@ -174,7 +174,7 @@ extern "C" void dhq_free(dhq_model *m)
     dhq_wide_destroy(m->wide);
     dhq_pair_destroy(m->pair);
     dhq_float_destroy(m->flt);
-    dhq_fused2_destroy(m->fused2);
+    dhq_fused_destroy(m->fused2);
     delete m;
 }
 
@@ -481,8 +481,8 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
     if (rc == DHQ_OK && !m->rot_out) rc = dhq_fused_create(m, true, &m->pad_fused);
     if (rc == DHQ_OK && !m->rot_out) rc = dhq_pair_create(m, true, &m->pad_pair);
     if (rc == DHQ_OK) rc = dhq_pair2_create(m, &m->pair2);
+    if (rc == DHQ_OK && m->rot_out) rc = dhq_fused_create(m, false, &m->fused2);
     for (int l = 0; l < L; ++l) std::vector<int32_t>().swap(m->layer[l].u_host);
-    if (rc == DHQ_OK && m->rot_out) rc = dhq_fused2_create(m, &m->fused2);
     if (rc != DHQ_OK) {
         dhq_free(m);
         return rc;
@@ -579,7 +579,7 @@ static int update_fused_scales(dhq_model *m)
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pair2);
     if (rc == DHQ_OK) rc = dhq_wide_update_scales(m, m->wide);
     if (rc == DHQ_OK) rc = dhq_pair_update_scales(m, m->pair);
-    if (rc == DHQ_OK) rc = dhq_fused2_update_scales(m, m->fused2);
+    if (rc == DHQ_OK) rc = dhq_fused_update_scales(m, m->fused2);
     return rc;
 }
 
@@ -809,7 +809,7 @@ static size_t dyn_act_bytes(const dhq_model *m, int64_t n, size_t act)
 static dyn_sizes dyn_buffer_sizes(const dhq_model *m, int64_t n)
 {
     // the per-layer fused kernels store whole workgroup tiles
-    const size_t rows = m->fused ? dhq_fused_dynamic_rows(n) : m->fused2 ? dhq_fused2_dynamic_rows(n) : m->pair ? dhq_pair_dynamic_rows(n) : (size_t)n;
+    const size_t rows = m->fused || m->fused2 ? dhq_fused_dynamic_rows(n) : m->pair ? dhq_pair_dynamic_rows(n) : (size_t)n;
     dyn_sizes z;
     z.act = sizeof(float) * rows * m->max_dim;
     z.codes = (size_t)n * m->max_kp;
@@ -864,8 +864,7 @@ static int forward_dynamic(const dhq_model *m, const dyn_ws &ws, const float *co
     if (per_layer_fused) {
         void *const bufs[2] = {ws.act0, ws.act1};
         const hipError_t e =
-            m->fused2 ? dhq_fused2_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st)
-            : (m->fused || m->pad_fused) ? dhq_fused_dynamic_launch(m, m->fused ? m->fused : m->pad_fused, coords_dev, n, out_dev, bufs, ws.act_bytes, ws.partial, ws.params, st)
+            (m->fused || m->fused2 || m->pad_fused) ? dhq_fused_dynamic_launch(m, m->fused2 ? m->fused2 : m->fused ? m->fused : m->pad_fused, coords_dev, n, out_dev, bufs, ws.act_bytes, ws.partial, ws.params, st)
                        : dhq_pair_dynamic_launch(m, coords_dev, n, out_dev, ws.act0, ws.act1, ws.partial, ws.params, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
@@ -942,7 +941,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if (!m->have_scales) return DHQ_ENOSCALE;
     if (path == DHQ_FUSED && !fused_ok) return DHQ_EUNSUPPORTED;
     if ((path == DHQ_FUSED && fused_ok) || (path == DHQ_AUTO && fused_ok && m->pieces_ok)) {
-        const hipError_t e = m->fused2 ? dhq_fused2_launch(m->fused2, coords_dev, n, out_dev, st)
+        const hipError_t e = m->fused2 ? dhq_fused_launch(m, m->fused2, coords_dev, n, out_dev, st)
                              : m->fused ? dhq_fused_launch(m, m->fused, coords_dev, n, out_dev, st)
                              : dhq_use_pair(m) ? dhq_pair_launch(m->pair, coords_dev, n, out_dev, st)
                                                : dhq_wide_launch(m->wide, coords_dev, n, out_dev, st);
@@ -1073,8 +1072,8 @@ extern "C" int dhq_forward_debug_fused(const dhq_model *m, const int8_t *codes_i
     if (!m->have_scales) return DHQ_ENOSCALE;
     if (!m->fused_sine_ok) return DHQ_EUNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
-    const hipError_t e = m->fused2 ? dhq_fused2_debug_launch(m, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st)
-                         : m->fused ? dhq_fused_debug_launch(m, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st)
+    const hipError_t e = m->fused2 ? dhq_fused_debug_launch(m, m->fused2, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st)
+                         : m->fused ? dhq_fused_debug_launch(m, m->fused, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st)
                          : dhq_use_pair(m) ? dhq_pair_debug_launch(m, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st)
                                            : dhq_wide_debug_launch(m, layer, codes_in_dev, n, xhat_dev, codes_out_dev, acc_dev, st);
     return e == hipSuccess ? DHQ_OK : DHQ_EHIP;

@@ -29,6 +29,14 @@
 // form one contiguous block; while layer l computes, the block of layer l+1 is copied from
 // device memory (L2-resident) straight into the other LDS buffer with 16-byte
 // global->LDS loads, so the copy costs no registers and no VALU work.
+//
+// Two-sided rotation (Eq. 4 with both factors): the layer's output in the rotated basis is multiplied by H once more, exactly, in
+// int32.  That product is linear in the weights, z = (q W'^T) H = q (H W')^T, so these kernels multiply by U = H W' and have no
+// un-rotation.  An entry of U is a sum of up to 256 codes of 127, at most 32 512 = two int8 digits, 256 u1 + u0
+// (DHQ_TWO_DIGITS): twice the int8 MFMAs and a shift against eight integer butterfly stages and a lane exchange per value.  Five
+// layers, 262 144 rows, butterflies / digits in us: width 32 25.9 / 22.0, 64 (wavelet) 55.9 / 48.6, 128 90.3 / 75.8, 256 197.7 /
+// 194.2 (there the digits' products load the matrix unit as much as the epilogue does the vector ALU); 1 000 rows of 256,
+// which the kernel for few rows now takes as well, 49.9 / 13.3.
 #include <math.h>
 #include <string.h>
 
@@ -68,6 +76,7 @@ struct dhq_fused_plan {
     int nf = 0;                      // hidden width
     int act_kind = DHQ_ACT_KIND_SINE;
     bool padded = false;             // the network's own hidden widths are smaller, padded to nf
+    int digits = 1;                  // int8 digits of a weight: two in two-sided models
     int skip = 0;                    // tiles of 32 features that are all padding
     unsigned char *blob_dev = nullptr;
     size_t blob_bytes = 0;
@@ -92,10 +101,11 @@ struct dhq_fused_plan {
 // the butterflies' sums.  Per tile: 8 + 8 packed conversions, 16 mixed-precision subtractions
 // and 4 MFMAs replace 80 add/sub and 8 lane swaps.  The three stages over the tile index stay
 // on the vector ALU.  Afterwards register s of lane half u holds rotated feature hm_index(s, u).
-template <int NT, int KB>
+// KB: MFMAs of a tile; DS: steps its drain is spread over.
+template <int NT, int KB, int DS>
 struct hm_sched {
     static constexpr bool STAGGER = (NT >= 2 && KB >= 2);
-    static constexpr int STEPS = (STAGGER ? ((NT + 1) / 2) * 2 * KB + KB + 1 : NT * KB) + KB + 6;
+    static constexpr int STEPS = (STAGGER ? ((NT + 1) / 2) * 2 * KB + KB + 1 : NT * KB) + DS + 6;
     static constexpr int NM = NT * KB;
     int tile[STEPS], kb[STEPS], seq[STEPS];   // GEMM MFMA issued at this step (tile -1: none)
     int drain[STEPS], drain_pos[STEPS];       // tile drained at this step and which slice of it
@@ -119,17 +129,17 @@ struct hm_sched {
         for (int g = 0; g < STEPS; ++g)
             if (tile[g] >= 0) { seq[g] = m; seq_tile[m] = tile[g]; seq_kb[m] = kb[g]; ++m; }
         for (int t = 0; t < NT; ++t) {
-            int at[KB + 3] = {};
+            int at[DS + 3] = {};
             int g = done[t] + 1;
-            for (int k = 0; k < KB; ++k) {
+            for (int k = 0; k < DS; ++k) {
                 while (drain[g] >= 0) ++g;
                 drain[g] = t; drain_pos[g] = k; at[k] = g;
                 ++g;
             }
-            at[KB] = at[KB - 1] + 1; at[KB + 1] = at[KB - 1] + 2;
-            // pieces of block 0 (accumulators 0..7) are complete after slice KB/2 - 1, of block 1 after the last
-            int when[4] = {at[KB], at[KB], at[KB], at[KB]};
-            if (KB >= 4) { when[0] = at[KB / 2]; when[1] = at[KB / 2 + 1]; when[2] = at[KB]; when[3] = at[KB + 1]; }
+            at[DS] = at[DS - 1] + 1; at[DS + 1] = at[DS - 1] + 2;
+            // pieces of block 0 (accumulators 0..7) are complete after slice DS/2 - 1, of block 1 after the last
+            int when[4] = {at[DS], at[DS], at[DS], at[DS]};
+            if (DS >= 4) { when[0] = at[DS / 2]; when[1] = at[DS / 2 + 1]; when[2] = at[DS]; when[3] = at[DS + 1]; }
             for (int k = 0; k < 4; ++k) {
                 const int w = when[k];
                 hm_tile[w][hm_n[w]] = t; hm_k[w][hm_n[w]] = k; ++hm_n[w];
@@ -144,20 +154,22 @@ struct hm_sched {
 // holds, for this lane's coordinate, row 8 (v / 4) + 4 h + v % 4 of H_32 * (activations of tile T).
 // ACTK: the activation (sine, or the wavelet with envelope constant c2), plus DHQ_SPLIT_RN where the activations are scaled
 // before they are split and hi rounds to nearest (xt then comes out times `scale`).  With DHQ_PLAIN xt[T][v] is the activation
-// itself, any finite argument.
+// itself, any finite argument.  With DHQ_TWO_DIGITS a tile takes the products with the upper digits, shifts its sums by eight
+// bits and takes the products with the lower ones into the same accumulators (wrapping, the exact int32).
 template <int NT, int KB, int NCD, int ACTK = DHQ_ACT_KIND_SINE>
 __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ wA, const float4 *__restrict__ wB,
                                                    const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
                                                    const dhq_v4i (&hA)[2], int lane, int h, float c2 = 0.f, float scale = 1.f)
 {
     constexpr int RT = NT - DHQ_SKIP(ACTK);  // tiles that are not all padding
-    constexpr hm_sched<RT, KB> S{};
+    constexpr int KM = KB * DHQ_DIGITS(ACTK);  // MFMAs of a tile
+    constexpr hm_sched<RT, KM, KB> S{};
     // the multiplier in a vector register: a multiply-add whose operands are all vector registers issues in about
     // 3 clocks per wave, one with a scalar operand in about 4.5 (measured with a register-only loop)
     asm volatile("" : "+v"(c1));
     if constexpr ((ACTK & DHQ_SPLIT_RN) != 0) asm volatile("" : "+v"(scale));
     constexpr int LAST = S.last;
-    constexpr int NM = RT * KB;
+    constexpr int NM = RT * KM;
     constexpr int EPS = 16 / KB;  // accumulators drained per step (KB <= 8: an even number)
     constexpr int PF = (NM >= 4) ? 4 : (NM >= 2 ? 2 : 1);  // LDS prefetch distance in MFMAs
     dhq_v4i fr[PF + 1];
@@ -166,7 +178,7 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
     unsigned hp[2][8], lp[2][8];  // packed pieces of the tile being drained (and of the one before)
 #pragma unroll
     for (int m = 0; m < PF; ++m)
-        if (m < NM) fr[m % (PF + 1)] = wA[(S.seq_tile[m] * KB + S.seq_kb[m]) * 64 + lane];
+        if (m < NM) fr[m % (PF + 1)] = wA[(S.seq_tile[m] * KM + S.seq_kb[m]) * 64 + lane];
     constexpr int GB = 8;
 #pragma unroll
     for (int g0 = 0; g0 <= LAST; g0 += GB) {
@@ -178,17 +190,21 @@ __device__ __forceinline__ void fused_gemm_sine_hm(const dhq_v4i *__restrict__ w
         if (T >= 0) {
             const int m = S.seq[g], kb = S.kb[g];
             if (m + PF < NM) {
-                fr[(m + PF) % (PF + 1)] = wA[(S.seq_tile[m + PF] * KB + S.seq_kb[m + PF]) * 64 + lane];
+                fr[(m + PF) % (PF + 1)] = wA[(S.seq_tile[m + PF] * KM + S.seq_kb[m + PF]) * 64 + lane];
                 __builtin_amdgcn_sched_barrier(0);  // keep the prefetch at the top of the step
             }
 #pragma unroll
             for (int gg = 0; gg < 4; ++gg)
-                if ((gg * KB) / 4 == kb) bq[T % 3][gg] = wB[(T * 4 + gg) * 2 + h];
+                if ((gg * KM) / 4 == kb) bq[T % 3][gg] = wB[(T * 4 + gg) * 2 + h];
             if (kb == 0) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[T % 3][v] = 0;
             }
-            acc[T % 3] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[m % (PF + 1)], cd[kb], acc[T % 3], 0, 0, 0);
+            if (KM > KB && kb == KB) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[T % 3][v] = (int)((unsigned)acc[T % 3][v] << 8);
+            }
+            acc[T % 3] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[m % (PF + 1)], cd[kb % KB], acc[T % 3], 0, 0, 0);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -368,7 +384,7 @@ __device__ __forceinline__ void fused_quantize(const dhq_v16f (&xt)[NT], dhq_v4i
 }
 
 // The output layer: one zero-padded M tile, no sine.
-template <int NKB>
+template <int NKB, int DIGITS = 1>
 __device__ __forceinline__ void fused_output_layer(const dhq_v4i *__restrict__ wA, const float *__restrict__ wB,
                                                    const dhq_v4i (&cd)[NKB], float c1, float *__restrict__ out, int64_t ci,
                                                    bool valid, int m_out, int lane, int h)
@@ -377,9 +393,13 @@ __device__ __forceinline__ void fused_output_layer(const dhq_v4i *__restrict__ w
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0;
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
+    for (int kb = 0; kb < NKB * DIGITS; ++kb) {
+        if (DIGITS > 1 && kb == NKB) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+        }
         const dhq_v4i a = wA[kb * 64 + lane];
-        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, cd[kb], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, cd[kb % NKB], acc, 0, 0, 0);
     }
     if (valid) {
 #pragma unroll
@@ -388,6 +408,31 @@ __device__ __forceinline__ void fused_output_layer(const dhq_v4i *__restrict__ w
             if (row < m_out) out[ci * m_out + row] = __builtin_fmaf((float)acc[v], c1, wB[((v >> 2) * 2 + h) * 4 + (v & 3)]);
         }
     }
+}
+
+// A hidden layer's block: fragments [tile][digit][k block] KiB, then one KiB of biases.  Two digits at width 256 are 128 KiB of
+// fragments, which the two buffers of the whole-network kernel take as two blocks of half the tiles each.
+template <int NT, int KB, int ACTK>
+constexpr int fused_halves = NT * KB * DHQ_DIGITS(ACTK) > 64 ? 2 : 1;
+template <int NT, int KB, int ACTK>
+constexpr int fused_block_kib = NT * KB * DHQ_DIGITS(ACTK) / fused_halves<NT, KB, ACTK> + 1;
+// The GEMM of one of them (HALF), and of a whole layer in LDS.
+template <int NT, int KB, int NCD, int ACTK, int HALF>
+__device__ __forceinline__ void fused_half(const unsigned char *blk, const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
+                                           const dhq_v4i (&hA)[2], int lane, int h, float c2, float scale)
+{
+    constexpr int TH = NT / fused_halves<NT, KB, ACTK>;
+    fused_gemm_sine_hm<TH, KB, NCD, ACTK>(reinterpret_cast<const dhq_v4i *>(blk),
+                                          reinterpret_cast<const float4 *>(blk + (fused_block_kib<NT, KB, ACTK> - 1) * 1024), cd, c1,
+                                          reinterpret_cast<dhq_v16f(&)[TH]>(xt[HALF * TH]), hA, lane, h, c2, scale);
+}
+template <int NT, int KB, int NCD, int ACTK>
+__device__ __forceinline__ void fused_layer_gemm(const unsigned char *blk, const dhq_v4i (&cd)[NCD], float c1, dhq_v16f (&xt)[NT],
+                                                 const dhq_v4i (&hA)[2], int lane, int h, float c2, float scale = 1.f)
+{
+    fused_half<NT, KB, NCD, ACTK, 0>(blk, cd, c1, xt, hA, lane, h, c2, scale);
+    if constexpr (fused_halves<NT, KB, ACTK> > 1)
+        fused_half<NT, KB, NCD, ACTK, 1>(blk + fused_block_kib<NT, KB, ACTK> * 1024, cd, c1, xt, hA, lane, h, c2, scale);
 }
 
 // ROWS: which rows a wave takes, and whether it has to look.
@@ -404,7 +449,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
 {
     constexpr int NT = NF / 32;   // M tiles of a hidden layer
     constexpr int NKB = NF / 32;  // k blocks of a hidden layer
-    constexpr int BLK = (NT * NKB + 1) * 1024;  // LDS bytes per weight buffer
+    constexpr int BLK = fused_block_kib<NT, NKB, ACTK> * 1024;  // LDS bytes per weight buffer
+    constexpr bool HALVES = fused_halves<NT, NKB, ACTK> > 1;
 
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -439,19 +485,26 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             // weights of layer l have landed; everyone is done with the other buffer
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            {
-                const fused_layer_desc &nx = A.layer[l + 1];
-                fused_issue_copy(A.blob + nx.blob_off, lds + (p ^ 1) * BLK, (int)nx.chunks, wave, lane, FUSED_WAVES);
-            }
-            const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds + p * BLK);
+            const fused_layer_desc &nx = A.layer[l + 1];
+            const unsigned char *const next = A.blob + nx.blob_off;
+            const int next_kib = HALVES && l + 1 < L - 1 ? BLK / 1024 : (int)nx.chunks;
             const float c1 = A.layer[l].c1;
-            if (!active) {
-            } else if (l == 0)
-                fused_gemm_sine_hm<NT, 1, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + p * BLK + NT * 1024), cd, c1, xt,
-                                                     hA, lane, h, A.c2, A.scale);
-            else
-                fused_gemm_sine_hm<NT, NKB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + p * BLK + NT * NKB * 1024), cd,
-                                                       c1, xt, hA, lane, h, A.c2, A.scale);
+            if (HALVES && l > 0) {
+                fused_issue_copy(A.blob + A.layer[l].blob_off + BLK, lds + (p ^ 1) * BLK, BLK / 1024, wave, lane, FUSED_WAVES);
+                if (active) fused_half<NT, NKB, NKB, ACTK, 0>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                fused_issue_copy(next, lds + p * BLK, next_kib, wave, lane, FUSED_WAVES);
+                if (active) fused_half<NT, NKB, NKB, ACTK, HALVES ? 1 : 0>(lds + (p ^ 1) * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
+                p ^= 1;
+            } else {
+                fused_issue_copy(next, lds + (p ^ 1) * BLK, next_kib, wave, lane, FUSED_WAVES);
+                if (!active) {
+                } else if (l == 0)
+                    fused_layer_gemm<NT, 1, NKB, ACTK>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
+                else if constexpr (!HALVES)
+                    fused_layer_gemm<NT, NKB, NKB, ACTK>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
+            }
             // The two waves of a SIMD overlap well while both feed the matrix unit or both
             // do vector work, but a wave in its vector phase starves the MFMA chain of the
             // other; keep the phases aligned across the workgroup.
@@ -470,8 +523,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             if (tile + stride < n_tiles)
                 fused_issue_copy(A.blob + A.layer[0].blob_off, lds + (p ^ 1) * BLK, (int)A.layer[0].chunks, wave, lane, FUSED_WAVES);
             if (active)
-                fused_output_layer<NKB>(reinterpret_cast<const dhq_v4i *>(lds + p * BLK),
-                                        reinterpret_cast<const float *>(lds + p * BLK + NKB * 1024), cd, A.layer[L - 1].c1, A.out, ci,
+                fused_output_layer<NKB, DHQ_DIGITS(ACTK)>(reinterpret_cast<const dhq_v4i *>(lds + p * BLK),
+                                        reinterpret_cast<const float *>(lds + p * BLK + NKB * DHQ_DIGITS(ACTK) * 1024), cd, A.layer[L - 1].c1, A.out, ci,
                                         valid, A.m_out, lane, h);
             p ^= 1;
         }
@@ -486,11 +539,12 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
 // every wave reads the whole B operand, as the two waves of a pair do at width 512.  The weights are not staged: a fragment is
 // read by one wave only, straight from device memory, while the layer before is in its epilogue.  Same operations in the
 // same order per value, hence the same bits as the kernel above; what a layer takes is latency: a forward of
-// five 256-wide layers on 1 000 rows 31.7 -> 11.1 us.
+// five 256-wide layers on 1 000 rows 31.7 -> 11.0 us.  (Two accumulator chains of every other k block: unchanged.)
 template <int NF, int ACTK>
-__global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_args A)
+__global__ __launch_bounds__(NF * 2, DHQ_DIGITS(ACTK) > 1 ? 2 : 4) void dhq_fused_split_kernel(const fused_args A)
 {
-    constexpr int NT = NF / 32, NKB = NF / 32, RPW = 16 / NT;
+    constexpr int NT = NF / 32, NKB = NF / 32, RPW = 16 / NT, D = DHQ_DIGITS(ACTK);
+    constexpr int BLK = fused_block_kib<NT, NKB, ACTK> * 1024, TH = NT / fused_halves<NT, NKB, ACTK>;  // a hidden layer's blocks
     __shared__ float4 xs[NT * 4 * 64];    // [tile][row group g][lane]: rows 4 g .. 4 g + 3 of the lane's coordinate
     __shared__ dhq_v4i codes[NKB * 64];   // [k block][lane]: the next layer's B operand
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -504,13 +558,14 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
         const int64_t ci = (int64_t)tile * 32 + c;
         const bool valid = ci < A.n;
         const int64_t cl = valid ? ci : A.n - 1;
-        dhq_v4i fr[NKB];
+        dhq_v4i fr[D * NKB];  // [digit][k block]
         float4 bias[4];
         {
             const unsigned char *blk = A.blob + A.layer[0].blob_off;
-            fr[0] = reinterpret_cast<const dhq_v4i *>(blk)[wave * 64 + lane];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * 1024)[(wave * 4 + g) * 2 + h];
+            for (int d = 0; d < D; ++d) fr[d] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * D + d) * 64 + lane];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * D * 1024)[(wave * 4 + g) * 2 + h];
         }
         dhq_v16i acc;
 #pragma unroll
@@ -518,7 +573,14 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
         {
             dhq_v4i cd = dhq_v4i{0, 0, 0, 0};
             cd[0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[0], cd, acc, 0, 0, 0);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (d > 0) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+                }
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[d], cd, acc, 0, 0, 0);
+            }
         }
         for (int l = 0; l < L - 1; ++l) {
             const float c1 = A.layer[l].c1;
@@ -527,14 +589,15 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
             for (int g = 0; g < 4; ++g) b[g] = bias[g];
             // the next layer's fragments and biases, in time for its GEMM (the output layer: one tile, wave 0's)
             {
-                const unsigned char *blk = A.blob + A.layer[l + 1].blob_off;
+                const unsigned char *blk = A.blob + A.layer[l + 1].blob_off + wave / TH * BLK;
                 const bool last = (l + 1 == L - 1);
                 if (!last || wave == 0) {
+                    const int t = wave % TH;  // (wave 0: 0)
 #pragma unroll
-                    for (int kb = 0; kb < NKB; ++kb) fr[kb] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * NKB + kb) * 64 + lane];
-                    const float4 *wB = reinterpret_cast<const float4 *>(blk + (last ? 1 : NT) * NKB * 1024);
+                    for (int kb = 0; kb < D * NKB; ++kb) fr[kb] = reinterpret_cast<const dhq_v4i *>(blk)[(t * D * NKB + kb) * 64 + lane];
+                    const float4 *wB = reinterpret_cast<const float4 *>(blk + (last ? 1 : TH) * D * NKB * 1024);
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) bias[g] = wB[(wave * 4 + g) * 2 + h];
+                    for (int g = 0; g < 4; ++g) bias[g] = wB[(t * 4 + g) * 2 + h];
                 }
             }
             unsigned hp[8], lp[8];
@@ -615,7 +678,13 @@ __global__ __launch_bounds__(NF * 2, 4) void dhq_fused_split_kernel(const fused_
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = 0;
 #pragma unroll
-                for (int kb = 0; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[kb], codes[kb * 64 + lane], acc, 0, 0, 0);
+                for (int kb = 0; kb < D * NKB; ++kb) {
+                    if (D > 1 && kb == NKB) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+                    }
+                    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[kb], codes[kb % NKB * 64 + lane], acc, 0, 0, 0);
+                }
             }
         }
         if (wave == 0 && valid) {
@@ -712,7 +781,6 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_xhat_kernel(con
 {
     constexpr int NT = NF / 32, NKB = NF / 32, NR = NF / 2;
     constexpr int KB = (MODE == 0) ? 1 : NKB;      // k blocks of this layer's GEMM
-    constexpr int MT = (MODE == 2) ? 1 : NT;       // M tiles of this layer's GEMM
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ float red_in[FUSED_WAVES], red[FUSED_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -725,7 +793,6 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_xhat_kernel(con
     float inv, c1;
     fusedl_constants(A, red_in, wave, lane, inv, c1);
     const float inv_x = inv * A.unscale;
-    const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
     float mx = 0.f;
     bool landed = false;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -751,12 +818,12 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_xhat_kernel(con
             landed = true;
         }
         if constexpr (MODE == 2) {
-            fused_output_layer<NKB>(wA, reinterpret_cast<const float *>(lds + MT * KB * 1024), cd, c1, A.out, ci, valid, A.m_out,
+            fused_output_layer<NKB, DHQ_DIGITS(ACTK)>(reinterpret_cast<const dhq_v4i *>(lds),
+                                    reinterpret_cast<const float *>(lds + KB * DHQ_DIGITS(ACTK) * 1024), cd, c1, A.out, ci, valid, A.m_out,
                                     lane, h);
         } else {
             dhq_v16f xt[NT];
-            fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + MT * KB * 1024), cd, c1, xt, hA, lane, h,
-                                                  A.c2, A.scale);
+            fused_layer_gemm<NT, KB, NKB, ACTK>(lds, cd, c1, xt, hA, lane, h, A.c2, A.scale);
             fused_tile_stages<NT>(xt);
 #pragma unroll
             for (int q = 0; q < NR / 4; ++q) {
@@ -919,7 +986,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
-    if (A.acc) {
+    if (DHQ_DIGITS(ACTK) == 1 && A.acc) {
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
             dhq_v16i acc;
@@ -934,7 +1001,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
         }
     }
     dhq_v16f xt[NT];
-    fused_gemm_sine_hm<NT, KB, NKB, ACTK>(wA, reinterpret_cast<const float4 *>(lds + NT * KB * 1024), cd, A.c1, xt, hA, lane, h, A.c2);
+    fused_layer_gemm<NT, KB, NKB, ACTK>(lds, cd, A.c1, xt, hA, lane, h, A.c2);
     __syncthreads();
     fused_tile_stages<NT>(xt);
     fused_quantize<NT>(xt, cd, A.inv_next, qlo, qhi);
@@ -950,6 +1017,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 
 // ------------------------------------------------------------------------------- host code
 // `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
+// Two-sided models: whole-network kernels for the exact widths only.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
 {
     const int L = m->n_layers;
@@ -976,51 +1044,57 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     P->nf = nf;
     P->act_kind = m->act_kind;
     P->padded = padded;
+    P->digits = m->rot_out ? 2 : 1;
+    const int D = P->digits, halves = NT * NKB * D > 64 ? 2 : 1;
     int widest = 0;
     for (int l = 1; l < L; ++l) widest = m->dims[l] > widest ? m->dims[l] : widest;
     P->skip = NT - (widest + 31) / 32;
     memset(&P->args, 0, sizeof(P->args));
     P->args.scale = padded ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, dhq_hidden_act(m).c2)) : 1.f;
 
-    // block sizes: fragments [Mt][Kb] KiB + one KiB of biases
+    // block sizes: fragments [Mt][digit][Kb] KiB + one KiB of biases; hidden layers in `halves` such blocks
     std::vector<unsigned char> blob;
     for (int l = 0; l < L; ++l) {
         const dhq_layer &Ly = m->layer[l];
         const int Mt = (l == L - 1) ? 1 : NT;
         const int Kb = (l == 0) ? 1 : NKB;
-        const size_t off = blob.size();
-        const size_t bytes = (size_t)(Mt * Kb + 1) * 1024;
-        blob.resize(off + bytes, 0);
-        int8_t *frag = reinterpret_cast<int8_t *>(blob.data() + off);
-        const int8_t *wq = Ly.wq_host.data();  // M x Kp, rotated-index order
+        const int H = (l == 0 || l == L - 1) ? 1 : halves, th = Mt / H;  // blocks, tiles of a block
+        const size_t off = blob.size(), block = (size_t)(th * D * Kb + 1) * 1024;
+        blob.resize(off + H * block, 0);
+        // rotated-index order: the codes (M x Kp), or their product with H over the outputs (Mp x Kp), of which the outputs' rows
+        const int8_t *wq = Ly.wq_host.data();
+        const int32_t *u2 = Ly.u_host.data();
         for (int T = 0; T < Mt; ++T)
             for (int kb = 0; kb < Kb; ++kb)
                 for (int ln = 0; ln < 64; ++ln) {
                     const int row = 32 * T + (ln & 31), u = ln >> 5;
+                    if (row >= Ly.M) continue;
                     for (int jj = 0; jj < 16; ++jj) {
-                        int8_t val = 0;
-                        if (row < Ly.M) {
-                            if (l == 0) {
-                                // un-permuted: the input layer's codes sit in bytes 0..Kp-1 of half 0
-                                if (u == 0 && jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + jj];
-                            } else {
-                                const int k = hm_index(16 * kb + jj, u);
-                                val = wq[(size_t)row * Ly.Kp + k];
-                            }
+                        // the input layer's codes sit un-permuted in bytes 0..Kp-1 of half 0
+                        const int k = l == 0 ? (u == 0 && jj < Ly.Kp ? jj : -1) : hm_index(16 * kb + jj, u);
+                        if (k < 0) continue;
+                        int8_t *dst = reinterpret_cast<int8_t *>(blob.data() + off + (T / th) * block) +
+                                      ((size_t)(((T % th) * D) * Kb + kb) * 64 + ln) * 16 + jj;
+                        if (D == 1) {
+                            *dst = wq[(size_t)row * Ly.Kp + k];
+                        } else {
+                            const int32_t w = u2[(size_t)row * Ly.Kp + k], w0 = ((w + 128) & 255) - 128;
+                            dst[0] = (int8_t)((w - w0) / 256);
+                            dst[(size_t)Kb * 1024] = (int8_t)w0;
                         }
-                        frag[((size_t)(T * Kb + kb) * 64 + ln) * 16 + jj] = val;
                     }
                 }
-        // the bias block: [T][g][h][e], in revolutions for the sine layers
+        // the bias blocks: [T][g][h][e], in revolutions for the sine layers
         {
-            float *bias = reinterpret_cast<float *>(blob.data() + off + (size_t)Mt * Kb * 1024);
             const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
-            for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = src[f];
-            if (l < L - 1)
-                for (int f = Ly.M; f < nf; ++f) bias[bias_slot(f)] = dhq_pad_bias(m->act_kind, f);
+            const int F = (l == L - 1) ? Ly.M : nf;
+            for (int f = 0; f < F; ++f) {
+                float *bias = reinterpret_cast<float *>(blob.data() + off + (f / 32 / th) * block + block - 1024);
+                bias[bias_slot(f % (32 * th))] = f < Ly.M ? src[f] : dhq_pad_bias(m->act_kind, f);
+            }
         }
         P->args.layer[l].blob_off = (uint32_t)off;
-        P->args.layer[l].chunks = (uint32_t)(bytes / 1024);
+        P->args.layer[l].chunks = (uint32_t)(H * block / 1024);
     }
     P->blob_bytes = blob.size();
     if (hipMalloc((void **)&P->blob_dev, P->blob_bytes) != hipSuccess) {
@@ -1038,7 +1112,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     P->args.k0p = m->layer[0].Kp;
     P->args.m_out = m->dims[L];
     P->args.qmax = m->qmax_a;
-    P->lds_bytes = (size_t)2 * (NT * NKB + 1) * 1024;
+    P->lds_bytes = (size_t)2 * (NT * NKB * D / halves + 1) * 1024;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, m->device) != hipSuccess) {
         (void)hipFree(P->blob_dev);
@@ -1079,8 +1153,12 @@ int dhq_fused_update_scales(const dhq_model *m, dhq_fused_plan *P)
 //   width 128 alone   9.2 / 12.3 / 16    9.5 / 12.8 / 17   11.7 / 13.1 / 17   14.1 / 13.5 / 17
 //   width 128 rest   26.8 / 29.2 / 33   27.7 / 29.4 / 32   29.7 / 29.3 / 32   32.3 / 29.3 / 32
 // Width 64 (six layers) alone 9.2 against 11.6 for all waves of fewer workgroups; as a rest it gains nothing over the launch.
-static int fused_split_most(int nf, bool rest)
+// Two digits, split kernel / all waves of fewer workgroups, tiles per CU 2, 3, 4, 5, 6: width 256 alone 25/45 36/45 47/45, rest
+// 76/91 86/91 97/91; width 128 alone 9.9/20 13/20 15/20 19/20 22/20, rest 31/39 33/39 35/39 41/38; width 64 alone 9.8/11.3 at 5,
+// 11.5/11.3 at 6.
+static int fused_split_most(int nf, int digits, bool rest)
 {
+    if (digits == 2) return nf == 256 ? 3 : nf == 128 ? (rest ? 4 : 5) : (rest ? 0 : 5);
     return nf == 256 ? (rest ? 1 : 2) : nf == 128 ? (rest ? 2 : 3) : (rest ? 0 : 4);
 }
 // A call's rows go to full passes of dhq_fused_kernel (FUSED_WAVES wave tiles of 32 rows per CU); what is left of a last
@@ -1091,7 +1169,7 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
     const int64_t tiles = (a.n + 31) / 32, pass = (int64_t)P->n_cu * FUSED_WAVES, rest = tiles % pass;
     int64_t head = a.n;  // rows for the full passes
     if constexpr (NF >= 64) {
-        if (rest != 0 && rest <= (int64_t)fused_split_most(NF, tiles > pass) * P->n_cu) head = (tiles - rest) * 32;
+        if (rest != 0 && rest <= (int64_t)fused_split_most(NF, DHQ_DIGITS(ACTK), tiles > pass) * P->n_cu) head = (tiles - rest) * 32;
     }
     const int64_t n = a.n;
     if (head > 0) {
@@ -1104,12 +1182,14 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
         // ahead, 6.6 / 6.7, 16.0 / 16.2, 73.4 / 73.7.
         constexpr bool ROWS_MATTER = NF >= 64 || DHQ_KIND(ACTK) != DHQ_ACT_KIND_SINE;
         const int64_t head_tiles = (head + 31) / 32, last = head_tiles % pass;
-        const bool most = last > 4 * (int64_t)P->n_cu, in_a_row = ROWS_MATTER && (most || head_tiles > 11 * pass);
+        // (With two digits the dealt form does not fit the registers: 676 bytes of scratch.)
+        constexpr bool NO_DEALING = DHQ_DIGITS(ACTK) > 1;
+        const bool most = NO_DEALING || last > 4 * (int64_t)P->n_cu, in_a_row = ROWS_MATTER && (most || head_tiles > 11 * pass);
         const int64_t want = most ? (head_tiles + FUSED_WAVES - 1) / FUSED_WAVES : head_tiles;
         const unsigned grid = (unsigned)(want < P->n_cu ? want : P->n_cu);
-        auto kern = last == 0  ? dhq_fused_kernel<NF, ACTK, FUSED_WHOLE>
-                    : in_a_row ? dhq_fused_kernel<NF, ACTK, FUSED_IN_A_ROW>
-                               : dhq_fused_kernel<NF, ACTK, FUSED_DEALT>;
+        auto kern = last == 0                ? dhq_fused_kernel<NF, ACTK, FUSED_WHOLE>
+                    : in_a_row || NO_DEALING ? dhq_fused_kernel<NF, ACTK, FUSED_IN_A_ROW>
+                                             : dhq_fused_kernel<NF, ACTK, NO_DEALING ? FUSED_IN_A_ROW : FUSED_DEALT>;
         hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
         if (e != hipSuccess) return e;
         kern<<<grid, FUSED_THREADS, P->lds_bytes, st>>>(a);
@@ -1149,6 +1229,9 @@ static hipError_t fused_launch_t(const dhq_fused_plan *P, fused_args &a, int act
             return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | S>(P, a, st)
                                                     : fused_launch_act<NF, DHQ_ACT_KIND_SINE | S>(P, a, st);
         });
+    if (P->digits == 2)
+        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_TWO_DIGITS>(P, a, st)
+                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_TWO_DIGITS>(P, a, st);
     if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(P, a, st);
     return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET>(P, a, st)
                                             : fused_launch_act<NF, DHQ_ACT_KIND_SINE>(P, a, st);
@@ -1199,6 +1282,7 @@ static bool fused_pass_floats(const dhq_fused_plan *P, int64_t n)
     const int64_t tiles = (n + FUSED_TILE - 1) / FUSED_TILE, pass = (tiles - 1) / P->n_cu, in_last = tiles - pass * P->n_cu;
     const int w = P->nf == 32 ? 0 : P->nf == 64 ? 1 : P->nf == 128 ? 2 : 3;
     const int k = P->act_kind == DHQ_ACT_KIND_WAVELET ? 1 : P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX ? 2 : 0;
+    if (P->digits == 2) return n > 0;  // the layer below again would need its weights in LDS as well
     return n > 0 && pass < 3 && in_last * 256 <= (int64_t)most[w][k][pass] * P->n_cu;
 }
 
@@ -1211,7 +1295,7 @@ size_t dhq_fused_dynamic_rows(int64_t n) { return (size_t)((n + FUSED_TILE - 1) 
 size_t dhq_fused_dynamic_bytes(const dhq_fused_plan *P, int64_t n)
 {
     const int64_t last = (int64_t)3 * P->n_cu * FUSED_TILE;
-    int64_t floats = n < last ? n : last;
+    int64_t floats = n < last || P->digits == 2 ? n : last;
     while (floats > 0 && !fused_pass_floats(P, floats)) floats -= FUSED_TILE;
     const size_t codes = dhq_fused_dynamic_rows(n) * (size_t)P->nf;
     const size_t xhat = floats > 0 ? dhq_fused_dynamic_rows(floats) * (size_t)P->nf * sizeof(float) : 0;
@@ -1255,9 +1339,9 @@ static hipError_t fusedl_launch_layer(int layer, int n_layers, const fusedl_args
     const bool last = (layer == n_layers - 1);
     if (a.xout) {  // floats; the output layer has no activation
         if (layer == 0) return fusedl_launch_xhat<NF, 0, ACTK & 0xff>(a, grid, device, st);
-        if (last) return fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE>(a, grid, device, st);
+        if (last) return fusedl_launch_xhat<NF, 2, DHQ_ACT_KIND_NONE | (ACTK & DHQ_TWO_DIGITS)>(a, grid, device, st);
         if constexpr (!ONE_HIDDEN) return fusedl_launch_xhat<NF, 1, ACTK & 0xff>(a, grid, device, st);
-    } else {
+    } else if constexpr (DHQ_DIGITS(ACTK) == 1) {
         if (layer == 0) return fusedl_launch_t<NF, 0, false, ACTK>(a, grid, device, st);
         if (last && layer == 1) return fusedl_launch_t<NF, 2, true, ACTK>(a, grid, device, st);
         if constexpr (!ONE_HIDDEN) {
@@ -1277,6 +1361,9 @@ static hipError_t fusedl_launch_nf(const dhq_fused_plan *P, int layer, int L, co
             if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(layer, L, a, grid, P->device, st);
             return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | S>(layer, L, a, grid, P->device, st);
         });
+    if (P->digits == 2)
+        return P->act_kind == DHQ_ACT_KIND_WAVELET ? fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET | DHQ_TWO_DIGITS>(layer, L, a, grid, P->device, st)
+                                                   : fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE | DHQ_TWO_DIGITS>(layer, L, a, grid, P->device, st);
     if (P->act_kind == DHQ_ACT_KIND_WAVELET) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET>(layer, L, a, grid, P->device, st);
     if (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fusedl_launch_layer<NF, DHQ_ACT_KIND_WAVELET_COMPLEX>(layer, L, a, grid, P->device, st);
     return fusedl_launch_layer<NF, DHQ_ACT_KIND_SINE>(layer, L, a, grid, P->device, st);
@@ -1434,9 +1521,14 @@ static hipError_t fusedd_launch_t(const fusedd_args &a, unsigned grid, int devic
     return hipGetLastError();
 }
 template <int NF>
-static hipError_t fusedd_launch_nf(bool first, int act_kind, const fusedd_args &a, unsigned grid, int device, hipStream_t st)
+static hipError_t fusedd_launch_nf(bool first, int digits, int act_kind, const fusedd_args &a, unsigned grid, int device, hipStream_t st)
 {
     const bool wav = (act_kind == DHQ_ACT_KIND_WAVELET);
+    if (digits == 2) {
+        constexpr int W = DHQ_ACT_KIND_WAVELET | DHQ_TWO_DIGITS, N = DHQ_ACT_KIND_SINE | DHQ_TWO_DIGITS;
+        if (first) return wav ? fusedd_launch_t<NF, true, W>(a, grid, device, st) : fusedd_launch_t<NF, true, N>(a, grid, device, st);
+        return wav ? fusedd_launch_t<NF, false, W>(a, grid, device, st) : fusedd_launch_t<NF, false, N>(a, grid, device, st);
+    }
     if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX)
         return first ? fusedd_launch_t<NF, true, DHQ_ACT_KIND_WAVELET_COMPLEX>(a, grid, device, st)
                      : fusedd_launch_t<NF, false, DHQ_ACT_KIND_WAVELET_COMPLEX>(a, grid, device, st);
@@ -1444,12 +1536,15 @@ static hipError_t fusedd_launch_nf(bool first, int act_kind, const fusedd_args &
     return wav ? fusedd_launch_t<NF, false, DHQ_ACT_KIND_WAVELET>(a, grid, device, st) : fusedd_launch_t<NF, false, DHQ_ACT_KIND_SINE>(a, grid, device, st);
 }
 
-hipError_t dhq_fused_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
-                                  int32_t *acc, hipStream_t st)
+hipError_t dhq_fused_debug_launch(const dhq_model *m, const dhq_fused_plan *P, int layer, const int8_t *codes_in, int64_t n, float *xhat,
+                                  int8_t *codes_out, int32_t *acc, hipStream_t st)
 {
-    const dhq_fused_plan *P = m->fused;
     if (!P || layer < 0 || layer >= m->n_layers - 1) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
+    if (P->digits == 2 && acc) {  // the rotated accumulators, which the kernel never has
+        const hipError_t e = dhq_launch_gemm(m->layer[layer], codes_in, n, acc, nullptr, 0.0f, nullptr, dhq_act{DHQ_ACT_KIND_NONE, 0.f}, nullptr, st);
+        if (e != hipSuccess || (!xhat && !codes_out)) return e;
+    }
     fusedd_args a;
     memset(&a, 0, sizeof(a));
     a.codes_in = codes_in;
@@ -1466,10 +1561,10 @@ hipError_t dhq_fused_debug_launch(const dhq_model *m, int layer, const int8_t *c
     a.c2 = dhq_hidden_act(m).c2;
     const unsigned grid = (unsigned)((n + FUSED_TILE - 1) / FUSED_TILE);
     switch (P->nf) {
-        case 32: return fusedd_launch_nf<32>(layer == 0, m->act_kind, a, grid, P->device, st);
-        case 64: return fusedd_launch_nf<64>(layer == 0, m->act_kind, a, grid, P->device, st);
-        case 128: return fusedd_launch_nf<128>(layer == 0, m->act_kind, a, grid, P->device, st);
-        case 256: return fusedd_launch_nf<256>(layer == 0, m->act_kind, a, grid, P->device, st);
+        case 32: return fusedd_launch_nf<32>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
+        case 64: return fusedd_launch_nf<64>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
+        case 128: return fusedd_launch_nf<128>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
+        case 256: return fusedd_launch_nf<256>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -88,6 +88,9 @@ __device__ __forceinline__ void hm_remainders(float a0, float a1, unsigned hi, f
 #define DHQ_SPLIT_RN 16
 // Instances that leave the activations as they are, for the transform of the layer-by-layer kernels (fused_butterflies).
 #define DHQ_PLAIN 32
+// Instances for weights of two int8 digits, w = 256 w1 + w0 (two-sided rotation, dhq_fused.hip).
+#define DHQ_TWO_DIGITS 64
+#define DHQ_DIGITS(ACTK) (((ACTK) & DHQ_TWO_DIGITS) != 0 ? 2 : 1)
 // Instances for padded networks whose last tiles of 32 features are all padding: how many of them are left out.
 #define DHQ_SKIP(ACTK) ((ACTK) >> 8)
 #define DHQ_SKIPPING(tiles) ((tiles) << 8)

@@ -44,7 +44,6 @@ struct dhq_layer {
 struct dhq_fused_plan;  // defined in dhq_fused.hip
 struct dhq_wide_plan;   // defined in dhq_fused_wide.hip
 struct dhq_float_plan;  // defined in dhq_float.hip
-struct dhq_fused2_plan; // defined in dhq_fused_two_sided.hip
 struct dhq_pair_plan;   // defined in dhq_fused_pair.hip
 
 struct dhq_model {
@@ -88,7 +87,7 @@ struct dhq_model {
     dhq_pair_plan *pair2 = nullptr;
     int wide_kernel = 0;              // which of the two runs: 0 the default, 1 one wave, 2 two waves (dhq_select_wide_kernel)
     dhq_float_plan *flt = nullptr;    // floating-point activations (DHQ_W8A32 / DHQ_W32A32)
-    dhq_fused2_plan *fused2 = nullptr;  // two-sided variant, hidden width 32..256, fan-out <= 4
+    dhq_fused_plan *fused2 = nullptr;  // two-sided variant, hidden width 32..256
     int device = 0;
     unsigned char *scratch = nullptr;  // this device's copy of the library's fixed scratch buffer (dhq_forward_noalloc)
 };
@@ -241,29 +240,17 @@ static inline bool dhq_use_pair(const dhq_model *m)
     return m->wide_kernel == 2 || (m->wide_kernel == 0 && DHQ_WIDE_DEFAULT_TWO_WAVES);
 }
 
-// Two-sided variant, whole network in one kernel (defined in dhq_fused_two_sided.hip); same
-// contract as the dhq_fused_* functions.
-int dhq_fused2_create(const dhq_model *m, dhq_fused2_plan **plan);
-void dhq_fused2_destroy(dhq_fused2_plan *plan);
-int dhq_fused2_update_scales(const dhq_model *m, dhq_fused2_plan *plan);
-hipError_t dhq_fused2_launch(const dhq_fused2_plan *plan, const float *coords, int64_t n, float *out, hipStream_t st);
-size_t dhq_fused2_dynamic_rows(int64_t n);
-hipError_t dhq_fused2_dynamic_launch(const dhq_model *m, const float *coords, int64_t n, float *out, float *ws0, float *ws1,
-                                     float *partial, float *dyn, hipStream_t st);
-
 // Test hooks: layer `layer` (one that ends in an activation) of a whole-network kernel on the
 // caller's input codes (n x Kp int8, rotated-feature order).  Outputs, each n x hidden width,
 // row-major in rotated-feature order, any may be null: the un-normalised transform x^ of the
 // layer's output, the codes the next layer's quantizer makes of it, the layer's int32 accumulators
-// (two-sided: the rotated ones).
-hipError_t dhq_fused_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
-                                  int32_t *acc, hipStream_t st);
+// (two-sided: the rotated ones, from the layer-by-layer GEMM).
+hipError_t dhq_fused_debug_launch(const dhq_model *m, const dhq_fused_plan *plan, int layer, const int8_t *codes_in, int64_t n, float *xhat,
+                                  int8_t *codes_out, int32_t *acc, hipStream_t st);
 hipError_t dhq_wide_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
                                  int32_t *acc, hipStream_t st);
 hipError_t dhq_pair_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
                                  int32_t *acc, hipStream_t st);
-hipError_t dhq_fused2_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
-                                   int32_t *acc, hipStream_t st);
 
 // Floating-point activations (defined in dhq_float.hip): the plain network (sine, or the wavelet `act`) on the given fp32
 // weights W[l] (dims[l+1] x dims[l]) and biases: one kernel over all layers (dhq_float_launch) or one per layer
