@@ -697,6 +697,9 @@ static hipError_t run_layers(const dhq_model *m, const layer_ws &ws, const float
 
 static layer_ws chunk_ws(const dhq_model *m) { return layer_ws{{m->act0, m->act1}, m->codes, m->acc_ws}; }
 
+// The padded plan whose per-layer launches take this network: fan-ins of up to 4 (beyond, only the whole-network kernels read codes).
+static const dhq_fused_plan *per_layer_padded(const dhq_model *m) { return m->dims[0] <= 4 ? m->pad_fused : nullptr; }
+
 // The scales of all layers over the n rows.  One-sided networks up to 256 wide: dhq_fused_measure_launch.  The others in
 // chunks of the workspace, as follows.  A layer's scale needs the maximum over every row
 // before its first code can be written, so between two layers the network has to wait somewhere: as the codes of the layer
@@ -721,7 +724,7 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
         for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];
         return DHQ_OK;
     };
-    if (const dhq_fused_plan *P = m->fused ? m->fused : m->pad_fused) {
+    if (const dhq_fused_plan *P = m->fused ? m->fused : per_layer_padded(m)) {
         void *const buf[2] = {m->act0, m->act1};
         const hipError_t e = dhq_fused_measure_launch(m, P, coords_dev, n, buf, sizeof(float) * DHQ_CHUNK * m->max_dim, partial, params, st);
         if (e == hipSuccess) return finish();
@@ -803,7 +806,7 @@ struct dyn_sizes {
 // kernels of a padded network pass on, which is wider than its activations: dyn_act_bytes.)
 static size_t dyn_act_bytes(const dhq_model *m, int64_t n, size_t act)
 {
-    const size_t need = m->pad_fused ? dhq_fused_dynamic_bytes(m->pad_fused, n) : 0;
+    const size_t need = per_layer_padded(m) ? dhq_fused_dynamic_bytes(m->pad_fused, n) : 0;
     return need > act ? need : act;
 }
 static dyn_sizes dyn_buffer_sizes(const dhq_model *m, int64_t n)
@@ -897,7 +900,7 @@ static int check_dynamic_call(const dhq_model *m, int64_t n, uint32_t path, bool
     if (m->flt) return DHQ_EUNSUPPORTED;
     if (path == DHQ_FUSED && !dyn_fused_ok) return DHQ_EUNSUPPORTED;
     *per_layer_fused = (path == DHQ_FUSED && dyn_fused_ok) ||
-                       (path == DHQ_AUTO && (dyn_fused_ok || (m->pad_fused && m->dyn_sine_ok)) && m->dyn_pieces_ok);
+                       (path == DHQ_AUTO && (dyn_fused_ok || (per_layer_padded(m) && m->dyn_sine_ok)) && m->dyn_pieces_ok);
     return DHQ_OK;
 }
 
@@ -943,7 +946,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if ((path == DHQ_FUSED && fused_ok) || (path == DHQ_AUTO && fused_ok && m->pieces_ok)) {
         const hipError_t e = m->fused2 ? dhq_fused_launch(m, m->fused2, coords_dev, n, out_dev, st)
                              : m->fused ? dhq_fused_launch(m, m->fused, coords_dev, n, out_dev, st)
-                             : dhq_use_pair(m) ? dhq_pair_launch(m->pair, coords_dev, n, out_dev, st)
+                             : dhq_use_pair(m) ? dhq_pair_launch(m, m->pair, coords_dev, n, out_dev, st)
                                                : dhq_wide_launch(m->wide, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
@@ -953,7 +956,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     // 34, the one case the other way, for wavelets of 257 and more, which keep one path for the same bits at every size).
     if (path == DHQ_AUTO && m->fused_sine_ok && (m->pad_fused || m->pad_pair)) {
         const hipError_t e = m->pad_fused ? dhq_fused_launch(m, m->pad_fused, coords_dev, n, out_dev, st)
-                                          : dhq_pair_launch(m->pad_pair, coords_dev, n, out_dev, st);
+                                          : dhq_pair_launch(m, m->pad_pair, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
     // Two-sided at width 512: the whole-network kernel with the layer-by-layer path's bits (and its range of arguments).

@@ -70,6 +70,8 @@ struct fused_args {
     fused_layer_desc layer[DHQ_MAX_LAYERS];
     float scale;   // padded networks: what the activations are multiplied by before they are split (last: with the layers four
                    // bytes on in the argument block a one-pass forward took 1 % longer, 28.6 against 28.35 us)
+    int kb0;       // k blocks of the input layer
+    const int8_t *codes0;  // its codes, where the fan-in is above 4 (padded instances)
 };
 
 struct dhq_fused_plan {
@@ -451,6 +453,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     constexpr int NKB = NF / 32;  // k blocks of a hidden layer
     constexpr int BLK = fused_block_kib<NT, NKB, ACTK> * 1024;  // LDS bytes per weight buffer
     constexpr bool HALVES = fused_halves<NT, NKB, ACTK> > 1;
+    constexpr int INPUT_KB = (ACTK & DHQ_SPLIT_RN) != 0 && NKB > 1 ? 2 : 1;  // most k blocks of the input layer
 
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -478,7 +481,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
         dhq_v4i cd[NKB];  // activation codes: the B operands of the next GEMM
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
-        cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
+        if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) fused_load_codes(A.codes0, cl, A.k0p, h, cd);
+        else cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
 
         dhq_v16f xt[NT];
         for (int l = 0; l < L - 1; ++l) {
@@ -500,7 +504,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             } else {
                 fused_issue_copy(next, lds + (p ^ 1) * BLK, next_kib, wave, lane, FUSED_WAVES);
                 if (!active) {
-                } else if (l == 0)
+                } else if (INPUT_KB > 1 && l == 0 && A.kb0 == 2)
+                    fused_layer_gemm<NT, INPUT_KB, NKB, ACTK>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
+                else if (l == 0)
                     fused_layer_gemm<NT, 1, NKB, ACTK>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
                 else if constexpr (!HALVES)
                     fused_layer_gemm<NT, NKB, NKB, ACTK>(lds + p * BLK, cd, c1, xt, hA, lane, h, A.c2, A.scale);
@@ -562,24 +568,27 @@ __global__ __launch_bounds__(NF * 2, DHQ_DIGITS(ACTK) > 1 ? 2 : 4) void dhq_fuse
         float4 bias[4];
         {
             const unsigned char *blk = A.blob + A.layer[0].blob_off;
+            const int F = (ACTK & DHQ_SPLIT_RN) != 0 ? A.kb0 : D;  // fragments of a tile
 #pragma unroll
-            for (int d = 0; d < D; ++d) fr[d] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * D + d) * 64 + lane];
+            for (int d = 0; d < 2; ++d)
+                if (d < F) fr[d] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * F + d) * 64 + lane];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * D * 1024)[(wave * 4 + g) * 2 + h];
+            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * F * 1024)[(wave * 4 + g) * 2 + h];
         }
         dhq_v16i acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0;
         {
-            dhq_v4i cd = dhq_v4i{0, 0, 0, 0};
-            cd[0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
+            dhq_v4i cd[2] = {dhq_v4i{0, 0, 0, 0}, dhq_v4i{0, 0, 0, 0}};
+            if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) fused_load_codes(A.codes0, cl, A.k0p, h, cd);
+            else cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[0], cd[0], acc, 0, 0, 0);
+            if constexpr (D > 1) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                if (d > 0) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
-                }
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[d], cd, acc, 0, 0, 0);
+                for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[1], cd[0], acc, 0, 0, 0);
+            } else if ((ACTK & DHQ_SPLIT_RN) != 0 && A.kb0 == 2) {
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[1], cd[1], acc, 0, 0, 0);
             }
         }
         for (int l = 0; l < L - 1; ++l) {
@@ -1017,15 +1026,19 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 
 // ------------------------------------------------------------------------------- host code
 // `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
-// Two-sided models: whole-network kernels for the exact widths only.
+// Two-sided models: whole-network kernels for the exact widths only.  Fan-ins above 4: on the padded instances, exact widths too.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
 {
     const int L = m->n_layers;
     if (L < 2) return false;
-    if (m->dims[0] > 4 || m->dims[L] > 32) return false;
+    if (m->dims[L] > 32) return false;
     const int nf = dhq_padded_width(m->dims, L);
     if (nf != 32 && nf != 64 && nf != 128 && nf != 256) return false;
-    if (dhq_all_hidden_are(m->dims, L, nf) == padded) return false;
+    if (m->dims[0] > 4) {
+        if (!padded || m->layer[0].Kp > dhq_most_input_codes(nf / 32)) return false;
+    } else if (dhq_all_hidden_are(m->dims, L, nf) == padded) {
+        return false;
+    }
     if (padded && !dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2)) return false;
     *nf_out = nf;
     return true;
@@ -1057,7 +1070,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     for (int l = 0; l < L; ++l) {
         const dhq_layer &Ly = m->layer[l];
         const int Mt = (l == L - 1) ? 1 : NT;
-        const int Kb = (l == 0) ? 1 : NKB;
+        const int Kb = (l == 0) ? (Ly.Kp + 31) / 32 : NKB;
         const int H = (l == 0 || l == L - 1) ? 1 : halves, th = Mt / H;  // blocks, tiles of a block
         const size_t off = blob.size(), block = (size_t)(th * D * Kb + 1) * 1024;
         blob.resize(off + H * block, 0);
@@ -1070,9 +1083,9 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
                     const int row = 32 * T + (ln & 31), u = ln >> 5;
                     if (row >= Ly.M) continue;
                     for (int jj = 0; jj < 16; ++jj) {
-                        // the input layer's codes sit un-permuted in bytes 0..Kp-1 of half 0
-                        const int k = l == 0 ? (u == 0 && jj < Ly.Kp ? jj : -1) : hm_index(16 * kb + jj, u);
-                        if (k < 0) continue;
+                        // the input layer's codes sit in natural order, 16 to a lane half
+                        const int k = l == 0 ? 32 * kb + 16 * u + jj : hm_index(16 * kb + jj, u);
+                        if (k >= Ly.Kp) continue;
                         int8_t *dst = reinterpret_cast<int8_t *>(blob.data() + off + (T / th) * block) +
                                       ((size_t)(((T % th) * D) * Kb + kb) * 64 + ln) * 16 + jj;
                         if (D == 1) {
@@ -1110,6 +1123,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     P->args.n_layers = L;
     P->args.k0 = m->dims[0];
     P->args.k0p = m->layer[0].Kp;
+    P->args.kb0 = (m->layer[0].Kp + 31) / 32;
     P->args.m_out = m->dims[L];
     P->args.qmax = m->qmax_a;
     P->lds_bytes = (size_t)2 * (NT * NKB * D / halves + 1) * 1024;
@@ -1198,6 +1212,7 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
     }
     if constexpr (NF >= 64) {
         a.coords += head * a.k0;
+        if (a.codes0) a.codes0 += head * a.k0p;
         a.out += head * a.m_out;
         a.n = n - head;
         dhq_fused_split_kernel<NF, ACTK & 0xff><<<(unsigned)rest, NF * 2, 0, st>>>(a);
@@ -1240,19 +1255,36 @@ static hipError_t fused_launch_t(const dhq_fused_plan *P, fused_args &a, int act
 hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
-    if (n <= 0) return hipSuccess;
-    fused_args a = P->args;
-    a.coords = coords;
-    a.out = out;
-    a.n = n;
-    a.c2 = dhq_hidden_act(m).c2;
-    switch (P->nf) {
-        case 32: return fused_launch_t<32>(P, a, m->act_kind, st);
-        case 64: return fused_launch_t<64>(P, a, m->act_kind, st);
-        case 128: return fused_launch_t<128>(P, a, m->act_kind, st);
-        case 256: return fused_launch_t<256>(P, a, m->act_kind, st);
-        default: return hipErrorInvalidValue;
+    // A fan-in above 4: the rotation and quantizer of the input are the layer-by-layer path's kernel, whose codes the whole-network
+    // kernel reads (a launch more, n x Kp bytes of the model's workspace), a workspace full of rows at a time.  4 hidden layers,
+    // 65 536 rows, layer by layer / this way in us: 5 x 30 features 51.9 / 10.3, 12 x 90 (wavelet) 104 / 18.9, 40 x 60 69.9 / 16.4, 5 x 200 167 /
+    // 31.1, 40 x 200 147 / 35.1; 12 x 200 on 700 rows 69.9 / 12.1; 12 x 300 319 / 61.8, 5 x 512 345 / 89.5 (dhq_fused_pair.hip).
+    const bool wide_input = m->dims[0] > 4;
+    const int64_t pass = (int64_t)P->n_cu * FUSED_TILE, room = DHQ_CHUNK * (int64_t)m->max_kp / P->args.k0p;
+    const int64_t step = wide_input ? (room >= pass ? room / pass * pass : room) : n;
+    for (int64_t off = 0; off < n; off += step) {
+        fused_args a = P->args;
+        a.coords = coords + off * a.k0;
+        a.out = out + off * a.m_out;
+        a.n = n - off < step ? n - off : step;
+        a.c2 = dhq_hidden_act(m).c2;
+        if (wide_input) {
+            const dhq_layer &Ly = m->layer[0];
+            const hipError_t e = dhq_launch_wht_quant(a.coords, a.n, Ly.K, Ly.Kp, a.layer[0].inv_in, m->qmax_a, m->codes, nullptr, st);
+            if (e != hipSuccess) return e;
+            a.codes0 = m->codes;
+        }
+        hipError_t e;
+        switch (P->nf) {
+            case 32: e = fused_launch_t<32>(P, a, m->act_kind, st); break;
+            case 64: e = fused_launch_t<64>(P, a, m->act_kind, st); break;
+            case 128: e = fused_launch_t<128>(P, a, m->act_kind, st); break;
+            case 256: e = fused_launch_t<256>(P, a, m->act_kind, st); break;
+            default: return hipErrorInvalidValue;
+        }
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
 }
 
 // Whether the launches of a dynamic call on n rows pass floats (see the kernels).  The codes' time goes by whole passes of the

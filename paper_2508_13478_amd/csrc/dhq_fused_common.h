@@ -219,6 +219,27 @@ __device__ __forceinline__ void fused_h32_operand(int c, int h, dhq_v4i (&hA)[2]
     }
 }
 
+// Larger fan-ins (networks on the padded instances): the codes come from the layer-by-layer path's transform, n x k0p in natural
+// order, k0p = 8, 16, 32 or 64; lane half h takes positions 32 kb + 16 h .. + 15 of k block kb (what is beyond k0p stays zero).
+template <int NKB>
+__device__ __forceinline__ void fused_load_codes(const int8_t *__restrict__ codes, int64_t cl, int k0p, int h, dhq_v4i (&cd)[NKB])
+{
+    const int8_t *row = codes + cl * k0p;
+    if (k0p == 8) {
+        if (h == 0) {
+            const int2 v = *reinterpret_cast<const int2 *>(row);
+            cd[0][0] = v.x;
+            cd[0][1] = v.y;
+        }
+        return;
+    }
+#pragma unroll
+    for (int kb = 0; kb < (NKB < 2 ? NKB : 2); ++kb)
+        if (32 * kb + 16 * h < k0p) cd[kb] = *reinterpret_cast<const dhq_v4i *>(row + 32 * kb + 16 * h);
+}
+// The most positions of a rotated input the kernels take that way, by the k blocks a wave holds.
+static inline int dhq_most_input_codes(int k_blocks) { return k_blocks >= 2 ? 64 : 32; }
+
 // The coordinate vector of the input layer (fan-in <= 4): rotated and quantized into code dword 0.
 __device__ __forceinline__ int fused_input_codes(const float *__restrict__ coords, int64_t cl, int k0, int k0p, float inv, int qmax)
 {

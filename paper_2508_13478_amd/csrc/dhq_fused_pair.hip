@@ -72,6 +72,7 @@ struct pair_args {
     float c1[DHQ_MAX_LAYERS];
     float inv_in[DHQ_MAX_LAYERS];  // (behind split activations divided by `scale`)
     float scale;               // padded networks: what the activations are multiplied by before they are split
+    const int8_t *codes0;      // the input layer's codes, where the fan-in is above 4 (padded instances)
 };
 
 struct dhq_pair_plan {
@@ -596,7 +597,13 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair
             asm volatile("" : "+v"(tid));
             const int64_t ci = tile * PAIR_TILE + S.grp * 32 + (tid & 31);
             const int64_t cl = ci < A.n ? ci : A.n - 1;  // lanes past the end repeat the last coordinate and store nothing
-            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
+            if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) {
+                dhq_v4i first[1] = {dhq_v4i{0, 0, 0, 0}};
+                fused_load_codes(A.codes0, cl, A.k0p, (int)(tid >> 5) & 1, first);
+                cd[0] = first[0];
+            } else {
+                cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
+            }
         }
 
         dhq_v16f y[PAIR_NT];
@@ -1237,13 +1244,17 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel_debug(cons
 }
 
 // ------------------------------------------------------------------------------- host code
-// `padded`: hidden widths of 257 .. 511, or of both kinds.
+// `padded`: hidden widths of 257 .. 511, or of both kinds, and fan-ins of 5 .. 32.
 static bool pair_shape_ok(const dhq_model *m, bool padded)
 {
     const int L = m->n_layers;
     if (L < 2) return false;
-    if (m->dims[0] > 4 || m->dims[L] > 32) return false;
-    if (dhq_padded_width(m->dims, L) != 512 || dhq_all_hidden_are(m->dims, L, 512) == padded) return false;
+    if (m->dims[L] > 32 || dhq_padded_width(m->dims, L) != 512) return false;
+    if (m->dims[0] > 4) {
+        if (!padded || m->layer[0].Kp > 32) return false;
+    } else if (dhq_all_hidden_are(m->dims, L, 512) == padded) {
+        return false;
+    }
     return !padded || dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2);
 }
 
@@ -1266,7 +1277,7 @@ static void pair_pack_tile(const dhq_layer &Ly, bool padded, int T, int Kb, bool
                 int8_t val = 0;
                 if (row < Ly.M) {
                     if (first) {
-                        if (u == 0 && jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + jj];
+                        if (16 * u + jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + 16 * u + jj];
                     } else {
                         val = wq[(size_t)row * Ly.Kp + hm_index(16 * pair_tile(padded, kb) + jj, u)];
                     }
@@ -1381,23 +1392,35 @@ static void (*pair_kernel_of(const dhq_pair_plan *P))(const pair_args)
     }
 }
 
-hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
+hipError_t dhq_pair_launch(const dhq_model *m, const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
-    if (n <= 0) return hipSuccess;
-    pair_args a = P->args;
-    a.coords = coords;
-    a.out = out;
-    a.n = n;
-    const int64_t tiles = (n + PAIR_TILE - 1) / PAIR_TILE;
-    const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
     auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET)           ? pair_kernel_of<DHQ_ACT_KIND_WAVELET>(P)
                 : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? pair_kernel_of<DHQ_ACT_KIND_WAVELET_COMPLEX>(P)
                                                                 : pair_kernel_of<DHQ_ACT_KIND_SINE>(P);
     hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
-    kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
-    return hipGetLastError();
+    // a fan-in above 4: as in dhq_fused_launch
+    const bool wide_input = m->dims[0] > 4;
+    const int64_t step = wide_input ? DHQ_CHUNK * (int64_t)m->max_kp / P->args.k0p : n;
+    for (int64_t off = 0; off < n; off += step) {
+        pair_args a = P->args;
+        a.coords = coords + off * a.k0;
+        a.out = out + off * a.m_out;
+        a.n = n - off < step ? n - off : step;
+        if (wide_input) {
+            const dhq_layer &Ly = m->layer[0];
+            e = dhq_launch_wht_quant(a.coords, a.n, Ly.K, Ly.Kp, a.inv_in[0], m->qmax_a, m->codes, nullptr, st);
+            if (e != hipSuccess) return e;
+            a.codes0 = m->codes;
+        }
+        const int64_t tiles = (a.n + PAIR_TILE - 1) / PAIR_TILE;
+        const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
+        kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ---- the two-sided kernel ----
