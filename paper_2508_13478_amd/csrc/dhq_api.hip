@@ -10,6 +10,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -152,6 +153,39 @@ static void free_layer(dhq_layer &L)
     L.bias_dev = L.bias_rev_dev = nullptr;
 }
 
+// Pinned memory for what a calibration brings to the host: one block for the process, of which a model holds a slot while it
+// lives (an allocation of its own took 150 us of a model's creation).  Without one (more than 64 models, or no pinned memory) a model
+// copies into pageable memory.
+static struct {
+    std::mutex lock;
+    float *base = nullptr;
+    uint64_t taken = 0;
+} g_cal_slots;
+#define CAL_SLOT_FLOATS 64
+static_assert(3 * DHQ_MAX_LAYERS <= CAL_SLOT_FLOATS, "a slot holds three constants of every layer");
+static float *cal_slot_take()
+{
+    std::lock_guard<std::mutex> hold(g_cal_slots.lock);
+    if (!g_cal_slots.base &&
+        hipHostMalloc((void **)&g_cal_slots.base, sizeof(float) * CAL_SLOT_FLOATS * 64, hipHostMallocPortable) != hipSuccess) {
+        g_cal_slots.base = nullptr;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    for (int i = 0; i < 64; ++i)
+        if (!(g_cal_slots.taken >> i & 1)) {
+            g_cal_slots.taken |= (uint64_t)1 << i;
+            return g_cal_slots.base + i * CAL_SLOT_FLOATS;
+        }
+    return nullptr;
+}
+static void cal_slot_give(float *slot)
+{
+    if (!slot) return;
+    std::lock_guard<std::mutex> hold(g_cal_slots.lock);
+    g_cal_slots.taken &= ~((uint64_t)1 << ((slot - g_cal_slots.base) / CAL_SLOT_FLOATS));
+}
+
 extern "C" void dhq_free(dhq_model *m)
 {
     if (!m) return;
@@ -166,7 +200,7 @@ extern "C" void dhq_free(dhq_model *m)
     if (m->dyn_acc) (void)hipFree(m->dyn_acc);
     if (m->dyn_absmax) (void)hipFree(m->dyn_absmax);
     if (m->dyn_params) (void)hipFree(m->dyn_params);
-    if (m->cal_host) (void)hipHostFree(m->cal_host);
+    cal_slot_give(m->cal_host);
     dhq_fused_destroy(m->fused);
     dhq_fused_destroy(m->pad_fused);
     dhq_pair_destroy(m->pad_pair);
@@ -467,10 +501,7 @@ static int create_model(const dhq_net_desc *desc, uint32_t mode, int act_kind, f
             rc = DHQ_ENOMEM;
         if (rc == DHQ_OK && hipMalloc((void **)&m->dyn_absmax, sizeof(unsigned) * (DHQ_MAX_LAYERS + 2 * DHQ_ABSMAX_PARTIALS)) != hipSuccess) rc = DHQ_ENOMEM;
         if (rc == DHQ_OK && hipMalloc((void **)&m->dyn_params, sizeof(float) * 6 * DHQ_MAX_LAYERS) != hipSuccess) rc = DHQ_ENOMEM;
-        if (rc == DHQ_OK && hipHostMalloc((void **)&m->cal_host, sizeof(float) * 3 * DHQ_MAX_LAYERS) != hipSuccess) {
-            m->cal_host = nullptr;  // calibration copies into pageable memory then
-            (void)hipGetLastError();
-        }
+        if (rc == DHQ_OK) m->cal_host = cal_slot_take();
         // dhq_get_dynamic_scales before any dynamic forward reports zeros
         if (rc == DHQ_OK && hipMemset(m->dyn_params, 0, sizeof(float) * 6 * DHQ_MAX_LAYERS) != hipSuccess) rc = DHQ_EHIP;
     }

@@ -74,7 +74,7 @@ struct dhq_model {
     int64_t dyn_rows = 0;
     size_t dyn_act_bytes = 0;  // of dyn_act0 and of dyn_act1
     unsigned *dyn_absmax = nullptr;  // DHQ_MAX_LAYERS absmax words, then 2 x DHQ_ABSMAX_PARTIALS floats of scratch
-    float *cal_host = nullptr;       // pinned: what a calibration brings to the host
+    float *cal_host = nullptr;       // pinned slot (or null) for what a calibration brings to the host
     float *dyn_params = nullptr;     // DHQ_MAX_LAYERS x 3 of the last dynamic forward, as many of the last calibration
     dhq_fused_plan *fused = nullptr;  // hidden width 32..256; null if the shape has no such kernel
     dhq_wide_plan *wide = nullptr;    // hidden width 512, one wave per SIMD
