@@ -1077,26 +1077,31 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
         // rotated-index order: the codes (M x Kp), or their product with H over the outputs (Mp x Kp), of which the outputs' rows
         const int8_t *wq = Ly.wq_host.data();
         const int32_t *u2 = Ly.u_host.data();
+        // position of byte jj of lane half u in k block kb: the input layer's codes sit in natural order, 16 to a lane half
+        int pos[2 * 32 * 8];
+        for (int kb = 0; kb < Kb; ++kb)
+            for (int u = 0; u < 2; ++u)
+                for (int jj = 0; jj < 16; ++jj) pos[(kb * 2 + u) * 16 + jj] = l == 0 ? 32 * kb + 16 * u + jj : hm_index(16 * kb + jj, u);
         for (int T = 0; T < Mt; ++T)
-            for (int kb = 0; kb < Kb; ++kb)
-                for (int ln = 0; ln < 64; ++ln) {
-                    const int row = 32 * T + (ln & 31), u = ln >> 5;
-                    if (row >= Ly.M) continue;
-                    for (int jj = 0; jj < 16; ++jj) {
-                        // the input layer's codes sit in natural order, 16 to a lane half
-                        const int k = l == 0 ? 32 * kb + 16 * u + jj : hm_index(16 * kb + jj, u);
-                        if (k >= Ly.Kp) continue;
-                        int8_t *dst = reinterpret_cast<int8_t *>(blob.data() + off + (T / th) * block) +
-                                      ((size_t)(((T % th) * D) * Kb + kb) * 64 + ln) * 16 + jj;
-                        if (D == 1) {
-                            *dst = wq[(size_t)row * Ly.Kp + k];
-                        } else {
-                            const int32_t w = u2[(size_t)row * Ly.Kp + k], w0 = ((w + 128) & 255) - 128;
-                            dst[0] = (int8_t)((w - w0) / 256);
-                            dst[(size_t)Kb * 1024] = (int8_t)w0;
-                        }
+            for (int ln = 0; ln < 64; ++ln) {
+                const int row = 32 * T + (ln & 31), u = ln >> 5;
+                if (row >= Ly.M) continue;
+                int8_t *frag = reinterpret_cast<int8_t *>(blob.data() + off + (T / th) * block) + ((size_t)(T % th) * D * Kb * 64 + ln) * 16;
+                for (int kb = 0; kb < Kb; ++kb, frag += 1024) {
+                    const int *k = pos + (kb * 2 + u) * 16;
+                    if (D == 1) {
+                        for (int jj = 0; jj < 16; ++jj)
+                            if (k[jj] < Ly.Kp) frag[jj] = wq[(size_t)row * Ly.Kp + k[jj]];
+                    } else {
+                        for (int jj = 0; jj < 16; ++jj)
+                            if (k[jj] < Ly.Kp) {
+                                const int32_t w = u2[(size_t)row * Ly.Kp + k[jj]], w0 = ((w + 128) & 255) - 128;
+                                frag[jj] = (int8_t)((w - w0) / 256);
+                                frag[(size_t)Kb * 1024 + jj] = (int8_t)w0;
+                            }
                     }
                 }
+            }
         // the bias blocks: [T][g][h][e], in revolutions for the sine layers
         {
             const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
