@@ -739,6 +739,9 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
+            // ahead of the other workgroup's epilogue on the SIMD, which fills what the products leave (425 -> 412 us at 256, 1.93 ->
+            // 1.91 ms at 512, 101 -> 99 us at 128; raised for the epilogue instead: 433 -> 436)
+            __builtin_amdgcn_s_setprio(3);
             int s = 0;
             for (; s + D - 1 < ns; s += D) {
                 stage(std::integral_constant<int, 0>{}, s);
@@ -747,6 +750,7 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
             }
             if (s < ns) stage(std::integral_constant<int, 0>{}, s);
             if (D > 2 && s + 1 < ns) stage(std::integral_constant<int, 1>{}, s + 1);
+            __builtin_amdgcn_s_setprio(0);
         }
         // the output layer: tiles of 32 outputs x 32 coordinates dealt over the waves
         {
