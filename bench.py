@@ -31,9 +31,9 @@ VALU_LANE_RATE = 256 * 4 * 16 * 2.4e9  # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz 
 # unit were busy.  Valid only for the kernel sources they were taken with: the hash below is compared with
 # the current sources and the figures are dropped if they differ.
 TRAFFIC_SOURCES = ("dhq_fused.hip", "dhq_fused_pair.hip", "dhq_fused_common.h", "dhq_device.h")
-TRAFFIC_SHA256 = "8570e9cecb0022805fc45315bf6773cd1a515ea80e0cf042dd033fb396230567"
-TRAFFIC_BYTES = {"C2": 2589696 + 786432, "C5": 45164544 + 50331648}
-COUNTER_BUSY = {"C2": {"valu": 0.659, "mfma": 0.261}, "C4": {"valu": 0.901, "mfma": 0.375}, "C5": {"valu": 0.695, "mfma": 0.438}}
+TRAFFIC_SHA256 = "b38b6f3da310d2c1af9730bdd8ff7112557bb2730ee9a6ce073b615f0bebf66e"
+TRAFFIC_BYTES = {"C2": 2588672 + 786432, "C5": 45158400 + 50331648}
+COUNTER_BUSY = {"C2": {"valu": 0.642, "mfma": 0.255}, "C4": {"valu": 0.890, "mfma": 0.371}, "C5": {"valu": 0.689, "mfma": 0.434}}
 
 
 def kernel_sources_sha256():
