@@ -983,7 +983,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     }
     // Hidden widths that round up to a whole-network kernel's: the padded features cost less than the layer-by-layer path's
     // passes over memory (complex width 181 = 362 real features, 3 layers, 65 536 rows: 322 us layer by layer,
-    // 69 us padded; 4 x 200 features, 150 001 rows: 289 us less of 370; a single row 27 us against 28 at 3 x 257, and 32 against
+    // 55 us padded; 4 x 200 features, 150 001 rows: 289 us less of 370; a single row 27 us against 28 at 3 x 257, and 32 against
     // 34, the one case the other way, for wavelets of 257 and more, which keep one path for the same bits at every size).
     if (path == DHQ_AUTO && m->fused_sine_ok && (m->pad_fused || m->pad_pair)) {
         const hipError_t e = m->pad_fused ? dhq_fused_launch(m, m->pad_fused, coords_dev, n, out_dev, st)
