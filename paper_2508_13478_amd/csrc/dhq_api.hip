@@ -755,11 +755,20 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
         for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];
         return DHQ_OK;
     };
+    // Whether a layer's dequantized sums (at most 2^22 steps of c1) may be infinite, its activations NaN and the codes of those
+    // their signs, which each kernel leaves as its sums are ordered: infinite or huge coordinates.  The general path then decides.
+    auto unbounded = [&]() {
+        for (int l = 0; l < L; ++l)
+            if (!(fabs(dhq_c1_over_sa(m, l) * (double)m->layer[l].s_a) < 0x1p100)) return true;
+        return false;
+    };
     if (const dhq_fused_plan *P = m->fused ? m->fused : per_layer_padded(m)) {
         void *const buf[2] = {m->act0, m->act1};
         const hipError_t e = dhq_fused_measure_launch(m, P, coords_dev, n, buf, sizeof(float) * DHQ_CHUNK * m->max_dim, partial, params, st);
-        if (e == hipSuccess) return finish();
-        if (e != hipErrorInvalidValue) return DHQ_EHIP;
+        if (e == hipSuccess) {
+            const int rc = finish();
+            if (rc != DHQ_OK || !unbounded()) return rc;
+        } else if (e != hipErrorInvalidValue) return DHQ_EHIP;
     }
     if (dhq_launch_clear_words(m->dyn_absmax, L, st) != hipSuccess) return DHQ_EHIP;
     // the input of layer l for one chunk: the coordinates, or the output of the layer below from its codes

@@ -50,3 +50,19 @@ def test_rows_beyond_the_buffers_room(n):
     got, exp = _scales(m, x)
     assert np.array_equal(got, exp)
     m.close()
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), 3.0e38, 1.0e32, float("nan")])
+@pytest.mark.parametrize("dims,s0", [([2, 64, 64, 64, 3], None), ([2, 64, 64, 64, 3], 10.0), ([3, 256, 256, 256, 2], None), ([2, 200, 200, 1], 10.0)],
+                         ids=["64", "64_wavelet", "256", "200_wavelet"])
+def test_a_coordinate_beyond_the_range(dims, s0, value):
+    """A scale without a bound makes activations that are no numbers: their codes, and the scales behind them, are the general path's."""
+    import torch
+    W, b = synth.siren_init(dims, 30.0, 5)
+    m = dhq.Model(dims, 30.0, W, b, wavelet_s0=s0)
+    x = torch.rand((5003, dims[0]), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") * 2 - 1
+    x[2501, 0] = value
+    print(f"[calibrate] {dims} {s0} coordinate {value}", flush=True)
+    got, exp = _scales(m, x)
+    assert np.array_equal(got, exp, equal_nan=True)
+    m.close()
