@@ -410,8 +410,8 @@ __device__ __forceinline__ void pair_input_layer(pair_stream &S, int &cc, float 
 
 // What the partner parked for tile T, combined with the kept half of this wave's tile T:
 // zl = own + partner (tile T of the stage over tile-index bit 3), zh = own - partner (tile T + 8;
-// minus that for role 1, which owns T + 8).
-template <int T, int RT = PAIR_NT>
+// minus that for role 1, which owns T + 8).  PADDED: the two as they are, own in zl, the partner's in zh.
+template <int T, int RT = PAIR_NT, bool PADDED = false>
 __device__ __forceinline__ void pair_recv(const pair_stream &S, const dhq_v16f (&y)[PAIR_NT], float (&zl)[PAIR_NT][8],
                                           float (&zh)[PAIR_NT][8])
 {
@@ -421,8 +421,8 @@ __device__ __forceinline__ void pair_recv(const pair_stream &S, const dhq_v16f (
     const float p[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        zl[T][i] = y[T][i] + p[i];
-        zh[T][i] = y[T][i] - p[i];
+        zl[T][i] = PADDED ? y[T][i] : y[T][i] + p[i];
+        zh[T][i] = PADDED ? p[i] : y[T][i] - p[i];
     }
 }
 
@@ -445,47 +445,69 @@ __device__ __forceinline__ void pair_barrier()
 // The rest of the transform: on return zl[T][i] / zh[T][i] hold the un-normalised x^ of rotated features
 // 32 T + 8 (i / 4 + 2 role) + 4 h + i % 4 and 256 + the same (zh of role 1 with its sign flipped), and
 // the exchange area is free.
-template <bool AFTER_INPUT_LAYER, int RT = PAIR_NT>
+// PADDED networks, whose role r holds tiles 2 t + r (pair_tile): zl[t] is tile 2 t, zh[t] tile 2 t + 1.  The stages come in the same
+// order over the tile index, bits 3, 0, 1, 2, so that a value's sum does not depend on who holds it: bit 3 is then bit 2 of
+// t, and the stage between the two roles is the second.
+template <bool AFTER_INPUT_LAYER, int RT = PAIR_NT, bool PADDED = false>
 __device__ __forceinline__ void pair_transform(pair_stream &S, dhq_v16f (&y)[PAIR_NT], float (&zl)[PAIR_NT][8], float (&zh)[PAIR_NT][8])
 {
     // the halves sent during the GEMM phase are in place: a hidden layer's last sends (step 16 * 3 + 12 + 29) precede its last
     // chunk's barrier (step 16 (RT - 1) - PAIR_PF) from seven tiles on, the input layer has none
     if constexpr (AFTER_INPUT_LAYER || 16 * (RT - 1) - PAIR_PF <= 16 * (PAIR_EARLY - 1) + 12 + 29) pair_barrier();
-    pair_recv<0, RT>(S, y, zl, zh);
-    pair_recv<1, RT>(S, y, zl, zh);
-    pair_recv<2, RT>(S, y, zl, zh);
-    pair_recv<3, RT>(S, y, zl, zh);
+    pair_recv<0, RT, PADDED>(S, y, zl, zh);
+    pair_recv<1, RT, PADDED>(S, y, zl, zh);
+    pair_recv<2, RT, PADDED>(S, y, zl, zh);
+    pair_recv<3, RT, PADDED>(S, y, zl, zh);
     pair_barrier();  // everyone has read them: the slots are free again
     pair_send_late<4, RT>(S, y);
     pair_send_late<5, RT>(S, y);
     pair_send_late<6, RT>(S, y);
     pair_send_late<7, RT>(S, y);
     pair_barrier();
-    pair_recv<4, RT>(S, y, zl, zh);
-    pair_recv<5, RT>(S, y, zl, zh);
-    pair_recv<6, RT>(S, y, zl, zh);
-    pair_recv<7, RT>(S, y, zl, zh);
+    pair_recv<4, RT, PADDED>(S, y, zl, zh);
+    pair_recv<5, RT, PADDED>(S, y, zl, zh);
+    pair_recv<6, RT, PADDED>(S, y, zl, zh);
+    pair_recv<7, RT, PADDED>(S, y, zl, zh);
     pair_barrier();  // the exchange area is free for the codes
-    // stages over tile-index bits 0..2, within each half; before stage s tile t is still zero if all tiles that differ from it
-    // in lower bits only are padding
+    if constexpr (PADDED) {
+        // a padding tile t | 4 is zero, so that tiles t and t | 4 are then the same, and so are the sums that the next stages make of
+        // them, which the compiler takes once
+        static_assert(RT >= 4, "tiles 0 .. 3 are written");
 #pragma unroll
-    for (int s = 1; s < PAIR_NT; s <<= 1) {
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = zl[t][i], b = zh[t][i];
+                zl[t][i] = t + 4 < RT ? a + zl[t + 4][i] : a;
+                zh[t][i] = t + 4 < RT ? b + zh[t + 4][i] : b;
+                zl[t + 4][i] = t + 4 < RT ? a - zl[t + 4][i] : a;
+                zh[t + 4][i] = t + 4 < RT ? b - zh[t + 4][i] : b;
+            }
+        }
 #pragma unroll
         for (int t = 0; t < PAIR_NT; ++t) {
-            if ((t & s) == 0 && (t & -s) < RT) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = zl[t][i], b = zh[t][i];
+                zl[t][i] = a + b;
+                zh[t][i] = a - b;
+            }
+        }
+    }
+    // the other stages within each half
+#pragma unroll
+    for (int s = 1; s < (PADDED ? 4 : PAIR_NT); s <<= 1) {
+#pragma unroll
+        for (int t = 0; t < PAIR_NT; ++t) {
+            if ((t & s) == 0) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    if (((t | s) & -s) >= RT) {
-                        zl[t | s][i] = zl[t][i];
-                        zh[t | s][i] = zh[t][i];
-                        continue;
-                    }
                     const float a = zl[t][i], b = zl[t | s][i];
                     zl[t][i] = a + b;
                     zl[t | s][i] = a - b;
-                    const float c = zh[t][i], d = zh[t | s][i];
-                    zh[t][i] = c + d;
-                    zh[t | s][i] = c - d;
+                    const float a2 = zh[t][i], b2 = zh[t | s][i];
+                    zh[t][i] = a2 + b2;
+                    zh[t | s][i] = a2 - b2;
                 }
             }
         }
@@ -495,12 +517,12 @@ __device__ __forceinline__ void pair_transform(pair_stream &S, dhq_v16f (&y)[PAI
 // The rest of the transform and the next layer's quantizer.  On return the exchange area holds,
 // per coordinate group, the next layer's whole B operand ([k block][lane] x 16 B); it may be read
 // after the next barrier.  xrow (test hook): where this lane's coordinate keeps its row of x^.
-template <bool DUMP, bool AFTER_INPUT_LAYER = true, int RT = PAIR_NT>
+template <bool DUMP, bool AFTER_INPUT_LAYER = true, int RT = PAIR_NT, bool PADDED = false>
 __device__ __forceinline__ void pair_transform_quant(pair_stream &S, dhq_v16f (&y)[PAIR_NT], float inv, int qlo, int qhi, int h,
                                                      float *xrow = nullptr, int *crow = nullptr)
 {
     float zl[PAIR_NT][8], zh[PAIR_NT][8];
-    pair_transform<AFTER_INPUT_LAYER, RT>(S, y, zl, zh);
+    pair_transform<AFTER_INPUT_LAYER, RT, PADDED>(S, y, zl, zh);
     const float inv_hi = S.role ? -inv : inv;
     if constexpr (DUMP) {
         // rotated feature of zl[T][i]: 32 T + 8 (i / 4 + 2 role) + 4 h + i % 4; zh: tile T + 8, sign as above
@@ -565,6 +587,7 @@ __device__ __forceinline__ void pair_copy_now(const pair_stream &S, int j, int b
 template <int ACTK, int RT>
 __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair_args A)
 {
+    constexpr bool PADDED = (ACTK & DHQ_SPLIT_RN) != 0;
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
@@ -608,10 +631,10 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair
 
         dhq_v16f y[PAIR_NT];
         pair_input_layer<ACTK, RT>(S, cc, A.c1[0], cd, y, hA, h);
-        pair_transform_quant<false, true, RT>(S, y, A.inv_in[1], qlo, qhi, h);
+        pair_transform_quant<false, true, RT, PADDED>(S, y, A.inv_in[1], qlo, qhi, h);
         for (int l = 1; l < L - 1; ++l) {
             pair_hidden<ACTK, RT>(S, cc, l, A.c1[l], cd, y, hA, h);
-            pair_transform_quant<false, false, RT>(S, y, A.inv_in[l + 1], qlo, qhi, h);
+            pair_transform_quant<false, false, RT, PADDED>(S, y, A.inv_in[l + 1], qlo, qhi, h);
         }
 
         // output layer: one zero-padded M tile, no activation; role 0 computes it while all waves
@@ -1260,8 +1283,8 @@ static bool pair_shape_ok(const dhq_model *m, bool padded)
 
 // Which M tile wave role r computes as its t-th.  Exact networks: role 0 tiles 0..7, role 1 tiles 8..15, as described above.
 // In the padded ones the last tiles are padding, and role r has tiles 2 t + r, so that both have as much of it (RT = 5..8 tiles
-// each that are not; the exchange is then the stage over tile-index bit 0).  Complex width 181, twelve real tiles of sixteen,
-// 3 layers, 65 536 rows: 70.5 -> 57.5 us; 4 x 300 features 81.5 -> 60.1, 4 x 400 (wavelet) 96.7 -> 88.2.
+// each that are not; the exchange is then in front of the stage over tile-index bit 0).  Complex width 181, twelve real tiles of
+// sixteen, 3 layers, 65 536 rows: 70.5 -> 57.5 us; 4 x 300 features 81.5 -> 60.1, 4 x 400 (wavelet) 96.7 -> 88.2.
 static int pair_place(bool padded, int T) { return padded ? (T & 1) * 8 + (T >> 1) : T; }  // 8 r + t
 static int pair_tile(bool padded, int place) { return padded ? 2 * (place & 7) + (place >> 3) : place; }
 
