@@ -37,6 +37,9 @@
 // layers, 262 144 rows, butterflies / digits in us: width 32 25.9 / 22.0, 64 (wavelet) 55.9 / 48.6, 128 90.3 / 75.8, 256 197.7 /
 // 194.2 (there the digits' products load the matrix unit as much as the epilogue does the vector ALU); 1 000 rows of 256,
 // which the kernel for few rows now takes as well, 49.9 / 13.3.
+// Row r of a tile is the feature whose tile index has bits 0 and 2 of r exchanged, which is where the lane exchange of the
+// butterflies left it: the products with H_32 then add a tile's activations in the same order as behind them, and the values are
+// theirs bit for bit.
 #include <math.h>
 #include <string.h>
 
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
 
     dhq_v4i hA[2];
-    fused_h32_operand(c, h, hA);
+    fused_h32_operand<(ACTK & DHQ_TWO_DIGITS) != 0>(c, h, hA);
 
     int p = 0;  // LDS buffer holding the layer about to run
     if ((int64_t)blockIdx.x < n_tiles)
@@ -559,7 +562,7 @@ __global__ __launch_bounds__(NF * 2, DHQ_DIGITS(ACTK) > 1 ? 2 : 4) void dhq_fuse
     const int n_tiles = (int)((A.n + 31) / 32);  // fewer than a full pass of the kernel above has
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
     dhq_v4i hA[2];
-    fused_h32_operand(c, h, hA);
+    fused_h32_operand<(ACTK & DHQ_TWO_DIGITS) != 0>(c, h, hA);
     for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const int64_t ci = (int64_t)tile * 32 + c;
         const bool valid = ci < A.n;
@@ -797,7 +800,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_xhat_kernel(con
     const int64_t n_tiles = (A.n + FUSED_TILE - 1) / FUSED_TILE;
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
     dhq_v4i hA[2];
-    fused_h32_operand(c, h, hA);
+    fused_h32_operand<(ACTK & DHQ_TWO_DIGITS) != 0>(c, h, hA);
     fused_issue_copy(A.blk, lds, A.chunks, wave, lane, FUSED_WAVES);
     float inv, c1;
     fusedl_constants(A, red_in, wave, lane, inv, c1);
@@ -864,7 +867,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
     dhq_v4i hA[2];
-    fused_h32_operand(c, h, hA);
+    fused_h32_operand<(ACTK & DHQ_TWO_DIGITS) != 0>(c, h, hA);
     fused_issue_copy(A.blk, lds, A.chunks, wave, lane, FUSED_WAVES);
     const unsigned char *lds_below = lds + (MT * KB + 1) * 1024;
     float inv_below = 0.f, c1_below = 0.f;
@@ -971,7 +974,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
     const int c = lane & 31, h = lane >> 5;
     const int qlo = DHQ_MAGIC_I - A.qmax, qhi = DHQ_MAGIC_I + A.qmax;
     dhq_v4i hA[2];
-    fused_h32_operand(c, h, hA);
+    fused_h32_operand<(ACTK & DHQ_TWO_DIGITS) != 0>(c, h, hA);
     fused_issue_copy(A.blk, lds, A.chunks, wave, lane, FUSED_WAVES);
     const int64_t ci = (int64_t)blockIdx.x * FUSED_TILE + wave * 32 + c;
     const bool valid = ci < A.n;
@@ -1025,6 +1028,9 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 }
 
 // ------------------------------------------------------------------------------- host code
+// The feature of row r of a two-digit layer (its own inverse).
+static int two_digit_feature(int r) { return (r & ~5) | (r & 1) << 2 | (r >> 2 & 1); }
+
 // `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
 // Two-sided models: whole-network kernels for the exact widths only.  Fan-ins above 4: on the padded instances, exact widths too.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
@@ -1084,7 +1090,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
                 for (int jj = 0; jj < 16; ++jj) pos[(kb * 2 + u) * 16 + jj] = l == 0 ? 32 * kb + 16 * u + jj : hm_index(16 * kb + jj, u);
         for (int T = 0; T < Mt; ++T)
             for (int ln = 0; ln < 64; ++ln) {
-                const int row = 32 * T + (ln & 31), u = ln >> 5;
+                const int u = ln >> 5, row = 32 * T + (D == 2 && l < L - 1 ? two_digit_feature(ln & 31) : ln & 31);
                 if (row >= Ly.M) continue;
                 int8_t *frag = reinterpret_cast<int8_t *>(blob.data() + off + (T / th) * block) + ((size_t)(T % th) * D * Kb * 64 + ln) * 16;
                 for (int kb = 0; kb < Kb; ++kb, frag += 1024) {
@@ -1106,9 +1112,10 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
         {
             const std::vector<float> &src = (l == L - 1) ? Ly.bias_host : Ly.bias_rev_host;
             const int F = (l == L - 1) ? Ly.M : nf;
-            for (int f = 0; f < F; ++f) {
-                float *bias = reinterpret_cast<float *>(blob.data() + off + (f / 32 / th) * block + block - 1024);
-                bias[bias_slot(f % (32 * th))] = f < Ly.M ? src[f] : dhq_pad_bias(m->act_kind, f);
+            for (int r = 0; r < F; ++r) {
+                const int f = D == 2 && l < L - 1 ? two_digit_feature(r) : r;
+                float *bias = reinterpret_cast<float *>(blob.data() + off + (r / 32 / th) * block + block - 1024);
+                bias[bias_slot(r % (32 * th))] = f < Ly.M ? src[f] : dhq_pad_bias(m->act_kind, f);
             }
         }
         P->args.layer[l].blob_off = (uint32_t)off;

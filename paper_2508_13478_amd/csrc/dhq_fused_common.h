@@ -205,7 +205,8 @@ __device__ __forceinline__ unsigned fused_quant4(float v0, float v1, float v2, f
 
 // A operand of the H_32 products: a lane supplies row c of H_32 at the eight contraction slots
 // 8 h + j of block kk, which stand for tile row 8 (v / 4) + 4 h + v % 4 with v = 8 kk + j (the row
-// lane half h holds in accumulator v), as binary16 +-1.
+// lane half h holds in accumulator v), as binary16 +-1.  TWO_DIGITS: for the tile rows of the two-digit layers (dhq_fused.hip).
+template <bool TWO_DIGITS = false>
 __device__ __forceinline__ void fused_h32_operand(int c, int h, dhq_v4i (&hA)[2])
 {
 #pragma unroll
@@ -213,8 +214,8 @@ __device__ __forceinline__ void fused_h32_operand(int c, int h, dhq_v4i (&hA)[2]
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             const int v = 8 * kk + 2 * d;  // accumulators v and v + 1: consecutive tile rows
-            const int row = 8 * (v >> 2) + 4 * h + (v & 3);
-            hA[kk][d] = (int)hm_h32_pair(c, row, row + 1);
+            const int row = 8 * (v >> 2) + 4 * h + (v & 3), swapped = 8 * (v >> 2) + (v & 2) + h;
+            hA[kk][d] = (int)(TWO_DIGITS ? hm_h32_pair(c, swapped, swapped + 4) : hm_h32_pair(c, row, row + 1));
         }
     }
 }

@@ -19,6 +19,26 @@ PADDED = [
     ("in complex 2x150x150x3", "auto", "21c2b36e33da30f9"),
 ]
 
+# both sides rotated (the un-rotation as integer butterflies)
+TWO_SIDED = [
+    ("both sine 2x32x32x32x3", "auto", "6eb4212a6e9038e6"),
+    ("both sine 2x32x32x32x3", "dyn", "03d032e767e16821"),
+    ("both wavelet 2x32x32x32x3", "auto", "a76277c6d07f11e5"),
+    ("both wavelet 2x32x32x32x3", "dyn", "a862b5dff340f1a2"),
+    ("both sine 2x64x64x64x3", "auto", "a1b894b88fb3cbd6"),
+    ("both sine 2x64x64x64x3", "dyn", "581c3bb2658b034b"),
+    ("both wavelet 2x64x64x64x3", "auto", "5200c4b1c9d2a815"),
+    ("both wavelet 2x64x64x64x3", "dyn", "b98db785a9a75d0a"),
+    ("both sine 2x128x128x128x3", "auto", "1df235189f36de92"),
+    ("both sine 2x128x128x128x3", "dyn", "3c11f1cfa807c942"),
+    ("both wavelet 2x128x128x128x3", "auto", "d399539f2d5eac5d"),
+    ("both wavelet 2x128x128x128x3", "dyn", "bd22c42e7395522c"),
+    ("both sine 2x256x256x256x3", "auto", "036e92c9c0b17707"),
+    ("both sine 2x256x256x256x3", "dyn", "140522b41dc497ba"),
+    ("both wavelet 2x256x256x256x3", "auto", "b12cfc6e4a73f57e"),
+    ("both wavelet 2x256x256x256x3", "dyn", "e7119cdabd6b81a2"),
+]
+
 
 def _points(n, k):
     """Points of [-1, 1)^k from integers alone."""
@@ -50,4 +70,9 @@ def _digest(network, path):
 
 @pytest.mark.parametrize("network,path,digest", PADDED, ids=lambda v: v.replace(" ", "_"))
 def test_padded_networks(network, path, digest):
+    assert _digest(network, path) == digest
+
+
+@pytest.mark.parametrize("network,path,digest", TWO_SIDED, ids=lambda v: v.replace(" ", "_"))
+def test_two_sided_networks(network, path, digest):
     assert _digest(network, path) == digest
