@@ -986,7 +986,7 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     if ((path == DHQ_FUSED && fused_ok) || (path == DHQ_AUTO && fused_ok && m->pieces_ok)) {
         const hipError_t e = m->fused2 ? dhq_fused_launch(m, m->fused2, coords_dev, n, out_dev, st)
                              : m->fused ? dhq_fused_launch(m, m->fused, coords_dev, n, out_dev, st)
-                             : dhq_use_pair(m) ? dhq_pair_launch(m, m->pair, coords_dev, n, out_dev, st)
+                             : dhq_use_pair(m) ? dhq_pair_launch(m->pair, coords_dev, n, out_dev, st)
                                                : dhq_wide_launch(m->wide, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
@@ -996,11 +996,11 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
     // 34, the one case the other way, for wavelets of 257 and more, which keep one path for the same bits at every size).
     if (path == DHQ_AUTO && m->fused_sine_ok && (m->pad_fused || m->pad_pair)) {
         const hipError_t e = m->pad_fused ? dhq_fused_launch(m, m->pad_fused, coords_dev, n, out_dev, st)
-                                          : dhq_pair_launch(m, m->pad_pair, coords_dev, n, out_dev, st);
+                                          : dhq_pair_launch(m->pad_pair, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
     // Two-sided at width 512: the whole-network kernel with the layer-by-layer path's bits (and its range of arguments).
-    if (path == DHQ_AUTO && m->pair2) return dhq_pair2_launch(m->pair2, coords_dev, n, out_dev, st) == hipSuccess ? DHQ_OK : DHQ_EHIP;
+    if (path == DHQ_AUTO && m->pair2) return dhq_pair2_launch(m, m->pair2, coords_dev, n, out_dev, st) == hipSuccess ? DHQ_OK : DHQ_EHIP;
     const int K0 = m->dims[0], Mo = m->dims[m->n_layers];
     for (int64_t off = 0; off < n; off += DHQ_CHUNK) {
         const int64_t rows = (n - off) < DHQ_CHUNK ? (n - off) : DHQ_CHUNK;

@@ -74,7 +74,7 @@ struct fused_args {
     float scale;   // padded networks: what the activations are multiplied by before they are split (last: with the layers four
                    // bytes on in the argument block a one-pass forward took 1 % longer, 28.6 against 28.35 us)
     int kb0;       // k blocks of the input layer
-    const int8_t *codes0;  // its codes, where the fan-in is above 4 (padded instances)
+    const int8_t *codes0;  // its codes, where the fan-in is above 4 (DHQ_CODES_IN)
 };
 
 struct dhq_fused_plan {
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
     constexpr int NKB = NF / 32;  // k blocks of a hidden layer
     constexpr int BLK = fused_block_kib<NT, NKB, ACTK> * 1024;  // LDS bytes per weight buffer
     constexpr bool HALVES = fused_halves<NT, NKB, ACTK> > 1;
-    constexpr int INPUT_KB = (ACTK & DHQ_SPLIT_RN) != 0 && NKB > 1 ? 2 : 1;  // most k blocks of the input layer
+    constexpr int INPUT_KB = (ACTK & DHQ_CODES_IN) != 0 && NKB > 1 ? 2 : 1;  // most k blocks of the input layer
 
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
         dhq_v4i cd[NKB];  // activation codes: the B operands of the next GEMM
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) cd[kb] = dhq_v4i{0, 0, 0, 0};
-        if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) fused_load_codes(A.codes0, cl, A.k0p, h, cd);
+        if constexpr ((ACTK & DHQ_CODES_IN) != 0) fused_load_codes(A.codes0, cl, A.k0p, h, cd);
         else cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
 
         dhq_v16f xt[NT];
@@ -519,8 +519,10 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_kernel(const fused_ar
             // other; keep the phases aligned across the workgroup.
             __syncthreads();
             if (active) {
-                fused_tile_stages<NT, DHQ_SKIP(ACTK)>(xt);
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_butterflies<NT, DHQ_SKIP(ACTK)>(xt);
+                else fused_tile_stages<NT, DHQ_SKIP(ACTK)>(xt);
                 fused_quantize<NT>(xt, cd, A.layer[l + 1].inv_in, qlo, qhi);
+                if constexpr ((ACTK & DHQ_PLAIN) != 0) fused_plain_codes<NT>(cd);
             }
             p ^= 1;
         }
@@ -571,27 +573,21 @@ __global__ __launch_bounds__(NF * 2, DHQ_DIGITS(ACTK) > 1 ? 2 : 4) void dhq_fuse
         float4 bias[4];
         {
             const unsigned char *blk = A.blob + A.layer[0].blob_off;
-            const int F = (ACTK & DHQ_SPLIT_RN) != 0 ? A.kb0 : D;  // fragments of a tile
 #pragma unroll
-            for (int d = 0; d < 2; ++d)
-                if (d < F) fr[d] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * F + d) * 64 + lane];
+            for (int d = 0; d < D; ++d) fr[d] = reinterpret_cast<const dhq_v4i *>(blk)[(wave * D + d) * 64 + lane];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * F * 1024)[(wave * 4 + g) * 2 + h];
+            for (int g = 0; g < 4; ++g) bias[g] = reinterpret_cast<const float4 *>(blk + NT * D * 1024)[(wave * 4 + g) * 2 + h];
         }
         dhq_v16i acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0;
         {
-            dhq_v4i cd[2] = {dhq_v4i{0, 0, 0, 0}, dhq_v4i{0, 0, 0, 0}};
-            if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) fused_load_codes(A.codes0, cl, A.k0p, h, cd);
-            else cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax);
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[0], cd[0], acc, 0, 0, 0);
+            const dhq_v4i cd = {fused_input_codes(A.coords, cl, A.k0, A.k0p, A.layer[0].inv_in, A.qmax), 0, 0, 0};
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[0], cd, acc, 0, 0, 0);
             if constexpr (D > 1) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[1], cd[0], acc, 0, 0, 0);
-            } else if ((ACTK & DHQ_SPLIT_RN) != 0 && A.kb0 == 2) {
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[1], cd[1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[1], cd, acc, 0, 0, 0);
             }
         }
         for (int l = 0; l < L - 1; ++l) {
@@ -1032,7 +1028,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
 static int two_digit_feature(int r) { return (r & ~5) | (r & 1) << 2 | (r >> 2 & 1); }
 
 // `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
-// Two-sided models: whole-network kernels for the exact widths only.  Fan-ins above 4: on the padded instances, exact widths too.
+// Two-sided models: whole-network kernels for the exact widths only.  Fan-ins above 4: with the padded plans, exact widths too.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
 {
     const int L = m->n_layers;
@@ -1069,7 +1065,7 @@ int dhq_fused_create(const dhq_model *m, bool padded, dhq_fused_plan **plan_out)
     for (int l = 1; l < L; ++l) widest = m->dims[l] > widest ? m->dims[l] : widest;
     P->skip = NT - (widest + 31) / 32;
     memset(&P->args, 0, sizeof(P->args));
-    P->args.scale = padded ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, dhq_hidden_act(m).c2)) : 1.f;
+    P->args.scale = padded && m->dims[0] <= 4 ? ldexpf(1.f, dhq_piece_scale_log2(m->act_kind, dhq_hidden_act(m).c2)) : 1.f;
 
     // block sizes: fragments [Mt][digit][Kb] KiB + one KiB of biases; hidden layers in `halves` such blocks
     std::vector<unsigned char> blob;
@@ -1194,7 +1190,8 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
 {
     const int64_t tiles = (a.n + 31) / 32, pass = (int64_t)P->n_cu * FUSED_WAVES, rest = tiles % pass;
     int64_t head = a.n;  // rows for the full passes
-    if constexpr (NF >= 64) {
+    constexpr bool SPLIT = NF >= 64 && (ACTK & DHQ_PLAIN) == 0;
+    if constexpr (SPLIT) {
         if (rest != 0 && rest <= (int64_t)fused_split_most(NF, DHQ_DIGITS(ACTK), tiles > pass) * P->n_cu) head = (tiles - rest) * 32;
     }
     const int64_t n = a.n;
@@ -1222,9 +1219,8 @@ static hipError_t fused_launch_act(const dhq_fused_plan *P, fused_args &a, hipSt
         e = hipGetLastError();
         if (e != hipSuccess || head == n) return e;
     }
-    if constexpr (NF >= 64) {
+    if constexpr (SPLIT) {
         a.coords += head * a.k0;
-        if (a.codes0) a.codes0 += head * a.k0p;
         a.out += head * a.m_out;
         a.n = n - head;
         dhq_fused_split_kernel<NF, ACTK & 0xff><<<(unsigned)rest, NF * 2, 0, st>>>(a);
@@ -1249,13 +1245,18 @@ static hipError_t fused_with_skip(int skip, F f)
 template <int NF>
 static hipError_t fused_launch_t(const dhq_fused_plan *P, fused_args &a, int act_kind, hipStream_t st)
 {
-    if (P->padded)
+    auto padded = [&](auto flags) {
+        constexpr int S = decltype(flags)::value;
+        if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(P, a, st);
+        return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | S>(P, a, st)
+                                                : fused_launch_act<NF, DHQ_ACT_KIND_SINE | S>(P, a, st);
+    };
+    if (a.codes0)
         return fused_with_skip<NF>(P->skip, [&](auto skip) {
-            constexpr int S = DHQ_SPLIT_RN | decltype(skip)::value;
-            if (act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) return fused_launch_act<NF, DHQ_ACT_KIND_WAVELET_COMPLEX | S>(P, a, st);
-            return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | S>(P, a, st)
-                                                    : fused_launch_act<NF, DHQ_ACT_KIND_SINE | S>(P, a, st);
+            return padded(std::integral_constant<int, DHQ_PLAIN | DHQ_CODES_IN | decltype(skip)::value>{});
         });
+    if (P->padded)
+        return fused_with_skip<NF>(P->skip, [&](auto skip) { return padded(std::integral_constant<int, DHQ_SPLIT_RN | decltype(skip)::value>{}); });
     if (P->digits == 2)
         return act_kind == DHQ_ACT_KIND_WAVELET ? fused_launch_act<NF, DHQ_ACT_KIND_WAVELET | DHQ_TWO_DIGITS>(P, a, st)
                                                 : fused_launch_act<NF, DHQ_ACT_KIND_SINE | DHQ_TWO_DIGITS>(P, a, st);
@@ -1268,9 +1269,10 @@ hipError_t dhq_fused_launch(const dhq_model *m, const dhq_fused_plan *P, const f
 {
     if (!P) return hipErrorInvalidValue;
     // A fan-in above 4: the rotation and quantizer of the input are the layer-by-layer path's kernel, whose codes the whole-network
-    // kernel reads (a launch more, n x Kp bytes of the model's workspace), a workspace full of rows at a time.  4 hidden layers,
-    // 65 536 rows, layer by layer / this way in us: 5 x 30 features 51.9 / 10.3, 12 x 90 (wavelet) 104 / 18.9, 40 x 60 69.9 / 16.4, 5 x 200 167 /
-    // 31.1, 40 x 200 147 / 35.1; 12 x 200 on 700 rows 69.9 / 12.1; 12 x 300 319 / 61.8, 5 x 512 345 / 89.5 (dhq_fused_pair.hip).
+    // kernel reads (a launch more, n x Kp bytes of the model's workspace), a workspace full of rows at a time.  Its transform is
+    // the calibration's (DHQ_PLAIN), so that the values are the layer-by-layer path's bit for bit.  4 hidden layers, 65 536 rows,
+    // layer by layer / this way in us: 5 x 30 features 52.7 / 9.7, 12 x 90 (wavelet) 105 / 23.8, 40 x 60 69.1 / 18.3, 5 x 200 174 / 41.8,
+    // 40 x 200 153 / 47.0; 12 x 200 on 700 rows 70.3 / 23.9; 12 x 300 325 / 131, 5 x 512 349 / 132 (dhq_pair2_launch).
     const bool wide_input = m->dims[0] > 4;
     const int64_t pass = (int64_t)P->n_cu * FUSED_TILE, room = DHQ_CHUNK * (int64_t)m->max_kp / P->args.k0p;
     const int64_t step = wide_input ? (room >= pass ? room / pass * pass : room) : n;

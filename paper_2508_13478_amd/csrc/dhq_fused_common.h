@@ -91,6 +91,8 @@ __device__ __forceinline__ void hm_remainders(float a0, float a1, unsigned hi, f
 // Instances for weights of two int8 digits, w = 256 w1 + w0 (two-sided rotation, dhq_fused.hip).
 #define DHQ_TWO_DIGITS 64
 #define DHQ_DIGITS(ACTK) (((ACTK) & DHQ_TWO_DIGITS) != 0 ? 2 : 1)
+// Instances that read the input layer's codes (fan-ins above 4).
+#define DHQ_CODES_IN 128
 // Instances for padded networks whose last tiles of 32 features are all padding: how many of them are left out.
 #define DHQ_SKIP(ACTK) ((ACTK) >> 8)
 #define DHQ_SKIPPING(tiles) ((tiles) << 8)
@@ -220,7 +222,7 @@ __device__ __forceinline__ void fused_h32_operand(int c, int h, dhq_v4i (&hA)[2]
     }
 }
 
-// Larger fan-ins (networks on the padded instances): the codes come from the layer-by-layer path's transform, n x k0p in natural
+// Larger fan-ins (instances with DHQ_CODES_IN): the codes come from the layer-by-layer path's transform, n x k0p in natural
 // order, k0p = 8, 16, 32 or 64; lane half h takes positions 32 kb + 16 h .. + 15 of k block kb (what is beyond k0p stays zero).
 template <int NKB>
 __device__ __forceinline__ void fused_load_codes(const int8_t *__restrict__ codes, int64_t cl, int k0p, int h, dhq_v4i (&cd)[NKB])

@@ -72,7 +72,7 @@ struct pair_args {
     float c1[DHQ_MAX_LAYERS];
     float inv_in[DHQ_MAX_LAYERS];  // (behind split activations divided by `scale`)
     float scale;               // padded networks: what the activations are multiplied by before they are split
-    const int8_t *codes0;      // the input layer's codes, where the fan-in is above 4 (padded instances)
+    const int8_t *codes0;      // the input layer's codes, where the fan-in is above 4 (DHQ_CODES_IN)
 };
 
 struct dhq_pair_plan {
@@ -620,13 +620,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel(const pair
             asm volatile("" : "+v"(tid));
             const int64_t ci = tile * PAIR_TILE + S.grp * 32 + (tid & 31);
             const int64_t cl = ci < A.n ? ci : A.n - 1;  // lanes past the end repeat the last coordinate and store nothing
-            if ((ACTK & DHQ_SPLIT_RN) != 0 && A.codes0) {
-                dhq_v4i first[1] = {dhq_v4i{0, 0, 0, 0}};
-                fused_load_codes(A.codes0, cl, A.k0p, (int)(tid >> 5) & 1, first);
-                cd[0] = first[0];
-            } else {
-                cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
-            }
+            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
         }
 
         dhq_v16f y[PAIR_NT];
@@ -780,7 +774,7 @@ __device__ __forceinline__ void pair2_step(pair2_ctx<ACTK> &C)
     if constexpr (E >= 0 && E < NM) {
         constexpr int td = E / 32, v = (E % 32) / 2;
         if constexpr ((E & 1) == 0) C.ey = __builtin_fmaf((float)C.acc[td & 1][v], C.c1, pair_comp(C.bq[(E / 8) & 1], v & 3));
-        else C.y[td][v] = dhq_activate_rev_any(C.ey, dhq_act{ACTK, C.c2});
+        else C.y[td][v] = dhq_activate_rev_any(C.ey, dhq_act{DHQ_KIND(ACTK), C.c2});
     }
     if constexpr (E + 8 >= 0 && (E + 8) % 8 == 0 && E + 8 < NM) {
         constexpr int ge = (E + 8) / 8;  // biases of values 4 (ge % 4) .. + 3 of tile ge / 4; the slot's last value is done
@@ -843,7 +837,7 @@ __device__ __forceinline__ void pair2_input_tile(pair2_ctx<ACTK> &C)
     acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, C.cd[0], acc, 0, 0, 0);
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-        C.y[T][v] = dhq_activate_rev_any(__builtin_fmaf((float)acc[v], C.c1, pair_comp(bq[v >> 2], v & 3)), dhq_act{ACTK, C.c2});
+        C.y[T][v] = dhq_activate_rev_any(__builtin_fmaf((float)acc[v], C.c1, pair_comp(bq[v >> 2], v & 3)), dhq_act{DHQ_KIND(ACTK), C.c2});
 }
 template <int ACTK, int... Ts>
 __device__ __forceinline__ void pair2_input_tiles(pair2_ctx<ACTK> &C, std::integer_sequence<int, Ts...>)
@@ -970,7 +964,13 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair2_kernel(const pai
             asm volatile("" : "+v"(tid));
             const int64_t ci = tile * PAIR_TILE + S.grp * 32 + (tid & 31);
             const int64_t cl = ci < A.n ? ci : A.n - 1;  // lanes past the end repeat the last coordinate and store nothing
-            cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
+            if constexpr ((ACTK & DHQ_CODES_IN) != 0) {
+                dhq_v4i first[1] = {dhq_v4i{0, 0, 0, 0}};
+                fused_load_codes(A.codes0, cl, A.k0p, (int)(tid >> 5) & 1, first);
+                cd[0] = first[0];
+            } else {
+                cd[0][0] = fused_input_codes(A.coords, cl, A.k0, A.k0p, A.inv_in[0], A.qmax);
+            }
         }
         dhq_v16f y[PAIR_NT];
         pair2_input_layer<ACTK>(S, cc, A.c1[0], cd, y, h);
@@ -1267,17 +1267,13 @@ __global__ __launch_bounds__(PAIR_THREADS) void dhq_fused_pair_kernel_debug(cons
 }
 
 // ------------------------------------------------------------------------------- host code
-// `padded`: hidden widths of 257 .. 511, or of both kinds, and fan-ins of 5 .. 32.
+// `padded`: hidden widths of 257 .. 511, or of both kinds.
 static bool pair_shape_ok(const dhq_model *m, bool padded)
 {
     const int L = m->n_layers;
     if (L < 2) return false;
-    if (m->dims[L] > 32 || dhq_padded_width(m->dims, L) != 512) return false;
-    if (m->dims[0] > 4) {
-        if (!padded || m->layer[0].Kp > 32) return false;
-    } else if (dhq_all_hidden_are(m->dims, L, 512) == padded) {
-        return false;
-    }
+    if (m->dims[0] > 4 || m->dims[L] > 32) return false;
+    if (dhq_padded_width(m->dims, L) != 512 || dhq_all_hidden_are(m->dims, L, 512) == padded) return false;
     return !padded || dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2);
 }
 
@@ -1300,7 +1296,7 @@ static void pair_pack_tile(const dhq_layer &Ly, bool padded, int T, int Kb, bool
                 int8_t val = 0;
                 if (row < Ly.M) {
                     if (first) {
-                        if (16 * u + jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + 16 * u + jj];
+                        if (u == 0 && jj < Ly.Kp) val = wq[(size_t)row * Ly.Kp + jj];
                     } else {
                         val = wq[(size_t)row * Ly.Kp + hm_index(16 * pair_tile(padded, kb) + jj, u)];
                     }
@@ -1415,41 +1411,29 @@ static void (*pair_kernel_of(const dhq_pair_plan *P))(const pair_args)
     }
 }
 
-hipError_t dhq_pair_launch(const dhq_model *m, const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
+hipError_t dhq_pair_launch(const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
+    if (n <= 0) return hipSuccess;
+    pair_args a = P->args;
+    a.coords = coords;
+    a.out = out;
+    a.n = n;
+    const int64_t tiles = (n + PAIR_TILE - 1) / PAIR_TILE;
+    const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
     auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET)           ? pair_kernel_of<DHQ_ACT_KIND_WAVELET>(P)
                 : (P->act_kind == DHQ_ACT_KIND_WAVELET_COMPLEX) ? pair_kernel_of<DHQ_ACT_KIND_WAVELET_COMPLEX>(P)
                                                                 : pair_kernel_of<DHQ_ACT_KIND_SINE>(P);
-    hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
+    const hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
-    // a fan-in above 4: as in dhq_fused_launch
-    const bool wide_input = m->dims[0] > 4;
-    const int64_t step = wide_input ? DHQ_CHUNK * (int64_t)m->max_kp / P->args.k0p : n;
-    for (int64_t off = 0; off < n; off += step) {
-        pair_args a = P->args;
-        a.coords = coords + off * a.k0;
-        a.out = out + off * a.m_out;
-        a.n = n - off < step ? n - off : step;
-        if (wide_input) {
-            const dhq_layer &Ly = m->layer[0];
-            e = dhq_launch_wht_quant(a.coords, a.n, Ly.K, Ly.Kp, a.inv_in[0], m->qmax_a, m->codes, nullptr, st);
-            if (e != hipSuccess) return e;
-            a.codes0 = m->codes;
-        }
-        const int64_t tiles = (a.n + PAIR_TILE - 1) / PAIR_TILE;
-        const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
-        kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
+    return hipGetLastError();
 }
 
 // ---- the two-sided kernel ----
 // Fragment of one tile and digit plane: byte jj of lane (i, u) of k block kb is the digit of U[row(i)][feature(kb, u, jj)].
-template <typename Row, typename Col>
-static void pair2_pack(const std::vector<int32_t> &U, int Kp, int n_rows, int Kb, int plane, Row row_of, Col col_of, int8_t *frag)
+template <typename Weight, typename Row, typename Col>
+static void pair2_pack(const std::vector<Weight> &U, int Kp, int n_rows, int Kb, int plane, Row row_of, Col col_of, int8_t *frag)
 {
     for (int kb = 0; kb < Kb; ++kb)
         for (int ln = 0; ln < 64; ++ln) {
@@ -1468,7 +1452,13 @@ int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
 {
     *plan_out = nullptr;
     const int L = m->n_layers;
-    if (!m->rot_out || L < 2 || m->dims[0] > 4 || m->dims[L] > 32 || !dhq_all_hidden_are(m->dims, L, 512)) return DHQ_OK;
+    if (L < 2 || m->dims[L] > 32) return DHQ_OK;
+    // One-sided networks of 257 to 512 with a fan-in of 5 to 32 run here too, with U = W' and an upper digit of zero: the values are
+    // then the layer-by-layer path's.
+    const bool wide_input = m->dims[0] > 4;
+    if (wide_input ? m->rot_out || m->layer[0].Kp > 32 || dhq_padded_width(m->dims, L) != 512 || !dhq_pad_act_ok(m->act_kind, dhq_hidden_act(m).c2)
+                   : !m->rot_out || !dhq_all_hidden_are(m->dims, L, 512))
+        return DHQ_OK;
     if (m->act_kind != DHQ_ACT_KIND_SINE && m->act_kind != DHQ_ACT_KIND_WAVELET) return DHQ_OK;
     for (int l = 0; l < L; ++l)
         for (int32_t u : m->layer[l].u_host)
@@ -1484,12 +1474,16 @@ int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
         const dhq_layer &Ly = m->layer[l];
         const bool first = (l == 0), last = (l == L - 1);
         const int Kp = Ly.Kp;
-        auto col = [&](int kb, int u, int jj) { return first ? (u == 0 && jj < Kp ? jj : -1) : pair2_code_feature(kb, u, jj); };
+        auto col = [&](int kb, int u, int jj) { return first ? (16 * u + jj < Kp ? 16 * u + jj : -1) : pair2_code_feature(kb, u, jj); };
+        auto pack = [&](int n_rows, int Kb, int plane, auto row, int8_t *frag) {
+            if (wide_input) pair2_pack(Ly.wq_host, Kp, n_rows, Kb, plane, row, col, frag);
+            else pair2_pack(Ly.u_host, Kp, n_rows, Kb, plane, row, col, frag);
+        };
         float *bias = reinterpret_cast<float *>(blob.data() + bias_off) + (size_t)l * 512;
         if (last) {
             auto row = [](int i) { return i; };
             for (int p = 0; p < 2; ++p)
-                pair2_pack(Ly.u_host, Kp, Ly.M, PAIR_KB, 1 - p, row, col, frags + (size_t)(n_chunks - 1) * PAIR_BUF + (size_t)p * 16384);
+                pack(Ly.M, PAIR_KB, 1 - p, row, frags + (size_t)(n_chunks - 1) * PAIR_BUF + (size_t)p * 16384);
             for (int f = 0; f < Ly.M; ++f) bias[bias_slot(f)] = Ly.bias_host[f];
             continue;
         }
@@ -1500,9 +1494,10 @@ int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
                 for (int p = 0; p < 2; ++p) {
                     int8_t *dst = first ? frags + (size_t)role * 16384 + (size_t)(2 * T + p) * 1024
                                         : frags + (size_t)(1 + 16 * (l - 1) + 2 * T + p) * PAIR_BUF + (size_t)role * 16384;
-                    pair2_pack(Ly.u_host, Kp, 512, first ? 1 : PAIR_KB, 1 - p, row, col, dst);
+                    pack(Ly.M, first ? 1 : PAIR_KB, 1 - p, row, dst);
                 }
-                for (int i = 0; i < 32; ++i) bias[bias_slot(32 * (8 * role + T) + i)] = Ly.bias_rev_host[row(i)];
+                for (int i = 0; i < 32; ++i)
+                    bias[bias_slot(32 * (8 * role + T) + i)] = row(i) < Ly.M ? Ly.bias_rev_host[row(i)] : dhq_pad_bias(m->act_kind, row(i));
             }
     }
     P->blob_bytes = blob.size();
@@ -1534,21 +1529,39 @@ int dhq_pair2_create(const dhq_model *m, dhq_pair_plan **plan_out)
     return DHQ_OK;
 }
 
-hipError_t dhq_pair2_launch(const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
+template <int FLAGS>
+static void (*pair2_kernel_of(const dhq_pair_plan *P))(const pair_args)
+{
+    return P->act_kind == DHQ_ACT_KIND_WAVELET ? dhq_fused_pair2_kernel<DHQ_ACT_KIND_WAVELET | FLAGS> : dhq_fused_pair2_kernel<DHQ_ACT_KIND_SINE | FLAGS>;
+}
+
+hipError_t dhq_pair2_launch(const dhq_model *m, const dhq_pair_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
-    if (n <= 0) return hipSuccess;
-    pair_args a = P->args;
-    a.coords = coords;
-    a.out = out;
-    a.n = n;
-    const int64_t tiles = (n + PAIR_TILE - 1) / PAIR_TILE;
-    const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
-    auto kern = (P->act_kind == DHQ_ACT_KIND_WAVELET) ? dhq_fused_pair2_kernel<DHQ_ACT_KIND_WAVELET> : dhq_fused_pair2_kernel<DHQ_ACT_KIND_SINE>;
-    const hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
+    const bool wide_input = m->dims[0] > 4;
+    auto kern = wide_input ? pair2_kernel_of<DHQ_CODES_IN>(P) : pair2_kernel_of<0>(P);
+    hipError_t e = dhq_lds_limit_once(kern, P->lds_bytes, P->device);
     if (e != hipSuccess) return e;
-    kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
-    return hipGetLastError();
+    // a fan-in above 4: as in dhq_fused_launch
+    const int64_t step = wide_input ? DHQ_CHUNK * (int64_t)m->max_kp / P->args.k0p : n;
+    for (int64_t off = 0; off < n; off += step) {
+        pair_args a = P->args;
+        a.coords = coords + off * a.k0;
+        a.out = out + off * a.m_out;
+        a.n = n - off < step ? n - off : step;
+        if (wide_input) {
+            const dhq_layer &Ly = m->layer[0];
+            e = dhq_launch_wht_quant(a.coords, a.n, Ly.K, Ly.Kp, a.inv_in[0], m->qmax_a, m->codes, nullptr, st);
+            if (e != hipSuccess) return e;
+            a.codes0 = m->codes;
+        }
+        const int64_t tiles = (a.n + PAIR_TILE - 1) / PAIR_TILE;
+        const unsigned grid = (unsigned)(tiles < P->n_cu ? tiles : P->n_cu);
+        kern<<<grid, PAIR_THREADS, P->lds_bytes, st>>>(a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The dynamic mode on the per-layer kernels above (same contract as dhq_fused_dynamic_launch): ws0 / ws1 hold

@@ -43,6 +43,31 @@ def test_against_oracle(dims, s0):
     m.close()
 
 
+@pytest.mark.parametrize("dims", [[5, 32, 32, 3], [9, 20, 20, 1], [33, 50, 50, 3], [12, 64, 64, 64, 3], [40, 128, 100, 2], [16, 90, 90, 90, 5], [64, 256, 256, 3],
+                                  [17, 200, 140, 3], [5, 180, 180, 180, 2], [5, 512, 512, 512, 3], [32, 300, 400, 2], [9, 257, 257, 32]],
+                         ids=lambda d: "x".join(map(str, d)))
+@pytest.mark.parametrize("act", ["sine", "wavelet", "complex"])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_same_bits_as_layer_by_layer(dims, act, bits):
+    """Whichever kernels run: rows at the edges of a wave's and a workgroup's tile, coordinates far outside and not finite."""
+    import torch
+    if act == "complex":
+        dims = [dims[0]] + [max(1, d // 2) for d in dims[1:-1]] + [dims[-1]]
+        W, b = synth.wire_init(dims, 30.0, 3)
+        m = dhq.Model.complex_wavelet(dims, 30.0, W, b, 10.0, bits, bits)
+    else:
+        W, b = synth.siren_init(dims, 30.0, 3)
+        m = dhq.Model(dims, 30.0, W, b, bits, bits, wavelet_s0=10.0 if act == "wavelet" else None)
+    x = torch.rand((70001, dims[0]), generator=torch.Generator(device="cuda").manual_seed(4), device="cuda") * 2 - 1
+    m.calibrate(x[:3000].contiguous())
+    x[5, 0], x[77, -1], x[300, 1], x[301, 2], x[4000] = float("inf"), float("nan"), -float("inf"), 3e38, 0.0
+    for n in (1, 31, 33, 257, 9007, 70001):
+        print(f"[wide input] {dims} {act} {bits} bits n={n}", flush=True)
+        auto, lw = (m.forward(x[:n].contiguous(), flags=f) for f in (dhq.DHQ_AUTO, dhq.DHQ_LAYERWISE))
+        assert torch.equal(auto.view(torch.int32), lw.view(torch.int32))
+    m.close()
+
+
 def test_rows_beyond_the_workspace_and_every_tile():
     """A coordinate's value does not depend on where it sits: in several workspaces full of codes, in full passes and their rest."""
     import torch
