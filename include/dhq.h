@@ -61,7 +61,9 @@ typedef enum {
 #define DHQ_LAYERWISE 1u /* two to four kernels per layer, activations round-trip device memory */
 #define DHQ_FUSED 2u     /* one kernel for the whole network (two launches for some row counts); DHQ_EUNSUPPORTED if the shape has none */
 /* Shapes with a whole-network kernel (DHQ_ROTATE_IN): at least two layers, fan-in <= 4, all hidden
- * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells. */
+ * widths equal and 32 / 64 / 128 / 256 / 512, fan-out <= 32.  dhq_has_fused() tells.  DHQ_AUTO runs others on such kernels too:
+ * hidden widths that round up to the same one of these, and fan-ins of 5 to 64 (to 32 at hidden widths of up to 32 and beyond
+ * 256), whose codes go through the model's workspace. */
 /* or-ed onto the above: measure every layer's activation scale on line, on this call's own
  * coordinates, instead of using the scales stored in the model (Sec. 3.3, "dynamic
  * quantization module ... between layers").  With DHQ_LAYERWISE: an absmax pass added to every layer, any
@@ -123,13 +125,13 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  * Sec. 1 / Table 2 with floating-point activations: y = W a + b, a = sin(omega0 y) with fp32
  * accuracy, where W is the original weight matrix (DHQ_W32A32) or
  * W~ = (s_w Wq) H_Kp / sqrt(Kp), the de-quantized weights taken back to the original basis
- * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  DHQ_AUTO runs the whole network
- * in one kernel that multiplies two-piece binary16 splits (fp32 accuracy), and DHQ_FUSED, which is accepted with
- * fan-in <= 4, equal hidden widths of 32 / 64 / 128 / 256 and fan-out <= 32, is the same.  DHQ_LAYERWISE, single layers, and
- * networks with a row of weights most of which are below 2^-17 of its largest (or one that is not finite; these take three-piece
- * bf16 splits) run one kernel per layer, which write the model's workspace between the layers: up to 192 MiB, held
- * from creation on (64 MiB where no hidden layer is wider than 64; 65 536 rows' worth, at most 96 MiB, in the shapes
- * DHQ_FUSED accepts up to 128 wide).
+ * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  Weights and activations are fp32 values of any
+ * size; the products take them as three-piece bf16 splits, which hold them without loss.  With fan-in <= 4, equal hidden
+ * widths of 32 / 64 / 128 / 256 and fan-out <= 32, DHQ_AUTO and DHQ_FUSED run the whole network in one kernel.  In other
+ * shapes DHQ_AUTO does so where that is faster.  DHQ_LAYERWISE, and DHQ_AUTO elsewhere (hidden layers of more than 416, large
+ * fan-ins and fan-outs, single layers), run one kernel per layer, with the same values bit for bit, which write the model's
+ * workspace between the layers: up to 192 MiB, held from creation on (64 MiB where no hidden layer is wider than 64; 65 536
+ * rows' worth, at most 96 MiB, in the shapes DHQ_FUSED accepts up to 128 wide).
  * Such a model has no activation scales: dhq_set_act_scales, dhq_calibrate,
  * DHQ_DYNAMIC and the test hooks return DHQ_EUNSUPPORTED; dhq_forward needs none.
  */

@@ -1,12 +1,12 @@
 // Forward with floating-point activations (gfx950): the "W32A32" and "W8A32" rows of the paper's comparison (Sec. 1,
 // Fig. 1-2, Table 2).  W32A32 is the plain SIREN, y = W a + b, a = sin(omega0 y); W8A32 is the same network run on the weights
 // after the offline step and de-quantization, W~ = (s_w Wq) Hn (the caller passes whichever weights apply; the kernels do
-// not know the difference).  fp32 accuracy from 16-bit matrix instructions: every value is the sum of two binary16 or three
-// bf16 pieces.
+// not know the difference).  Weights and activations are fp32 values; the products run on the 16-bit matrix instructions, every
+// value as the sum of three bf16 pieces, which hold it without loss.
 //
-// float_net_kernel runs a whole network of any shape, the activations in LDS.  float_layer_kernel and float_narrow_kernel
-// run one layer per launch, activations in device memory between the layers, a chunk of rows at a time: DHQ_LAYERWISE, and
-// networks whose weights two binary16 pieces do not hold (host_two_pieces).
+// float_net_kernel runs a whole network, the activations in LDS (float_net_takes).  float_layer_kernel and float_narrow_kernel
+// run one layer per launch, activations in device memory between the layers, a chunk of rows at a time: DHQ_LAYERWISE, and the
+// networks that the other does not take.
 #include <math.h>
 #include <string.h>
 
@@ -19,8 +19,8 @@
 #include "dhq_internal.h"
 
 // Bytes of each of the two activation buffers of the layer-by-layer path: both together stay within the 256 MiB
-// memory-side cache, which is worth more than fewer launches (width 512, 262 144 rows, six bytes a value: 3.47 ms in chunks of
-// 32 768 rows = 96 MiB per buffer, 3.68 ms in chunks of 65 536), while narrower networks take as many rows as fit (width 60: 0.24 ms in chunks of
+// memory-side cache, which is worth more than fewer launches (width 512, 262 144 rows: 3.47 ms in chunks of 32 768 rows = 96 MiB
+// per buffer, 3.68 ms in chunks of 65 536), while narrower networks take as many rows as fit (width 60: 0.24 ms in chunks of
 // 65 536 rows, 0.40 ms in chunks of 32 768).
 #define FLT_ACT_BYTES ((int64_t)96 << 20)
 // A third of that for the narrow networks, whose rows are short (131 072 rows of 64 features; the launches' latency no longer
@@ -41,17 +41,16 @@ struct float_net_args {
     int64_t n;
     int n_blocks, n_layers, k0, m_out;
     int max_kb;  // k blocks of the widest hidden layer's output
-    float c2;
+    float rev, c2;
     float_net_layer layer[DHQ_MAX_LAYERS];
 };
 
-// One layer of the layer-by-layer path: weights as fragments of their three bf16 pieces (see float_layer_kernel), biases
-// [feature tile][lane half][16] (times omega0 / 2 pi where an activation follows).
+// A layer's weights as fragments of their three bf16 pieces (see float_layer_kernel), biases [feature tile][lane half][16] (times
+// omega0 / 2 pi where an activation follows).
 struct float_lw_layer {
     const unsigned char *wfrag_dev = nullptr;  // inside the plan's lw_blob_dev, like the biases
     const float *bias_dev = nullptr;
     int K = 0, M = 0, nkb = 0, Mt = 0;
-    int np = 3;  // pieces a value is held in
 };
 
 struct dhq_float_plan {
@@ -63,9 +62,8 @@ struct dhq_float_plan {
     float_lw_layer lw[DHQ_MAX_LAYERS];
     unsigned char *lw_blob_dev = nullptr;
     unsigned char *act[2] = {nullptr, nullptr};  // chunk_rows rows of fragments of the widest layer
-    int64_t chunk_rows = 0, chunk_step = 0;  // most rows of a chunk, rows of the chunks of a larger call
-    int np = 3;           // pieces of the layers after the first
-    float_net_args net;   // the whole-network kernel (np = 2 and more than one layer)
+    int64_t chunk_rows = 0;
+    float_net_args net;   // the whole-network kernel
     int max_mt = 0;       // feature tiles of the widest hidden layer
     bool narrow = false;  // every layer input up to 64 wide: float_narrow_kernel
     int device = 0;
@@ -73,22 +71,13 @@ struct dhq_float_plan {
 
 // ----------------------------------------------------------------------------- device code
 // ---------------------------------------------------------------- layer by layer, any shape
-// One GEMM kernel per layer.  The fp32 MFMA delivers 64 multiply-adds per clock and SIMD, the binary16 and bf16 ones 1024.
-//
-// Inputs of the layers after the first (activations, |a| <= 1) and their weights are held in two binary16 pieces,
-// hi = f16(s a), lo = f16(s a - hi), rounded to nearest: with s a power of two (2^15 for the activations, for the weights
-// what brings a row's largest to 2^14 .. 2^15) that is a value to 2^-23 of itself down to 2^-17 of the largest, and to 2^-40
-// of the largest below.  Every product a w is taken as
-//     hi hi + (hi lo + lo hi),
-// each exact in the MFMA and summed in fp32; left out is lo lo, at most 2^-22 of |a w| and 2^-24.5 rms, with a random sign.
-// 3 / 16 of the fp32 MFMA's time.  The network's inputs (any size), and the networks whose weights host_two_pieces turns down,
-// take three bf16 pieces, which hold an fp32 value without loss -- hi = bf16(a), mid = bf16(a - hi), lo = a - hi - mid -- and
-// the six products whose weight is at least 2^-17,
-//     hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi).
-// Error of the outputs against fp64, over 90 kinds of network (widths 20 .. 512, 2 and 5 hidden layers, sine and wavelet,
-// first layers down to 1e-6 of the usual, weights spread over many powers of two, de-quantized weights; 20 000 rows, three
-// seeds each): 0.96 of what six products in every layer gave (0.96 sine, 0.92 / 0.98 wavelets with s0 = 10 / 100), since
-// fewer sums are rounded; the fp32 MFMA, which rounds after every two products, is 1.02 to 1.19 times those.
+// One GEMM kernel per layer.  The fp32 MFMA delivers 64 multiply-adds per clock and SIMD, the bf16 one 1024, and three
+// bf16 pieces hold an fp32 value without loss: hi = bf16(a), mid = bf16(a - hi), lo = a - hi - mid (rounded to nearest,
+// 8 significant bits each, both differences exact).  So every product a w is taken as the six bf16 products whose
+// weight is at least 2^-17 of it,
+//     hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi),
+// each exact in the MFMA and summed in fp32.  Left out are mid lo, lo mid and lo lo: at most 2^-24 of |a w| together,
+// half an ulp of the product, with a random sign.  A layer then costs 6 / 16 of the fp32 MFMA time.
 //
 // Layout.  Features are the MFMA M dimension (weights = A operand), coordinates its N dimension, so that a lane's
 // accumulators are half of one coordinate's features and become, split into pieces, that lane's B operands of the next
@@ -98,16 +87,13 @@ struct dhq_float_plan {
 // [feature tile][k block][piece][lane] x 16 B: every access of a wave is 1 KiB contiguous and goes straight into LDS.
 //
 // A workgroup of WF x WC waves computes WF TF feature tiles x WC TC coordinate tiles, a wave TF x TC of them.
-// A 49 152 x 512 x 512 layer takes 74 us = 1.04 PFLOP/s of binary16 products (six bf16 products: 130 us, 1.19 PFLOP/s; the fp32
-// MFMA: 278 us); a large bf16 library product reaches 1.22-1.35 on this card with random operands (1.69 with zeros: the clock
-// follows the operands).
+// Bound by the matrix unit: a 65 536 x 512 x 512 layer takes 173 us = 1.19 PFLOP/s of bf16 products, which is what a large
+// bf16 library product reaches on this card with random operands (1.22-1.35; 1.69 with zeros: the clock follows the
+// operands).  The fp32 MFMA form of this kernel took 370 us.  Relative error of the outputs against fp64 (20 000 rows; the same network
+// on the fp32 MFMA, which rounds after every two products instead of every sixteen, in brackets): sine, 5 layers of 64 2.1e-7 (2.3e-7),
+// of 128 3.2e-7 (3.4e-7), of 512 7.2e-7; wavelet, s0 = 10, 5 layers of 64 6.3e-8 (7.5e-8), of 128 1.1e-7 (1.2e-7).
 typedef __bf16 flt_v8b __attribute__((ext_vector_type(8)));
 typedef __bf16 flt_v2b __attribute__((ext_vector_type(2)));
-typedef _Float16 flt_v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 flt_v2h __attribute__((ext_vector_type(2)));
-// Power of two that activations (|a| <= 1) carry in their binary16 pieces.
-#define FLT_ACT_EXPONENT 15
-#define FLT_ACT_SCALE 32768.f
 
 __device__ __forceinline__ unsigned flt_pack_bf16(float a, float b)
 {
@@ -117,74 +103,52 @@ __device__ __forceinline__ unsigned flt_pack_bf16(float a, float b)
 // The three bf16 pieces of two values, value 0 in the low halves.
 __device__ __forceinline__ void flt_split3(float a0, float a1, unsigned &hi, unsigned &mid, unsigned &lo)
 {
+// (what is split is an fp32 value: the wavelet's last product must not melt into the subtractions, in one kernel and not in another)
+#pragma clang fp contract(off)
     hi = flt_pack_bf16(a0, a1);
     const float r0 = a0 - __uint_as_float(hi << 16), r1 = a1 - __uint_as_float(hi & 0xffff0000u);
     mid = flt_pack_bf16(r0, r1);
     lo = flt_pack_bf16(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
 }
-// The two binary16 pieces of two activations, times FLT_ACT_SCALE.
-__device__ __forceinline__ void flt_split2(float a0, float a1, unsigned &hi, unsigned &lo)
-{
-    const float s0 = a0 * FLT_ACT_SCALE, s1 = a1 * FLT_ACT_SCALE;
-    const flt_v2h h = {(_Float16)s0, (_Float16)s1};
-    const flt_v2h l = {(_Float16)(s0 - (float)h[0]), (_Float16)(s1 - (float)h[1])};
-    hi = __builtin_bit_cast(unsigned, h);
-    lo = __builtin_bit_cast(unsigned, l);
-}
-// Eight values as a lane's 16 bytes of each of the NP fragments.
-template <int NP>
-__device__ __forceinline__ void flt_split(const float (&y)[8], dhq_v4i (&x)[NP])
+// Eight values as a lane's 16 bytes of each of the three fragments.
+__device__ __forceinline__ void flt_split(const float (&y)[8], dhq_v4i (&x)[3])
 {
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        unsigned p[NP];
-        if constexpr (NP == 3) flt_split3(y[2 * d], y[2 * d + 1], p[0], p[1], p[2]);
-        else flt_split2(y[2 * d], y[2 * d + 1], p[0], p[1]);
-#pragma unroll
-        for (int i = 0; i < NP; ++i) x[i][d] = (int)p[i];
+        unsigned hi, mid, lo;
+        flt_split3(y[2 * d], y[2 * d + 1], hi, mid, lo);
+        x[0][d] = (int)hi; x[1][d] = (int)mid; x[2][d] = (int)lo;
     }
 }
-// The fragments at dst, dst + 1 KiB, ...
-template <int NP>
+// The fragments at dst, dst + 1 KiB, dst + 2 KiB.
 __device__ __forceinline__ void flt_store_pieces(const float (&y)[8], unsigned char *__restrict__ dst)
 {
-    dhq_v4i x[NP];
-    flt_split<NP>(y, x);
+    dhq_v4i x[3];
+    flt_split(y, x);
 #pragma unroll
-    for (int i = 0; i < NP; ++i) *reinterpret_cast<dhq_v4i *>(dst + i * 1024) = x[i];
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<dhq_v4i *>(dst + i * 1024) = x[i];
 }
 
-// The products of pieces that make up one product of values, small ones first: product i takes weight piece
-// flt_w_piece<NP>(i) and activation piece flt_x_piece<NP>(i).
-template <int NP>
-constexpr int flt_products = NP == 3 ? 6 : 3;
-template <int NP>
-constexpr __host__ __device__ int flt_w_piece(int i)
+// The six products of one k block, small ones first; w, x: {hi, mid, lo}.
+__device__ __forceinline__ dhq_v16f flt_mfma6(const dhq_v4i (&w)[3], const dhq_v4i (&x)[3], dhq_v16f acc)
 {
-    constexpr int p3[6] = {0, 2, 1, 0, 1, 0}, p2[3] = {0, 1, 0};
-    return NP == 3 ? p3[i] : p2[i];
-}
-template <int NP>
-constexpr __host__ __device__ int flt_x_piece(int i)
-{
-    constexpr int p3[6] = {2, 0, 1, 1, 0, 0}, p2[3] = {1, 0, 0};
-    return NP == 3 ? p3[i] : p2[i];
-}
-template <int NP>
-__device__ __forceinline__ dhq_v16f flt_mfma1(dhq_v4i w, dhq_v4i x, dhq_v16f acc)
-{
-    if constexpr (NP == 3)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w), __builtin_bit_cast(flt_v8b, x), acc, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(flt_v8h, w), __builtin_bit_cast(flt_v8h, x), acc, 0, 0, 0);
-}
-// All products of one k block.
-template <int NP>
-__device__ __forceinline__ dhq_v16f flt_mfma(const dhq_v4i (&w)[NP], const dhq_v4i (&x)[NP], dhq_v16f acc)
-{
+    constexpr int pw[6] = {0, 2, 1, 0, 1, 0}, px[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-    for (int i = 0; i < flt_products<NP>; ++i) acc = flt_mfma1<NP>(w[flt_w_piece<NP>(i)], x[flt_x_piece<NP>(i)], acc);
+    for (int i = 0; i < 6; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w[pw[i]]), __builtin_bit_cast(flt_v8b, x[px[i]]), acc, 0, 0, 0);
     return acc;
+}
+
+// The activation on any finite argument.  The whole revolutions are taken off by rounding, not by the fractional part: an argument
+// of less than half of one stays as it is, where a small negative one's fractional part, 1 + t, is t rounded to 2^-24.
+__device__ __forceinline__ float flt_activate(float t, dhq_act act)
+{
+    const float f = t - __builtin_rintf(t);
+    if (act.kind == DHQ_ACT_KIND_WAVELET) {
+        const float g = t * act.c2;
+        return __builtin_amdgcn_cosf(f) * __builtin_amdgcn_exp2f(-(g * g));
+    }
+    return __builtin_amdgcn_sinf(f);
 }
 
 // The network's input: n x K row-major fp32 to fragments in natural k order (slot j of lane half h of block kb is
@@ -200,17 +164,17 @@ __global__ __launch_bounds__(256) void float_pack_kernel(const float *__restrict
     float y[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) y[j] = (row < n && k0 + j < K) ? in[row * K + k0 + j] : 0.f;
-    flt_store_pieces<3>(y, out + (size_t)w * 3072 + lane * 16);
+    flt_store_pieces(y, out + (size_t)w * 3072 + lane * 16);
 }
 
 struct float_layer_args {
-    const unsigned char *in;   // activations, [n_ct][nkb][NP] KiB
-    const unsigned char *w;    // weights, [n_ft][nkb][NP] KiB
-    const float *bias;         // [n_ft][lane half][16 biases, 16 multipliers of the sums], both times omega0 / 2 pi
-    unsigned char *out;        // activations, [n_ct][2 n_ft][NPO] KiB
+    const unsigned char *in;   // activations, [n_ct][nkb][3] KiB
+    const unsigned char *w;    // weights, [n_ft][nkb][3] KiB
+    const float *bias;         // [n_ft][lane half][16], times omega0 / 2 pi where a sine follows
+    unsigned char *out;        // activations, [n_ct][2 n_ft][3] KiB
     int n_ct, n_ft, nkb;       // nkb: even
     int nF, nC;                // workgroups over the features and over the coordinates
-    float c2;
+    float rev, c2;
 };
 
 // 1 KiB from device memory straight into LDS (as fused_issue_copy does): src and dst wave-uniform, voff = lane * 16.
@@ -237,20 +201,20 @@ __device__ __forceinline__ void flt_wait_loads()
 // so that its first fragments are fetched before stage s ends.  The activations of a tile are used by WF waves only and
 // go straight into registers, one stage ahead.  A stage's requests are spread over its MFMAs: all at its start, the
 // 64 KiB a CU asks for there keep its memory pipeline busy for 1 kclk, in which no wave gets to its MFMAs.
-template <int NP, int WF, int WC, int TF, int TC, int KS>
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
 struct float_layer_tile {
     static constexpr int NW = WF * WC, FT = WF * TF, CT = WC * TC;
-    static constexpr int BLOCKS = NP * FT * KS;  // KiB of weights per stage: [feature tile][k block][piece]
+    static constexpr int BLOCKS = 3 * FT * KS;  // KiB of weights per stage: [feature tile][k block][piece]
     static constexpr int PER_WAVE = (BLOCKS + NW - 1) / NW;
-    static constexpr int NX = NP * TC * KS, REQUESTS = NX + PER_WAVE;  // per stage and wave
-    static constexpr int NM = flt_products<NP>, NI = KS * TF, GROUPS = NM * NI;  // steps of a stage, groups of TC MFMAs
+    static constexpr int NX = 3 * TC * KS, REQUESTS = NX + PER_WAVE;  // per stage and wave
+    static constexpr int NI = KS * TF, GROUPS = 6 * NI;               // steps of a stage, groups of TC MFMAs
     const float_layer_args &A;
     const unsigned char *lds;
     unsigned lds0, voff;
     int lane, wave, wf, wc, f0, c0, n_stages;
     const unsigned char *src[PER_WAVE];
     const unsigned char *xsrc[TC];
-    dhq_v4i x[2][TC][KS][NP], w[2][NP];
+    dhq_v4i x[2][TC][KS][3], w[2][3];
     dhq_v16f acc[TF][TC];
     __device__ __forceinline__ float_layer_tile(const float_layer_args &A_) : A(A_) {}
 
@@ -259,16 +223,16 @@ struct float_layer_tile {
     __device__ __forceinline__ void copy_weights(int s, int buf)
     {
         const int q = wave + I * NW;
-        if ((BLOCKS % NW != 0 && q >= BLOCKS) || s * KS + (KS > 1 ? (q / NP) % KS : 0) >= A.nkb) return;
-        flt_copy_kib(voff, src[I] + (size_t)s * (NP * 1024 * KS), lds0 + (buf * BLOCKS + q) * 1024);
+        if ((BLOCKS % NW != 0 && q >= BLOCKS) || s * KS + (KS > 1 ? (q / 3) % KS : 0) >= A.nkb) return;
+        flt_copy_kib(voff, src[I] + (size_t)s * (3072 * KS), lds0 + (buf * BLOCKS + q) * 1024);
     }
     // the I-th fragment of the activations of stage s (past the last k block: the last one again, not used)
     template <int XB, int I>
     __device__ __forceinline__ void load_x(int s)
     {
-        constexpr int k = I / (NP * TC), c = (I / NP) % TC, p = I % NP;
+        constexpr int k = I / (3 * TC), c = (I / 3) % TC, p = I % 3;
         const int kb = s * KS + k < A.nkb ? s * KS + k : A.nkb - 1;
-        x[XB][c][k][p] = *reinterpret_cast<const dhq_v4i *>(xsrc[c] + (size_t)(kb * NP + p) * 1024 + voff);
+        x[XB][c][k][p] = *reinterpret_cast<const dhq_v4i *>(xsrc[c] + (size_t)(kb * 3 + p) * 1024 + voff);
     }
     template <int XB, int... I>
     __device__ __forceinline__ void load_x_all(int s, std::integer_sequence<int, I...>) { (load_x<XB, I>(s), ...); }
@@ -279,7 +243,7 @@ struct float_layer_tile {
     {
         const dhq_v4i *b = reinterpret_cast<const dhq_v4i *>(lds + buf * BLOCKS * 1024) + lane;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) w[WB][p] = b[(((wf * TF + f) * KS + k) * NP + p) * 64];
+        for (int p = 0; p < 3; ++p) w[WB][p] = b[(((wf * TF + f) * KS + k) * 3 + p) * 64];
     }
     // Request R of stage s, issued in front of MFMA group G: the activations first.
     template <int S, int G, int R>
@@ -294,11 +258,12 @@ struct float_layer_tile {
             request<S, G, R + 1>(s, b2);
         }
     }
-    // Group G of stage s: product G % NM (small ones first) of step G / NM for this wave's TC coordinate tiles.
+    // Group G of stage s: product G % 6 (small ones first) of step G / 6 for this wave's TC coordinate tiles.
     template <int S, int G>
     __device__ __forceinline__ void group(int s, int b0, int b1, int b2)
     {
-        constexpr int I = G / NM, i = G % NM, k = I / TF, f = I % TF, wb = (S * NI + I) & 1;
+        constexpr int I = G / 6, i = G % 6, k = I / TF, f = I % TF, wb = (S * NI + I) & 1;
+        constexpr int pw[6] = {0, 2, 1, 0, 1, 0}, px[6] = {2, 0, 1, 1, 0, 0};
         if constexpr (i == 0) {  // the next step's weight fragments
             if constexpr (I + 1 < NI) load_w<wb ^ 1>(b0, (I + 1) / TF, (I + 1) % TF);
             else load_w<wb ^ 1>(b1, 0, 0);
@@ -308,7 +273,8 @@ struct float_layer_tile {
         if (KS == 1 || s * KS + k < A.nkb) {
 #pragma unroll
             for (int c = 0; c < TC; ++c)
-                acc[f][c] = flt_mfma1<NP>(w[wb][flt_w_piece<NP>(i)], x[S][c][k][flt_x_piece<NP>(i)], acc[f][c]);
+                acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w[wb][pw[i]]),
+                                                                    __builtin_bit_cast(flt_v8b, x[S][c][k][px[i]]), acc[f][c], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (G + 1 < GROUPS) group<S, G + 1>(s, b0, b1, b2);
@@ -323,10 +289,10 @@ struct float_layer_tile {
     }
 };
 
-template <int ACT, int NP, int NPO, int WF, int WC, int TF, int TC, int KS>
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
 __global__ __launch_bounds__(64 * WF * WC) void float_layer_kernel(const float_layer_args A)
 {
-    using tile_t = float_layer_tile<NP, WF, WC, TF, TC, KS>;
+    using tile_t = float_layer_tile<ACT, WF, WC, TF, TC, KS>;
     extern __shared__ __align__(16) unsigned char lds[];
     tile_t R(A);
     const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -348,14 +314,14 @@ __global__ __launch_bounds__(64 * WF * WC) void float_layer_kernel(const float_l
     // this wave's share of a stage's weights: 1 KiB blocks wave, wave + NW, ...; tiles past the last one are read again
 #pragma unroll
     for (int i = 0; i < tile_t::PER_WAVE; ++i) {
-        const int q = R.wave + i * tile_t::NW, t = q / (NP * KS), r = q % (NP * KS);
+        const int q = R.wave + i * tile_t::NW, t = q / (3 * KS), r = q % (3 * KS);
         const int f = R.f0 + t < A.n_ft ? R.f0 + t : A.n_ft - 1;
-        R.src[i] = A.w + ((size_t)f * A.nkb * NP + r) * 1024;
+        R.src[i] = A.w + ((size_t)f * A.nkb * 3 + r) * 1024;
     }
 #pragma unroll
     for (int c = 0; c < TC; ++c) {
         const int ct = R.c0 + R.wc * TC + c < A.n_ct ? R.c0 + R.wc * TC + c : A.n_ct - 1;
-        R.xsrc[c] = A.in + (size_t)ct * A.nkb * (NP * 1024);
+        R.xsrc[c] = A.in + (size_t)ct * A.nkb * 3072;
     }
 #pragma unroll
     for (int f = 0; f < TF; ++f)
@@ -380,24 +346,21 @@ __global__ __launch_bounds__(64 * WF * WC) void float_layer_kernel(const float_l
     for (int f = 0; f < TF; ++f) {
         const int T = R.f0 + R.wf * TF + f;
         if (T >= A.n_ft) break;
-        float bias[16], mul[16];
+        float bias[16];
 #pragma unroll
-        for (int v = 0; v < 16; v += 4) {
-            *reinterpret_cast<float4 *>(&bias[v]) = *reinterpret_cast<const float4 *>(A.bias + (T * 2 + h) * 32 + v);
-            *reinterpret_cast<float4 *>(&mul[v]) = *reinterpret_cast<const float4 *>(A.bias + (T * 2 + h) * 32 + 16 + v);
-        }
+        for (int v = 0; v < 16; v += 4) *reinterpret_cast<float4 *>(&bias[v]) = *reinterpret_cast<const float4 *>(A.bias + (T * 2 + h) * 16 + v);
 #pragma unroll
         for (int c = 0; c < TC; ++c) {
             const int ct = R.c0 + R.wc * TC + c;
             if (ct >= A.n_ct) break;
-            unsigned char *dst = A.out + ((size_t)ct * A.n_ft + T) * (2 * NPO * 1024) + lane * 16;
+            unsigned char *dst = A.out + ((size_t)ct * A.n_ft + T) * 6144 + lane * 16;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 float y[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    y[j] = dhq_activate_rev_any(__builtin_fmaf(R.acc[f][c][8 * b + j], mul[8 * b + j], bias[8 * b + j]), dhq_act{ACT, A.c2});
-                flt_store_pieces<NPO>(y, dst + b * (NPO * 1024));
+                    y[j] = flt_activate(__builtin_fmaf(R.acc[f][c][8 * b + j], A.rev, bias[8 * b + j]), dhq_act{ACT, A.c2});
+                flt_store_pieces(y, dst + b * 3072);
             }
         }
     }
@@ -405,7 +368,6 @@ __global__ __launch_bounds__(64 * WF * WC) void float_layer_kernel(const float_l
 
 // The output layer: one tile of 32 features x 32 coordinates per wave, fragments straight from device memory (each is
 // used once), no activation; bound by reading the activations.
-template <int NP>
 __global__ __launch_bounds__(256) void float_out_kernel(const unsigned char *__restrict__ in, const unsigned char *__restrict__ wfrag,
                                                         const float *__restrict__ bias, int64_t n, int n_ct, int nkb, int M,
                                                         float *__restrict__ out)
@@ -413,32 +375,32 @@ __global__ __launch_bounds__(256) void float_out_kernel(const unsigned char *__r
     const int ct = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), T = blockIdx.y;
     if (ct >= n_ct) return;
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
-    const dhq_v4i *xp = reinterpret_cast<const dhq_v4i *>(in + (size_t)ct * nkb * (NP * 1024)) + lane;
-    const dhq_v4i *wp = reinterpret_cast<const dhq_v4i *>(wfrag + (size_t)T * nkb * (NP * 1024)) + lane;
+    const dhq_v4i *xp = reinterpret_cast<const dhq_v4i *>(in + (size_t)ct * nkb * 3072) + lane;
+    const dhq_v4i *wp = reinterpret_cast<const dhq_v4i *>(wfrag + (size_t)T * nkb * 3072) + lane;
     dhq_v16f acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     for (int kb0 = 0; kb0 < nkb; kb0 += 4) {
-        dhq_v4i x[4][NP], w[4][NP];  // four k blocks in flight; blocks past the last one are read again and not used
+        dhq_v4i x[4][3], w[4][3];  // four k blocks in flight; blocks past the last one are read again and not used
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int kb = kb0 + i < nkb ? kb0 + i : nkb - 1;
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                x[i][p] = xp[(kb * NP + p) * 64];
-                w[i][p] = wp[(kb * NP + p) * 64];
+            for (int p = 0; p < 3; ++p) {
+                x[i][p] = xp[(kb * 3 + p) * 64];
+                w[i][p] = wp[(kb * 3 + p) * 64];
             }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (kb0 + i < nkb) acc = flt_mfma<NP>(w[i], x[i], acc);
+            if (kb0 + i < nkb) acc = flt_mfma6(w[i], x[i], acc);
     }
     const int64_t row = (int64_t)ct * 32 + c;
     if (row >= n) return;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int f = 32 * T + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (f < M) out[row * M + f] = __builtin_fmaf(acc[v], bias[(T * 2 + h) * 32 + 16 + v], bias[(T * 2 + h) * 32 + v]);
+        if (f < M) out[row * M + f] = acc[v] + bias[(T * 2 + h) * 16 + v];
     }
 }
 
@@ -447,19 +409,18 @@ __global__ __launch_bounds__(256) void float_out_kernel(const unsigned char *__r
 // with their stages of LDS copies and fragments of six bytes a value, were slower than one wave per tile that holds the
 // layer's whole weights in registers: 4 layers of 20 features on 65 536 rows 45 -> 19 us, 4 of 48 58 -> 37 us.  Between the
 // layers the activations travel as floats in the lanes' order, [tile of 32 coordinates][feature tile][float4 q][lane], and
-// are split into pieces by the wave that reads them: the same pieces, products and order of sums as above, so the same bits
-// (of sines; a wavelet above goes into its pieces before its last product is rounded to fp32).
+// are split into pieces by the wave that reads them: the same pieces, products and order of sums as above, so the same bits.
 // NT: feature tiles (of the output layer: one, gridDim.y of them); NKB: k blocks.  A wave takes every gridDim.x * 4-th tile.
 struct float_narrow_args {
     const float *in;           // FIRST: n x K coordinates, else the layer below's output
     float *out;                // LAST: n x M, else the layer above's input
     const unsigned char *w;    // [feature tile][k block][piece] KiB
-    const float *bias;         // [feature tile][lane half][16 biases, 16 multipliers]
+    const float *bias;         // [feature tile][lane half][16]
     int64_t n;
     int n_ct, K, M;
-    float c2;
+    float rev, c2;
 };
-template <int ACT, int NP, int NT, int NKB, bool FIRST, bool LAST>
+template <int ACT, int NT, int NKB, bool FIRST, bool LAST>
 __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_args A)
 {
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
@@ -485,24 +446,27 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
     };
     float v[NKB][8];
     load(ct, v);
-    dhq_v4i w[NT][NKB][NP];
-    float bias[NT][16], mul[NT][16];
+    dhq_v4i w[NT][NKB][3];
+    float bias[NT][16];
 #pragma unroll
     for (int T = 0; T < NT; ++T) {
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-            for (int p = 0; p < NP; ++p) w[T][kb][p] = reinterpret_cast<const dhq_v4i *>(A.w)[(((T0 + T) * NKB + kb) * NP + p) * 64 + lane];
+            for (int p = 0; p < 3; ++p) w[T][kb][p] = reinterpret_cast<const dhq_v4i *>(A.w)[(((T0 + T) * NKB + kb) * 3 + p) * 64 + lane];
 #pragma unroll
-        for (int i = 0; i < 16; i += 4) {
-            *reinterpret_cast<float4 *>(&bias[T][i]) = *reinterpret_cast<const float4 *>(A.bias + ((T0 + T) * 2 + h) * 32 + i);
-            *reinterpret_cast<float4 *>(&mul[T][i]) = *reinterpret_cast<const float4 *>(A.bias + ((T0 + T) * 2 + h) * 32 + 16 + i);
-        }
+        for (int i = 0; i < 16; i += 4) *reinterpret_cast<float4 *>(&bias[T][i]) = *reinterpret_cast<const float4 *>(A.bias + ((T0 + T) * 2 + h) * 16 + i);
     }
     for (; ct < A.n_ct; ct += stride) {
-        dhq_v4i x[NKB][NP];
+        dhq_v4i x[NKB][3];
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) flt_split<NP>(v[kb], x[kb]);
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                unsigned hi, mid, lo;
+                flt_split3(v[kb][2 * d], v[kb][2 * d + 1], hi, mid, lo);
+                x[kb][0][d] = (int)hi; x[kb][1][d] = (int)mid; x[kb][2][d] = (int)lo;
+            }
         if (ct + stride < A.n_ct) load(ct + stride, v);  // arrives during the products
         dhq_v16f acc[NT];
 #pragma unroll
@@ -510,7 +474,7 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[T][i] = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb) acc[T] = flt_mfma<NP>(w[T][kb], x[kb], acc[T]);
+            for (int kb = 0; kb < NKB; ++kb) acc[T] = flt_mfma6(w[T][kb], x[kb], acc[T]);
         }
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
@@ -520,7 +484,7 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int f = 32 * (T0 + T) + 8 * (i >> 2) + 4 * h + (i & 3);
-                        if (f < A.M) A.out[row * A.M + f] = __builtin_fmaf(acc[T][i], mul[T][i], bias[T][i]);
+                        if (f < A.M) A.out[row * A.M + f] = acc[T][i] + bias[T][i];
                     }
                 }
             } else {
@@ -530,7 +494,7 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
                     float y[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        y[e] = dhq_activate_rev_any(__builtin_fmaf(acc[T][4 * q + e], mul[T][4 * q + e], bias[T][4 * q + e]), dhq_act{ACT, A.c2});
+                        y[e] = flt_activate(__builtin_fmaf(acc[T][4 * q + e], A.rev, bias[T][4 * q + e]), dhq_act{ACT, A.c2});
                     dst[q * 64] = make_float4(y[0], y[1], y[2], y[3]);
                 }
             }
@@ -542,52 +506,49 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
 // A workgroup carries CT = WC TC tiles of 32 coordinates through all layers; their activations lie in LDS, in the fragments
 // above ([coordinate tile][k block][piece][lane] x 16 B), and nothing but coordinates and outputs crosses device memory.  The
 // WF WC waves split a layer's output: wave (wf, wc) computes feature tiles wf TF .. + TF - 1 of coordinate tiles wc TC ..
-// + TC - 1 in its accumulators, takes them through the epilogue into pieces, and when all waves have read their inputs the
+// + TC - 1 in its accumulators, takes them through the epilogue, and when all waves have read their inputs the activations'
 // pieces take the inputs' place.  A weight fragment is used by one wave (or WC of them) only: it comes from L2 straight into
-// registers, a stage (two k blocks) ahead of its MFMAs.  Biases and multipliers go through LDS, a layer ahead.
+// registers, a stage (KS k blocks) ahead of its MFMAs.  Biases go through LDS, a layer ahead.
 // The sums' order is the layer-by-layer kernels', so the values are theirs bit for bit.
 //
-// Bound by the matrix unit and the weights' way into the registers, at a clock that follows the load.  Five layers of 512,
-// 262 144 rows: 1.93 ms (layer by layer 2.20, with six products 3.49); timing-only copies: without the weights' loads 1.52,
-// without the activations' 1.86, without the epilogue 1.94, without either load 1.36 = the three products at 1.5 PFLOP/s.  A
-// prefetch of two stages: unchanged.  Four layers of 256: 0.43 ms (0.62; 0.94): two workgroups of four waves per CU, whose
-// epilogues run under each other's products; one of eight waves 0.45, a wave of 2 x 4 tiles per SIMD 0.44, one of
-// 1 x 4 tiles (half the weight reads, twice the LDS reads) 0.44.
-// D: stages of weights in registers.
-template <int ACT, int WF, int WC, int TF, int TC, int D>
+// Bound by the matrix unit and, where few coordinates share a weight fragment, by the weights' way into the registers.  Four layers of
+// 256, 262 144 rows: 580 us (layer by layer 744) = 1.07 PFLOP/s of bf16 products.  The activations stay in the accumulators until every
+// wave has read its inputs and are split then: split before, a tile of 64 x 64 kept 140 bytes a lane in scratch memory.
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
 __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_kernel(const float_net_args A)
 {
-    constexpr int NW = WF * WC, CT = WC * TC, NG = 6;  // products of a stage's two k blocks
-    constexpr int NLW = 4 * TF;                        // weight fragments of a stage and wave
-    constexpr bool ALONE = WF == 1 && TF == 1;         // a wave has all of its coordinates' features: no barriers
+    constexpr int NW = WF * WC, CT = WC * TC, NG = 6 * KS;  // products of a stage
+    constexpr int NLW = 3 * KS * TF;                        // weight fragments of a stage and wave
+    constexpr bool ALONE = WF == 1 && TF == 1;              // a wave has all of its coordinates' features: no barriers
+    constexpr int pw[6] = {0, 2, 1, 0, 1, 0}, px[6] = {2, 0, 1, 1, 0, 0};  // as in flt_mfma6
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wf = wave % WF, wc = wave / WF;
-    const int L = A.n_layers, ct_bytes = A.max_kb * 2048;
+    const int L = A.n_layers, ct_bytes = A.max_kb * 3072;
     unsigned char *act = lds + wc * TC * ct_bytes + lane * 16;
-    float *bm = reinterpret_cast<float *>(lds + CT * ct_bytes);  // [feature tile][lane half][16 biases, 16 multipliers]
+    float *bm = reinterpret_cast<float *>(lds + CT * ct_bytes);  // [feature tile][lane half][16 biases]
     dhq_v16f acc[TF][TC];
-    dhq_v4i w[D][2][TF][2];  // the weights of D stages
+    dhq_v4i w[2][KS][TF][3];  // the weights of two stages
 
-    // this thread's share of layer l's biases and multipliers
+    // this thread's share of layer l's biases
     auto fetch_bias = [&](int l) {
         const float4 *src = reinterpret_cast<const float4 *>(A.blob + (size_t)A.layer[l].b_off * 128);
-        return tid < A.layer[l].Mt * 16 ? src[tid] : make_float4(0.f, 0.f, 0.f, 0.f);
+        return tid < A.layer[l].Mt * 8 ? src[tid] : make_float4(0.f, 0.f, 0.f, 0.f);
     };
     auto store_bias = [&](int l, float4 v) {
-        if (tid < A.layer[l].Mt * 16) reinterpret_cast<float4 *>(bm)[tid] = v;
+        if (tid < A.layer[l].Mt * 8) reinterpret_cast<float4 *>(bm)[tid] = v;
     };
     // the weights of the wave's f-th feature tile in layer l (tiles past the last one: the last one's, not used)
     auto weights_of = [&](int l, int f) {
         const int T = wf * TF + f, Tc = T < A.layer[l].Mt ? T : A.layer[l].Mt - 1;
-        return A.blob + ((size_t)A.layer[l].w_off + (size_t)Tc * A.layer[l].nkb * 2) * 1024;
+        return A.blob + ((size_t)A.layer[l].w_off + (size_t)Tc * A.layer[l].nkb * 3) * 1024;
     };
     const unsigned voff = lane * 16;
 
-    float4 own[8];  // ALONE: the lane's biases and multipliers
+    float4 own[4];  // ALONE: the lane's biases
     auto fetch_own = [&](int l) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) own[i] = reinterpret_cast<const float4 *>(A.blob + (size_t)A.layer[l].b_off * 128)[h * 8 + i];
+        for (int i = 0; i < 4; ++i) own[i] = reinterpret_cast<const float4 *>(A.blob + (size_t)A.layer[l].b_off * 128)[h * 4 + i];
     };
 
     float4 bias_next;
@@ -602,7 +563,7 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
             for (int t = 0; t < TC; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[f][t][v] = 0.f;
-        // the input layer: coordinates in natural k order, three pieces
+        // the input layer: coordinates in natural k order
         if (wf * TF < A.layer[0].Mt) {
             const int nkb = A.layer[0].nkb;
             const dhq_v4i *w0 = reinterpret_cast<const dhq_v4i *>(A.blob + (size_t)A.layer[0].w_off * 1024) + lane;
@@ -615,7 +576,7 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
                     float y[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) y[j] = (row < A.n && kk + j < A.k0) ? A.coords[row * A.k0 + kk + j] : 0.f;
-                    flt_split<3>(y, x[t]);
+                    flt_split(y, x[t]);
                 }
 #pragma unroll
                 for (int f = 0; f < TF; ++f) {
@@ -624,14 +585,14 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
 #pragma unroll
                     for (int p = 0; p < 3; ++p) wk[p] = w0[((size_t)Tc * nkb + kb) * 192 + p * 64];
 #pragma unroll
-                    for (int t = 0; t < TC; ++t) acc[f][t] = flt_mfma<3>(wk, x[t], acc[f][t]);
+                    for (int t = 0; t < TC; ++t) acc[f][t] = flt_mfma6(wk, x[t], acc[f][t]);
                 }
             }
         }
         if constexpr (!ALONE) __syncthreads();  // the input layer's biases are in place
         for (int l = 0; l < L - 1; ++l) {
             // here: layer l's sums in the accumulators of the waves that have tiles in it
-            const int Mt = A.layer[l].Mt;
+            const int Mt = A.layer[l].Mt, ns = 2 * Mt / KS;  // stages of the next layer
             const bool busy = wf * TF < Mt;
             const int ln = l + 1 < L - 1 ? l + 1 : 0;  // whose biases come next
             if constexpr (!ALONE) bias_next = fetch_bias(ln);
@@ -641,37 +602,26 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
                 for (int f = 0; f < TF; ++f) {
                     wp[f] = weights_of(l + 1, f);
 #pragma unroll
-                    for (int d = 0; d < D - 1; ++d) {
-                        const int sd = d < Mt ? d : Mt - 1;
+                    for (int k = 0; k < KS; ++k)
 #pragma unroll
-                        for (int k = 0; k < 2; ++k)
-#pragma unroll
-                            for (int p = 0; p < 2; ++p) w[d][k][f][p] = *reinterpret_cast<const dhq_v4i *>(wp[f] + (size_t)sd * 4096 + voff + (k * 2 + p) * 1024);
-                    }
+                        for (int p = 0; p < 3; ++p) w[0][k][f][p] = *reinterpret_cast<const dhq_v4i *>(wp[f] + voff + (k * 3 + p) * 1024);
                 }
             }
-            dhq_v4i pc[TF][TC][2][2];
-            if (busy) {
+            if (busy) {  // the activations, in the sums' place
 #pragma unroll
                 for (int f = 0; f < TF; ++f) {
                     const int T = wf * TF + f, Tc = T < Mt ? T : Mt - 1;
-                    const float4 *bp = reinterpret_cast<const float4 *>(bm + (Tc * 2 + h) * 32);
+                    const float4 *bp = reinterpret_cast<const float4 *>(bm + (Tc * 2 + h) * 16);
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
-                        float bias[8], mul[8];
+                        float bias[8];
 #pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            *reinterpret_cast<float4 *>(&bias[4 * i]) = ALONE ? own[2 * b + i] : bp[2 * b + i];
-                            *reinterpret_cast<float4 *>(&mul[4 * i]) = ALONE ? own[4 + 2 * b + i] : bp[4 + 2 * b + i];
-                        }
+                        for (int i = 0; i < 2; ++i) *reinterpret_cast<float4 *>(&bias[4 * i]) = ALONE ? own[2 * b + i] : bp[2 * b + i];
 #pragma unroll
-                        for (int t = 0; t < TC; ++t) {
-                            float y[8];
+                        for (int t = 0; t < TC; ++t)
 #pragma unroll
                             for (int j = 0; j < 8; ++j)
-                                y[j] = dhq_activate_rev_any(__builtin_fmaf(acc[f][t][8 * b + j], mul[j], bias[j]), dhq_act{ACT, A.c2});
-                            flt_split<2>(y, pc[f][t][b]);
-                        }
+                                acc[f][t][8 * b + j] = flt_activate(__builtin_fmaf(acc[f][t][8 * b + j], A.rev, bias[j]), dhq_act{ACT, A.c2});
                     }
                 }
             }
@@ -684,10 +634,12 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
 #pragma unroll
                         for (int t = 0; t < TC; ++t)
 #pragma unroll
-                            for (int b = 0; b < 2; ++b)
+                            for (int b = 0; b < 2; ++b) {
+                                float y[8];
 #pragma unroll
-                                for (int p = 0; p < 2; ++p)
-                                    *reinterpret_cast<dhq_v4i *>(act + t * ct_bytes + ((2 * T + b) * 2 + p) * 1024) = pc[f][t][b][p];
+                                for (int j = 0; j < 8; ++j) y[j] = acc[f][t][8 * b + j];
+                                flt_store_pieces(y, act + t * ct_bytes + (2 * T + b) * 3072);
+                            }
                     }
                 }
             }
@@ -705,51 +657,49 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
                 for (int t = 0; t < TC; ++t)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[f][t][v] = 0.f;
-            const int ns = Mt;  // stages: a feature tile of layer l each
-            dhq_v4i x[2][TC][2];
+            dhq_v4i x[2][TC][3];
 #pragma unroll
             for (int t = 0; t < TC; ++t)
 #pragma unroll
-                for (int p = 0; p < 2; ++p) x[0][t][p] = *reinterpret_cast<const dhq_v4i *>(act + t * ct_bytes + p * 1024);
+                for (int p = 0; p < 3; ++p) x[0][t][p] = *reinterpret_cast<const dhq_v4i *>(act + t * ct_bytes + p * 1024);
             auto stage = [&](auto B, int s) {
                 constexpr int wb = decltype(B)::value;
-                const int sn = s + 1 < ns ? s + 1 : s, sl = s + D - 1 < ns ? s + D - 1 : ns - 1;
+                const int sn = s + 1 < ns ? s + 1 : s;
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
-                    const int k = g / 3, i = g % 3;
-                    // the next stage's weights, spread over the first groups
+                    const int k = g / 6, i = g % 6, xb = (wb * KS + k) & 1;
+                    // the next stage's weights, spread over the first two thirds of the groups
 #pragma unroll
                     for (int q = 0; q < NLW; ++q)
-                        if (q * 4 / NLW == g) {
-                            const int k2 = q / (2 * TF), f = (q / 2) % TF, p = q % 2;
-                            w[(wb + D - 1) % D][k2][f][p] = *reinterpret_cast<const dhq_v4i *>(wp[f] + (size_t)sl * 4096 + voff + (k2 * 2 + p) * 1024);
+                        if (q * (4 * KS) / NLW == g) {
+                            const int k2 = q / (3 * TF), f = (q / 3) % TF, p = q % 3;
+                            w[wb ^ 1][k2][f][p] = *reinterpret_cast<const dhq_v4i *>(wp[f] + (size_t)sn * (KS * 3072) + voff + (k2 * 3 + p) * 1024);
                         }
                     if (i == 0) {  // the next k block's activations
-                        const int kn = k == 0 ? 2 * s + 1 : 2 * sn;
+                        const int kn = k + 1 < KS ? s * KS + k + 1 : sn * KS;
 #pragma unroll
                         for (int t = 0; t < TC; ++t)
 #pragma unroll
-                            for (int p = 0; p < 2; ++p) x[k ^ 1][t][p] = *reinterpret_cast<const dhq_v4i *>(act + t * ct_bytes + (kn * 2 + p) * 1024);
+                            for (int p = 0; p < 3; ++p) x[xb ^ 1][t][p] = *reinterpret_cast<const dhq_v4i *>(act + t * ct_bytes + (kn * 3 + p) * 1024);
                     }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int f = 0; f < TF; ++f)
 #pragma unroll
-                        for (int t = 0; t < TC; ++t) acc[f][t] = flt_mfma1<2>(w[wb][k][f][flt_w_piece<2>(i)], x[k][t][flt_x_piece<2>(i)], acc[f][t]);
+                        for (int t = 0; t < TC; ++t)
+                            acc[f][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(flt_v8b, w[wb][k][f][pw[i]]),
+                                                                                __builtin_bit_cast(flt_v8b, x[xb][t][px[i]]), acc[f][t], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
-            // ahead of the other workgroup's epilogue on the SIMD, which fills what the products leave (425 -> 412 us at 256, 1.93 ->
-            // 1.91 ms at 512, 101 -> 99 us at 128; raised for the epilogue instead: 433 -> 436)
+            // ahead of the other workgroup's epilogue on the SIMD, which fills what the products leave
             __builtin_amdgcn_s_setprio(3);
             int s = 0;
-            for (; s + D - 1 < ns; s += D) {
+            for (; s + 1 < ns; s += 2) {
                 stage(std::integral_constant<int, 0>{}, s);
                 stage(std::integral_constant<int, 1>{}, s + 1);
-                if constexpr (D > 2) stage(std::integral_constant<int, D - 1>{}, s + 2);
             }
             if (s < ns) stage(std::integral_constant<int, 0>{}, s);
-            if (D > 2 && s + 1 < ns) stage(std::integral_constant<int, 1>{}, s + 1);
             __builtin_amdgcn_s_setprio(0);
         }
         // the output layer: tiles of 32 outputs x 32 coordinates dealt over the waves
@@ -757,30 +707,30 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
             const int Mt = A.layer[L - 1].Mt, nkb = A.layer[L - 1].nkb;
             for (int job = ALONE ? 0 : wave; job < (ALONE ? TC : CT) * Mt; job += ALONE ? 1 : NW) {
                 const int t = ALONE ? wave * TC + job % TC : job % CT, T = job / (ALONE ? TC : CT);
-                const dhq_v4i *wo = reinterpret_cast<const dhq_v4i *>(A.blob + (size_t)A.layer[L - 1].w_off * 1024) + (size_t)T * nkb * 128 + lane;
+                const dhq_v4i *wo = reinterpret_cast<const dhq_v4i *>(A.blob + (size_t)A.layer[L - 1].w_off * 1024) + (size_t)T * nkb * 192 + lane;
                 const dhq_v4i *xo = reinterpret_cast<const dhq_v4i *>(lds + t * ct_bytes) + lane;
                 dhq_v16f o;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[v] = 0.f;
                 for (int kb0 = 0; kb0 < nkb; kb0 += 2) {  // (an even number of k blocks)
-                    dhq_v4i wk[2][2], xk[2][2];
+                    dhq_v4i wk[2][3], xk[2][3];
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
 #pragma unroll
-                        for (int p = 0; p < 2; ++p) {
-                            wk[k][p] = wo[((kb0 + k) * 2 + p) * 64];
-                            xk[k][p] = xo[((kb0 + k) * 2 + p) * 64];
+                        for (int p = 0; p < 3; ++p) {
+                            wk[k][p] = wo[((kb0 + k) * 3 + p) * 64];
+                            xk[k][p] = xo[((kb0 + k) * 3 + p) * 64];
                         }
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) o = flt_mfma<2>(wk[k], xk[k], o);
+                    for (int k = 0; k < 2; ++k) o = flt_mfma6(wk[k], xk[k], o);
                 }
                 const int64_t row = row0 + t * 32 + c;
                 if (row < A.n) {
-                    const float *bo = reinterpret_cast<const float *>(A.blob + (size_t)A.layer[L - 1].b_off * 128) + (T * 2 + h) * 32;
+                    const float *bo = reinterpret_cast<const float *>(A.blob + (size_t)A.layer[L - 1].b_off * 128) + (T * 2 + h) * 16;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int f = 32 * T + 8 * (v >> 2) + 4 * h + (v & 3);
-                        if (f < A.m_out) A.out[row * A.m_out + f] = __builtin_fmaf(o[v], bo[16 + v], bo[v]);
+                        if (f < A.m_out) A.out[row * A.m_out + f] = o[v] + bo[v];
                     }
                 }
             }
@@ -865,107 +815,12 @@ static void host_split3(const float *a, int n, uint16_t *hi, uint16_t *mid, uint
     }
 }
 
-// Nearest binary16 of |v| < 65520 (nearest even, subnormals kept), and its value.
-static inline uint16_t host_f16(float v, float *value)
-{
-    uint32_t u, t;
-    memcpy(&u, &v, 4);
-    const uint32_t a = u & 0x7fffffffu;
-    float m, z;
-    memcpy(&m, &a, 4);
-    // a number of the size of v's binary16 ulp times 2^23, and of 1/2 below 2^-14: the sum keeps v's multiples of that ulp
-    const uint32_t g = (a & 0x7f800000u) + (13u << 23), g0 = 0x3f000000u;
-    t = (int32_t)a >= 0x38800000 ? g : g0;
-    memcpy(&z, &t, 4);
-    float r = (m + z) - z;
-    uint32_t q, n, w;
-    memcpy(&q, &r, 4);
-    n = (q >> 13) - (112u << 10);
-    const float f = r * 0x1p24f;  // below 2^-14: a whole number
-    w = (uint32_t)(int32_t)((int32_t)q >= 0x38800000 ? 0.f : f);
-    const uint32_t sign = u & 0x80000000u, b = ((int32_t)q >= 0x38800000 ? n : w) | (sign >> 16);
-    q |= sign;
-    memcpy(value, &q, 4);
-    return (uint16_t)b;
-}
-// The exponent of the power of two that brings the largest of a row's weights to 2^14 .. 2^15 (0 for a row of zeros);
-// false if there is none (infinities, NaN, or sums whose multiplier would leave fp32).
-static bool host_row_exponent(const float *w, int n, int *e)
-{
-    // (positive floats are ordered like their bits; infinities and NaN come out on top)
-    uint32_t top = 0;
-    for (int i = 0; i < n; ++i) {
-        uint32_t u;
-        memcpy(&u, &w[i], 4);
-        u &= 0x7fffffffu;
-        top = u > top ? u : top;
-    }
-    *e = 0;
-    if (top == 0) return true;
-    if (top >= 0x7f800000u) return false;
-    float mx;
-    memcpy(&mx, &top, 4);
-    int x;
-    (void)frexpf(mx, &x);
-    *e = 15 - x;
-    return *e > -90 && *e < 90;
-}
-// A row of n values times 2^e as two rows of pieces.  With the processor's own conversions where it has them: 1.0 against 3.2 ms
-// for five layers of 512 x 512.
-#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
-#define FLT_HOST_F16C 1
-__attribute__((target("avx2,f16c"))) static void host_split2_f16c(const float *a, int n, float scale, uint16_t *hi, uint16_t *lo)
-{
-    for (int i = 0; i < n; ++i) {
-        const float v = a[i] * scale;
-        const _Float16 h = (_Float16)v, l = (_Float16)(v - (float)h);
-        memcpy(&hi[i], &h, 2);
-        memcpy(&lo[i], &l, 2);
-    }
-}
-#endif
-static void host_split2(const float *a, int n, int e, uint16_t *hi, uint16_t *lo)
-{
-    const float scale = ldexpf(1.f, e);
-#ifdef FLT_HOST_F16C
-    static const bool own = __builtin_cpu_supports("f16c") && __builtin_cpu_supports("avx2");
-    if (own) return host_split2_f16c(a, n, scale, hi, lo);
-#endif
-    for (int i = 0; i < n; ++i) {
-        const float v = a[i] * scale;
-        float h, l;
-        hi[i] = host_f16(v, &h);
-        lo[i] = host_f16(v - h, &l);
-    }
-}
-// Whether the layers after the first can run on two binary16 pieces: in every row, all but a sixteenth of the weights
-// that are not zero are held to fp32 accuracy, i.e. are no smaller than 2^-17 of the row's largest.  (The smallest few of any
-// distribution fall below that and weigh nothing next to the others; a row most of whose weights do could be one whose few
-// large weights meet activations of zero.)
-static bool host_two_pieces(const int *dims, int L, const std::vector<std::vector<float>> &W)
-{
-    for (int l = 1; l < L; ++l)
-        for (int f = 0; f < dims[l + 1]; ++f) {
-            const float *w = W[l].data() + (size_t)f * dims[l];
-            int e, nonzero = 0, small = 0;
-            if (!host_row_exponent(w, dims[l], &e)) return false;
-            const float line = ldexpf(1.f, -3 - e);
-            for (int i = 0; i < dims[l]; ++i) {
-                nonzero += w[i] != 0.f;
-                small += w[i] != 0.f && fabsf(w[i]) < line;
-            }
-            if (small * 16 > nonzero) return false;
-        }
-    return true;
-}
-
 // Fragments, biases and the two activation buffers of the layer-by-layer path.
 static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, double rev, const std::vector<std::vector<float>> &W,
                                   const std::vector<std::vector<float>> &b)
 {
-    int64_t max_kib = 1;  // of the fragments of 32 rows
+    int max_nkb = 1;
     P->narrow = true;
-    P->np = host_two_pieces(dims, L, W) ? 2 : 3;
     size_t w_off[DHQ_MAX_LAYERS], b_off[DHQ_MAX_LAYERS], bytes = 0;
     for (int l = 0; l < L; ++l) {
         float_lw_layer &Ly = P->lw[l];
@@ -973,46 +828,38 @@ static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, dou
         Ly.M = dims[l + 1];
         Ly.nkb = (l == 0) ? (Ly.K + 31) / 32 * 2 : 2 * P->lw[l - 1].Mt;  // even
         Ly.Mt = (Ly.M + 31) / 32;
-        Ly.np = (l == 0) ? 3 : P->np;
-        max_kib = std::max(max_kib, (int64_t)Ly.nkb * Ly.np);
+        if (Ly.nkb > max_nkb) max_nkb = Ly.nkb;
         if (Ly.nkb > 4) P->narrow = false;
         w_off[l] = bytes;
-        b_off[l] = bytes + (size_t)Ly.Mt * Ly.nkb * Ly.np * 1024;
-        bytes = (b_off[l] + (size_t)Ly.Mt * 256 + 1023) / 1024 * 1024;
+        b_off[l] = bytes + (size_t)Ly.Mt * Ly.nkb * 3072;
+        bytes = (b_off[l] + (size_t)Ly.Mt * 128 + 1023) / 1024 * 1024;
     }
     std::vector<unsigned char> blob(bytes, 0);
     for (int l = 0; l < L; ++l) {
         const float_lw_layer &Ly = P->lw[l];
         uint16_t *frag = reinterpret_cast<uint16_t *>(blob.data() + w_off[l]);
         std::vector<uint16_t> pieces((size_t)3 * Ly.nkb * 16, 0);  // of one row, zero beyond K
-        float *bias = reinterpret_cast<float *>(blob.data() + b_off[l]);
         for (int f = 0; f < Ly.M; ++f) {
             uint16_t *row[3] = {pieces.data(), pieces.data() + Ly.nkb * 16, pieces.data() + 2 * Ly.nkb * 16};
-            const float *w = W[l].data() + (size_t)f * Ly.K;
-            int e = 0;  // of the power of two in the sums
-            if (Ly.np == 3) {
-                host_split3(w, Ly.K, row[0], row[1], row[2]);
-            } else {
-                (void)host_row_exponent(w, Ly.K, &e);
-                (void)host_split2(w, Ly.K, e, row[0], row[1]);
-                e += FLT_ACT_EXPONENT;
-            }
-            // flt_feature(16 T + v, h) = f
-            const int v = 4 * ((f >> 3) & 3) + (f & 3), h = (f >> 2) & 1;
-            float *bm = bias + (size_t)((f >> 5) * 2 + h) * 32 + v;
-            bm[0] = (l != L - 1) ? (float)((double)b[l][f] * rev) : b[l][f];
-            bm[16] = ldexpf((l != L - 1) ? P->rev : 1.f, -e);
+            host_split3(W[l].data() + (size_t)f * Ly.K, Ly.K, row[0], row[1], row[2]);
             for (int kb = 0; kb < Ly.nkb; ++kb)
                 for (int h = 0; h < 2; ++h) {
                     // slots 0..3 and 4..7 of a lane are four consecutive k each
                     const int k0 = (l == 0) ? 16 * kb + 8 * h : flt_feature(8 * kb, h), k4 = (l == 0) ? k0 + 4 : flt_feature(8 * kb + 4, h);
-                    uint16_t *dst = frag + ((size_t)((f >> 5) * Ly.nkb + kb) * Ly.np * 64 + 32 * h + (f & 31)) * 8;
-                    for (int p = 0; p < Ly.np; ++p) {
+                    uint16_t *dst = frag + ((size_t)((f >> 5) * Ly.nkb + kb) * 3 * 64 + 32 * h + (f & 31)) * 8;
+                    for (int p = 0; p < 3; ++p) {
                         memcpy(dst + (size_t)p * 512, row[p] + k0, 8);
                         memcpy(dst + (size_t)p * 512 + 4, row[p] + k4, 8);
                     }
                 }
         }
+        float *bias = reinterpret_cast<float *>(blob.data() + b_off[l]);
+        for (int T = 0; T < Ly.Mt; ++T)
+            for (int h = 0; h < 2; ++h)
+                for (int v = 0; v < 16; ++v) {
+                    const int f = flt_feature(16 * T + v, h);
+                    if (f < Ly.M) bias[(size_t)(T * 2 + h) * 16 + v] = (l != L - 1) ? (float)((double)b[l][f] * rev) : b[l][f];
+                }
     }
     if (hipMalloc((void **)&P->lw_blob_dev, bytes) != hipSuccess) return DHQ_ENOMEM;
     if (hipMemcpy(P->lw_blob_dev, blob.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return DHQ_EHIP;
@@ -1033,17 +880,13 @@ static int float_create_layerwise(dhq_float_plan *P, const int *dims, int L, dou
     P->net.k0 = dims[0];
     P->net.m_out = dims[L];
     P->net.max_kb = 2 * P->max_mt;
+    P->net.rev = P->rev;
     P->net.c2 = P->actf.c2;
     // bytes of 32 rows of the widest hidden layer: fragments, or floats in the narrow networks
-    int max_mt = 1;
-    for (int l = 0; l < L - 1; ++l) max_mt = P->lw[l].Mt > max_mt ? P->lw[l].Mt : max_mt;
-    const int64_t tile_bytes = P->narrow ? (int64_t)max_mt * 4096 : max_kib * 1024;
+    const int max_mt = std::max(P->max_mt, 1);
+    const int64_t tile_bytes = P->narrow ? (int64_t)max_mt * 4096 : (int64_t)max_nkb * 3072;
     P->chunk_rows = ((P->narrow ? FLT_ACT_BYTES_NARROW : FLT_ACT_BYTES) / tile_bytes * 32) / 256 * 256;
     if (dhq_float_shape_ok(dims, L) && dims[1] != 256 && P->chunk_rows > DHQ_CHUNK) P->chunk_rows = DHQ_CHUNK;
-    // Chunks of whole rounds of workgroups in the widest layer's launch (a tile of 128 features x 256 coordinates per CU and
-    // round).  512 wide, 262 144 rows: 5 x 49 152 + 16 384 rows, 16 rounds a layer; in six equal chunks, 18.
-    const int64_t row_blocks = P->chunk_rows / 256, nF = (max_mt + 3) / 4, rounds = row_blocks * nF / P->n_cu;
-    P->chunk_step = rounds > 0 ? rounds * P->n_cu / nF * 256 : P->chunk_rows;
     const size_t act_bytes = (size_t)(P->chunk_rows / 32 * tile_bytes);
     if (hipMalloc((void **)&P->act[0], 2 * act_bytes) != hipSuccess) return DHQ_ENOMEM;
     P->act[1] = P->act[0] + act_bytes;
@@ -1060,11 +903,11 @@ void dhq_float_destroy(dhq_float_plan *P)
 
 bool dhq_float_has_fused(const dhq_float_plan *P) { return P && P->nf != 0; }
 
-template <int ACT, int NP, int NPO, int WF, int WC, int TF, int TC, int KS>
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
 static hipError_t float_layer_launch_t(float_layer_args a, int device, hipStream_t st)
 {
-    using tile_t = float_layer_tile<NP, WF, WC, TF, TC, KS>;
-    auto kern = float_layer_kernel<ACT, NP, NPO, WF, WC, TF, TC, KS>;
+    using tile_t = float_layer_tile<ACT, WF, WC, TF, TC, KS>;
+    auto kern = float_layer_kernel<ACT, WF, WC, TF, TC, KS>;
     const size_t lds = (size_t)3 * tile_t::BLOCKS * 1024;
     const hipError_t e = dhq_lds_limit_once(kern, lds, device);
     if (e != hipSuccess) return e;
@@ -1080,51 +923,41 @@ static hipError_t float_layer_launch_t(float_layer_args a, int device, hipStream
 //   width 512 x 65 536 rows  559  605  603  891        width 300 x 33 000 rows  167  155  184  244
 //   width 512 x 9 000 rows   139  139  139  160        width 100 x 100 000 rows 118  135  136  160
 //   width 512 x 4 000 rows   137   96   98   84        width 48 x 100 000 rows   76   71   91  110
-template <int ACT, int NP, int NPO>
+template <int ACT>
 static hipError_t float_layer_launch(const float_layer_args &a, int n_cu, int device, hipStream_t st)
 {
     const int64_t f4 = (a.n_ft + 3) / 4, f2 = (a.n_ft + 1) / 2, c8 = (a.n_ct + 7) / 8, c4 = (a.n_ct + 3) / 4;
     auto cost = [&](int64_t workgroups, int64_t each) { return (workgroups + n_cu - 1) / n_cu * each; };
     const int64_t c128x256 = cost(f4 * c8, 32), c64x256 = cost(f2 * c8, 19), c128x128 = cost(f4 * c4, 19), c128x32 = cost(f4 * a.n_ct, 8);
     const int64_t least = std::min(std::min(c128x256, c64x256), std::min(c128x128, c128x32));
-    if (c128x32 == least) return float_layer_launch_t<ACT, NP, NPO, 4, 1, 1, 1, 2>(a, device, st);
-    if (c128x128 == least) return float_layer_launch_t<ACT, NP, NPO, 2, 2, 2, 2, 2>(a, device, st);
-    if (c64x256 == least) return float_layer_launch_t<ACT, NP, NPO, 1, 4, 2, 2, 2>(a, device, st);
-    return float_layer_launch_t<ACT, NP, NPO, 1, 4, 4, 2, 1>(a, device, st);
+    if (c128x32 == least) return float_layer_launch_t<ACT, 4, 1, 1, 1, 2>(a, device, st);
+    if (c128x128 == least) return float_layer_launch_t<ACT, 2, 2, 2, 2, 2>(a, device, st);
+    if (c64x256 == least) return float_layer_launch_t<ACT, 1, 4, 2, 2, 2>(a, device, st);
+    return float_layer_launch_t<ACT, 1, 4, 4, 2, 1>(a, device, st);
 }
 
-template <int ACT>
-static hipError_t float_layer_launch(const float_lw_layer &Ly, int np, const float_layer_args &a, int n_cu, int device, hipStream_t st)
-{
-    if (Ly.np == 2) return float_layer_launch<ACT, 2, 2>(a, n_cu, device, st);
-    return np == 2 ? float_layer_launch<ACT, 3, 2>(a, n_cu, device, st) : float_layer_launch<ACT, 3, 3>(a, n_cu, device, st);
-}
-
-template <int ACT, int NP, int NT, bool FIRST, bool LAST>
+template <int ACT, int NT, bool FIRST, bool LAST>
 static hipError_t float_narrow_launch_t(const float_narrow_args &a, int nkb, int m_tiles, int n_cu, hipStream_t st)
 {
     const int want = (a.n_ct + 3) / 4, most = 4 * n_cu;
     const dim3 grid((unsigned)(want < most ? want : most), (unsigned)(LAST ? m_tiles : 1));
-    if (nkb == 2) float_narrow_kernel<ACT, NP, NT, 2, FIRST, LAST><<<grid, 256, 0, st>>>(a);
-    else float_narrow_kernel<ACT, NP, NT, 4, FIRST, LAST><<<grid, 256, 0, st>>>(a);
+    if (nkb == 2) float_narrow_kernel<ACT, NT, 2, FIRST, LAST><<<grid, 256, 0, st>>>(a);
+    else float_narrow_kernel<ACT, NT, 4, FIRST, LAST><<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
-}
-template <int ACT, int NP>
-static hipError_t float_narrow_inner(const float_lw_layer &Ly, bool last, const float_narrow_args &a, int n_cu, hipStream_t st)
-{
-    if (last) return float_narrow_launch_t<DHQ_ACT_KIND_NONE, NP, 1, false, true>(a, Ly.nkb, Ly.Mt, n_cu, st);
-    return Ly.Mt == 1 ? float_narrow_launch_t<ACT, NP, 1, false, false>(a, Ly.nkb, 1, n_cu, st)
-                      : float_narrow_launch_t<ACT, NP, 2, false, false>(a, Ly.nkb, 1, n_cu, st);
 }
 template <int ACT>
 static hipError_t float_narrow_launch(const dhq_float_plan *P, int l, const float_narrow_args &a, hipStream_t st)
 {
     const float_lw_layer &Ly = P->lw[l];
-    const bool last = (l == P->n_layers - 1);
-    if (l > 0) return Ly.np == 2 ? float_narrow_inner<ACT, 2>(Ly, last, a, P->n_cu, st) : float_narrow_inner<ACT, 3>(Ly, last, a, P->n_cu, st);
-    if (last) return float_narrow_launch_t<DHQ_ACT_KIND_NONE, 3, 1, true, true>(a, Ly.nkb, Ly.Mt, P->n_cu, st);
-    return Ly.Mt == 1 ? float_narrow_launch_t<ACT, 3, 1, true, false>(a, Ly.nkb, 1, P->n_cu, st)
-                      : float_narrow_launch_t<ACT, 3, 2, true, false>(a, Ly.nkb, 1, P->n_cu, st);
+    const bool first = (l == 0), last = (l == P->n_layers - 1);
+    if (last)
+        return first ? float_narrow_launch_t<DHQ_ACT_KIND_NONE, 1, true, true>(a, Ly.nkb, Ly.Mt, P->n_cu, st)
+                     : float_narrow_launch_t<DHQ_ACT_KIND_NONE, 1, false, true>(a, Ly.nkb, Ly.Mt, P->n_cu, st);
+    if (Ly.Mt == 1)
+        return first ? float_narrow_launch_t<ACT, 1, true, false>(a, Ly.nkb, 1, P->n_cu, st)
+                     : float_narrow_launch_t<ACT, 1, false, false>(a, Ly.nkb, 1, P->n_cu, st);
+    return first ? float_narrow_launch_t<ACT, 2, true, false>(a, Ly.nkb, 1, P->n_cu, st)
+                 : float_narrow_launch_t<ACT, 2, false, false>(a, Ly.nkb, 1, P->n_cu, st);
 }
 
 hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
@@ -1132,7 +965,8 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
     if (!P) return hipErrorInvalidValue;
     const int L = P->n_layers;
     if (n <= 0) return hipSuccess;
-    const int64_t step = n <= P->chunk_rows ? n : P->chunk_step;
+    // as few chunks as the buffers allow, of equal size
+    const int64_t chunks = (n + P->chunk_rows - 1) / P->chunk_rows, per = (n + chunks - 1) / chunks, step = (per + 255) / 256 * 256;
     for (int64_t start = 0; start < n; start += step) {
         const int64_t rows = (n - start < step) ? n - start : step;
         const int n_ct = (int)((rows + 31) / 32);
@@ -1149,6 +983,7 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
                 a.n_ct = n_ct;
                 a.K = Ly.K;
                 a.M = Ly.M;
+                a.rev = P->rev;
                 a.c2 = P->actf.c2;
                 const hipError_t e = P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_narrow_launch<DHQ_ACT_KIND_WAVELET>(P, l, a, st)
                                                                           : float_narrow_launch<DHQ_ACT_KIND_SINE>(P, l, a, st);
@@ -1165,8 +1000,7 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
             const float_lw_layer &Ly = P->lw[l];
             if (l == L - 1) {
                 const dim3 grid((unsigned)((n_ct + 3) / 4), (unsigned)Ly.Mt);
-                auto kern = Ly.np == 2 ? float_out_kernel<2> : float_out_kernel<3>;
-                kern<<<grid, 256, 0, st>>>(P->act[l & 1], Ly.wfrag_dev, Ly.bias_dev, rows, n_ct, Ly.nkb, Ly.M, out + start * Ly.M);
+                float_out_kernel<<<grid, 256, 0, st>>>(P->act[l & 1], Ly.wfrag_dev, Ly.bias_dev, rows, n_ct, Ly.nkb, Ly.M, out + start * Ly.M);
                 e = hipGetLastError();
             } else {
                 float_layer_args a;
@@ -1178,9 +1012,10 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
                 a.n_ct = n_ct;
                 a.n_ft = Ly.Mt;
                 a.nkb = Ly.nkb;
+                a.rev = P->rev;
                 a.c2 = P->actf.c2;
-                e = P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_layer_launch<DHQ_ACT_KIND_WAVELET>(Ly, P->np, a, P->n_cu, P->device, st)
-                                                         : float_layer_launch<DHQ_ACT_KIND_SINE>(Ly, P->np, a, P->n_cu, P->device, st);
+                e = P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_layer_launch<DHQ_ACT_KIND_WAVELET>(a, P->n_cu, P->device, st)
+                                                         : float_layer_launch<DHQ_ACT_KIND_SINE>(a, P->n_cu, P->device, st);
             }
             if (e != hipSuccess) return e;
         }
@@ -1188,32 +1023,42 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
     return hipSuccess;
 }
 
-template <int ACT, int WF, int WC, int TF, int TC, int D>
-static hipError_t float_net_launch_t(const dhq_float_plan *P, float_net_args a, hipStream_t st)
+// Whether float_net_kernel takes a network and n rows (the values are the same).  Its tiles hold six bytes a hidden feature and coordinate
+// in LDS: two of 32 coordinates up to 13 feature tiles, one beyond, where the weights' way into the registers takes longer than the
+// layer-by-layer kernels' way through memory, except in the few rows that leave those short of workgroups.
+static bool float_net_takes(const dhq_float_plan *P, int64_t n)
 {
-    static_assert(64 * WF * WC >= 16 * WF * TF, "a thread carries one float4 of a layer's biases and multipliers");
-    auto kern = float_net_kernel<ACT, WF, WC, TF, TC, D>;
-    const size_t lds = (size_t)WC * TC * a.max_kb * 2048 + (size_t)P->max_mt * 256;
+    const int64_t round = 32 * (int64_t)P->n_cu;
+    return P->n_layers >= 2 && (P->max_mt <= 13 || (n > round / 4 && n <= round));
+}
+
+template <int ACT, int WF, int WC, int TF, int TC, int KS>
+static hipError_t float_net_launch_t(const dhq_float_plan *P, float_net_args a, int waves_per_cu, hipStream_t st)
+{
+    static_assert(64 * WF * WC >= 8 * WF * TF, "a thread carries one float4 of a layer's biases");
+    auto kern = float_net_kernel<ACT, WF, WC, TF, TC, KS>;
+    const size_t lds = (size_t)WC * TC * a.max_kb * 3072 + (size_t)P->max_mt * 128;
+    if (P->max_mt > WF * TF || lds > 160 * 1024) return hipErrorInvalidValue;
     const hipError_t e = dhq_lds_limit_once(kern, 160 * 1024, P->device);
     if (e != hipSuccess) return e;
     const int64_t rows = 32 * WC * TC, blocks = (a.n + rows - 1) / rows;
-    const int per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 8 / (WF * WC)));
+    const int per_cu = std::max(1, std::min((int)(160 * 1024 / lds), waves_per_cu / (WF * WC)));
     a.n_blocks = (int)blocks;
     const int64_t most = (int64_t)P->n_cu * per_cu;
     kern<<<(unsigned)(blocks < most ? blocks : most), 64 * WF * WC, lds, st>>>(a);
     return hipGetLastError();
 }
 // The tile of a workgroup, by the widest hidden layer's feature tiles and the rows: few rows take small tiles, as long as the
-// launch is one round of the chip (`round`: rows of a tile of 32 per CU; two workgroups of four waves fit a CU, eight of one);
-// beyond, the tile with the fewest weight bytes per product.  Whole forwards in us (four hidden layers; 512: five), tiles of
-// 32 / 64 / 128 / 256 rows, against layer by layer with six products (in brackets; widths 32, 64, 128: the fp32 MFMA kernel that
-// DHQ_AUTO had there):
-//   rows          4 096                        16 384                       65 536                    262 144
-//   width 32    6.7 (6.8)                    6.7 (6.9)                    8.3/ -/8.9 (11.4)         26/ -/23 (39)
-//   width 64    -/8.2/11.3/17 (13.6)         -/8.5/11.3/18 (13.8)         -/18/13.4/18 (25)         -/66/49/44 (93)
-//   width 128   9.3/12.7/19 (36)             11.7/13.1/19 (35)            43/34/30 (69)             157/123/107 (278)
-//   width 256   20/30 (50)                   44/35 (89)                   168/110 (235)             654/434 (928)
-//   width 512   59/92 (105)                  130/105 (210)                513/418 (715)             1980/1620 (2830)
+// launch is one round of the chip (`round`: rows of a tile of 32 per CU); beyond, more coordinates share a weight fragment.
+// Whole forwards in us, four hidden layers (512: five), by the rows of a tile, and layer by layer in brackets:
+//   rows          4 096               16 384                65 536                  262 144
+//   width 32    6.8 (16)            7.2 (16)              8.7 (21)                26 (84)
+//   width 64    32: 9.6 (20)        32: 10.0 (21)         32: 20.6, 64: 16 (36)   32: 76, 64: 59 (144)
+//   width 128   32: 12, 64: 16 (29) 32: 15, 64: 17 (44)   32: 51, 64: 46 (92)     64: 165, 96: 158 (371)
+//   width 256   23 (43)             43 (73)               150 (187)               584 (744); 96 with eight waves: 580
+//   width 300   32: 38, 64: 62 (60) 32: 76, 64: 67 (106)  32: 299, 64: 259 (358)  32: 1155, 64: 1003 (1491)
+//   width 400   32: 52, 64: 88 (76) 32: 116, 64: 97 (138) 32: 434, 64: 378 (452)  32: 1678, 64: 1476 (1820)
+//   width 512   91 (106)            206 (213)             812 (727)               3164 (2895)
 template <int ACT>
 static hipError_t float_net_launch(const dhq_float_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
@@ -1221,26 +1066,24 @@ static hipError_t float_net_launch(const dhq_float_plan *P, const float *coords,
     a.coords = coords;
     a.out = out;
     a.n = n;
-
     const int64_t round = 32 * (int64_t)P->n_cu;
-    if (P->max_mt > 8) return n <= round ? float_net_launch_t<ACT, 8, 1, 2, 1, 2>(P, a, st) : float_net_launch_t<ACT, 8, 1, 2, 2, 2>(P, a, st);
-    if (P->max_mt > 4) return n <= round ? float_net_launch_t<ACT, 8, 1, 1, 1, 2>(P, a, st) : float_net_launch_t<ACT, 4, 1, 2, 2, 2>(P, a, st);
+    if (P->max_mt > 8)
+        return n <= round || P->max_mt > 13 ? float_net_launch_t<ACT, 8, 1, 2, 1, 1>(P, a, 8, st) : float_net_launch_t<ACT, 8, 1, 2, 2, 1>(P, a, 8, st);
+    if (P->max_mt > 4) return float_net_launch_t<ACT, 4, 1, 2, 1, 1>(P, a, 12, st);
     if (P->max_mt > 2)
-        return n <= 2 * round   ? float_net_launch_t<ACT, 4, 1, 1, 1, 2>(P, a, st)
-               : n <= 4 * round ? float_net_launch_t<ACT, 4, 1, 1, 2, 2>(P, a, st)
-                                : float_net_launch_t<ACT, 2, 2, 2, 2, 2>(P, a, st);
+        return n <= 2 * round   ? float_net_launch_t<ACT, 4, 1, 1, 1, 2>(P, a, 8, st)
+               : n <= 8 * round ? float_net_launch_t<ACT, 4, 1, 1, 2, 2>(P, a, 12, st)
+                                : float_net_launch_t<ACT, 4, 1, 1, 3, 1>(P, a, 8, st);
     if (P->max_mt > 1)
-        return n <= 4 * round   ? float_net_launch_t<ACT, 2, 2, 1, 1, 2>(P, a, st)
-               : n <= 8 * round ? float_net_launch_t<ACT, 2, 2, 1, 2, 2>(P, a, st)
-                                : float_net_launch_t<ACT, 1, 4, 2, 2, 2>(P, a, st);
-    return n <= 8 * round ? float_net_launch_t<ACT, 1, 1, 1, 1, 2>(P, a, st) : float_net_launch_t<ACT, 1, 4, 1, 2, 2>(P, a, st);
+        return n <= 4 * round ? float_net_launch_t<ACT, 2, 2, 1, 1, 2>(P, a, 8, st) : float_net_launch_t<ACT, 2, 2, 1, 2, 2>(P, a, 8, st);
+    return float_net_launch_t<ACT, 1, 1, 1, 1, 2>(P, a, 12, st);
 }
 
 hipError_t dhq_float_launch(const dhq_float_plan *P, const float *coords, int64_t n, float *out, hipStream_t st)
 {
     if (!P) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
-    if (P->np != 2 || P->n_layers < 2) return dhq_float_launch_layerwise(P, coords, n, out, st);
+    if (!float_net_takes(P, n)) return dhq_float_launch_layerwise(P, coords, n, out, st);
     return P->actf.kind == DHQ_ACT_KIND_WAVELET ? float_net_launch<DHQ_ACT_KIND_WAVELET>(P, coords, n, out, st)
                                                 : float_net_launch<DHQ_ACT_KIND_SINE>(P, coords, n, out, st);
 }

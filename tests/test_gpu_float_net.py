@@ -1,4 +1,4 @@
-"""fp32-activation networks: the whole-network kernel against the layer-by-layer kernels, and weights that two binary16 pieces do not hold."""
+"""fp32-activation networks: the whole-network kernel against the layer-by-layer kernels, and weights and activations of every size."""
 import numpy as np
 import pytest
 
@@ -47,5 +47,32 @@ def test_weights_of_very_different_sizes(width):
         out = m.forward(torch.from_numpy(x).to("cuda"), flags=flags)
         err = np.abs(out.cpu().numpy().astype(np.float64) - exp).max()
         print(f"[float net] width {width} flags {flags}: max-abs err {err:.2e}", flush=True)
+        assert err <= FLOAT_TOL_WIDE
+    m.close()
+
+
+@pytest.mark.parametrize("scale", [1e-4, 1e-8, 1e-10])
+@pytest.mark.parametrize("width", [32, 48, 128, 256, 300, 512])
+@pytest.mark.parametrize("s0", [None, 10.0], ids=["sine", "wavelet"])
+def test_small_activations(s0, width, scale):
+    """A first layer whose activations are all of the size of `scale` (small arguments; the tail of the wavelet's envelope), a second one
+    whose weights bring them back: fp32 accuracy does not depend on a value's size.  The second layer's arguments, up to about 100
+    radians, are rounded to 2^-24 of themselves, 6e-6, which the output layer's weights (sqrt(6 / K) / 30, K of them with random
+    signs) take to 5e-7, and a few such roundings to a few times that; a scale that a layer shares leaves 1e-4 and more."""
+    import torch
+    dims = [2, width, width, 3]
+    W, b = synth.siren_init(dims, 30.0, 5)
+    if s0 is None:
+        W[0], b[0] = (W[0] * np.float32(scale)).astype(np.float32), (b[0] * np.float32(scale)).astype(np.float32)
+    else:
+        W[0] = (W[0] * np.float32(1e-3)).astype(np.float32)
+        b[0][:] = np.sqrt(-np.log(scale)) / s0
+    W[1] = (W[1] / np.float32(scale)).astype(np.float32)
+    x = synth.grid_coords(30)
+    exp, _ = o.mlp_float(dims, 30.0, W, b, x, **({"gabor_s0": s0} if s0 is not None else {}))
+    m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
+    for flags in (dhq.DHQ_AUTO, dhq.DHQ_LAYERWISE):
+        err = np.abs(m.forward(torch.from_numpy(x).to("cuda"), flags=flags).cpu().numpy().astype(np.float64) - exp).max()
+        print(f"[float net] width {width} s0={s0} scale {scale} flags {flags}: max-abs err {err:.2e}", flush=True)
         assert err <= FLOAT_TOL_WIDE
     m.close()

@@ -534,7 +534,7 @@ def test_variant_flags_are_checked():
 
 
 # --------------------------------------------- floating-point activations (W32A32, W8A32)
-FLOAT_TOL = 1e-6    # fp32 MFMA accumulation + hardware sine against the fp64 oracle (outputs are O(0.1); measured 1.3e-7)
+FLOAT_TOL = 1e-6    # fp32 sums of products of bf16 pieces + hardware sine against the fp64 oracle (outputs are O(0.1); measured 1.3e-7)
 
 
 @pytest.mark.parametrize("name", ["C1", "C2"])
@@ -577,8 +577,8 @@ FLOAT_TOL_WIDE = 4e-6   # the same arithmetic with up to 512 terms per sum and u
 def test_w32a32_layer_by_layer_any_shape(dims):
     """The layer-by-layer fp32 path: every shape the library accepts (widths that are no multiple of 8 or
     32, one to sixteen layers, 512 on every side), ragged rows, more rows than one workspace chunk; on
-    the shapes that also have the whole-network kernel (equal widths of 32, 64, 128) the two paths are compared as well,
-    and at width 256, where DHQ_FUSED is accepted and runs the same kernels, they give the same bits."""
+    the shapes that DHQ_FUSED is accepted for the two paths are compared as well (DHQ_AUTO and DHQ_LAYERWISE give the same bits
+    in every shape, tests/test_gpu_float_net.py)."""
     torch = _torch()
     W, b = synth.siren_init(dims, 30.0, 199 + len(dims) + dims[0])
     m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32)
