@@ -1025,11 +1025,27 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
 
 // Whether float_net_kernel takes a network and n rows (the values are the same).  Its tiles hold six bytes a hidden feature and coordinate
 // in LDS: two of 32 coordinates up to 13 feature tiles, one beyond, where the weights' way into the registers takes longer than the
-// layer-by-layer kernels' way through memory, except in the few rows that leave those short of workgroups.
+// layer-by-layer kernels' way through memory, except in the few rows that leave those short of workgroups.  Every wave of a tile
+// loads and splits its coordinates for itself, and an output tile is one wave's, which large fan-ins and fan-outs make the
+// longest part.  Whole forwards in us, here / layer by layer, by rows:
+//                          100          1 000        5 000        20 000       65 536       262 144
+//   2 x 400 (six layers)   88 / 77      87 / 81      86 / 127     294 / 291    614 / 713    2411 / 3206
+//   64 x 256 x 256 x 3     17 / 22      18 / 23      18 / 31      37 / 53      90 / 111     346 / 418
+//   256 x 256 x 256 x 256  37 / 32      37 / 34      38 / 51      87 / 93      230 / 204    870 / 841
+//   512 x 128 x 128 x 3    42 / 25      43 / 27      43 / 38      127 / 66     247 / 172    1005 / 778
+//   512 x 64 x 64 x 3      43 / 22      43 / 24      43 / 34      77 / 59      126 / 154    511 / 707
+//   512 x 32 x 32 x 3      22 / 21      23 / 23      22 / 32      39 / 55      75 / 145     289 / 663
+//   2 x 256 x 256 x 512    35 / 25      36 / 25      40 / 44      74 / 151     193 / 456    767 / 1823
+//   2 x 128 x 128 x 300    20 / 19      21 / 20      22 / 26      47 / 78      100 / 161    415 / 691
+//   2 x 64 x 64 x 512      40 / 13      43 / 13      44 / 20      53 / 49      110 / 105    565 / 428
 static bool float_net_takes(const dhq_float_plan *P, int64_t n)
 {
     const int64_t round = 32 * (int64_t)P->n_cu;
-    return P->n_layers >= 2 && (P->max_mt <= 13 || (n > round / 4 && n <= round));
+    const int L = P->n_layers, K = P->lw[0].K, mt = P->max_mt;
+    if (L < 2) return false;
+    if (mt > 13 ? n <= round / 4 || n > round : mt > 11 && n <= round / 4) return false;
+    if (K > 64 && !(mt == 1 && (K <= 256 || n > 1024)) && !(mt == 2 && n > 4 * round)) return false;
+    return P->lw[L - 1].Mt == 1 || (mt > 2 && n > round / 2);
 }
 
 template <int ACT, int WF, int WC, int TF, int TC, int KS>
