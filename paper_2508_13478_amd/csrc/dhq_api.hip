@@ -747,27 +747,42 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
     const bool one_chunk = n <= DHQ_CHUNK;
     float *const partial = reinterpret_cast<float *>(m->dyn_absmax + DHQ_MAX_LAYERS);
     float *const params = m->dyn_params + 3 * DHQ_MAX_LAYERS;  // like the dynamic forward's, which keep its last call's scales
-    auto finish = [&]() {
+    float scale[DHQ_MAX_LAYERS];
+    auto fetch = [&]() {
         // into pinned memory: a copy into pageable memory is staged, 24 us more of a calibration
         float pageable[3 * DHQ_MAX_LAYERS], *const host = m->cal_host ? m->cal_host : pageable;
         if (hipMemcpyAsync(host, params, sizeof(float) * 3 * L, hipMemcpyDeviceToHost, st) != hipSuccess) return DHQ_EHIP;
         if (hipStreamSynchronize(st) != hipSuccess) return DHQ_EHIP;
-        for (int l = 0; l < L; ++l) m->layer[l].s_a = host[3 * l + 2];
+        for (int l = 0; l < L; ++l) scale[l] = host[3 * l + 2];
         return DHQ_OK;
     };
-    // Whether a layer's dequantized sums (at most 2^22 steps of c1) may be infinite, its activations NaN and the codes of those
-    // their signs, which each kernel leaves as its sums are ordered: infinite or huge coordinates.  The general path then decides.
-    auto unbounded = [&]() {
-        for (int l = 0; l < L; ++l)
-            if (!(fabs(dhq_c1_over_sa(m, l) * (double)m->layer[l].s_a) < 0x1p100)) return true;
-        return false;
+    auto store = [&]() {
+        for (int l = 0; l < L; ++l) m->layer[l].s_a = scale[l];
+        return DHQ_OK;
     };
-    if (const dhq_fused_plan *P = m->fused ? m->fused : per_layer_padded(m)) {
+    // Where an activation or a sum of its transform may be infinite or no number, a maximum leaves it out, and its codes are the signs that each
+    // kernel's sums leave as they are ordered: the general path then decides.  Dequantized sums are at most 2^22 steps of c1, which
+    // infinite or huge coordinates raise; that leaves the biases, and the complex wavelet's modulus.
+    auto sums_bounded = [&]() {
+        for (int l = 0; l < L; ++l)
+            if (!(fabs(dhq_c1_over_sa(m, l) * (double)scale[l]) < 0x1p100)) return false;
+        return true;
+    };
+    auto activations_bounded = [&]() {
+        for (int l = 0; l < L - 1; ++l)
+            for (float b : m->layer[l].bias_rev_host)
+                if (!(fabsf(b) < 0x1p100f)) return false;
+        return m->act_kind != DHQ_ACT_KIND_WAVELET_COMPLEX ||
+               dhq_complex_log2_modulus(dhq_hidden_act(m).c2, INFINITY) + log2((double)m->max_kp) < 126.0;
+    };
+    const dhq_fused_plan *const P = m->fused ? m->fused : per_layer_padded(m);
+    if (P && activations_bounded()) {
         void *const buf[2] = {m->act0, m->act1};
         const hipError_t e = dhq_fused_measure_launch(m, P, coords_dev, n, buf, sizeof(float) * DHQ_CHUNK * m->max_dim, partial, params, st);
         if (e == hipSuccess) {
-            const int rc = finish();
-            if (rc != DHQ_OK || !unbounded()) return rc;
+            const int rc = fetch();
+            if (rc != DHQ_OK) return rc;
+            if (sums_bounded()) return store();
         } else if (e != hipErrorInvalidValue) return DHQ_EHIP;
     }
     if (dhq_launch_clear_words(m->dyn_absmax, L, st) != hipSuccess) return DHQ_EHIP;
@@ -811,7 +826,8 @@ static int calibrate_codes(dhq_model *m, const float *coords_dev, int64_t n, hip
             if (dhq_launch_wht_quant(res, rows, Ly.K, Ly.Kp, 0.0f, m->qmax_a, codes_at(off), &fold, st) != hipSuccess) return DHQ_EHIP;
         }
     }
-    return finish();
+    const int rc = fetch();
+    return rc == DHQ_OK ? store() : rc;
 }
 
 extern "C" int dhq_calibrate(dhq_model *m, const float *coords_dev, int64_t n, void *stream)

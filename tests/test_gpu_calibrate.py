@@ -66,3 +66,42 @@ def test_a_coordinate_beyond_the_range(dims, s0, value):
     got, exp = _scales(m, x)
     assert np.array_equal(got, exp, equal_nan=True)
     m.close()
+
+
+@pytest.mark.parametrize("dims,s0,imag", [([2, 32, 32, 3], 1.0, 4.0), ([2, 32, 32, 32, 3], 0.5, 16.0), ([2, 128, 128, 3], 1.0, 8.0), ([2, 90, 90, 2], 0.8, 8.0),
+                                          ([1, 16, 16, 1], 1.0, 8.0), ([2, 64, 64, 64, 3], 1.2, 4.0), ([3, 100, 3], 1.0, 8.0)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, list) else str(v))
+def test_complex_moduli_beyond_fp32(dims, s0, imag):
+    """A wide envelope's modulus, up to exp(omega0^2 / 4 s0^2) = 2^325 at s0 = 1, is infinite at arguments of ordinary size.  The whole
+    transform of such a coordinate is no number, which a maximum leaves out: with the other rows' the layer's scale is an ordinary
+    one, and that coordinate's codes are the general path's."""
+    import torch
+    rng = np.random.default_rng(dims[1])
+    W, b = synth.wire_init(dims, 30.0, 3)
+    W[0] = (rng.uniform(-0.5, 0.5, W[0].shape) + 2j * imag * rng.uniform(-0.5, 0.5, W[0].shape)).astype(np.complex64)
+    b[0] = b[0] * 0
+    m = dhq.Model.complex_wavelet(dims, 30.0, W, b, s0, 8, 8)
+    x = torch.rand((5003, dims[0]), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") * 2 - 1
+    corners = torch.sign(x[::50])
+    x *= 1e-2 / imag
+    x[::50] = corners
+    print(f"[calibrate] complex {dims} s0={s0}", flush=True)
+    got, exp = _scales(m, x)
+    print(f"  scales {got}", flush=True)
+    assert np.array_equal(got, exp, equal_nan=True)
+    m.close()
+
+
+@pytest.mark.parametrize("bias", [3.0e38, -3.0e38, 1.0e32])
+@pytest.mark.parametrize("dims", [[2, 64, 64, 64, 3], [3, 200, 200, 2]], ids=lambda d: "x".join(map(str, d)))
+def test_a_bias_beyond_the_range(dims, bias):
+    """A feature whose argument is infinite or huge in every row: the codes of the layer's output are the general path's."""
+    import torch
+    W, b = synth.siren_init(dims, 30.0, 5)
+    b[0][3] = bias
+    m = dhq.Model(dims, 30.0, W, b)
+    x = torch.rand((3001, dims[0]), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") * 2 - 1
+    print(f"[calibrate] {dims} bias {bias}", flush=True)
+    got, exp = _scales(m, x)
+    assert np.array_equal(got, exp, equal_nan=True)
+    m.close()
