@@ -942,13 +942,17 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_layer_kernel(const fu
     if constexpr (MODE != 2) fusedl_store_max(A, red, wave, lane, fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
 }
 
+// The feature of row r of a two-digit layer (its own inverse).
+constexpr __host__ __device__ int two_digit_feature(int r) { return (r & ~5) | (r & 1) << 2 | (r >> 2 & 1); }
+
 // ---- test hook: one layer of the whole-network kernel on caller-supplied codes ---------------
 // The layer body is the code dhq_fused_kernel runs (fused_gemm_sine_hm, fused_tile_stages,
 // fused_quant4 on the same packed weights); only the way in and out differs: the input codes
 // are gathered from a row-major n x Kp array into the lanes' register order, and the
 // un-normalised transform x^ of the layer's output and the codes the next layer's quantizer
 // makes of it are scattered back to row-major n x NF arrays in rotated-feature order.  The
-// integer accumulators come from a second, plain MFMA loop over the same fragments and codes.
+// integer accumulators come from a second, plain MFMA loop over the same fragments and codes.  Two digits: those are the
+// un-rotated ones, z = H acc' over the outputs, which fusedd_rotate_kernel takes back to the rotated ones, acc' = H z / NF.
 struct fusedd_args {
     const int8_t *codes_in;    // n x kp_in, rotated-feature order
     const unsigned char *blk;  // the layer's block of the packed weights
@@ -993,18 +997,28 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds);
-    if (DHQ_DIGITS(ACTK) == 1 && A.acc) {
+    if (A.acc) {
+        constexpr int D = DHQ_DIGITS(ACTK), TH = NT / fused_halves<NT, KB, ACTK>;  // tiles of a block
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
+            const dhq_v4i *wA = reinterpret_cast<const dhq_v4i *>(lds + T / TH * (fused_block_kib<NT, KB, ACTK> * 1024)) + T % TH * D * KB * 64 + lane;
             dhq_v16i acc;
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[v] = 0;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wA[(T * KB + kb) * 64 + lane], cd[kb], acc, 0, 0, 0);
+            for (int kb = 0; kb < D * KB; ++kb) {
+                if (D > 1 && kb == KB) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[v] = (int)((unsigned)acc[v] << 8);
+                }
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wA[kb * 64], cd[kb % KB], acc, 0, 0, 0);
+            }
             if (valid) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) A.acc[ci * NF + 32 * T + 8 * (v >> 2) + 4 * h + (v & 3)] = acc[v];
+                for (int v = 0; v < 16; ++v) {
+                    const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+                    A.acc[ci * NF + 32 * T + (D > 1 ? two_digit_feature(row) : row)] = acc[v];
+                }
             }
         }
     }
@@ -1023,10 +1037,20 @@ __global__ __launch_bounds__(FUSED_THREADS) void dhq_fused_debug_kernel(const fu
     }
 }
 
-// ------------------------------------------------------------------------------- host code
-// The feature of row r of a two-digit layer (its own inverse).
-static int two_digit_feature(int r) { return (r & ~5) | (r & 1) << 2 | (r >> 2 & 1); }
+// One row per workgroup of NF threads, in place.  (A sum that NF does not divide is no product with the rotated weights.)
+__global__ void fusedd_rotate_kernel(int32_t *acc)
+{
+    __shared__ int32_t z[256];
+    int32_t *const row = acc + (size_t)blockIdx.x * blockDim.x;
+    const int j = threadIdx.x, n = blockDim.x;
+    z[j] = row[j];
+    __syncthreads();
+    long long s = 0;
+    for (int k = 0; k < n; ++k) s += (__builtin_popcount(j & k) & 1) ? -(long long)z[k] : z[k];
+    row[j] = s % n == 0 ? (int32_t)(s / n) : INT32_MIN;
+}
 
+// ------------------------------------------------------------------------------- host code
 // `padded`: hidden widths that are no kernel's width, or differ, but all round up to the same one's.
 // Two-sided models: whole-network kernels for the exact widths only.  Fan-ins above 4: with the padded plans, exact widths too.
 static bool fused_shape_ok(const dhq_model *m, bool padded, int *nf_out)
@@ -1587,10 +1611,6 @@ hipError_t dhq_fused_debug_launch(const dhq_model *m, const dhq_fused_plan *P, i
 {
     if (!P || layer < 0 || layer >= m->n_layers - 1) return hipErrorInvalidValue;
     if (n <= 0) return hipSuccess;
-    if (P->digits == 2 && acc) {  // the rotated accumulators, which the kernel never has
-        const hipError_t e = dhq_launch_gemm(m->layer[layer], codes_in, n, acc, nullptr, 0.0f, nullptr, dhq_act{DHQ_ACT_KIND_NONE, 0.f}, nullptr, st);
-        if (e != hipSuccess || (!xhat && !codes_out)) return e;
-    }
     fusedd_args a;
     memset(&a, 0, sizeof(a));
     a.codes_in = codes_in;
@@ -1606,11 +1626,15 @@ hipError_t dhq_fused_debug_launch(const dhq_model *m, const dhq_fused_plan *P, i
     a.inv_next = P->args.layer[layer + 1].inv_in;
     a.c2 = dhq_hidden_act(m).c2;
     const unsigned grid = (unsigned)((n + FUSED_TILE - 1) / FUSED_TILE);
+    hipError_t e;
     switch (P->nf) {
-        case 32: return fusedd_launch_nf<32>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
-        case 64: return fusedd_launch_nf<64>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
-        case 128: return fusedd_launch_nf<128>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
-        case 256: return fusedd_launch_nf<256>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st);
+        case 32: e = fusedd_launch_nf<32>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st); break;
+        case 64: e = fusedd_launch_nf<64>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st); break;
+        case 128: e = fusedd_launch_nf<128>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st); break;
+        case 256: e = fusedd_launch_nf<256>(layer == 0, P->digits, m->act_kind, a, grid, P->device, st); break;
         default: return hipErrorInvalidValue;
     }
+    if (e != hipSuccess || P->digits != 2 || !acc) return e;
+    fusedd_rotate_kernel<<<(unsigned)n, P->nf, 0, st>>>(acc);
+    return hipGetLastError();
 }

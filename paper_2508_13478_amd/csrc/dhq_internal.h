@@ -244,7 +244,7 @@ static inline bool dhq_use_pair(const dhq_model *m)
 // caller's input codes (n x Kp int8, rotated-feature order).  Outputs, each n x hidden width,
 // row-major in rotated-feature order, any may be null: the un-normalised transform x^ of the
 // layer's output, the codes the next layer's quantizer makes of it, the layer's int32 accumulators
-// (two-sided: the rotated ones, from the layer-by-layer GEMM).
+// (two-sided: the rotated ones, worked out from the un-rotated ones that the kernel has).
 hipError_t dhq_fused_debug_launch(const dhq_model *m, const dhq_fused_plan *plan, int layer, const int8_t *codes_in, int64_t n, float *xhat,
                                   int8_t *codes_out, int32_t *acc, hipStream_t st);
 hipError_t dhq_wide_debug_launch(const dhq_model *m, int layer, const int8_t *codes_in, int64_t n, float *xhat, int8_t *codes_out,
