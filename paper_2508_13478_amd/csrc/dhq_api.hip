@@ -1015,8 +1015,10 @@ extern "C" int dhq_forward(const dhq_model *m, const float *coords_dev, int64_t 
                                           : dhq_pair_launch(m->pad_pair, coords_dev, n, out_dev, st);
         return e == hipSuccess ? DHQ_OK : DHQ_EHIP;
     }
-    // Two-sided at width 512: the whole-network kernel with the layer-by-layer path's bits (and its range of arguments).
-    if (path == DHQ_AUTO && m->pair2) return dhq_pair2_launch(m, m->pair2, coords_dev, n, out_dev, st) == hipSuccess ? DHQ_OK : DHQ_EHIP;
+    // Two-sided at width 512, and fan-ins of 5 to 32 at 257 to 512: the whole-network kernel with the layer-by-layer path's bits (and its
+    // range of arguments).  With such a fan-in a few rows are faster layer by layer (one-digit products; 5 x 512, six layers, 1, 64 and
+    // 256 rows 74, 77 and 97 us against 86; 12 x 300, three layers, 42, 51 and 61 against 43).
+    if (path == DHQ_AUTO && m->pair2 && (m->rot_out || n > 64)) return dhq_pair2_launch(m, m->pair2, coords_dev, n, out_dev, st) == hipSuccess ? DHQ_OK : DHQ_EHIP;
     const int K0 = m->dims[0], Mo = m->dims[m->n_layers];
     for (int64_t off = 0; off < n; off += DHQ_CHUNK) {
         const int64_t rows = (n - off) < DHQ_CHUNK ? (n - off) : DHQ_CHUNK;
