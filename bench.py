@@ -156,7 +156,7 @@ def main() -> int:
                          "two_sided: weights rotated on both sides, un-rotation in int32; "
                          "dynamic / two_sided_dynamic: activation scales measured on line per call (one fused kernel "
                          "per layer where there is one); "
-                         "w8a32 / w32a32: the comparison networks with fp32 activations (fused fp32 kernel)")
+                         "w8a32 / w32a32: the comparison networks with fp32 activations (one kernel up to width 256)")
     ap.add_argument("--activation", default="sine", choices=["sine", "wavelet", "wavelet_complex"],
                     help="sine: the SIREN of the workload; wavelet: the same shapes and weights with the activation "
                          "cos(omega0 y) exp(-(s0 y)^2) of the second architecture the paper evaluates (same fused kernels); "
@@ -212,6 +212,8 @@ def main() -> int:
         model.calibrate(x)
     fused = model.has_fused() and not dynamic and args.path == "auto"
     flags = dhq.DHQ_FUSED if fused else dhq.DHQ_LAYERWISE
+    if floating and args.path == "auto":
+        flags = dhq.DHQ_AUTO
     # dynamic scales: one fused kernel per layer where the library has a whole-network kernel (two-sided: up to
     # hidden width 256), the layer-by-layer kernels otherwise or with --path layerwise
     dyn_fused = dynamic and args.path == "auto" and model.has_fused()
@@ -272,7 +274,7 @@ def main() -> int:
     nf = wl.dims[1]
     per_feature = 3 + 2 + math.log2(nf / 32) + (1 if nf == 512 and args.wide_kernel == 1 else 0) + 2.75
     if two_sided:
-        per_feature += math.log2(nf) + 0.5   # the integer un-rotation: log2(n) add/sub and half a lane swap
+        per_feature += 1   # the shift between the products of the two weight digits
     lane_instr = sum(wl.dims[l + 1] for l in range(len(wl.dims) - 2)) * per_feature * n
     valu_peak = 256 * 4 * 2.4e9 / 4
     res["alu"] = {"bound": "alu", "achieved": lane_instr / 64 / (ms * 1e-3), "peak": valu_peak,
@@ -285,10 +287,11 @@ def main() -> int:
             res["alu"]["counter_mfma_busy_frac"] = busy["mfma"]
             res["alu"]["counter_source"] = "stored from the rocprofv3 --pmc run summarised in profiles/dhq_fused_utilisation_pmc.md"
     if floating:
-        # fp32 activations: every multiply-add as three products of binary16 pieces (2 500 / 3 TFLOP/s)
+        # fp32 activations: every multiply-add as six products of bf16 pieces (2 500 / 6 TFLOP/s).  DHQ_AUTO runs the workloads of up
+        # to 256 features in one kernel (has_fused) and the 512-wide one layer by layer
         tf = ops / (ms * 1e-3) / 1e12
-        one_kernel = args.path != "layerwise"
-        peak = 2500.0 / 3
+        one_kernel = fused
+        peak = 2500.0 / 6
         res["metric"] = "fp32-activation SIREN forward coords/sec"
         res["dtype"] = "f32"
         res["config"]["workload"] = res["config"]["workload"].replace("W8A8, static per-layer scales from absmax calibration on the same grid", args.variant.upper())
@@ -337,8 +340,7 @@ def main() -> int:
         res["layerwise_ms_per_step"] = ms_lw
     if not floating and not two_sided and not dynamic and not cplx:
         # the paper's W32A32-versus-W8A8 comparison (Table 2) on this GPU: the plain fp32 network through
-        # the library's own fp32 kernel, and how
-        # far the quantized output is from it
+        # the library's own fp32 kernels, and how far the quantized output is from it
         ref_model = dhq.Model(wl.dims, wl.omega0, W, b, 8, 8, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
         ref_out = torch.empty_like(out)
         ms_f, _ = time_forward(ref_model, x, ref_out, dhq.DHQ_AUTO, max(10, args.steps // 20), 5)
@@ -347,7 +349,7 @@ def main() -> int:
         mse = float(((out.double() - ref_out.double()) ** 2).mean())
         peak = float(ref_out.max() - ref_out.min())
         res["w32a32_ms_per_step"] = ms_f
-        res["w32a32_path"] = "fused"
+        res["w32a32_path"] = "fused" if ref_model.has_fused() else "layer by layer"
         res["speedup_vs_w32a32"] = ms_f / ms
         res["psnr_vs_w32a32_db"] = 10.0 * math.log10(peak * peak / mse) if mse > 0 else float("inf")
         ref_model.close()
