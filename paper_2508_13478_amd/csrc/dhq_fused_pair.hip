@@ -65,7 +65,9 @@ struct pair_args {
     int k0, k0p;
     int m_out;
     int qmax;
-    int n_chunks;              // weight chunks a coordinate pass goes through, in a cycle: 2 + 8 (n_layers - 2) (the whole network)
+    int n_chunks;              // weight chunks a coordinate pass goes through, in a cycle (the whole network: the input layer's, rt
+                               // (padded 5 .. 8, exact 8; two-sided 16) for each further hidden layer, the output layer's; an odd count
+                               // puts a pass's first chunk into the other buffer: buffers go by the running count)
     int chunk_base;            // first of them: 0 (the whole network), or a single layer's first chunk
     uint32_t bias_off;         // byte offset of the bias table in the blob: [layer][512] floats, bias_slot order per tile
     float c2;                  // wavelet activation: 2 pi s0 sqrt(log2 e) / omega0
@@ -814,7 +816,7 @@ __device__ __forceinline__ void pair2_hidden(pair_stream &S, int &cc, int layer,
     cc += 2 * PAIR_NT;
 }
 
-// The input layer (fan-in <= 4): one chunk, per role [tile][digit plane] fragments.
+// The input layer (one k block: fan-in <= 4, or <= 32 with DHQ_CODES_IN): one chunk, per role [tile][digit plane] fragments.
 template <int T, int ACTK>
 __device__ __forceinline__ void pair2_input_tile(pair2_ctx<ACTK> &C)
 {

@@ -38,6 +38,21 @@ def test_scales_of_every_activation_and_width(dims, act, bits):
     m.close()
 
 
+@pytest.mark.parametrize("dims", [[2, 64, 64, 3], [3, 200, 200, 200, 1]], ids=lambda d: "x".join(map(str, d)))
+def test_last_pass_of_half_the_waves(dims):
+    """A last pass that at most half of the waves have a tile in is dealt over all workgroups: both sides of that line."""
+    import torch
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    W, b = synth.siren_init(dims, 30.0, 3)
+    m = dhq.Model(dims, 30.0, W, b)
+    for n in (384 * cu, 384 * cu + 1):
+        print(f"[calibrate] {dims} n={n}", flush=True)
+        x = torch.rand((n, dims[0]), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda") * 2 - 1
+        got, exp = _scales(m, x)
+        assert np.array_equal(got, exp)
+    m.close()
+
+
 @pytest.mark.parametrize("n", [131072, 131073, 262145, 400001, 1048577], ids=["one_buffer", "two", "three_groups", "four_groups", "too_many_groups"])
 def test_rows_beyond_the_buffers_room(n):
     """33 features take 64 bytes of codes; a buffer has 33 floats for each of 65 536 rows, two passes' worth of them."""
