@@ -1038,12 +1038,18 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
 //   2 x 256 x 256 x 512    35 / 25      36 / 25      40 / 44      74 / 151     193 / 456    767 / 1823
 //   2 x 128 x 128 x 300    20 / 19      21 / 20      22 / 26      47 / 78      100 / 161    415 / 691
 //   2 x 64 x 64 x 512      40 / 13      43 / 13      44 / 20      53 / 49      110 / 105    565 / 428
+// With nine to eleven feature tiles and few rows one launch saves 2.5 us against one per layer where 32 rows are all there is, 6.5 us
+// beyond, and its weights' way into the registers takes about one more for every tile beyond eight of every hidden layer but the
+// first, and one for every 16 inputs beyond the first 16 (a fit over 1 to 6 hidden layers, fan-ins of 2, 40 and 64, sine and
+// wavelet; where the rule is wrong, it is by 10 % at most).  Three layers of 352, fan-in 40, sine: 1 row 32.5 / 27.8, 64 rows 35.7 / 33.3, 300 rows 36.0 / 36.5;
+// six of 257, fan-in 2: 1 row 48.3 / 46.5, 64 rows 49.7 / 51.1.
 static bool float_net_takes(const dhq_float_plan *P, int64_t n)
 {
     const int64_t round = 32 * (int64_t)P->n_cu;
     const int L = P->n_layers, K = P->lw[0].K, mt = P->max_mt;
     if (L < 2) return false;
     if (mt > 13 ? n <= round / 4 || n > round : mt > 11 && n <= round / 4) return false;
+    if (mt > 8 && n <= round / 16 && (mt - 8) * (L - 2) + (K + 15) / 16 - 1 > (n <= 32 ? 2 : 6)) return false;
     if (K > 64 && !(mt == 1 && (K <= 256 || n > 1024)) && !(mt == 2 && n > 4 * round)) return false;
     return P->lw[L - 1].Mt == 1 || (mt > 2 && n > round / 2);
 }
