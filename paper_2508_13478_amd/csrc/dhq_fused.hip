@@ -37,7 +37,7 @@
 // layers, 262 144 rows, butterflies / digits in us: width 32 25.9 / 22.0, 64 (wavelet) 55.9 / 48.6, 128 90.3 / 75.8, 256 197.7 /
 // 194.2 (there the digits' products load the matrix unit as much as the epilogue does the vector ALU); 1 000 rows of 256,
 // which the kernel for few rows now takes as well, 49.9 / 13.3.
-// Row r of a tile is the feature whose tile index has bits 0 and 2 of r exchanged, which is where the lane exchange of the
+// Row r of a tile is the feature whose index in the tile is r with bits 0 and 2 exchanged, which is where the lane exchange of the
 // butterflies left it: the products with H_32 then add a tile's activations in the same order as behind them, and the values are
 // theirs bit for bit.
 #include <math.h>
