@@ -31,9 +31,9 @@ VALU_LANE_RATE = 256 * 4 * 16 * 2.4e9  # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz 
 # unit were busy.  Valid only for the kernel sources they were taken with: the hash below is compared with
 # the current sources and the figures are dropped if they differ.
 TRAFFIC_SOURCES = ("dhq_fused.hip", "dhq_fused_pair.hip", "dhq_fused_common.h", "dhq_device.h")
-TRAFFIC_SHA256 = "b38b6f3da310d2c1af9730bdd8ff7112557bb2730ee9a6ce073b615f0bebf66e"
-TRAFFIC_BYTES = {"C2": 2588672 + 786432, "C5": 45158400 + 50331648}
-COUNTER_BUSY = {"C2": {"valu": 0.642, "mfma": 0.255}, "C4": {"valu": 0.890, "mfma": 0.371}, "C5": {"valu": 0.689, "mfma": 0.434}}
+TRAFFIC_SHA256 = "f7f57fbb2256c14c9f0f832393d368c807f370b427de5da62a984f58fa003874"
+TRAFFIC_BYTES = {"C2": 2593792 + 786432, "C5": 45159424 + 50331648}
+COUNTER_BUSY = {"C2": {"valu": 0.661, "mfma": 0.262}, "C4": {"valu": 0.890, "mfma": 0.371}, "C5": {"valu": 0.691, "mfma": 0.436}}
 
 
 def kernel_sources_sha256():
