@@ -126,7 +126,7 @@ int dhq_quantize_weights(const dhq_net_desc *desc, const float *const *W_host,
  * accuracy, where W is the original weight matrix (DHQ_W32A32) or
  * W~ = (s_w Wq) H_Kp / sqrt(Kp), the de-quantized weights taken back to the original basis
  * (DHQ_W8A32; bits_w applies, bits_a is ignored).  Any shape within the limits.  Weights and activations are fp32 values of any
- * size; the products take them as three-piece bf16 splits, which hold them without loss.  With fan-in <= 4, equal hidden
+ * size; the products take them as three-piece bf16 splits, which hold them without loss (but for bits below 2^-126).  With fan-in <= 4, equal hidden
  * widths of 32 / 64 / 128 / 256 and fan-out <= 32, DHQ_AUTO and DHQ_FUSED run the whole network in one kernel.  In other
  * shapes DHQ_AUTO does so where that is faster.  DHQ_LAYERWISE, and DHQ_AUTO elsewhere (hidden layers of more than 416, large
  * fan-ins and fan-outs, single layers), run one kernel per layer, with the same values bit for bit, which write the model's

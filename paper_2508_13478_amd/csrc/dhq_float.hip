@@ -77,7 +77,7 @@ struct dhq_float_plan {
 // weight is at least 2^-17 of it,
 //     hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi),
 // each exact in the MFMA and summed in fp32.  Left out are mid lo, lo mid and lo lo: at most 2^-24 of |a w| together,
-// half an ulp of the product, with a random sign.  A layer then costs 6 / 16 of the fp32 MFMA time.
+// half an ulp of the product, with a random sign.  (The MFMA takes subnormal pieces as zero: bits of a value below 2^-126.)  A layer then costs 6 / 16 of the fp32 MFMA time.
 //
 // Layout.  Features are the MFMA M dimension (weights = A operand), coordinates its N dimension, so that a lane's
 // accumulators are half of one coordinate's features and become, split into pieces, that lane's B operands of the next
@@ -100,31 +100,40 @@ __device__ __forceinline__ unsigned flt_pack_bf16(float a, float b)
     const flt_v2b p = {(__bf16)a, (__bf16)b};  // one packed conversion, rounded to nearest even
     return __builtin_bit_cast(unsigned, p);
 }
-// The three bf16 pieces of two values, value 0 in the low halves.
+// The three bf16 pieces of two values, value 0 in the low halves.  INPUT: coordinates, which may be beyond the largest bf16; the first
+// piece of one that would round to infinity is truncated instead (activations are at most 1).
+template <bool INPUT = false>
 __device__ __forceinline__ void flt_split3(float a0, float a1, unsigned &hi, unsigned &mid, unsigned &lo)
 {
 // (what is split is an fp32 value: the wavelet's last product must not melt into the subtractions, in one kernel and not in another)
 #pragma clang fp contract(off)
     hi = flt_pack_bf16(a0, a1);
+    if constexpr (INPUT) {
+        const unsigned u0 = __float_as_uint(a0), u1 = __float_as_uint(a1);
+        if ((u0 & 0x7fffffffu) - 0x7f7f8000u < 0x8000u) hi = (hi & 0xffff0000u) | u0 >> 16;
+        if ((u1 & 0x7fffffffu) - 0x7f7f8000u < 0x8000u) hi = (hi & 0xffffu) | (u1 & 0xffff0000u);
+    }
     const float r0 = a0 - __uint_as_float(hi << 16), r1 = a1 - __uint_as_float(hi & 0xffff0000u);
     mid = flt_pack_bf16(r0, r1);
     lo = flt_pack_bf16(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
 }
 // Eight values as a lane's 16 bytes of each of the three fragments.
+template <bool INPUT = false>
 __device__ __forceinline__ void flt_split(const float (&y)[8], dhq_v4i (&x)[3])
 {
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         unsigned hi, mid, lo;
-        flt_split3(y[2 * d], y[2 * d + 1], hi, mid, lo);
+        flt_split3<INPUT>(y[2 * d], y[2 * d + 1], hi, mid, lo);
         x[0][d] = (int)hi; x[1][d] = (int)mid; x[2][d] = (int)lo;
     }
 }
 // The fragments at dst, dst + 1 KiB, dst + 2 KiB.
+template <bool INPUT = false>
 __device__ __forceinline__ void flt_store_pieces(const float (&y)[8], unsigned char *__restrict__ dst)
 {
     dhq_v4i x[3];
-    flt_split(y, x);
+    flt_split<INPUT>(y, x);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *reinterpret_cast<dhq_v4i *>(dst + i * 1024) = x[i];
 }
@@ -164,7 +173,7 @@ __global__ __launch_bounds__(256) void float_pack_kernel(const float *__restrict
     float y[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) y[j] = (row < n && k0 + j < K) ? in[row * K + k0 + j] : 0.f;
-    flt_store_pieces(y, out + (size_t)w * 3072 + lane * 16);
+    flt_store_pieces<true>(y, out + (size_t)w * 3072 + lane * 16);
 }
 
 struct float_layer_args {
@@ -464,7 +473,7 @@ __global__ __launch_bounds__(256) void float_narrow_kernel(const float_narrow_ar
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 unsigned hi, mid, lo;
-                flt_split3(v[kb][2 * d], v[kb][2 * d + 1], hi, mid, lo);
+                flt_split3<FIRST>(v[kb][2 * d], v[kb][2 * d + 1], hi, mid, lo);
                 x[kb][0][d] = (int)hi; x[kb][1][d] = (int)mid; x[kb][2][d] = (int)lo;
             }
         if (ct + stride < A.n_ct) load(ct + stride, v);  // arrives during the products
@@ -576,7 +585,7 @@ __global__ __launch_bounds__(64 * WF * WC, TF * TC <= 4 ? 2 : 1) void float_net_
                     float y[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) y[j] = (row < A.n && kk + j < A.k0) ? A.coords[row * A.k0 + kk + j] : 0.f;
-                    flt_split(y, x[t]);
+                    flt_split<true>(y, x[t]);
                 }
 #pragma unroll
                 for (int f = 0; f < TF; ++f) {

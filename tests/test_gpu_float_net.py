@@ -79,3 +79,23 @@ def test_small_activations(s0, width, scale):
         print(f"[float net] width {width} s0={s0} scale {scale} flags {flags}: max-abs err {err:.2e}", flush=True)
         assert err <= FLOAT_TOL_WIDE
     m.close()
+
+
+@pytest.mark.parametrize("width", [32, 48, 128, 256, 300])
+@pytest.mark.parametrize("s0", [None, 0.1], ids=["sine", "wavelet"])
+def test_coordinates_beyond_the_largest_bf16(s0, width):
+    """Coordinates of 3.39e38 to 3.40e38, of which the first bf16 piece would round to infinity, with weights that are powers of two (their
+    own first piece): arguments of up to 24."""
+    import torch
+    dims = [2, width, width, 3]
+    W, b = synth.siren_init(dims, 30.0, 5)
+    rng = np.random.default_rng(width)
+    W[0] = (rng.choice([-1.0, 1.0], W[0].shape) * np.exp2(rng.choice([-126.0, -125.0], W[0].shape))).astype(np.float32)
+    x = (rng.choice([-1.0, 1.0], (700, 2)) * rng.uniform(3.38e38, 3.4028e38, (700, 2))).astype(np.float32)
+    exp, _ = o.mlp_float(dims, 1.0, W, b, x, **({"gabor_s0": s0} if s0 is not None else {}))
+    m = dhq.Model(dims, 1.0, W, b, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
+    for flags in (dhq.DHQ_AUTO, dhq.DHQ_LAYERWISE):
+        err = np.abs(m.forward(torch.from_numpy(x).to("cuda"), flags=flags).cpu().numpy().astype(np.float64) - exp).max()
+        print(f"[float net] width {width} s0={s0} flags {flags}: max-abs err {err:.2e}", flush=True)
+        assert err <= FLOAT_TOL_WIDE
+    m.close()
