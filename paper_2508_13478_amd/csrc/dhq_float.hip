@@ -1052,6 +1052,10 @@ hipError_t dhq_float_launch_layerwise(const dhq_float_plan *P, const float *coor
 // first, and one for every 16 inputs beyond the first 16 (a fit over 1 to 6 hidden layers, fan-ins of 2, 40 and 64, sine and
 // wavelet; where the rule is wrong, it is by 10 % at most).  Three layers of 352, fan-in 40, sine: 1 row 32.5 / 27.8, 64 rows 35.7 / 33.3, 300 rows 36.0 / 36.5;
 // six of 257, fan-in 2: 1 row 48.3 / 46.5, 64 rows 49.7 / 51.1.
+// With nine to thirteen tiles a round of the chip takes as long for one coordinate tile as for all: beyond two rounds both ways' times in us,
+// fitted over 257 to 416 features, 1, 2 and 4 hidden layers and fan-ins of 2 to 64 (rms 10 %), say which is faster.  257 features, two
+// hidden layers: fan-in 2, 51 200 rows (a fourth round with an eighth of its tiles) at 0.89 of the layer kernels' rate; fan-in 64 0.69.
+// One hidden layer behind a large fan-in: 64 x 128 x 3, 81 920 rows at 0.81; 64 x 64 x 3 at 0.90; 64 x 200 x 3, 51 200 rows at 0.91.
 static bool float_net_takes(const dhq_float_plan *P, int64_t n)
 {
     const int64_t round = 32 * (int64_t)P->n_cu;
@@ -1059,6 +1063,13 @@ static bool float_net_takes(const dhq_float_plan *P, int64_t n)
     if (L < 2) return false;
     if (mt > 13 ? n <= round / 4 || n > round : mt > 11 && n <= round / 4) return false;
     if (mt > 8 && n <= round / 16 && (mt - 8) * (L - 2) + (K + 15) / 16 - 1 > (n <= 32 ? 2 : 6)) return false;
+    const int kb = (K + 15) / 16;
+    if (mt > 8 && n > 2 * round) {
+        const double x = (double)n / (2 * round);  // rounds of tiles of 64
+        const double here = ceil(x) * (7.7 + 3.8 * kb + 1.94 * (L - 2) * mt), layers = 12 + x * (1.25 * (L - 1) * mt + 1.35 * kb + 0.087 * (L - 2) * mt * mt);
+        if (1.03 * here > layers) return false;
+    }
+    if (mt <= 8 && L == 2 && (mt <= 2 ? K > 16 && n > (K > 48 ? 2 : 8) * round : K > 48 && n > 6 * round)) return false;
     if (K > 64 && !(mt == 1 && (K <= 256 || n > 1024)) && !(mt == 2 && n > 4 * round)) return false;
     return P->lw[L - 1].Mt == 1 || (mt > 2 && n > round / 2);
 }

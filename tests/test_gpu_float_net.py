@@ -14,7 +14,7 @@ SHAPES = [[1, 1, 1], [2, 32, 32, 3], [4, 33, 33, 5], [2, 64, 64, 3], [3, 65, 128
           [17, 257, 64, 33], [2, 100, 500, 40, 3], [2, 512, 512, 3],
           # both sides of the rule that sends large fan-ins, fan-outs and widths layer by layer
           [300, 30, 3], [200, 60, 60, 2], [65, 256, 256, 3], [2, 128, 128, 70], [2, 40, 40, 40], [3, 384, 416, 2],
-          [2, 300, 300, 300, 3], [40, 352, 352, 352, 32]]
+          [2, 300, 300, 300, 3], [40, 352, 352, 352, 32], [64, 257, 3], [64, 128, 3], [17, 64, 3]]
 
 
 @pytest.mark.parametrize("dims", SHAPES, ids=["x".join(map(str, d)) for d in SHAPES])
@@ -26,7 +26,7 @@ def test_same_bits_as_layer_by_layer(dims, s0):
     W, b = synth.siren_init(dims, 30.0, 77 + sum(dims))
     m = dhq.Model(dims, 30.0, W, b, mode=dhq.DHQ_W32A32, wavelet_s0=s0)
     g = torch.Generator(device="cuda").manual_seed(9)
-    for n in (1, 32, 33, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16385, 32769, 65537, 140001):
+    for n in (1, 32, 33, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16385, 32769, 49153, 65537, 140001):
         print(f"[float net] {dims} s0={s0} n={n}", flush=True)
         x = torch.rand((n, dims[0]), generator=g, device="cuda") * 2 - 1
         assert torch.equal(m.forward(x), m.forward(x, flags=dhq.DHQ_LAYERWISE))
