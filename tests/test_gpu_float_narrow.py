@@ -28,7 +28,7 @@ def _rows(dims, n, seed):
 @pytest.mark.parametrize("dims", SHAPES, ids=["x".join(map(str, d)) for d in SHAPES])
 @pytest.mark.parametrize("s0", [None, 10.0], ids=["sine", "wavelet"])
 def test_narrow_against_oracle_and_the_wide_kernels(dims, s0):
-    """Against the oracle, and bit for bit against the same network on the kernels of the wider ones: embedded in hidden widths of
+    """Against the oracle, and (sines bit for bit) against the same network on the kernels of the wider ones: embedded in hidden widths of
     80, whose further features have no weights in or out and add nothing but zeros to any sum.  (A single layer has no hidden
     width to embed; its fan-in is embedded in 80.)"""
     import torch
@@ -54,12 +54,31 @@ def test_narrow_against_oracle_and_the_wide_kernels(dims, s0):
         xe = torch.zeros((n, wide[0]), device="cuda")
         xe[:, :dims[0]] = x
         ref = mw.forward(xe, flags=dhq.DHQ_LAYERWISE)
-        assert torch.equal(out, ref)
+        # (wavelets bit for bit: test_narrow_wavelets_are_the_wide_kernels)
+        assert torch.equal(out, ref) if s0 is None or L == 1 else float((out - ref).abs().max()) <= _tol(dims)
         idx = np.unique(np.concatenate([np.arange(min(n, 70)), np.arange(max(0, n - 70), n)]))
         exp, _ = o.mlp_float(dims, 30.0, W, b, x.cpu().numpy()[idx], **({"gabor_s0": s0} if s0 is not None else {}))
         err = np.abs(out.cpu().numpy()[idx].astype(np.float64) - exp).max()
         print(f"  max-abs err {err:.2e}", flush=True)
         assert err <= _tol(dims) * max(1.0, np.abs(exp).max())
+    m.close()
+    mw.close()
+
+
+@pytest.mark.parametrize("dims", [d for d in SHAPES if len(d) > 2], ids=lambda d: "x".join(map(str, d)))
+def test_narrow_wavelets_are_the_wide_kernels(dims):
+    """Bit for bit, in the same embedding: what both split into pieces is the wavelet rounded to fp32."""
+    import torch
+    L = len(dims) - 1
+    W, b = synth.siren_init(dims, 30.0, 900 + sum(dims))
+    wide = [dims[0]] + [80] * (L - 1) + [dims[-1]]
+    We = [np.pad(W[l], ((0, wide[l + 1] - dims[l + 1]), (0, wide[l] - dims[l]))) for l in range(L)]
+    be = [np.pad(b[l], (0, wide[l + 1] - dims[l + 1])) for l in range(L)]
+    m, mw = (dhq.Model(d, 30.0, w, v, mode=dhq.DHQ_W32A32, wavelet_s0=10.0) for d, w, v in ((dims, W, b), (wide, We, be)))
+    for n in (1, 33, 4097):
+        print(f"[float narrow] {dims} wavelet n={n}", flush=True)
+        x = _rows(dims, n, n)
+        assert torch.equal(m.forward(x, flags=dhq.DHQ_LAYERWISE), mw.forward(x, flags=dhq.DHQ_LAYERWISE))
     m.close()
     mw.close()
 
